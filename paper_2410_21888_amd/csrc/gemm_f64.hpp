@@ -77,7 +77,8 @@ struct GemmParams {
   int32_t skip_nvir, skip_k0, skip_j0, skip_nocc;
   // pair_upper (same row/column to pair mapping): a tile all of whose pairs
   // have pair_lo <= j < k is not computed (their blocks are the transposes of
-  // blocks the same launch computes).
+  // blocks the same launch computes); workgroups are launched for the tiles
+  // that pair_cols_skipped keeps.  Never with split-K.
   int32_t pair_upper, pair_lo;
 };
 
@@ -115,14 +116,76 @@ enum GemmRole { ROLE_INTS = 0, ROLE_GAMMA = 1, ROLE_PAB = 2, ROLE_PIJ = 3, ROLE_
 // Roles whose A operand is M-contiguous.
 constexpr bool role_a_mcontig(int role) { return role == ROLE_GAMMA_T || role == ROLE_AO; }
 
+// Column tiles that a pair_upper launch leaves out for a whole raster group:
+// with k_lo the occupied orbital of the group's first row, the tiles
+// [from, from + return) hold only pairs pair_lo <= j < k_lo.  Columns are j0 +
+// n / nvir.  The rows of a group start at the same or a later orbital, so a
+// tile left out here is one tile_screened would drop.
+__host__ __device__ inline int64_t pair_cols_skipped(int64_t k_lo, int64_t j0, int64_t pair_lo, int64_t nvir, int64_t bn,
+                                                     int64_t tiles_n, int64_t* from) {
+  const int64_t below = (k_lo - j0) * nvir / bn;   // tiles whose last column has j < k_lo
+  const int64_t lo = pair_lo > j0 ? ((pair_lo - j0) * nvir + bn - 1) / bn : 0;
+  *from = lo;
+  const int64_t n = (below < tiles_n ? below : tiles_n) - lo;
+  return n > 0 ? n : 0;
+}
+
+// Tile t of a pair_upper launch, counted over the tiles its raster groups
+// keep: one lane counts one group and a wave prefix sum finds t's group.  The
+// launch then holds no workgroups for the skipped half of a whole-slab
+// (ia|jb), whose tiles all lie in the later groups: with every tile launched
+// and consecutive tiles going to one XCD (xcd_remap), the first XCDs held
+// nearly all of the work and the last ones nearly none, and the product ran
+// at half its rate.  MFMA-bound; energy of nocc = 100, nvir = 600, naux =
+// 1800: 178 -> 99 ms (36.7 -> 66 TFLOP/s); nocc = 97, nvir = 485, naux =
+// 1746: 107 -> 59 ms.
+__device__ __forceinline__ void decode_pair_tile(int64_t t, int64_t k0, int64_t j0, int64_t pair_lo,
+                                                 int64_t nvir, int bm, int bn, int tiles_m, int tiles_n, int group_m,
+                                                 int& tm, int& tn) {
+  const int lane = threadIdx.x & 63, ngrp = (tiles_m + group_m - 1) / group_m;
+  for (int base = 0;; base += 64) {
+    const int grp = base + lane;
+    int64_t from = 0, skipped = 0;
+    int gm = 0;
+    if (grp < ngrp) {
+      gm = min(group_m, tiles_m - grp * group_m);
+      skipped = pair_cols_skipped(k0 + (int64_t)grp * group_m * bm / nvir, j0, pair_lo, nvir, bn, tiles_n, &from);
+    }
+    const int64_t cnt = gm * (tiles_n - skipped);
+    int64_t incl = cnt;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const int64_t v = __shfl_up(incl, d, 64);
+      if (lane >= d) incl += v;
+    }
+    const unsigned long long past = __ballot(incl > t);
+    if (past == 0 && base + 64 < ngrp) {
+      t -= __shfl(incl, 63, 64);
+      continue;
+    }
+    const int w = past ? __ffsll(past) - 1 : 0;
+    const int64_t u = t - (__shfl(incl, w, 64) - __shfl(cnt, w, 64));
+    const int g = __shfl(gm, w, 64);
+    const int64_t c = u / g;
+    const int64_t f = __shfl(from, w, 64), s = __shfl(skipped, w, 64);
+    tm = (base + w) * group_m + (int)(u - c * g);
+    tn = (int)(c < f ? c : c + s);
+    return;
+  }
+}
+
 // Decodes logical tile index t (< tiles of one split) into (tm, tn):
-// triangular order (TRI) or groups of group_m m-tiles.
-template <bool TRI>
+// triangular order (TRI), the kept tiles of a pair_upper launch, or groups of
+// group_m m-tiles.
+template <int BM, int BN, bool TRI>
 __device__ __forceinline__ void decode_tile(const GemmParams& p, int t, int& tm, int& tn) {
   if (TRI) {
     tm = 0;
     while (t >= p.tiles_m - tm) { t -= p.tiles_m - tm; ++tm; }
     tn = tm + t;
+  } else if (p.pair_upper) {
+    decode_pair_tile(t, p.skip_k0, p.skip_j0, p.pair_lo, p.skip_nvir, BM, BN, p.tiles_m, p.tiles_n, p.group_m, tm,
+                     tn);
   } else {
     const int gsz = p.group_m * p.tiles_n;
     const int grp = t / gsz;
@@ -516,9 +579,9 @@ __global__ __launch_bounds__(256, 2) void gemm_f64_kernel(GemmParams p) {
   __shared__ GemmLds<BM, BN, BK> lds;
   const int wl = xcd_remap(blockIdx.x, gridDim.x);
   const int ntiles = TRI ? p.tiles_m * (p.tiles_m + 1) / 2 : p.tiles_m * p.tiles_n;
-  const int z = wl / ntiles;
+  const int z = wl / ntiles;   // 0 in a pair_upper launch: at most ntiles workgroups
   int tm, tn;
-  decode_tile<TRI>(p, wl - z * ntiles, tm, tn);
+  decode_tile<BM, BN, TRI>(p, wl - z * ntiles, tm, tn);
   if (tile_screened<BM, BN>(p, tm, tn)) return;
   gemm_tile<BM, BN, BK, B_NCONTIG, VEC, TRI, FAST, role_a_mcontig(ROLE)>(p, tm, tn, z, lds);
 }
@@ -557,7 +620,7 @@ __global__ __launch_bounds__(256, 2) void gemm_f64_grouped(GemmGroup G) {
     const int ntiles = TRI ? p.tiles_m * (p.tiles_m + 1) / 2 : p.tiles_m * p.tiles_n;
     const int z = u / ntiles;
     int tm, tn;
-    decode_tile<TRI>(p, u - z * ntiles, tm, tn);
+    decode_tile<BM, BN, TRI>(p, u - z * ntiles, tm, tn);
     if (tile_screened<BM, BN>(p, tm, tn)) continue;
     gemm_tile<BM, BN, BK, B_NCONTIG, VEC, TRI, FAST>(p, tm, tn, z, lds);
   }

@@ -364,6 +364,21 @@ int gemm_fast(const GemmParams& gp, bool nc, bool amc = false) {
   return gemm_vec(gp, nc, amc) ? fast_level(gp, nc, amc) : 0;
 }
 
+// Output tiles (of one split) a GEMM launches workgroups for: the upper
+// triangle, the tiles a pair_upper launch keeps (decode_pair_tile), or all.
+int64_t gemm_tiles(const GemmParams& gp, int64_t bm, int64_t bn, bool tri) {
+  if (tri) return (int64_t)gp.tiles_m * (gp.tiles_m + 1) / 2;
+  int64_t n = (int64_t)gp.tiles_m * gp.tiles_n;
+  if (gp.pair_upper)
+    for (int64_t m = 0; m < gp.tiles_m; m += gp.group_m) {
+      int64_t from;
+      n -= std::min<int64_t>(gp.group_m, gp.tiles_m - m) *
+           pair_cols_skipped(gp.skip_k0 + m * bm / gp.skip_nvir, gp.skip_j0, gp.pair_lo, gp.skip_nvir, bn, gp.tiles_n,
+                             &from);
+    }
+  return n;
+}
+
 template <int BM, int BN, bool NC, int ROLE, bool TRI>
 int launch_gemm(GemmParams gp, hipStream_t st, int role, double af, double ab, bool general) {
   gp.tiles_m = (int32_t)cdiv(gp.M, BM);
@@ -373,8 +388,8 @@ int launch_gemm(GemmParams gp, hipStream_t st, int role, double af, double ab, b
   gp.kchunk = cdiv(gp.kchunk, kBK) * kBK;
   gp.splits = (int32_t)cdiv(gp.K, gp.kchunk);
   if (TRI && (gp.M != gp.N || BM != BN)) return fail(RIMP2_EINVAL, "triangular GEMM needs a square tile grid");
-  const int64_t tiles = TRI ? (int64_t)gp.tiles_m * (gp.tiles_m + 1) / 2 : (int64_t)gp.tiles_m * gp.tiles_n;
-  const int64_t nwg = tiles * gp.splits;
+  if (gp.pair_upper && gp.splits != 1) return fail(RIMP2_EINVAL, "pair_upper GEMM without split-K only");
+  const int64_t nwg = gemm_tiles(gp, BM, BN, TRI) * gp.splits;
   if (int rc = check_grid(nwg, "GEMM")) return rc;
   constexpr bool AMC = role_a_mcontig(ROLE);
   if (AMC && gp.splits != 1) return fail(RIMP2_EINVAL, "M-contiguous GEMM without split-K only");
@@ -1112,8 +1127,7 @@ int64_t finalize_gemm(GemmParams& gp, int BM, int BN, bool tri) {
   if (gp.kchunk <= 0) gp.kchunk = gp.K;
   gp.kchunk = cdiv(gp.kchunk, kBK) * kBK;
   gp.splits = (int32_t)cdiv(gp.K, gp.kchunk);
-  const int64_t tiles = tri ? (int64_t)gp.tiles_m * (gp.tiles_m + 1) / 2 : (int64_t)gp.tiles_m * gp.tiles_n;
-  return tiles * gp.splits;
+  return gemm_tiles(gp, BM, BN, tri) * gp.splits;
 }
 
 size_t place(size_t& off, size_t bytes) {
