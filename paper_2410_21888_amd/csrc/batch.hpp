@@ -75,10 +75,6 @@ __global__ void relocate_tables_kernel(char* base, GemmParams* gp, int ngp, AmpD
   }
 }
 
-__global__ void zero_counters_kernel(unsigned long long* c, int n) {
-  if ((int)threadIdx.x < n) c[threadIdx.x] = 0ull;
-}
-
 // last f with prefix[f] <= t
 __device__ __forceinline__ int find_problem(const int64_t* prefix, int n, int64_t t) {
   int lo = 0, hi = n - 1;

@@ -168,8 +168,9 @@ __device__ __forceinline__ void decode_pair_tile(int64_t t, int64_t k0, int64_t 
     const int g = __shfl(gm, w, 64);
     const int64_t c = u / g;
     const int64_t f = __shfl(from, w, 64), s = __shfl(skipped, w, 64);
-    tm = (base + w) * group_m + (int)(u - c * g);
-    tn = (int)(c < f ? c : c + s);
+    // the same in every lane; readfirstlane keeps the tile's addresses scalar
+    tm = __builtin_amdgcn_readfirstlane((base + w) * group_m + (int)(u - c * g));
+    tn = __builtin_amdgcn_readfirstlane((int)(c < f ? c : c + s));
     return;
   }
 }

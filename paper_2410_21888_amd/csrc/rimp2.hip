@@ -629,9 +629,17 @@ void launch_split_cols(const double* X, int64_t K, int64_t N, int64_t ld, const 
   hipLaunchKernelGGL(split_cols_kernel<S>, dim3((unsigned)cdiv(kp, 32), (unsigned)cdiv(N, 32)), dim3(256), 0, st, X, K,
                      N, ld, cmax, D, kp, e, status);
 }
+// Tiles of a pair launch of 64 x 64 split products, as gemm_tiles counts them.
+int64_t oz8_tiles(const OzParams& op) {
+  GemmParams gp{};
+  gp.tiles_m = op.tiles_m; gp.tiles_n = op.tiles_n; gp.group_m = op.group_m;
+  gp.pair_upper = op.pair_nvir > 0; gp.skip_nvir = op.pair_nvir; gp.skip_k0 = op.pair_k0; gp.skip_j0 = op.pair_j0;
+  gp.pair_lo = op.pair_lo;
+  return gemm_tiles(gp, 64, 64, false);
+}
 template <int S>
 void launch_oz8(OzParams op, bool windowed, hipStream_t st) {
-  const int64_t nwg = (int64_t)op.tiles_m * op.tiles_n;
+  const int64_t nwg = oz8_tiles(op);
   // one LDS stage (two workgroups per CU) unless a windowed product with at
   // most 5 digits, where the double-buffered stage (still two per CU) was faster
   if (windowed && S <= 5)
@@ -664,9 +672,14 @@ constexpr int64_t kOzWindow = 2816, kOzWindowMax = 8192;
 
 // C[m, n] (m < M, n < N) from split digits; A rows start at a_row0.
 // acc0: the first window adds into C too (C already holds a partial sum).
+// pairs: null, or the pair fields of an (ia|jb) launch (OzParams).
+struct OzPairs {
+  int64_t nvir, k0, j0, lo;
+};
 int run_oz8(int S, const int8_t* A, int64_t a_slice, int64_t a_row0, const int32_t* ea, const int8_t* B,
             int64_t b_slice, const int32_t* eb, int64_t M, int64_t N, int64_t kp, double* C, int64_t ldc,
-            const int32_t* status, int role, double af, double ab, hipStream_t st, int acc0 = 0) {
+            const int32_t* status, int role, double af, double ab, hipStream_t st, int acc0 = 0,
+            const OzPairs* pairs = nullptr) {
   OzParams op{};
   op.M = M; op.N = N; op.kp = kp;
   op.A = A; op.a_slice = a_slice; op.a_row0 = a_row0;
@@ -675,9 +688,13 @@ int run_oz8(int S, const int8_t* A, int64_t a_slice, int64_t a_row0, const int32
   const bool windowed = kp > kOzWindowMax;
   op.tiles_m = (int32_t)cdiv(M, 64); op.tiles_n = (int32_t)cdiv(N, 64); op.group_m = windowed ? 4 : 8;
   op.status = status;
-  const int64_t nwg = (int64_t)op.tiles_m * op.tiles_n;
+  if (pairs) {
+    op.pair_nvir = (int32_t)pairs->nvir; op.pair_k0 = (int32_t)pairs->k0; op.pair_j0 = (int32_t)pairs->j0;
+    op.pair_lo = (int32_t)pairs->lo;
+  }
+  const int64_t nwg = oz8_tiles(op);
   if (int rc = check_grid(nwg, "split GEMM")) return rc;
-  const double ef = 2.0 * (double)M * N * kp;
+  const double ef = 2.0 * (double)M * N * kp * ((double)nwg / ((double)op.tiles_m * op.tiles_n));
   const int64_t kc = windowed ? kOzWindow : kp;
   for (int64_t k0 = 0;; k0 += kc) {
     op.k0 = k0;
@@ -708,9 +725,6 @@ int run_fragment(const Plan& P, const double* B, const double* eo, const double*
        })))
     return rc;
   const bool energy_only = !(P.gamma || P.density);
-  // pairs with both orbitals in the slab group: blocks (k, j < k) are not
-  // computed and the amplitude pass forms them from their transposes
-  const bool mirror = !P.split && !energy_only;
   int8_t* dbv = (int8_t*)(ws + P.off_dbv);
   int32_t* exv = (int32_t*)(ws + P.off_ev);
   int8_t* dbg = (int8_t*)(ws + P.off_dbg);
@@ -757,7 +771,9 @@ int run_fragment(const Plan& P, const double* B, const double* eo, const double*
       gp.C = V; gp.ldc = Lc; gp.split_stride = 0; gp.status = status;
       gp.skip = skip; gp.skip_nvir = (int32_t)nvir; gp.skip_k0 = (int32_t)k0; gp.skip_j0 = (int32_t)j0;
       gp.skip_nocc = (int32_t)nocc;
-      gp.pair_upper = (energy_only || mirror) ? 1 : 0;
+      // pairs with both orbitals in the slab group: blocks (k, j < k) are not
+      // computed and the amplitude pass forms them from their transposes
+      gp.pair_upper = 1;
       gp.pair_lo = (int32_t)k0;
       // algorithmic FLOPs: unordered pairs whose first orbital is in the group
       // (energy only: exactly the pairs (k, j >= k) computed; otherwise the
@@ -766,9 +782,15 @@ int run_fragment(const Plan& P, const double* B, const double* eo, const double*
                                                    : g * o * (o + 1.0) / (2.0 * o);
       const double af = 2.0 * v * v * x * npairs;
       if (P.split) {
+        // digit sums are exact and symmetric in the two operands, so the blocks
+        // the amplitude pass takes from their transposes are bit for bit those
+        // a product would give; leaving them out halves the product of a
+        // one-slab fragment (MFMA and staging bound; 40/900/3000, 7 digits:
+        // 100 -> 52 ms)
+        const OzPairs pairs{nvir, k0, j0, k0};
         if ((rc = run_oz8(P.sv, dbv, L * P.kpv, k0 * nvir, exv, dbv + j0 * nvir * P.kpv, L * P.kpv, exv + j0 * nvir,
                           gc * nvir, Lc, P.kpv, V, Lc, status, R_INTS8, af,
-                          (double)P.sv * (g * v + o * v) * P.kpv + slab, st)))
+                          (double)P.sv * (g * v + o * v) * P.kpv + slab, st, 0, &pairs)))
           return rc;
       } else if ((rc = launch_tuned(R_INTS, gp, P.autotune, P.general, st, af, 8.0 * (g + o) * v * x + slab))) {
         return rc;
@@ -777,7 +799,7 @@ int run_fragment(const Plan& P, const double* B, const double* eo, const double*
     {
       const int64_t W = amp_splits(gc * ncols, nvir);
       double* epart = (double*)(ws + P.off_epart);
-      const int sym = energy_only ? 1 : (P.sym ? 3 : (mirror ? 2 : 0));
+      const int sym = energy_only ? 1 : (P.sym ? 3 : 2);
       if ((rc = check_grid(gc * ncols * W, "amplitude"))) return rc;
       if ((rc = traced(R_AMP, 0, 0, energy_only ? slab : 3.0 * slab, st, [&] {
              hipLaunchKernelGGL(amplitude_kernel, dim3((unsigned)(gc * ncols * W)), dim3(256), 0, st, V, T, eo, ev,
@@ -1220,7 +1242,7 @@ int batch_plan(int32_t nfrag, const rimp2_frag_desc* d, const rimp2_opts* opts, 
         W.win_oz[0] = std::max<int>(W.win_oz[0], (int)cdiv(P.kpv, kOzWindow));
         if (P.gamma) W.win_oz[1] = std::max<int>(W.win_oz[1], (int)cdiv(P.kpg, kOzWindow));
       }
-      W.o_cnt_oz = place(t, sizeof(unsigned long long) * (W.win_oz[0] + W.win_oz[1]));
+      W.o_cnt_oz = place(t, sizeof(unsigned long long) * kQueues * (W.win_oz[0] + W.win_oz[1]));
       for (int r = 0; r < Wave::kDigitLists; ++r) {
         W.o_dop[r] = place(t, sizeof(DigitOp) * n);
         for (int m = 0; m < 4; ++m) W.o_dpre[r][m] = place(t, sizeof(int64_t) * (n + 1));
@@ -1290,10 +1312,10 @@ int batch_plan(int32_t nfrag, const rimp2_frag_desc* d, const rimp2_opts* opts, 
         z.ea = relp<int32_t>(base + P.off_ev); z.eb = z.ea;
         z.C = V; z.ldc = L;
         z.tiles_m = (int32_t)cdiv(L, 64); z.tiles_n = z.tiles_m; z.group_m = 8;
-        z.pair_nvir = (int32_t)nvir;   // blocks j < k: the amplitude pass mirrors them
+        z.pair_nvir = (int32_t)nvir;   // blocks j < k: the amplitude pass mirrors them (pair_k0 = pair_j0 = pair_lo = 0)
         z.status = status;
         oz[0].push_back(z);
-        oz_pre[0].push_back(oz_pre[0].back() + (int64_t)z.tiles_m * z.tiles_n);
+        oz_pre[0].push_back(oz_pre[0].back() + oz8_tiles(z));
         // digits of every B row (both operands of the (ia|jb) products)
         add_dop(0, DigitOp{q.B, naux, L, naux, P.kpv, 0, relp<int8_t>(base + P.off_dbv),
                            relp<int32_t>(base + P.off_ev), nullptr, status}, L, 0, 0, 0);
@@ -1307,7 +1329,7 @@ int batch_plan(int32_t nfrag, const rimp2_frag_desc* d, const rimp2_opts* opts, 
           y.tiles_m = (int32_t)cdiv(L, 64); y.tiles_n = (int32_t)cdiv(naux, 64); y.group_m = 8;
           y.status = status;
           oz[1].push_back(y);
-          oz_pre[1].push_back(oz_pre[1].back() + (int64_t)y.tiles_m * y.tiles_n);
+          oz_pre[1].push_back(oz_pre[1].back() + oz8_tiles(y));
           // column digits of B (maxima first) and row digits of the T slab
           unsigned long long* cm = relp<unsigned long long>(base + P.off_cmax);
           const int64_t gxm = cdiv(naux, 256), gxd = cdiv(P.kpg, 32);
@@ -1537,8 +1559,8 @@ int batch_run(rimp2_batch_s* B, int32_t* status_dev, void* workspace, size_t byt
            hipLaunchKernelGGL(relocate_tables_kernel, dim3((unsigned)cdiv(m, 256)), dim3(256), 0, st, ws, gp0, 0,
                               (AmpDesc*)at(W.o_amp), n, (ReduceDesc*)at(W.o_red), W.nred_ab, (FragSmall*)at(W.o_fs),
                               n);
-           hipLaunchKernelGGL(zero_counters_kernel, dim3(1), dim3(64), 0, st, (unsigned long long*)at(W.o_cnt),
-                              kGLists);
+           hipLaunchKernelGGL(zero_u64_kernel, dim3(1), dim3(256), 0, st, (unsigned long long*)at(W.o_cnt),
+                              (int64_t)kGLists);
            hipLaunchKernelGGL(gap_check_grouped, dim3((unsigned)n), dim3(256), 0, st, (const FragSmall*)at(W.o_fs));
            if (B->split) {
              for (int r = 0; r < 2; ++r)
@@ -1549,7 +1571,7 @@ int batch_run(rimp2_batch_s* B, int32_t* status_dev, void* workspace, size_t byt
                if (W.n_dop[r])
                  hipLaunchKernelGGL(relocate_digit_kernel, dim3((unsigned)cdiv(W.n_dop[r], 256)), dim3(256), 0, st,
                                     ws, (DigitOp*)at(W.o_dop[r]), W.n_dop[r]);
-             const int nc = W.win_oz[0] + W.win_oz[1];
+             const int nc = kQueues * (W.win_oz[0] + W.win_oz[1]);
              if (nc)
                hipLaunchKernelGGL(zero_u64_kernel, dim3((unsigned)cdiv(nc, 256)), dim3(256), 0, st,
                                   (unsigned long long*)at(W.o_cnt_oz), (int64_t)nc);
@@ -1619,9 +1641,9 @@ int batch_run(rimp2_batch_s* B, int32_t* status_dev, void* workspace, size_t byt
       }
       if (W.n_oz[r] == 0) return RIMP2_OK;
       const int S = r == 0 ? B->plan[W.frags[0]].sv : B->plan[W.frags[0]].sg;
-      unsigned long long* cnt = (unsigned long long*)at(W.o_cnt_oz) + (r == 0 ? 0 : W.win_oz[0]);
+      unsigned long long* cnt = (unsigned long long*)at(W.o_cnt_oz) + (r == 0 ? 0 : W.win_oz[0] * kQueues);
       for (int w = 0; w < W.win_oz[r]; ++w) {
-        const OzGroup G{(const OzParams*)at(W.o_oz[r]), (const int64_t*)at(W.o_oz_pre[r]), W.n_oz[r], cnt + w};
+        const OzGroup G{(const OzParams*)at(W.o_oz[r]), (const int64_t*)at(W.o_oz_pre[r]), W.n_oz[r], cnt + w * kQueues};
         const int role = r == 0 ? R_INTS8 : R_GAMMA8;
         RIMP2_SWITCH_S(S, rc2 = launch_oz8_grouped<SS>(G, W.items_oz[r], w, role, st));
         if (rc2) return rc2;

@@ -136,7 +136,10 @@ struct OzParams {
   double* C;
   int64_t ldc;
   int32_t tiles_m, tiles_n, group_m;
-  int32_t pair_nvir;           // > 0: skip tiles below the pair-block diagonal (see oz8_tile_skipped)
+  // pair_nvir > 0: rows are (k, a) from orbital pair_k0 (a_row0 = pair_k0
+  // pair_nvir), columns (j, b) from orbital pair_j0, and tiles that hold only
+  // pairs pair_lo <= j < k are left out (oz8_tile_skipped, decode_pair_tile)
+  int32_t pair_nvir, pair_k0, pair_j0, pair_lo;
   const int32_t* status;
 };
 
@@ -155,13 +158,25 @@ struct OzLds {
   static constexpr int STAGE = S * 2 * 4 * 1024;   // S slices x (A, B) x 4 row blocks x 1 KB
 };
 
-// Tiles entirely below the pair-block diagonal (every column block j before
-// every row block k) are skipped when p.pair_nvir > 0: the amplitude pass
-// forms those blocks from their mirror.
+// A tile whose pairs all have pair_lo <= j < k is skipped when p.pair_nvir >
+// 0: the amplitude pass forms those blocks from their mirror.
 __device__ __forceinline__ bool oz8_tile_skipped(const OzParams& p, int64_t m0, int64_t n0) {
   if (p.pair_nvir <= 0) return false;
-  const int64_t last_j = min(n0 + 63, p.N - 1) / p.pair_nvir, first_k = (p.a_row0 + m0) / p.pair_nvir;
-  return last_j < first_k;
+  return p.pair_j0 + min(n0 + 63, p.N - 1) / p.pair_nvir < p.pair_k0 + m0 / p.pair_nvir &&
+         p.pair_j0 + n0 / p.pair_nvir >= p.pair_lo;
+}
+
+// Logical tile t of a launch: raster groups of group_m row tiles, of a pair
+// launch the tiles they keep.
+__device__ __forceinline__ void oz8_decode(const OzParams& p, int t, int& tm, int& tn) {
+  if (p.pair_nvir > 0) {
+    decode_pair_tile(t, p.pair_k0, p.pair_j0, p.pair_lo, p.pair_nvir, 64, 64, p.tiles_m, p.tiles_n, p.group_m, tm, tn);
+  } else {
+    const int gsz = p.group_m * p.tiles_n, grp = t / gsz, first_m = grp * p.group_m;
+    const int gm = min(p.group_m, p.tiles_m - first_m), tin = t - grp * gsz;
+    tm = first_m + tin % gm;
+    tn = tin / gm;
+  }
 }
 
 // One 64 x 64 output tile at (m0, n0) over the reduction window [k0, k0 + kc).
@@ -299,17 +314,45 @@ __global__ __launch_bounds__(256, 2) void gemm_oz8_kernel(OzParams p) {
   if (p.status != nullptr && *p.status != 0) return;
   __shared__ __attribute__((aligned(1024))) int8_t lds[NBUF][OzLds<S>::STAGE];
   const int wl = xcd_remap(blockIdx.x, gridDim.x);
-  const int gsz = p.group_m * p.tiles_n, grp = wl / gsz, first_m = grp * p.group_m;
-  const int gm = min(p.group_m, p.tiles_m - first_m), tin = wl - grp * gsz;
-  const int64_t m0 = (int64_t)(first_m + tin % gm) * 64, n0 = (int64_t)(tin / gm) * 64;
+  int tm, tn;
+  oz8_decode(p, wl, tm, tn);
+  const int64_t m0 = (int64_t)tm * 64, n0 = (int64_t)tn * 64;
   if (oz8_tile_skipped(p, m0, n0)) return;
   oz8_tile<S, NBUF>(p, m0, n0, lds);
 }
 
+// Work queues of a persistent grouped launch: kQueues counters (all zero at
+// launch), one per XCD (workgroups are dispatched round-robin over them).
+// Queue q owns the blocks q, q + 8, q + 16, ... of kQueueBlock consecutive
+// items, so the 64 workgroups an XCD holds work on neighbouring tiles and share
+// their operand panels in its L2, as the one-tile launches do (xcd_remap); a
+// workgroup whose queue is used up goes on to the next one, and ends after the
+// last.  A queue's items grow with its counter, so once one is past the end
+// all later ones are.  No workgroup waits on another.  From one counter each
+// XCD saw every eighth tile: the grouped split Gamma products of eight
+// fragments (nocc 5 to 72) took 72 ms, and 60 ms with queues and rasters.
+// (The FP64 grouped products are MFMA-bound and keep one counter: queues left
+// the large ones as they were, and the P_ij splits, few items, lost 30%.)
+constexpr int kQueues = 8, kQueueBlock = 64;
+__device__ __forceinline__ long long queue_item(unsigned long long n, int q) {
+  return (long long)((n / kQueueBlock * kQueues + q) * kQueueBlock + n % kQueueBlock);
+}
+// Item of count n taken from queue q, or of the following queues (-1: none is
+// left); `left` counts the queues not yet seen to be used up.
+__device__ __forceinline__ long long queue_resolve(unsigned long long* counter, long long total, unsigned long long n,
+                                                   int& q, int& left) {
+  long long t = queue_item(n, q);
+  while (t >= total && --left > 0) {
+    q = (q + 1) % kQueues;
+    t = queue_item(atomicAdd(counter + q, 1ull), q);
+  }
+  return t < total ? t : -1;
+}
+
 // Persistent grouped launch over the split products of many fragments:
 // problem f owns work items [prefix[f], prefix[f+1]) = its tiles, problems
-// ordered largest first.  Each workgroup takes items from *counter (zero at
-// launch) until all are taken, so every workgroup exits.  window >= 0 runs
+// ordered largest first.  Each workgroup takes items from the queues
+// (queue_resolve) until all are taken.  window >= 0 runs
 // reduction window `window` of every problem (k0 = window * wlen, the first
 // window stores and later ones add into C; problems with fewer windows skip
 // their items); window < 0 runs each problem's whole reduction.
@@ -317,20 +360,26 @@ struct OzGroup {
   const OzParams* probs;
   const int64_t* prefix;   // [nprob + 1]
   int32_t nprob;
-  unsigned long long* counter;
+  unsigned long long* counter;   // [kQueues]
 };
 
 template <int S, int NBUF>
 __global__ __launch_bounds__(256, 2) void gemm_oz8_grouped(OzGroup G, int64_t window, int64_t wlen) {
   __shared__ __attribute__((aligned(1024))) int8_t lds[NBUF][OzLds<S>::STAGE];
-  __shared__ long long item;
+  // the item is passed on in the stage's own LDS: with two stages of 5 digits
+  // (80 KB) a word more would leave one workgroup on a CU instead of two
+  // (Gamma windows of two fragments of 72/360/1296: 6.2 -> 2.9 ms each)
+  long long* item = (long long*)&lds[0][0];
   const long long total = G.prefix[G.nprob];
+  int queue = blockIdx.x % kQueues, left = kQueues;
   for (;;) {
-    if (threadIdx.x == 0) item = (long long)atomicAdd(G.counter, 1ull);
+    __syncthreads();   // every wave is done with the last tile's stage
+    if (threadIdx.x == 0)
+      *item = queue_resolve(G.counter, total, left > 0 ? atomicAdd(G.counter + queue, 1ull) : 0, queue, left);
     __syncthreads();
-    const long long t = item;
+    const long long t = *item;
     __syncthreads();
-    if (t >= total) break;
+    if (t < 0) break;
     int lo = 0, hi = G.nprob - 1;   // last f with prefix[f] <= t
     while (lo < hi) {
       const int mid = (lo + hi + 1) >> 1;
@@ -345,7 +394,9 @@ __global__ __launch_bounds__(256, 2) void gemm_oz8_grouped(OzGroup G, int64_t wi
       p.accumulate = window > 0;
     }
     const int64_t u = t - G.prefix[lo];
-    const int64_t m0 = (u % p.tiles_m) * 64, n0 = (u / p.tiles_m) * 64;
+    int tm, tn;
+    oz8_decode(p, (int)u, tm, tn);
+    const int64_t m0 = (int64_t)tm * 64, n0 = (int64_t)tn * 64;
     if (oz8_tile_skipped(p, m0, n0)) continue;
     oz8_tile<S, NBUF>(p, m0, n0, lds);
   }

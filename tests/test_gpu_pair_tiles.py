@@ -18,7 +18,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("shape,g", [((3, 5, 6), 1), ((9, 128, 16), 4), ((13, 211, 18), 5), ((40, 33, 20), 7),
                                      ((82, 808, 2), 20)])
-@pytest.mark.parametrize("precision", [rm.FP64])
+@pytest.mark.parametrize("precision", [rm.FP64, rm.SPLIT_INT8])
 def test_one_slab_equals_small_groups(shape, g, precision):
     nocc, nvir, naux = shape
     gen = torch.Generator(device="cuda:0")
