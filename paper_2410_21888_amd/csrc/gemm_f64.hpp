@@ -21,11 +21,12 @@
 // register r of lane l holds D[4r + l/16][l%16].  Operand tiles are staged
 // k-major in LDS (double-buffered, one barrier per BK chunk).  Global loads
 // are 16 bytes (two consecutive reduction indices, or two consecutive columns
-// of an N-contiguous operand) when the operands allow it (VEC).  Two loaders:
-// the general one (FAST = 0) issues the next chunk's loads before the current
-// chunk's MFMAs and stores them to LDS halfway through them, with masks on
-// edge tiles; the fast one (FAST = 1, 2; chosen by the host) keeps loads two
-// chunks ahead without any branch around them (see gemm_tile).
+// of an N-contiguous operand).  Two loaders: the general one (FAST = 0, 16-byte
+// loads where VEC says that they are aligned) issues the next chunk's loads
+// before the current chunk's MFMAs and stores them to LDS halfway through
+// them, with masks on edge tiles; the fast one (FAST = 1, 2, 3; chosen by the
+// host) keeps loads two chunks ahead without any branch around them (see
+// gemm_tile).
 //
 // Triangular launches (TRI): for a symmetric result only tiles with
 // tile_m <= tile_n are computed; every element m < n is written at (m, n) and
@@ -220,6 +221,7 @@ template <int BM, int BN, int BK, bool B_NCONTIG, bool VEC, bool TRI, int FAST, 
 __device__ __forceinline__ void gemm_tile(const GemmParams& p, int tm, int tn, int z, GemmLds<BM, BN, BK>& lds) {
   static_assert(BM % 32 == 0 && BN % 32 == 0 && BK % 8 == 0, "tile shape");
   typedef double d2 __attribute__((ext_vector_type(2)));
+  typedef double d2u __attribute__((ext_vector_type(2), aligned(8)));   // a 16-byte load at any double
 
   constexpr int LDA = BM + 2, LDB = BN + 2;
   constexpr int WTM = BM / 2, WTN = BN / 2, MI = WTM / 16, NI = WTN / 16;
@@ -342,6 +344,9 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, int tm, int tn, i
     }
   };
 #undef RIMP2_KLOAD
+  // FAST: the pair of an odd matrix's last row (column) is read one element
+  // early, at M - 2 (N - 2), and its second element moved to the first place
+  const bool lastA = FAST > 0 && A_MC && m0 + mm == p.M - 1, lastB = FAST > 0 && B_NCONTIG && n0 + nn == p.N - 1;
   auto store_from = [&](int buf, const d2 (&sa)[AREG], const d2 (&sb)[BREG]) {
     if (!A_MC) {
 #pragma unroll
@@ -351,7 +356,7 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, int tm, int tn, i
       }
     } else {
 #pragma unroll
-      for (int s = 0; s < AREG; ++s) *(d2*)&As[buf][(km0 + s * MSTEP) * LDA + mm] = sa[s];
+      for (int s = 0; s < AREG; ++s) *(d2*)&As[buf][(km0 + s * MSTEP) * LDA + mm] = d2{lastA ? sa[s][1] : sa[s][0], sa[s][1]};
     }
     if (!B_NCONTIG) {
 #pragma unroll
@@ -361,7 +366,7 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, int tm, int tn, i
       }
     } else {
 #pragma unroll
-      for (int s = 0; s < BNN; ++s) *(d2*)&Bs[buf][(kn0 + s * NSTEP) * LDB + nn] = sb[s];
+      for (int s = 0; s < BNN; ++s) *(d2*)&Bs[buf][(kn0 + s * NSTEP) * LDB + nn] = d2{lastB ? sb[s][1] : sb[s][0], sb[s][1]};
     }
   };
   auto store_chunk = [&](int buf) { store_from(buf, ra, rb); };
@@ -380,17 +385,22 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, int tm, int tn, i
 #pragma unroll
     for (int j = 0; j < NI; ++j) acc[i][j] = dbl4{0.0, 0.0, 0.0, 0.0};
 
-  // FAST > 0 (chosen by the host: 16-byte loads, an even reduction length,
-  // runs of the K operands at least one chunk long): the split's full chunks
-  // go through a branch-free loader that issues each chunk's global loads two
-  // chunks ahead into two register sets.  Rows (and N-contiguous column
-  // pairs) past the edge of the matrix read the last valid ones, which only
-  // reach accumulators that are never stored.  The loads are unconditional
-  // (after the last full chunk it is loaded again), so the compiler's wait
-  // counts stay exact, and the barriers order LDS only, so the loads stay in
-  // flight across them.  Chunk starts advance by uniform run steps; with
-  // FAST = 2 (runs shorter than the reduction and not a multiple of the chunk)
-  // a thread whose pair lies in the next run adds one run step.  A ragged
+  // FAST > 0 (chosen by the host: runs of the K operands at least one chunk
+  // long, at least two rows or columns of an M- or N-contiguous operand): the
+  // split's full chunks go through a branch-free loader that issues each
+  // chunk's global loads two chunks ahead into two register sets.  Rows (and
+  // N-contiguous column pairs) past the edge of the matrix read the last valid
+  // ones, which only reach accumulators that are never stored.  The loads are
+  // unconditional (after the last full chunk it is loaded again), so the
+  // compiler's wait counts stay exact, and the barriers order LDS only, so the
+  // loads stay in flight across them.  A pair of doubles is one 16-byte load
+  // at any 8-byte address: an odd row stride costs a second cache line per
+  // 128-byte run, which the loads' two-chunk lead covers (measured against the
+  // general loader's 8-byte loads: see fast_level).  Chunk starts advance by
+  // uniform run steps; with FAST = 2 (even runs shorter than the reduction and
+  // not a multiple of the chunk) a thread whose pair lies in the next run adds
+  // one run step, and with FAST = 3 (odd runs, so that a pair can lie in two)
+  // each element of a pair is loaded by itself with its own step.  A ragged
   // last chunk is then loaded with per-element masks and run on its own.
   // Every path sums each output element in the same order.
   if constexpr (FAST > 0) {
@@ -410,7 +420,7 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, int tm, int tn, i
 #pragma unroll
         for (int s = 0; s < AREG; ++s) ap[s] = p.A.base + min(m0 + r0 + s * RSTEP, p.M - 1) * p.A.rs + kk;
       } else {
-        const int64_t m = min(m0 + mm, p.M - 2);   // M is even here
+        const int64_t m = min(m0 + mm, p.M - 2);
 #pragma unroll
         for (int s = 0; s < AREG; ++s) ap[s] = p.Am.base + (int64_t)(km0 + s * MSTEP) * p.Am.ld + m;
       }
@@ -419,21 +429,33 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, int tm, int tn, i
 #pragma unroll
         for (int s = 0; s < BREG; ++s) bp[s] = p.Bk.base + min(n0 + r0 + s * RSTEP, p.N - 1) * p.Bk.rs + kk;
       } else {
-        const int64_t n = min(n0 + nn, p.N - 2);   // N is even here
+        const int64_t n = min(n0 + nn, p.N - 2);
 #pragma unroll
         for (int s = 0; s < BREG; ++s) bp[s] = p.Bn.base + (int64_t)(kn0 + s * NSTEP) * p.Bn.ld + n;
       }
-      // this thread's extra offset when its pair lies in the run after the chunk start's
-      auto wrap = [&](const KOperand& o, int64_t pos) -> int64_t {
-        return (FAST == 2 && pos + kk >= o.kdiv) ? o.ks1 - o.kdiv : 0;
+      // extra offset of element kk + d of this thread when it lies in the run after the chunk start's
+      auto wrap = [&](const KOperand& o, int64_t pos, int d) -> int64_t {
+        return (FAST >= 2 && pos + kk + d >= o.kdiv) ? o.ks1 - o.kdiv : 0;
       };
       auto fload = [&](d2 (&da)[AREG], d2 (&db)[BREG]) {
-        const int64_t xa_ = A_MC ? oa : oa + wrap(p.A, pa);
+        if (!A_MC && FAST == 3) {
+          const int64_t x0 = oa + wrap(p.A, pa, 0), x1 = oa + wrap(p.A, pa, 1) + 1;
 #pragma unroll
-        for (int s = 0; s < AREG; ++s) da[s] = *(const d2*)(ap[s] + xa_);
-        const int64_t xb_ = B_NCONTIG ? ob : ob + wrap(p.Bk, pb);
+          for (int s = 0; s < AREG; ++s) da[s] = d2{ap[s][x0], ap[s][x1]};
+        } else {
+          const int64_t xa_ = A_MC ? oa : oa + wrap(p.A, pa, 0);
 #pragma unroll
-        for (int s = 0; s < BREG; ++s) db[s] = *(const d2*)(bp[s] + xb_);
+          for (int s = 0; s < AREG; ++s) da[s] = *(const d2u*)(ap[s] + xa_);
+        }
+        if (!B_NCONTIG && FAST == 3) {
+          const int64_t x0 = ob + wrap(p.Bk, pb, 0), x1 = ob + wrap(p.Bk, pb, 1) + 1;
+#pragma unroll
+          for (int s = 0; s < BREG; ++s) db[s] = d2{bp[s][x0], bp[s][x1]};
+        } else {
+          const int64_t xb_ = B_NCONTIG ? ob : ob + wrap(p.Bk, pb, 0);
+#pragma unroll
+          for (int s = 0; s < BREG; ++s) db[s] = *(const d2u*)(bp[s] + xb_);
+        }
         if (++nload < nfull) {
           if (A_MC) {
             oa += (int64_t)BK * p.Am.ld;
@@ -479,39 +501,40 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, int tm, int tn, i
       if (c < nfull) step(c, std::integral_constant<int, 0>{});
     }
     if (nfull < nchunks) {
-      // the ragged last chunk: per-element masks (pairs, as the reduction length is even)
+      // the ragged last chunk: per-element masks
       const int64_t kt = kbeg + (int64_t)nfull * BK;
       const d2 zero = {0.0, 0.0};
-      if (!A_MC) {
+      // elements k and k + 1 of the row at `row` (0 past the end of the reduction)
+      auto kpair = [&](const KOperand& o, const double* row) {
         const int64_t k = kt + kk;
-        const bool in = k < kend;
-        const int64_t q = in ? k / p.A.kdiv : 0;
-        const int64_t off = in ? q * p.A.ks1 + (k - q * p.A.kdiv) : 0;
+        d2 v = zero;
+        if (k < kend) {
+          const int64_t q = k / o.kdiv, r = k - q * o.kdiv;
+          v[0] = row[q * o.ks1 + r];
+          if (k + 1 < kend) v[1] = row[r + 1 < o.kdiv ? q * o.ks1 + r + 1 : (q + 1) * o.ks1];
+        }
+        return v;
+      };
+      if (!A_MC) {
 #pragma unroll
-        for (int s = 0; s < AREG; ++s)
-          ra[s] = in ? *(const d2*)(p.A.base + min(m0 + r0 + s * RSTEP, p.M - 1) * p.A.rs + off) : zero;
+        for (int s = 0; s < AREG; ++s) ra[s] = kpair(p.A, p.A.base + min(m0 + r0 + s * RSTEP, p.M - 1) * p.A.rs);
       } else {
         const int64_t m = min(m0 + mm, p.M - 2);
 #pragma unroll
         for (int s = 0; s < AREG; ++s) {
           const int64_t k = kt + km0 + s * MSTEP;
-          ra[s] = k < kend ? *(const d2*)(p.Am.base + k * p.Am.ld + m) : zero;
+          ra[s] = k < kend ? (d2)*(const d2u*)(p.Am.base + k * p.Am.ld + m) : zero;
         }
       }
       if (!B_NCONTIG) {
-        const int64_t k = kt + kk;
-        const bool in = k < kend;
-        const int64_t q = in ? k / p.Bk.kdiv : 0;
-        const int64_t off = in ? q * p.Bk.ks1 + (k - q * p.Bk.kdiv) : 0;
 #pragma unroll
-        for (int s = 0; s < BREG; ++s)
-          rb[s] = in ? *(const d2*)(p.Bk.base + min(n0 + r0 + s * RSTEP, p.N - 1) * p.Bk.rs + off) : zero;
+        for (int s = 0; s < BREG; ++s) rb[s] = kpair(p.Bk, p.Bk.base + min(n0 + r0 + s * RSTEP, p.N - 1) * p.Bk.rs);
       } else {
         const int64_t n = min(n0 + nn, p.N - 2);
 #pragma unroll
         for (int s = 0; s < BREG; ++s) {
           const int64_t k = kt + kn0 + s * NSTEP;
-          rb[s] = k < kend ? *(const d2*)(p.Bn.base + k * p.Bn.ld + n) : zero;
+          rb[s] = k < kend ? (d2)*(const d2u*)(p.Bn.base + k * p.Bn.ld + n) : zero;
         }
       }
       store_chunk(0);
@@ -607,7 +630,8 @@ __global__ __launch_bounds__(256, 2) void gemm_f64_grouped(GemmGroup G) {
   for (;;) {
     if (threadIdx.x == 0) item = (long long)atomicAdd(G.counter, 1ull);
     __syncthreads();
-    const long long t = item;
+    // the same in every lane: readfirstlane keeps the problem in scalar registers
+    const long long t = __builtin_amdgcn_readfirstlane((int)item);
     __syncthreads();
     if (t >= total) break;
     int lo = 0, hi = G.nprob - 1;   // last f with prefix[f] <= t

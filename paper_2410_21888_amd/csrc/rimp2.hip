@@ -346,22 +346,18 @@ bool gemm_vec(const GemmParams& gp, bool nc, bool amc = false) {
   return a && (nc ? ((uintptr_t)gp.Bn.base % 16 == 0 && gp.Bn.ld % 2 == 0) : kop_vec(gp.Bk, gp.K));
 }
 
-// The kernels' FAST path (returns 0 when it does not apply): 16-byte loads,
-// an even reduction length (no reduction pair straddles the end), runs of the
-// K operands at least one chunk long (a chunk crosses at most one run
-// boundary) and an even N for an N-contiguous B (its column pairs past the
-// edge are read at N - 2; likewise an even M for an M-contiguous A).  2 when
-// a K operand's runs can end inside a chunk.
+// The kernels' FAST level of a GEMM (0: the general loader).  It needs runs of
+// the K operands at least one chunk long (a chunk crosses at most one run
+// boundary) and two rows (columns) of an M-contiguous A (N-contiguous B) to
+// read a pair from.  2 when a K operand's runs are even and can end inside a
+// chunk, 3 when they are odd; alignment, odd strides and odd lengths do not
+// matter.  (Odd sizes took the general loader with 8-byte loads: Gamma of
+// nocc = 97, nvir = 485, naux = 1746 ran at 57 TFLOP/s, and at 64 here.)
 int fast_level(const GemmParams& gp, bool nc, bool amc = false) {
   auto runs = [&](const KOperand& o) { return o.kdiv >= gp.K || o.kdiv >= kBK; };
-  auto wraps = [&](const KOperand& o) { return o.kdiv < gp.K && o.kdiv % kBK != 0; };
-  if (!(gp.K % 2 == 0 && gp.kchunk % kBK == 0 && (amc ? gp.M % 2 == 0 : runs(gp.A)) &&
-        (nc ? gp.N % 2 == 0 : runs(gp.Bk))))
-    return 0;
-  return ((!amc && wraps(gp.A)) || (!nc && wraps(gp.Bk))) ? 2 : 1;
-}
-int gemm_fast(const GemmParams& gp, bool nc, bool amc = false) {
-  return gemm_vec(gp, nc, amc) ? fast_level(gp, nc, amc) : 0;
+  auto level = [&](const KOperand& o) { return o.kdiv >= gp.K || o.kdiv % kBK == 0 ? 1 : o.kdiv % 2 == 0 ? 2 : 3; };
+  if (!(gp.kchunk % kBK == 0 && (amc ? gp.M >= 2 : runs(gp.A)) && (nc ? gp.N >= 2 : runs(gp.Bk)))) return 0;
+  return std::max(amc ? 1 : level(gp.A), nc ? 1 : level(gp.Bk));
 }
 
 // Output tiles (of one split) a GEMM launches workgroups for: the upper
@@ -406,14 +402,20 @@ int launch_gemm(GemmParams gp, hipStream_t st, int role, double af, double ab, b
     }
     ef *= (double)kept / ((double)gp.tiles_m * gp.tiles_n);
   }
-  const int fast = general ? 0 : gemm_fast(gp, NC, AMC);
+  const int fast = general ? 0 : fast_level(gp, NC, AMC);
+  // the roles whose K operands have runs
+  constexpr bool RUNS = ROLE == ROLE_PAB || ROLE == ROLE_PIJ || ROLE == ROLE_LTERM;
+  if (!RUNS && fast > 1) return fail(RIMP2_EINVAL, "GEMM role %d with a two-level reduction", ROLE);
   return traced(role, af, ef, ab, st, [&] {
     if (fast == 1)
       hipLaunchKernelGGL((gemm_f64_kernel<BM, BN, kBK, NC, ROLE, true, TRI, 1>), dim3((unsigned)nwg), dim3(256), 0,
                          st, gp);
-    else if (fast == 2)
-      hipLaunchKernelGGL((gemm_f64_kernel<BM, BN, kBK, NC, ROLE, true, TRI, 2>), dim3((unsigned)nwg), dim3(256), 0,
-                         st, gp);
+    else if (RUNS && fast == 2)
+      hipLaunchKernelGGL((gemm_f64_kernel<BM, BN, kBK, NC, ROLE, true, TRI, RUNS ? 2 : 0>), dim3((unsigned)nwg),
+                         dim3(256), 0, st, gp);
+    else if (RUNS && fast == 3)
+      hipLaunchKernelGGL((gemm_f64_kernel<BM, BN, kBK, NC, ROLE, true, TRI, RUNS ? 3 : 0>), dim3((unsigned)nwg),
+                         dim3(256), 0, st, gp);
     else if (vec)
       hipLaunchKernelGGL((gemm_f64_kernel<BM, BN, kBK, NC, ROLE, true, TRI>), dim3((unsigned)nwg), dim3(256), 0, st, gp);
     else
@@ -1064,10 +1066,10 @@ struct DigitOp {
 };
 
 // ---- batches -----------------------------------------------------------------
-// Grouped GEMM lists of a wave: 4 roles x 2 candidate tiles x 4 loaders
-// (0: two chunks ahead, 1: the same with runs ending inside chunks, 2: the
-// general loader with 16-byte loads, 3: the general loader, 8-byte loads).
-constexpr int kGLists = 32;
+// Grouped GEMM lists of a wave: 4 roles x 2 candidate tiles x 5 loaders
+// (0, 1, 2: the fast loader's levels 1, 2, 3; 3: the general loader with
+// 16-byte loads, 4: the general loader, 8-byte loads).
+constexpr int kGLoaders = 5, kGLists = 8 * kGLoaders;
 struct GemmList {            // grouped GEMM problems of one role in one wave
   std::vector<GemmParams> p;
   std::vector<int64_t> prefix;  // work items (tiles x splits)
@@ -1131,14 +1133,12 @@ bool kop_vec_rel(const KOperand& o, int64_t K) {
 // first) and list index.
 const int kBatchRole[4] = {R_INTS, R_GAMMA, R_PAB, R_PIJ};
 const int kBatchTile[4][2] = {{128, 64}, {128, 64}, {128, 64}, {64, 32}};
-int glist(int rho, int cand, int loader) { return (rho * 2 + cand) * 4 + loader; }
-// loader of a grouped GEMM (see kGLists); vec: 16-byte loads apply; general:
-// the general loader only
+int glist(int rho, int cand, int loader) { return (rho * 2 + cand) * kGLoaders + loader; }
+// loader of a grouped GEMM (see kGLists); vec: 16-byte loads are aligned;
+// general: the general loader only
 int loader_of(const GemmParams& g, bool nc, bool vec, bool general) {
-  if (!vec) return 3;
-  if (general) return 2;
-  const int f = fast_level(g, nc);
-  return f ? f - 1 : 2;
+  const int f = general ? 0 : fast_level(g, nc);
+  return f ? f - 1 : vec ? 3 : 4;
 }
 
 // tiles, splits and group size of a GEMM, as launch_gemm sets them
@@ -1437,24 +1437,24 @@ int launch_grouped(const GemmGroup& G, int64_t items, int role, hipStream_t st) 
 // its list of one loader (see kGLists).
 int launch_group_list(int rho, int c, int loader, const GemmGroup& G, int64_t items, hipStream_t st) {
   const int role = kBatchRole[rho];
-// (the 128 x 128 Gamma tile with the fast loader runs out of registers in the
-// persistent loop: its fast lists take the general 16-byte loader)
-#define RIMP2_G(BM, NC, ROLE, TRI, F1, F2)                                                            \
+#define RIMP2_G(BM, NC, ROLE, TRI, F2, F3)                                                            \
   switch (loader) {                                                                                   \
-    case 0: return launch_grouped<BM, BM, NC, ROLE, true, TRI, F1>(G, items, role, st);               \
+    case 0: return launch_grouped<BM, BM, NC, ROLE, true, TRI, 1>(G, items, role, st);                \
     case 1: return launch_grouped<BM, BM, NC, ROLE, true, TRI, F2>(G, items, role, st);               \
-    case 2: return launch_grouped<BM, BM, NC, ROLE, true, TRI, 0>(G, items, role, st);                \
+    case 2: return launch_grouped<BM, BM, NC, ROLE, true, TRI, F3>(G, items, role, st);               \
+    case 3: return launch_grouped<BM, BM, NC, ROLE, true, TRI, 0>(G, items, role, st);                \
     default: return launch_grouped<BM, BM, NC, ROLE, false, TRI, 0>(G, items, role, st);              \
   }
   switch (rho * 2 + c) {
-    case 0: RIMP2_G(128, false, ROLE_INTS, false, 1, 2);
-    case 1: RIMP2_G(64, false, ROLE_INTS, false, 1, 2);
-    case 2: RIMP2_G(128, true, ROLE_GAMMA, false, 0, 0);
-    case 3: RIMP2_G(64, true, ROLE_GAMMA, false, 1, 2);
-    case 4: RIMP2_G(128, false, ROLE_PAB, true, 1, 2);
-    case 5: RIMP2_G(64, false, ROLE_PAB, true, 1, 2);
-    case 6: RIMP2_G(64, false, ROLE_PIJ, true, 1, 2);
-    default: RIMP2_G(32, false, ROLE_PIJ, true, 1, 2);
+    // (ia|jb) and Gamma have no runs: their lists hold loader 0 or a general one
+    case 0: RIMP2_G(128, false, ROLE_INTS, false, 1, 1);
+    case 1: RIMP2_G(64, false, ROLE_INTS, false, 1, 1);
+    case 2: RIMP2_G(128, true, ROLE_GAMMA, false, 1, 1);
+    case 3: RIMP2_G(64, true, ROLE_GAMMA, false, 1, 1);
+    case 4: RIMP2_G(128, false, ROLE_PAB, true, 2, 3);
+    case 5: RIMP2_G(64, false, ROLE_PAB, true, 2, 3);
+    case 6: RIMP2_G(64, false, ROLE_PIJ, true, 2, 3);
+    default: RIMP2_G(32, false, ROLE_PIJ, true, 2, 3);
   }
 #undef RIMP2_G
 }
@@ -1587,13 +1587,13 @@ int batch_run(rimp2_batch_s* B, int32_t* status_dev, void* workspace, size_t byt
     auto run_role = [&](int rho) -> int {
       auto items_of = [&](int c) {
         int64_t n = 0;
-        for (int k = 0; k < 4; ++k) n += W.items_g[glist(rho, c, k)];
+        for (int k = 0; k < kGLoaders; ++k) n += W.items_g[glist(rho, c, k)];
         return n;
       };
       const int64_t i0 = items_of(0);
       if (i0 == 0) return RIMP2_OK;
       auto launch = [&](int c) -> int {
-        for (int k = 0; k < 4; ++k) {
+        for (int k = 0; k < kGLoaders; ++k) {
           const int li = glist(rho, c, k);
           const int r = launch_group_list(rho, c, k, grp(li), W.items_g[li], st);
           if (r) return r;
