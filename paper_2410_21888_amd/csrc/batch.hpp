@@ -102,13 +102,13 @@ __global__ __launch_bounds__(256) void amplitude_grouped(const AmpDesc* descs, c
                   j, 0, 1, nullptr);
 }
 
-// prefix counts 256-element blocks per problem
+// prefix counts reduce_blocks per problem
 __global__ __launch_bounds__(256) void reduce_grouped(const ReduceDesc* descs, const int64_t* prefix, int n) {
   const int f = find_problem(prefix, n, blockIdx.x);
   const ReduceDesc r = descs[f];
   if (*r.status != 0) return;
-  const int64_t idx = (blockIdx.x - prefix[f]) * 256 + threadIdx.x;
-  splitk_reduce_at(r.out, r.ldo, r.W, r.ldw, r.zs, r.splits, r.M, r.N, r.alpha, r.accumulate, idx);
+  splitk_reduce_block(r.out, r.ldo, r.W, r.ldw, r.zs, r.splits, r.M, r.N, r.alpha, r.accumulate,
+                      blockIdx.x - prefix[f]);
 }
 
 __global__ __launch_bounds__(256) void energy_sum_grouped(const FragSmall* fs) {

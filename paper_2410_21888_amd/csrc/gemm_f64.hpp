@@ -245,7 +245,12 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, int tm, int tn, i
 
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int wm = wv >> 1, wn = wv & 1;
-  const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
+  // FAST: the last tile along an M-contiguous A (N-contiguous B) starts early
+  // enough to hold whole pairs only, and stores its own rows (columns) from
+  // mlo (nlo) on; a matrix narrower than the tile is even (fast_level)
+  const int64_t mlo = (int64_t)tm * BM, nlo = (int64_t)tn * BN;
+  const int64_t m0 = FAST > 0 && A_MC ? max((int64_t)0, min(mlo, p.M - BM)) : mlo;
+  const int64_t n0 = FAST > 0 && B_NCONTIG ? max((int64_t)0, min(nlo, p.N - BN)) : nlo;
 
   const int64_t kbeg = (int64_t)z * p.kchunk;
   const int64_t kend = min(p.K, kbeg + p.kchunk);
@@ -344,9 +349,6 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, int tm, int tn, i
     }
   };
 #undef RIMP2_KLOAD
-  // FAST: the pair of an odd matrix's last row (column) is read one element
-  // early, at M - 2 (N - 2), and its second element moved to the first place
-  const bool lastA = FAST > 0 && A_MC && m0 + mm == p.M - 1, lastB = FAST > 0 && B_NCONTIG && n0 + nn == p.N - 1;
   auto store_from = [&](int buf, const d2 (&sa)[AREG], const d2 (&sb)[BREG]) {
     if (!A_MC) {
 #pragma unroll
@@ -356,7 +358,7 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, int tm, int tn, i
       }
     } else {
 #pragma unroll
-      for (int s = 0; s < AREG; ++s) *(d2*)&As[buf][(km0 + s * MSTEP) * LDA + mm] = d2{lastA ? sa[s][1] : sa[s][0], sa[s][1]};
+      for (int s = 0; s < AREG; ++s) *(d2*)&As[buf][(km0 + s * MSTEP) * LDA + mm] = sa[s];
     }
     if (!B_NCONTIG) {
 #pragma unroll
@@ -366,7 +368,7 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, int tm, int tn, i
       }
     } else {
 #pragma unroll
-      for (int s = 0; s < BNN; ++s) *(d2*)&Bs[buf][(kn0 + s * NSTEP) * LDB + nn] = d2{lastB ? sb[s][1] : sb[s][0], sb[s][1]};
+      for (int s = 0; s < BNN; ++s) *(d2*)&Bs[buf][(kn0 + s * NSTEP) * LDB + nn] = sb[s];
     }
   };
   auto store_chunk = [&](int buf) { store_from(buf, ra, rb); };
@@ -386,7 +388,7 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, int tm, int tn, i
     for (int j = 0; j < NI; ++j) acc[i][j] = dbl4{0.0, 0.0, 0.0, 0.0};
 
   // FAST > 0 (chosen by the host: runs of the K operands at least one chunk
-  // long, at least two rows or columns of an M- or N-contiguous operand): the
+  // long, and M- or N-contiguous operands that hold whole pairs): the
   // split's full chunks go through a branch-free loader that issues each
   // chunk's global loads two chunks ahead into two register sets.  Rows (and
   // N-contiguous column pairs) past the edge of the matrix read the last valid
@@ -504,11 +506,16 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, int tm, int tn, i
       // the ragged last chunk: per-element masks
       const int64_t kt = kbeg + (int64_t)nfull * BK;
       const d2 zero = {0.0, 0.0};
-      // elements k and k + 1 of the row at `row` (0 past the end of the reduction)
+      // elements k and k + 1 of the row at `row`, 0 past the end of the
+      // reduction: without runs one load of the last whole pair, shifted
+      const int64_t k = kt + kk;
       auto kpair = [&](const KOperand& o, const double* row) {
-        const int64_t k = kt + kk;
         d2 v = zero;
-        if (k < kend) {
+        if (FAST == 1 && o.kdiv >= p.K && p.K >= 2) {
+          const d2 x = *(const d2u*)(row + min(k, kend - 2));
+          v[0] = k + 1 < kend ? x[0] : k < kend ? x[1] : 0.0;
+          v[1] = k + 1 < kend ? x[1] : 0.0;
+        } else if (k < kend) {
           const int64_t q = k / o.kdiv, r = k - q * o.kdiv;
           v[0] = row[q * o.ks1 + r];
           if (k + 1 < kend) v[1] = row[r + 1 < o.kdiv ? q * o.ks1 + r + 1 : (q + 1) * o.ks1];
@@ -583,7 +590,7 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, int tm, int tn, i
       for (int r = 0; r < 4; ++r) {
         const int64_t m = m0 + wm * WTM + i * 16 + 4 * r + (lane >> 4);
         const int64_t n = n0 + wn * WTN + j * 16 + (lane & 15);
-        if (m < p.M && n < p.N) {
+        if (m < p.M && n < p.N && (!(FAST > 0 && A_MC) || m >= mlo) && (!(FAST > 0 && B_NCONTIG) || n >= nlo)) {
           if (!TRI) {
             if (p.accumulate) C[m * p.ldc + n] += acc[i][j][r];
             else C[m * p.ldc + n] = acc[i][j][r];

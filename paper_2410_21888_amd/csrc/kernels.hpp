@@ -356,15 +356,43 @@ __global__ __launch_bounds__(256) void pair_energy_reduce_kernel(const double* e
   if (paired) e_pair[(int64_t)j * nocc + k] = h + l;
 }
 
-// out[m*ldo + n] = (accumulate ? out : 0) + alpha * sum_{z < splits} W[z*zs + m*ldw + n],
-// summed in increasing z.
-__device__ __forceinline__ void splitk_reduce_at(double* out, int64_t ldo, const double* W, int64_t ldw, int64_t zs,
-                                                 int splits, int64_t M, int64_t N, double alpha, int accumulate,
-                                                 int64_t idx) {
-  if (idx >= M * N) return;
-  const int64_t m = idx / N, n = idx - m * N;
+// out[m*ldo + n] = (accumulate ? out : 0) + alpha * sum_{z < splits} W[z*zs + m*ldw + n].
+// Workgroup `block` of 256 threads covers kReduceWide elements with one thread
+// each, or with `lanes` kReduceNarrow elements with kReduceLanes threads each:
+// lane q sums z = q, q + kReduceLanes, ... and the lanes are added in order.
+// Bound by the latency of the partials' loads where the output is small (400
+// elements of 64 partials took 18 us with one thread each: P_ij of nocc = 20),
+// by their bytes where it is not; the order depends on the sizes alone.
+constexpr int kReduceLanes = 16, kReduceWide = 256, kReduceNarrow = 256 / kReduceLanes;
+// Lanes where one thread an element would leave most of the chip idle.
+__host__ __device__ inline bool reduce_lanes(int64_t elems, int64_t splits) { return elems < 65536 && splits >= 8; }
+__host__ __device__ inline int64_t reduce_blocks(int64_t elems, int64_t splits) {
+  const int per = reduce_lanes(elems, splits) ? kReduceNarrow : kReduceWide;
+  return (elems + per - 1) / per;
+}
+__device__ __forceinline__ void splitk_reduce_block(double* out, int64_t ldo, const double* W, int64_t ldw, int64_t zs,
+                                                    int splits, int64_t M, int64_t N, double alpha, int accumulate,
+                                                    int64_t block) {
+  __shared__ double part[kReduceLanes][kReduceNarrow + 1];
+  const bool lanes = reduce_lanes(M * N, splits);
+  const int t = threadIdx.x, q = lanes ? t / kReduceNarrow : 0, e = lanes ? t % kReduceNarrow : t;
+  const int64_t idx = block * (lanes ? kReduceNarrow : kReduceWide) + e;
+  const bool in = idx < M * N;
+  const int64_t m = in ? idx / N : 0, n = in ? idx - m * N : 0;
+  const double* src = W + m * ldw + n;
+  const int step = lanes ? kReduceLanes : 1;
   double s = 0.0;
-  for (int z = 0; z < splits; ++z) s += W[z * zs + m * ldw + n];
+  if (in) {
+#pragma unroll 8
+    for (int z = q; z < splits; z += step) s += src[z * zs];
+  }
+  if (lanes) {
+    part[q][e] = s;
+    __syncthreads();
+    if (q != 0) return;
+    for (int l = 1; l < kReduceLanes; ++l) s += part[l][e];
+  }
+  if (!in) return;
   double* o = out + m * ldo + n;
   *o = (accumulate ? *o : 0.0) + alpha * s;
 }
@@ -373,7 +401,7 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(double* out, int64_t
                                                             int64_t zs, int splits, int64_t M, int64_t N, double alpha,
                                                             int accumulate, const int32_t* status) {
   if (*status != 0) return;
-  splitk_reduce_at(out, ldo, W, ldw, zs, splits, M, N, alpha, accumulate, (int64_t)blockIdx.x * 256 + threadIdx.x);
+  splitk_reduce_block(out, ldo, W, ldw, zs, splits, M, N, alpha, accumulate, blockIdx.x);
 }
 
 // E = sum of count values, compensated, fixed order; writes (hi, lo).

@@ -110,10 +110,8 @@ int traced(int role, double af, double ef, double ab, hipStream_t st, F&& launch
 }
 
 constexpr size_t kAlign = 256;
-constexpr int64_t kTile = 128;        // M/N tile of the large GEMMs
-constexpr int64_t kSmallTile = 64;    // tile of the P_ij GEMM
 constexpr int kBK = 16;
-constexpr int64_t kSlots = 512;       // resident GEMM workgroups: 2 per CU on 256 CUs
+constexpr int64_t kSlots = 512;       // resident workgroups of a persistent launch: 2 per CU on 256 CUs
 
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
@@ -127,32 +125,83 @@ int check_grid(int64_t wgs, const char* what) {
 }
 int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
-// Split-K factor for a launch of `tiles` output tiles over reduction length K:
-// the factor (at most 64, each split at least 2048 long) whose workgroup count
-// best fills whole waves of kSlots workgroups.  Launches of eight or more
-// full waves split at most 4 ways, only to fill a ragged last wave (4653
-// tiles run 9.09 waves unsplit, 9.83 of every 10 slots used with 4 splits).
-int64_t choose_splits(int64_t tiles, int64_t K) {
-  const bool big = tiles >= 8 * kSlots;
-  int64_t smax = std::max<int64_t>(1, std::min<int64_t>(64, K / 2048));
-  if (big) smax = std::min<int64_t>(smax, 4);
-  int64_t best = 1;
-  double best_eff = -1.0;
-  for (int64_t s = 1; s <= smax; ++s) {
-    const int64_t total = tiles * s;
-    const double waves = (double)cdiv(total, kSlots);
-    // fill of the last wave, plus a small preference for more waves (tail effects)
-    const double eff = (double)total / (waves * kSlots) + 0.002 * std::min(waves, 8.0);
-    if (eff > best_eff + (big && s > 1 ? 0.01 : 1e-9)) { best_eff = eff; best = s; }
+// ---- tile shape and split-K factor of a GEMM ------------------------------
+// Measured on the NT kernel (us): with w workgroups resident on a CU, one
+// chunk of kBK reduction indices takes a + b w, up to `resident` workgroups
+// (tile 128: 2.35, 4.05; tile 96: 1.45, 2.45, 3.45; tile 64: 0.80, 1.25, 1.70,
+// 2.15; tile 32: 0.39, 0.54, 0.71, .., 1.44 with 8); filling the pipeline and
+// writing the tile take about kTileFill more.  Large tiles reach the higher
+// rate (66 TFLOP/s at 512 tiles of 128, 62 at 1024 of 64), small ones fill the
+// chip sooner (256 tiles of 64 run at 42, 64 tiles of 128 at 14).
+struct TileCost {
+  int bm;
+  double a, b;
+  int resident;
+};
+constexpr TileCost kTileCost[4] = {{128, 0.65, 1.70, 2}, {96, 0.47, 0.99, 3}, {64, 0.35, 0.45, 4}, {32, 0.24, 0.15, 8}};
+constexpr double kTileFill = 5.0, kCUs = 256.0;
+// Split-K costs one launch that reads the partials at about 3.5 TB/s (their
+// writes run under the other workgroups' MFMAs).
+constexpr double kReduceUs = 5.0, kReduceBytesPerUs = 3.5e6;
+constexpr int64_t kMaxSplits = 1024;
+
+double gemm_us(const TileCost& t, int64_t tiles, int64_t K, int64_t splits) {
+  const double chunks = (double)cdiv(cdiv(K, splits), kBK);
+  const int64_t w = cdiv(tiles * splits, (int64_t)kCUs), rounds = w / t.resident, rest = w % t.resident;
+  return rounds * (kTileFill + chunks * (t.a + t.b * t.resident)) + (rest ? kTileFill + chunks * (t.a + t.b * rest) : 0.0);
+}
+
+// A smaller tile has to be estimated 3% faster than the larger one: it stages
+// more operand bytes per multiply-add, which the table (operands in the
+// caches) does not hold ((ia|jb) of 16/1800/6000: 79 ms with tiles of 128, 84
+// with 64, estimated alike).
+constexpr double kSmallerTile = 0.97;
+
+struct GemmChoice {
+  int bm;           // square tile
+  int64_t splits;   // split-K factor
+};
+
+// The tile (one of `bms`, 0 ends the list) and split-K factor (at most smax)
+// with the smallest estimate for an M x N x K product (tri: upper-triangular
+// tiles).  Split factors tried: 1 to 4 (they fill a ragged last round of many
+// tiles) and those that give every CU 1 to 8 workgroups.  With one tile shape and 64 splits of 2048 at most, P_ij of
+// nocc = 61 ran on 64 workgroups (8.0 ms, 1.6 ms now) and Gamma of 20/100/400 on
+// 64 (288 us, 90 us now).
+GemmChoice choose_gemm(int64_t M, int64_t N, int64_t K, bool tri, const int* bms, int64_t smax = kMaxSplits) {
+  GemmChoice best{0, 1};
+  double best_us = 0.0;
+  smax = std::max<int64_t>(1, std::min<int64_t>(smax, K / (4 * kBK)));
+  for (; *bms; ++bms) {
+    const TileCost* t = kTileCost;
+    while (t->bm != *bms) ++t;
+    const int64_t tm = cdiv(M, t->bm), tn = cdiv(N, t->bm), tiles = tri ? tm * (tm + 1) / 2 : tm * tn;
+    for (int64_t w = 1; w <= 12; ++w) {
+      const int64_t s = std::min<int64_t>(smax, w <= 4 ? w : (w - 4) * (int64_t)kCUs / tiles);
+      if (s < 1) continue;
+      const double us = gemm_us(*t, tiles, K, s) + (s > 1 ? kReduceUs + 8.0 * (s + 1) * M * N / kReduceBytesPerUs : 0.0);
+      if (best.bm == 0 || us < best_us * (t->bm < best.bm ? kSmallerTile : 1.0)) {
+        best_us = us;
+        best = GemmChoice{t->bm, s};
+      }
+    }
   }
   return best;
 }
-
-// P_ab tile: 96 when it pads nvir by at least 8% less area than 128.
-bool pab_tile96(int64_t nvir) {
-  const double a128 = (double)cdiv(nvir, 128) * 128.0, a96 = (double)cdiv(nvir, 96) * 96.0;
-  return a96 * a96 < 0.92 * a128 * a128;
+// Grouped (batch) roles (ia|jb), Gamma, P_ab, P_ij: candidate square tiles, the
+// default first.
+constexpr int kBatchTile[4][2] = {{128, 64}, {128, 64}, {128, 64}, {64, 32}};
+// Split-K factor of a grouped P_ab or P_ij product of K reduction indices: a
+// wave's fragments fill the chip together, so the splits only keep its items
+// short (klen).  With 64 splits whatever the length, the P_ij items of nocc =
+// 60, nvir = 300 were 84000 long, and the launch waited for them.
+constexpr int64_t kGroupedPab = 4096, kGroupedPij = 2048;
+GemmChoice grouped_choice(int bm, int64_t K, int64_t klen) {
+  return GemmChoice{bm, std::max<int64_t>(1, std::min<int64_t>(kMaxSplits, cdiv(K, klen)))};
 }
+// Tile shapes instantiated for each product.
+constexpr int kIntsTiles[] = {128, 64, 0}, kGammaTiles[] = {128, 64, 0}, kPabTiles[] = {128, 96, 64, 0},
+              kPijTiles[] = {128, 64, 32, 0}, kLtermTiles[] = {128, 64, 0};
 
 struct Plan {
   int64_t nocc, nvir, naux;
@@ -163,6 +212,7 @@ struct Plan {
   bool split;                // RIMP2_SPLIT_INT8
   bool autotune;             // in-situ tile choice of the FP64 GEMMs
   bool general;              // FP64 GEMMs take the general loader only
+  int64_t max_splits;        // cap of every split-K factor
   int sv, sg;                // digits per operand of (ia|jb) and of Gamma
   int64_t kpv, kpg;          // padded reduction lengths of the split products
   size_t off_dbv, off_ev, off_dbg, off_eg, off_cmax, off_dt, off_et;
@@ -170,7 +220,7 @@ struct Plan {
   // of the group's B rows (the transposed-block product), per group
   size_t off_dtt, off_ett, off_cmt, off_dbk, off_ebk;
   int64_t g;                 // occupied orbitals per slab group
-  int64_t s_ab, s_ij, s_gam; // split-K factors
+  GemmChoice c_ab, c_ij, c_gam;   // tile and split-K factor of P_ab, P_ij and (ordered path) Gamma
   size_t off_status, off_V, off_T, off_e, off_pab, off_pij, off_gam, off_epart, total;
 };
 
@@ -197,16 +247,17 @@ int64_t group_at(const Plan& P, int64_t k0) {
   return std::max<int64_t>(1, std::min<int64_t>({(int64_t)(P.budget / per_k), P.nocc - k0, red}));
 }
 
-// Split-K factor of the symmetric path's Gamma GEMM over the row blocks of a
-// group of gc orbitals starting at k0 (reduction over the pairs j >= k0).
-int64_t sym_gamma_splits(const Plan& P, int64_t k0, int64_t gc) {
-  return choose_splits(cdiv(gc * P.nvir, kTile) * cdiv(P.naux, kTile), (P.nocc - k0) * P.nvir);
+// Tile and split-K factor of the symmetric path's Gamma GEMM over the row
+// blocks of a group of gc orbitals starting at k0 (reduction over the pairs
+// j >= k0).
+GemmChoice sym_gamma_choice(const Plan& P, int64_t k0, int64_t gc) {
+  return choose_gemm(gc * P.nvir, P.naux, (P.nocc - k0) * P.nvir, false, kGammaTiles, P.max_splits);
 }
 
 // grouped: the fragment runs in a batch wave (whole slab, no split amplitude
-// partials).
+// partials).  max_splits bounds the split-K partials in the workspace.
 int make_plan(int64_t nocc, int64_t nvir, int64_t naux, bool gamma, bool density, const rimp2_opts* o, Plan* p,
-              bool grouped = false) {
+              bool grouped = false, int64_t max_splits = kMaxSplits) {
   if (nocc < 1 || nvir < 1 || naux < 1 || nocc > (1 << 20) || nvir > (1 << 24) || naux > (1 << 24))
     return fail(RIMP2_EINVAL, "sizes must be >= 1 (nocc=%lld nvir=%lld naux=%lld)", (long long)nocc,
                 (long long)nvir, (long long)naux);
@@ -239,18 +290,23 @@ int make_plan(int64_t nocc, int64_t nvir, int64_t naux, bool gamma, bool density
     g = std::max<int64_t>(1, std::min<int64_t>(g, nocc));
   }
   p->g = g;
-  // split-K factors (see choose_splits); P_ab and P_ij use upper-triangular tiles
-  const int64_t tab = cdiv(nvir, pab_tile96(nvir) ? 96 : kTile), tij = cdiv(nocc, kSmallTile);
-  p->s_ab = density ? choose_splits(tab * (tab + 1) / 2, g * nocc * nvir) : 0;
-  p->s_ij = density ? choose_splits(tij * (tij + 1) / 2, g * nvir * nvir) : 0;
-  p->s_gam = gamma ? choose_splits(cdiv(g * nvir, kTile) * cdiv(naux, kTile), nocc * nvir) : 0;
+  p->max_splits = max_splits;
+  p->c_ab = p->c_ij = p->c_gam = GemmChoice{0, 0};
+  if (density && grouped) {
+    p->c_ab = grouped_choice(kBatchTile[2][0], nocc * nocc * nvir, kGroupedPab);
+    p->c_ij = grouped_choice(kBatchTile[3][0], nocc * nvir * nvir, kGroupedPij);
+  } else if (density) {
+    p->c_ab = choose_gemm(nvir, nvir, g * nocc * nvir, true, kPabTiles, max_splits);
+    p->c_ij = choose_gemm(nocc, nocc, g * nvir * nvir, true, kPijTiles, max_splits);
+  }
+  if (gamma) p->c_gam = choose_gemm(g * nvir, naux, nocc * nvir, false, kGammaTiles, grouped ? 1 : max_splits);
   // slab elements (g x ncols pair blocks) and Gamma split partials of the
   // largest group
-  double slab_elems = (double)g * nocc * nvir * nvir, gam_part = (double)p->s_gam * g * nvir * naux;
+  double slab_elems = (double)g * nocc * nvir * nvir, gam_part = (double)p->c_gam.splits * g * nvir * naux;
   if (p->sym) {
     slab_elems = gam_part = 0.0;
     for (int64_t k0 = 0; k0 < nocc;) {
-      const int64_t gc = group_at(*p, k0), s = sym_gamma_splits(*p, k0, gc);
+      const int64_t gc = group_at(*p, k0), s = sym_gamma_choice(*p, k0, gc).splits;
       slab_elems = std::max(slab_elems, (double)gc * (nocc - k0) * nvir * nvir);
       if (s > 1) gam_part = std::max(gam_part, (double)s * gc * nvir * naux);
       k0 += gc;
@@ -261,11 +317,11 @@ int make_plan(int64_t nocc, int64_t nvir, int64_t naux, bool gamma, bool density
   p->off_V = off; off = align_up(off + (size_t)(8.0 * slab_elems));
   p->off_T = off; if (need_T) off = align_up(off + (size_t)(8.0 * slab_elems));
   p->off_e = off; off = align_up(off + 8 * (size_t)nocc * nocc);
-  p->off_pab = off; if (density) off = align_up(off + 8 * (size_t)p->s_ab * nvir * nvir);
-  p->off_pij = off; if (density) off = align_up(off + 8 * (size_t)p->s_ij * nocc * nocc);
+  p->off_pab = off; if (density) off = align_up(off + 8 * (size_t)p->c_ab.splits * nvir * nvir);
+  p->off_pij = off; if (density) off = align_up(off + 8 * (size_t)p->c_ij.splits * nocc * nocc);
   p->off_gam = off;
   // (grouped fragments run their Gamma GEMM without split-K: no partials)
-  if (gamma && !p->split && !grouped && (p->sym || p->s_gam > 1)) off = align_up(off + (size_t)(8.0 * gam_part));
+  if (gamma && !p->split && !grouped && (p->sym || p->c_gam.splits > 1)) off = align_up(off + (size_t)(8.0 * gam_part));
   p->off_epart = off;
   if (!grouped) {  // largest partial array of the amplitude launches (see run_fragment)
     const bool eonly = !(gamma || density);
@@ -325,7 +381,7 @@ int make_plan(int64_t nocc, int64_t nvir, int64_t naux, bool gamma, bool density
   }
   p->total = off;
   int rc;
-  if (gamma && p->s_gam > 1 && !p->sym && (rc = check_grid(cdiv(g * nvir * naux, 256), "reduction"))) return rc;
+  if (gamma && p->c_gam.splits > 1 && !p->sym && (rc = check_grid(cdiv(g * nvir * naux, 256), "reduction"))) return rc;
   if (p->sym && p->g_fixed && (rc = check_grid(cdiv(g * nvir * naux, 256), "reduction"))) return rc;
   if (p->split && ((rc = check_grid(nocc * nvir, "digit split")) || (rc = check_grid(cdiv(p->kpg, 32), "digit split"))))
     return rc;
@@ -348,15 +404,16 @@ bool gemm_vec(const GemmParams& gp, bool nc, bool amc = false) {
 
 // The kernels' FAST level of a GEMM (0: the general loader).  It needs runs of
 // the K operands at least one chunk long (a chunk crosses at most one run
-// boundary) and two rows (columns) of an M-contiguous A (N-contiguous B) to
-// read a pair from.  2 when a K operand's runs are even and can end inside a
+// boundary), and of an M-contiguous A (N-contiguous B) an even number of rows
+// (columns) or a whole tile of side bm to read pairs from.  2 when a K operand's runs are even and can end inside a
 // chunk, 3 when they are odd; alignment, odd strides and odd lengths do not
 // matter.  (Odd sizes took the general loader with 8-byte loads: Gamma of
 // nocc = 97, nvir = 485, naux = 1746 ran at 57 TFLOP/s, and at 64 here.)
-int fast_level(const GemmParams& gp, bool nc, bool amc = false) {
+int fast_level(const GemmParams& gp, int bm, bool nc, bool amc = false) {
   auto runs = [&](const KOperand& o) { return o.kdiv >= gp.K || o.kdiv >= kBK; };
+  auto pairs = [&](int64_t n) { return n % 2 == 0 || n >= bm; };
   auto level = [&](const KOperand& o) { return o.kdiv >= gp.K || o.kdiv % kBK == 0 ? 1 : o.kdiv % 2 == 0 ? 2 : 3; };
-  if (!(gp.kchunk % kBK == 0 && (amc ? gp.M >= 2 : runs(gp.A)) && (nc ? gp.N >= 2 : runs(gp.Bk)))) return 0;
+  if (!(gp.kchunk % kBK == 0 && (amc ? pairs(gp.M) : runs(gp.A)) && (nc ? pairs(gp.N) : runs(gp.Bk)))) return 0;
   return std::max(amc ? 1 : level(gp.A), nc ? 1 : level(gp.Bk));
 }
 
@@ -402,7 +459,7 @@ int launch_gemm(GemmParams gp, hipStream_t st, int role, double af, double ab, b
     }
     ef *= (double)kept / ((double)gp.tiles_m * gp.tiles_n);
   }
-  const int fast = general ? 0 : fast_level(gp, NC, AMC);
+  const int fast = general ? 0 : fast_level(gp, BM, NC, AMC);
   // the roles whose K operands have runs
   constexpr bool RUNS = ROLE == ROLE_PAB || ROLE == ROLE_PIJ || ROLE == ROLE_LTERM;
   if (!RUNS && fast > 1) return fail(RIMP2_EINVAL, "GEMM role %d with a two-level reduction", ROLE);
@@ -424,6 +481,25 @@ int launch_gemm(GemmParams gp, hipStream_t st, int role, double af, double ab, b
 }
 
 
+// Tile of an (ia|jb) launch, over the tiles it keeps (no split-K: the
+// amplitude pass needs whole sums).
+int ints_tile(GemmParams gp) {
+  int best = 0;
+  double best_us = 0.0;
+  for (const int* t = kIntsTiles; *t; ++t) {
+    const TileCost* c = kTileCost;
+    while (c->bm != *t) ++c;
+    // (raster groups of one row: exactly the tiles that are not skipped)
+    gp.tiles_m = (int32_t)cdiv(gp.M, *t); gp.tiles_n = (int32_t)cdiv(gp.N, *t); gp.group_m = 1;
+    const double us = gemm_us(*c, gemm_tiles(gp, *t, *t, false), gp.K, 1);
+    if (best == 0 || us < best_us * kSmallerTile) {
+      best = *t;
+      best_us = us;
+    }
+  }
+  return best;
+}
+
 // ---- in-situ tile autotuner (Sec. "GEMM runtime auto-tuning") -------------
 // Candidates are output tile shapes; the split length (and with it every
 // element's summation order) comes from the plan and is the same for all.
@@ -432,27 +508,14 @@ struct TileShape {
 };
 constexpr int kTuneVars = 4, kTuneTrials = 2;
 
-// Candidate tile shapes of a role's GEMM, the fixed default first.
-int tile_candidates(int role, const GemmParams& gp, TileShape* c) {
-  switch (role) {
-    case R_INTS:
-    case R_GAMMA:
-    case R_GAMMA_T:
-      c[0] = {128, 128}; c[1] = {64, 64};
-      return 2;
-    case R_PAB: {
-      const bool t96 = pab_tile96(gp.M);
-      c[0] = t96 ? TileShape{96, 96} : TileShape{128, 128};
-      c[1] = t96 ? TileShape{128, 128} : TileShape{96, 96};
-      c[2] = {64, 64};
-      return 3;
-    }
-    case R_PIJ:
-      c[0] = {64, 64}; c[1] = {128, 128}; c[2] = {32, 32};
-      return 3;
-    default:
-      return 0;
-  }
+// Candidate tile shapes of a role's GEMM: bm0 (the plan's choice) first.
+int tile_candidates(int role, int bm0, TileShape* c) {
+  const int* t = role == R_PAB ? kPabTiles : role == R_PIJ ? kPijTiles : kGammaTiles;
+  int n = 0;
+  c[n++] = {bm0, bm0};
+  for (; *t; ++t)
+    if (*t != bm0) c[n++] = {*t, *t};
+  return n;
 }
 
 // The GEMM of `role` with square tiles of side bm (one of its candidates).
@@ -605,12 +668,13 @@ int tuned(const TuneKey& key, int nvar, const TileShape* cand, hipStream_t st, F
   return rc;
 }
 
-// Launches the GEMM of `role`: the default tile shape, or with autotuning the
+// Launches the GEMM of `role` with tiles of side bm0, or with autotuning the
 // shape's tuned candidate.
-int launch_tuned(int role, const GemmParams& gp, bool autotune, bool general, hipStream_t st, double af, double ab) {
+int launch_tuned(int role, int bm0, const GemmParams& gp, bool autotune, bool general, hipStream_t st, double af,
+                 double ab) {
+  if (!autotune) return launch_role(role, bm0, gp, st, af, ab, general);
   TileShape c[kTuneVars];
-  const int nvar = tile_candidates(role, gp, c);
-  if (!autotune || nvar < 2) return launch_role(role, c[0].bm, gp, st, af, ab, general);
+  const int nvar = tile_candidates(role, bm0, c);
   int dev = 0;
   HIP_TRY(hipGetDevice(&dev));
   // the key's loader field: 16-byte loads, and whether the fast loaders are allowed
@@ -794,7 +858,8 @@ int run_fragment(const Plan& P, const double* B, const double* eo, const double*
                           gc * nvir, Lc, P.kpv, V, Lc, status, R_INTS8, af,
                           (double)P.sv * (g * v + o * v) * P.kpv + slab, st, 0, &pairs)))
           return rc;
-      } else if ((rc = launch_tuned(R_INTS, gp, P.autotune, P.general, st, af, 8.0 * (g + o) * v * x + slab))) {
+      } else if ((rc = launch_tuned(R_INTS, ints_tile(gp), gp, P.autotune, P.general, st, af,
+                                    8.0 * (g + o) * v * x + slab))) {
         return rc;
       }
     }
@@ -816,18 +881,18 @@ int run_fragment(const Plan& P, const double* B, const double* eo, const double*
     }
     if (P.gamma && P.sym) {
       // Gamma rows of the group: Gamma[k] (+)= sum over pairs (k, j >= k0) of T_kj B_j
-      const int64_t s_g = sym_gamma_splits(P, k0, gc);
+      const GemmChoice cg = sym_gamma_choice(P, k0, gc);
       const int acc = k0 > 0 ? 1 : 0;   // earlier groups' transposed blocks are already in these rows
       GemmParams gp{};
       gp.M = gc * nvir; gp.N = naux; gp.K = Lc;
-      gp.kchunk = cdiv(Lc, s_g);
+      gp.kchunk = cdiv(Lc, cg.splits);
       gp.A = kop(T, Lc, INT64_MAX, 0);
       gp.Bn = NOperand{B + j0 * nvir * naux, naux};
       gp.status = status;
       double* out = Gam + k0 * nvir * naux;
       const double c = (double)ncols;
       const double af = 2.0 * g * v * x * c * v, ab = slab + 8.0 * c * v * x + 8.0 * (1 + acc) * g * v * x;
-      const int64_t splits = cdiv(Lc, cdiv(cdiv(Lc, s_g), kBK) * kBK);
+      const int64_t splits = cdiv(Lc, cdiv(cdiv(Lc, cg.splits), kBK) * kBK);
       if (P.split) {
         // row product: T rows of the group (reduction over (j >= k0, b)) times
         // the column digits of B's rows j >= k0
@@ -849,16 +914,16 @@ int run_fragment(const Plan& P, const double* B, const double* eo, const double*
       } else if (splits > 1) {
         double* W = (double*)(ws + P.off_gam);
         gp.C = W; gp.ldc = naux; gp.split_stride = gc * nvir * naux;
-        if ((rc = launch_tuned(R_GAMMA, gp, P.autotune, P.general, st, af, ab))) return rc;
+        if ((rc = launch_tuned(R_GAMMA, cg.bm, gp, P.autotune, P.general, st, af, ab))) return rc;
         const int64_t n = gc * nvir * naux;
         if ((rc = traced(R_REDUCE, 0, 0, 8.0 * (splits + 1 + acc) * n, st, [&] {
-               hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)cdiv(n, 256)), dim3(256), 0, st, out, naux, W,
+               hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)reduce_blocks(n, splits)), dim3(256), 0, st, out, naux, W,
                                   naux, gc * nvir * naux, (int)splits, gc * nvir, naux, 1.0, acc, status);
              })))
           return rc;
       } else {
         gp.C = out; gp.ldc = naux; gp.split_stride = 0; gp.accumulate = acc;
-        if ((rc = launch_tuned(R_GAMMA, gp, P.autotune, P.general, st, af, ab))) return rc;
+        if ((rc = launch_tuned(R_GAMMA, cg.bm, gp, P.autotune, P.general, st, af, ab))) return rc;
       }
       // Gamma rows of the later orbitals j >= k0 + gc, from the transposed
       // blocks: Gamma[j, b, P] += sum over (kk, a) of T_kj[a, b] B[k0 + kk, a, P]
@@ -908,14 +973,14 @@ int run_fragment(const Plan& P, const double* B, const double* eo, const double*
                             Gam + (k0 + gc) * nvir * naux, naux, status, R_GAMMA_T8, aft,
                             (double)P.sg * (r * v + x) * kg + 8.0 * (1 + acc) * r * v * x, st, acc)))
             return rc;
-        } else if ((rc = launch_tuned(R_GAMMA_T, gt, P.autotune, P.general, st, aft, abt))) {
+        } else if ((rc = launch_tuned(R_GAMMA_T, choose_gemm(gt.M, gt.N, gt.K, false, kGammaTiles, 1).bm, gt, P.autotune, P.general, st, aft, abt))) {
           return rc;
         }
       }
     } else if (P.gamma) {
       GemmParams gp{};
       gp.M = gc * nvir; gp.N = naux; gp.K = L;
-      gp.kchunk = cdiv(L, P.s_gam);
+      gp.kchunk = cdiv(L, P.c_gam.splits);
       gp.A = kop(T, L, INT64_MAX, 0);
       gp.Bn = NOperand{B, naux};
       double* out = Gam + k0 * nvir * naux;
@@ -928,20 +993,20 @@ int run_fragment(const Plan& P, const double* B, const double* eo, const double*
         if ((rc = run_oz8(P.sg, dt, gc * nvir * P.kpg, 0, ext, dbg, naux * P.kpg, exg, gc * nvir, naux, P.kpg, out,
                           naux, status, R_GAMMA8, af, (double)P.sg * (g * v + x) * P.kpg + 8.0 * g * v * x, st)))
           return rc;
-      } else if (P.s_gam > 1) {
+      } else if (P.c_gam.splits > 1) {
         double* W = (double*)(ws + P.off_gam);
         gp.C = W; gp.ldc = naux; gp.split_stride = gc * nvir * naux; gp.status = status;
-        if ((rc = launch_tuned(R_GAMMA, gp, P.autotune, P.general, st, af, ab))) return rc;
-        const int64_t splits = cdiv(L, cdiv(cdiv(L, P.s_gam), kBK) * kBK);
+        if ((rc = launch_tuned(R_GAMMA, P.c_gam.bm, gp, P.autotune, P.general, st, af, ab))) return rc;
+        const int64_t splits = cdiv(L, cdiv(cdiv(L, P.c_gam.splits), kBK) * kBK);
         const int64_t n = gc * nvir * naux;
         if ((rc = traced(R_REDUCE, 0, 0, 8.0 * (splits + 1) * n, st, [&] {
-               hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)cdiv(n, 256)), dim3(256), 0, st, out, naux, W,
+               hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)reduce_blocks(n, splits)), dim3(256), 0, st, out, naux, W,
                                   naux, gc * nvir * naux, (int)splits, gc * nvir, naux, 1.0, 0, status);
              })))
           return rc;
       } else {
         gp.C = out; gp.ldc = naux; gp.split_stride = 0; gp.status = status;
-        if ((rc = launch_tuned(R_GAMMA, gp, P.autotune, P.general, st, af, ab))) return rc;
+        if ((rc = launch_tuned(R_GAMMA, P.c_gam.bm, gp, P.autotune, P.general, st, af, ab))) return rc;
       }
     }
     if (P.density) {
@@ -950,17 +1015,17 @@ int run_fragment(const Plan& P, const double* B, const double* eo, const double*
         GemmParams gp{};
         const int64_t K = gc * L;
         gp.M = nvir; gp.N = nvir; gp.K = K;
-        gp.kchunk = cdiv(K, P.s_ab);
+        gp.kchunk = cdiv(K, P.c_ab.splits);
         gp.A = kop(T, L, L, nvir * L);
         gp.Bk = kop(V, L, L, nvir * L);
         double* W = (double*)(ws + P.off_pab);
         gp.C = W; gp.ldc = nvir; gp.split_stride = nvir * nvir; gp.status = status;
-        const int64_t splits = cdiv(K, cdiv(cdiv(K, P.s_ab), kBK) * kBK);
-        if ((rc = launch_tuned(R_PAB, gp, P.autotune, P.general, st, 2.0 * v * v * g * o * v,
+        const int64_t splits = cdiv(K, cdiv(cdiv(K, P.c_ab.splits), kBK) * kBK);
+        if ((rc = launch_tuned(R_PAB, P.c_ab.bm, gp, P.autotune, P.general, st, 2.0 * v * v * g * o * v,
                                2.0 * slab + 8.0 * splits * v * v)))
           return rc;
         if ((rc = traced(R_REDUCE, 0, 0, 8.0 * (splits + 2) * v * v, st, [&] {
-               hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)cdiv(nvir * nvir, 256)), dim3(256), 0, st, Pab,
+               hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)reduce_blocks(nvir * nvir, splits)), dim3(256), 0, st, Pab,
                                   nvir, W, nvir, nvir * nvir, (int)splits, nvir, nvir, 1.0, accumulate, status);
              })))
           return rc;
@@ -969,18 +1034,18 @@ int run_fragment(const Plan& P, const double* B, const double* eo, const double*
         GemmParams gp{};
         const int64_t K = gc * nvir * nvir;
         gp.M = nocc; gp.N = nocc; gp.K = K;
-        gp.kchunk = cdiv(K, P.s_ij);
+        gp.kchunk = cdiv(K, P.c_ij.splits);
         gp.A = kop(T, nvir, nvir, L);
         gp.Bk = kop(V, nvir, nvir, L);
         double* W = (double*)(ws + P.off_pij);
         gp.C = W; gp.ldc = nocc; gp.split_stride = nocc * nocc; gp.status = status;
-        const int64_t splits = cdiv(K, cdiv(cdiv(K, P.s_ij), kBK) * kBK);
+        const int64_t splits = cdiv(K, cdiv(cdiv(K, P.c_ij.splits), kBK) * kBK);
         // each slab's contribution to P_ij is symmetric: upper-triangular tiles, mirrored
-        if ((rc = launch_tuned(R_PIJ, gp, P.autotune, P.general, st, 2.0 * o * o * g * v * v,
+        if ((rc = launch_tuned(R_PIJ, P.c_ij.bm, gp, P.autotune, P.general, st, 2.0 * o * o * g * v * v,
                                2.0 * slab + 8.0 * splits * o * o)))
           return rc;
         if ((rc = traced(R_REDUCE, 0, 0, 8.0 * (splits + 2) * o * o, st, [&] {
-               hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)cdiv(nocc * nocc, 256)), dim3(256), 0, st, Pij,
+               hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)reduce_blocks(nocc * nocc, splits)), dim3(256), 0, st, Pij,
                                   nocc, W, nocc, nocc * nocc, (int)splits, nocc, nocc, -1.0, accumulate, status);
              })))
           return rc;
@@ -1023,6 +1088,7 @@ int scratch_address(char** out) {
   return RIMP2_OK;
 }
 
+constexpr int64_t kNoallocSplits = 1;
 // The plan of rimp2_fragment_noalloc: the caller's options with, unless the
 // caller fixed the slab group, the largest slab budget whose workspace fits
 // the scratch array.
@@ -1030,23 +1096,27 @@ int noalloc_plan(int64_t nocc, int64_t nvir, int64_t naux, int want, const rimp2
   rimp2_opts o{};
   if (opts) o = *opts;
   if (o.autotune) return fail(RIMP2_ENOTSUP, "autotuning records events: not available without allocation");
+  const bool gamma = want & RIMP2_WANT_GAMMA, density = want & RIMP2_WANT_DENSITY;
   int rc;
-  if (o.slab_group == 0) {
-    o.slab_budget_bytes = kScratchBytes;
-    for (int it = 0; it < 64; ++it) {
-      if ((rc = make_plan(nocc, nvir, naux, want & RIMP2_WANT_GAMMA, want & RIMP2_WANT_DENSITY, &o, P))) return rc;
-      if (P->total <= kScratchBytes) return RIMP2_OK;
-      const size_t over = P->total - kScratchBytes;
-      if (o.slab_budget_bytes <= over + 1) break;
-      o.slab_budget_bytes -= over + 1;   // the slabs shrink by at least the overshoot (or g reaches 1)
+  // with the plan's own split-K factors, and where their partials leave no
+  // room with few splits
+  for (int64_t max_splits : {kMaxSplits, kNoallocSplits}) {
+    if (o.slab_group == 0) {
+      o.slab_budget_bytes = kScratchBytes;
+      for (int it = 0; it < 64; ++it) {
+        if ((rc = make_plan(nocc, nvir, naux, gamma, density, &o, P, false, max_splits))) return rc;
+        if (P->total <= kScratchBytes) return RIMP2_OK;
+        const size_t over = P->total - kScratchBytes;
+        if (o.slab_budget_bytes <= over + 1) break;
+        o.slab_budget_bytes -= over + 1;   // the slabs shrink by at least the overshoot (or g reaches 1)
+      }
     }
+    if ((rc = make_plan(nocc, nvir, naux, gamma, density, &o, P, false, max_splits))) return rc;
+    if (P->total <= kScratchBytes) return RIMP2_OK;
   }
-  if ((rc = make_plan(nocc, nvir, naux, want & RIMP2_WANT_GAMMA, want & RIMP2_WANT_DENSITY, &o, P))) return rc;
-  if (P->total > kScratchBytes)
-    return fail(RIMP2_ENOMEM, "fragment nocc=%lld nvir=%lld naux=%lld needs %zu bytes of scratch, more than the "
+  return fail(RIMP2_ENOMEM, "fragment nocc=%lld nvir=%lld naux=%lld needs %zu bytes of scratch, more than the "
                 "%zu of rimp2_fragment_noalloc", (long long)nocc, (long long)nvir, (long long)naux, P->total,
                 kScratchBytes);
-  return RIMP2_OK;
 }
 
 
@@ -1129,15 +1199,13 @@ bool kop_vec_rel(const KOperand& o, int64_t K) {
   return aligned16(o.base) && o.rs % 2 == 0 && (plain || (o.kdiv % 2 == 0 && o.ks1 % 2 == 0));
 }
 
-// Grouped GEMM roles of a wave, their two candidate square tiles (default
-// first) and list index.
+// Grouped GEMM roles of a wave (candidate tiles: kBatchTile) and list index.
 const int kBatchRole[4] = {R_INTS, R_GAMMA, R_PAB, R_PIJ};
-const int kBatchTile[4][2] = {{128, 64}, {128, 64}, {128, 64}, {64, 32}};
 int glist(int rho, int cand, int loader) { return (rho * 2 + cand) * kGLoaders + loader; }
 // loader of a grouped GEMM (see kGLists); vec: 16-byte loads are aligned;
 // general: the general loader only
-int loader_of(const GemmParams& g, bool nc, bool vec, bool general) {
-  const int f = general ? 0 : fast_level(g, nc);
+int loader_of(const GemmParams& g, int bm, bool nc, bool vec, bool general) {
+  const int f = general ? 0 : fast_level(g, bm, nc);
   return f ? f - 1 : vec ? 3 : 4;
 }
 
@@ -1189,7 +1257,6 @@ int batch_plan(int32_t nfrag, const rimp2_frag_desc* d, const rimp2_opts* opts, 
     Plan P;
     if ((rc = make_plan(d[f].nocc, d[f].nvir, d[f].naux, want & 1, want & 2, &o, &P, true)))
       return fail(rc, "fragment %d: %s", f, g_err);
-    P.s_gam = 1;
     if (P.total > budget) {
       solo[f] = 1;
       if ((rc = make_plan(d[f].nocc, d[f].nvir, d[f].naux, want & 1, want & 2, opts, &P)))
@@ -1281,7 +1348,7 @@ int batch_plan(int32_t nfrag, const rimp2_frag_desc* d, const rimp2_opts* opts, 
       for (int c = 0; c < 2; ++c) {
         GemmParams g = g0;
         const int64_t items = finalize_gemm(g, kBatchTile[rho][c], kBatchTile[rho][c], rho >= 2);
-        GemmList& l = gl[glist(rho, c, loader_of(g, rho == 1, vec, general))];
+        GemmList& l = gl[glist(rho, c, loader_of(g, kBatchTile[rho][c], rho == 1, vec, general))];
         l.p.push_back(g);
         l.prefix.push_back(l.prefix.back() + items);
       }
@@ -1362,23 +1429,23 @@ int batch_plan(int32_t nfrag, const rimp2_frag_desc* d, const rimp2_opts* opts, 
         double* Wab = relp<double>(base + P.off_pab);
         double* Wij = relp<double>(base + P.off_pij);
         GemmParams ga{};
-        ga.M = nvir; ga.N = nvir; ga.K = nocc * L; ga.kchunk = cdiv(ga.K, P.s_ab);
+        ga.M = nvir; ga.N = nvir; ga.K = nocc * L; ga.kchunk = cdiv(ga.K, P.c_ab.splits);
         ga.A = KOperand{T, L, L, nvir * L};
         ga.Bk = KOperand{V, L, L, nvir * L};
         ga.C = Wab; ga.ldc = nvir; ga.split_stride = nvir * nvir; ga.status = status;
         add(2, ga, kop_vec_rel(ga.A, ga.K) && kop_vec_rel(ga.Bk, ga.K));
-        (void)finalize_gemm(ga, kTile, kTile, false);   // splits for the reduction
+        (void)finalize_gemm(ga, kBatchTile[2][0], kBatchTile[2][0], true);   // splits for the reduction
         GemmParams gi{};
-        gi.M = nocc; gi.N = nocc; gi.K = nocc * nvir * nvir; gi.kchunk = cdiv(gi.K, P.s_ij);
+        gi.M = nocc; gi.N = nocc; gi.K = nocc * nvir * nvir; gi.kchunk = cdiv(gi.K, P.c_ij.splits);
         gi.A = KOperand{T, nvir, nvir, L};
         gi.Bk = KOperand{V, nvir, nvir, L};
         gi.C = Wij; gi.ldc = nocc; gi.split_stride = nocc * nocc; gi.status = status;
         add(3, gi, kop_vec_rel(gi.A, gi.K) && kop_vec_rel(gi.Bk, gi.K));
-        (void)finalize_gemm(gi, kSmallTile, kSmallTile, true);
+        (void)finalize_gemm(gi, kBatchTile[3][0], kBatchTile[3][0], true);
         ReduceDesc ra{q.P_ab, Wab, status, nvir, nvir, nvir * nvir, nvir, nvir, 1.0, ga.splits, 0};
         ReduceDesc ri{q.P_ij, Wij, status, nocc, nocc, nocc * nocc, nocc, nocc, -1.0, gi.splits, 0};
-        red.push_back(ra); red_pre.push_back(red_pre.back() + cdiv(nvir * nvir, 256));
-        red.push_back(ri); red_pre.push_back(red_pre.back() + cdiv(nocc * nocc, 256));
+        red.push_back(ra); red_pre.push_back(red_pre.back() + reduce_blocks(nvir * nvir, ga.splits));
+        red.push_back(ri); red_pre.push_back(red_pre.back() + reduce_blocks(nocc * nocc, gi.splits));
       }
     }
     W.bytes = poff;
@@ -1950,15 +2017,19 @@ int rimp2_gamma_ao(int32_t nocc, int32_t nvir, int32_t nao, int32_t naux, int32_
 
 namespace {
 // Split-K plan of the two L-term GEMMs: M x N outputs over reduction K.
+int launch_lterm(int bm, const GemmParams& gp, hipStream_t st, int role, double af, double ab) {
+  return bm == 64 ? launch_gemm<64, 64, false, ROLE_LTERM, false>(gp, st, role, af, ab, false)
+                  : launch_gemm<128, 128, false, ROLE_LTERM, false>(gp, st, role, af, ab, false);
+}
 struct LPlan {
-  int64_t s1, s2;
+  GemmChoice c1, c2;
   size_t part_bytes;
 };
 LPlan l_plan(int64_t nocc, int64_t nvir, int64_t nmo, int64_t naux) {
   LPlan L;
-  L.s1 = choose_splits(cdiv(nocc, kTile) * cdiv(nmo, kTile), nvir * naux);
-  L.s2 = choose_splits(cdiv(nvir, kTile) * cdiv(nmo, kTile), nocc * naux);
-  L.part_bytes = std::max((size_t)8 * L.s1 * nocc * nmo, (size_t)8 * L.s2 * nvir * nmo);
+  L.c1 = choose_gemm(nocc, nmo, nvir * naux, false, kLtermTiles);
+  L.c2 = choose_gemm(nvir, nmo, nocc * naux, false, kLtermTiles);
+  L.part_bytes = std::max((size_t)8 * L.c1.splits * nocc * nmo, (size_t)8 * L.c2.splits * nvir * nmo);
   return L;
 }
 }  // namespace
@@ -1991,15 +2062,15 @@ int rimp2_l_terms(int32_t nocc, int32_t nvir, int32_t nmo, int32_t naux, const d
          hipLaunchKernelGGL(zero_u64_kernel, dim3(1), dim3(256), 0, st, (unsigned long long*)status, 1);
        })))
     return rc;
-  auto run = [&](GemmParams gp, int64_t s, double* out, double af, double ab) -> int {
-    gp.kchunk = cdiv(gp.K, s);
+  auto run = [&](GemmParams gp, const GemmChoice& c, double* out, double af, double ab) -> int {
+    gp.kchunk = cdiv(gp.K, c.splits);
     gp.C = W; gp.ldc = gp.N; gp.split_stride = gp.M * gp.N; gp.status = status;
     const int64_t splits = cdiv(gp.K, cdiv(gp.kchunk, kBK) * kBK);
     int r;
-    if ((r = launch_gemm<128, 128, false, ROLE_LTERM, false>(gp, st, R_LTERM, af, ab, false))) return r;
+    if ((r = launch_lterm(c.bm, gp, st, R_LTERM, af, ab))) return r;
     const int64_t n = gp.M * gp.N;
     return traced(R_REDUCE, 0, 0, 8.0 * (splits + 1) * n, st, [&] {
-      hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)cdiv(n, 256)), dim3(256), 0, st, out, gp.N,
+      hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)reduce_blocks(n, splits)), dim3(256), 0, st, out, gp.N,
                          (const double*)W, gp.N, gp.M * gp.N, (int)splits, gp.M, gp.N, 1.0, 0, status);
     });
   };
@@ -2008,14 +2079,14 @@ int rimp2_l_terms(int32_t nocc, int32_t nvir, int32_t nmo, int32_t naux, const d
     gp.M = nocc; gp.N = nmo; gp.K = (int64_t)nvir * naux;
     gp.A = kop(Gamma, gp.K, INT64_MAX, 0);
     gp.Bk = kop(I_qa, gp.K, INT64_MAX, 0);
-    if ((rc = run(gp, lp.s1, L1, 2.0 * o * q * v * x, 8.0 * (o + q) * v * x + 8.0 * o * q))) return rc;
+    if ((rc = run(gp, lp.c1, L1, 2.0 * o * q * v * x, 8.0 * (o + q) * v * x + 8.0 * o * q))) return rc;
   }
   if (L2) {   // L''[a][q] = sum over (i, P) of Gamma[i][a][P] I_iq[i][q][P]
     GemmParams gp{};
     gp.M = nvir; gp.N = nmo; gp.K = (int64_t)nocc * naux;
     gp.A = kop(Gamma, naux, naux, (int64_t)nvir * naux);
     gp.Bk = kop(I_iq, naux, naux, (int64_t)nmo * naux);
-    if ((rc = run(gp, lp.s2, L2, 2.0 * v * q * o * x, 8.0 * (v + q) * o * x + 8.0 * v * q))) return rc;
+    if ((rc = run(gp, lp.c2, L2, 2.0 * v * q * o * x, 8.0 * (v + q) * o * x + 8.0 * v * q))) return rc;
   }
   return RIMP2_OK;
 }
@@ -2057,7 +2128,8 @@ __global__ __launch_bounds__(256) void antisym_combine_kernel(const double* Bf, 
 }
 
 struct AntisymPlan {
-  int64_t nmo, naux, nrows, ncols, chunks, chunk, s_k;
+  int64_t nmo, naux, nrows, ncols, chunks, chunk;
+  GemmChoice c_k;
   size_t off_status, off_cpart, off_c, off_Y, off_Kp, off_K, total;
 };
 
@@ -2068,13 +2140,13 @@ AntisymPlan antisym_plan(int64_t nmo, int64_t naux, int64_t nrows, int64_t ncols
   A.chunks = std::max<int64_t>(1, std::min<int64_t>(256, npairs / 64));
   A.chunk = cdiv(npairs, A.chunks);
   A.chunks = cdiv(npairs, A.chunk);
-  A.s_k = choose_splits(cdiv(nrows, kTile) * cdiv(ncols, kTile), nmo * naux);
+  A.c_k = choose_gemm(nrows, ncols, nmo * naux, false, kLtermTiles);
   size_t off = 0;
   A.off_status = off; off = align_up(off + 64);
   A.off_cpart = off; off = align_up(off + 8 * (size_t)A.chunks * naux);
   A.off_c = off; off = align_up(off + 8 * (size_t)naux);
   A.off_Y = off; off = align_up(off + 8 * (size_t)nmo * ncols * naux);
-  A.off_Kp = off; off = align_up(off + 8 * (size_t)A.s_k * nrows * ncols);
+  A.off_Kp = off; off = align_up(off + 8 * (size_t)A.c_k.splits * nrows * ncols);
   A.off_K = off; off = align_up(off + 8 * (size_t)nrows * ncols);
   A.total = off;
   return A;
@@ -2099,7 +2171,7 @@ int antisym_run(const AntisymPlan& A, const double* Bf, const double* D, int64_t
   if ((rc = traced(R_RESPONSE, 0, 0, 8.0 * nmo * nmo * (naux + 1), st, [&] {
          hipLaunchKernelGGL(coulomb_vector_kernel, dim3((unsigned)cdiv(naux, 256), (unsigned)A.chunks), dim3(256), 0,
                             st, Bf, D, nmo * nmo, naux, A.chunk, cpart, status);
-         hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)cdiv(naux, 256)), dim3(256), 0, st, c, naux,
+         hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)reduce_blocks(naux, A.chunks)), dim3(256), 0, st, c, naux,
                             (const double*)cpart, naux, naux, (int)A.chunks, (int64_t)1, naux, 1.0, 0, status);
        })))
     return rc;
@@ -2116,17 +2188,17 @@ int antisym_run(const AntisymPlan& A, const double* Bf, const double* D, int64_t
   {  // K[p][q] = sum over (s, P) of Bf[r0 + p][s][P] Y[s][q][P]
     GemmParams gp{};
     gp.M = nrows; gp.N = ncols; gp.K = nmo * naux;
-    gp.kchunk = cdiv(gp.K, A.s_k);
+    gp.kchunk = cdiv(gp.K, A.c_k.splits);
     gp.A = kop(Bf + r0 * nmo * naux, nmo * naux, INT64_MAX, 0);
     gp.Bk = kop(Y, naux, naux, ncols * naux);
     gp.C = Kp; gp.ldc = ncols; gp.split_stride = nrows * ncols; gp.status = status;
     const int64_t splits = cdiv(gp.K, cdiv(gp.kchunk, kBK) * kBK);
-    if ((rc = launch_gemm<128, 128, false, ROLE_LTERM, false>(gp, st, R_RESPONSE, 2.0 * nrows * ncols * nmo * naux,
-                                                               8.0 * (nrows + ncols) * nmo * naux, false)))
+    if ((rc = launch_lterm(A.c_k.bm, gp, st, R_RESPONSE, 2.0 * nrows * ncols * nmo * naux,
+                           8.0 * (nrows + ncols) * nmo * naux)))
       return rc;
     const int64_t n = nrows * ncols;
     if ((rc = traced(R_REDUCE, 0, 0, 8.0 * (splits + 1) * n, st, [&] {
-           hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)cdiv(n, 256)), dim3(256), 0, st, K, ncols,
+           hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)reduce_blocks(n, splits)), dim3(256), 0, st, K, ncols,
                               (const double*)Kp, ncols, n, (int)splits, nrows, ncols, 1.0, 0, status);
          })))
       return rc;
