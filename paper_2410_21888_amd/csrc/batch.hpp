@@ -33,7 +33,7 @@ struct AmpDesc {
   const double* ev;
   double* e_pair;
   const int32_t* status;
-  int32_t nocc, nvir, energy_only;
+  int32_t nocc, nvir, energy_only, write_x;
 };
 struct ReduceDesc {
   double* out;
@@ -90,16 +90,18 @@ __global__ __launch_bounds__(256) void gap_check_grouped(const FragSmall* fs) {
   gap_check_block(f.eo, f.nocc, f.ev, f.nvir, f.status);
 }
 
-// one workgroup per occupied pair of every fragment (whole slab, k0 = 0,
-// blocks j < k not computed by the (ia|jb) GEMM: mirrored)
-__global__ __launch_bounds__(256) void amplitude_grouped(const AmpDesc* descs, const int64_t* prefix, int n) {
+// one workgroup per occupied pair of every fragment whose prefix counts it
+// (the fragments of one tile shape; whole slab, k0 = 0, blocks j < k not
+// computed by the (ia|jb) GEMM: mirrored)
+template <int AT, int NT>
+__global__ __launch_bounds__(NT) void amplitude_grouped(const AmpDesc* descs, const int64_t* prefix, int n) {
   const int f = find_problem(prefix, n, blockIdx.x);
   const AmpDesc d = descs[f];
   if (*d.status != 0) return;
   const int64_t u = blockIdx.x - prefix[f];
   const int kk = (int)(u / d.nocc), j = (int)(u - (int64_t)kk * d.nocc);
-  amplitude_block(d.V, d.T, d.eo, d.ev, d.nocc, d.nvir, 0, 0, d.nocc, 2, d.nocc, d.energy_only, nullptr, d.e_pair, kk,
-                  j, 0, 1, nullptr);
+  amplitude_block<AT, NT>(d.V, d.T, d.eo, d.ev, d.nocc, d.nvir, 0, 0, d.nocc, 2, d.nocc, d.energy_only, d.write_x,
+                          nullptr, d.e_pair, kk, j, 0, 1, nullptr);
 }
 
 // prefix counts reduce_blocks per problem

@@ -28,14 +28,15 @@ __device__ __forceinline__ void dd_add(double& ah, double& al, double bh, double
   fast_two_sum(s, e, ah, al);
 }
 
-// Fixed-order double-double reduction over the 256 threads of a workgroup.
+// Fixed-order double-double reduction over the NT threads of a workgroup.
+template <int NT = 256>
 __device__ __forceinline__ void block_dd_reduce(double& hi, double& lo) {
-  __shared__ double sh[256], sl[256];
+  __shared__ double sh[NT], sl[NT];
   const int t = threadIdx.x;
   sh[t] = hi;
   sl[t] = lo;
   __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
+  for (int w = NT / 2; w > 0; w >>= 1) {
     if (t < w) {
       double h = sh[t], l = sl[t];
       dd_add(h, l, sh[t + w], sl[t + w]);
@@ -104,11 +105,12 @@ __device__ __forceinline__ void tile_pair_next(int nt, int& ta, int& tb) {
 
 // Writes a workgroup's pair-energy sum: to its (hi, lo) partial slot when the
 // pair is split over several workgroups (epart), else to e_kj (and e_jk).
+template <int NT>
 __device__ __forceinline__ void put_pair_energy(double sh, double sl, double* e_pair, int nocc, int k, int j,
                                                 bool mirror, double* epart) {
   double h, l;
   fast_two_sum(sh, sl, h, l);
-  block_dd_reduce(h, l);
+  block_dd_reduce<NT>(h, l);
   if (threadIdx.x == 0) {
     if (epart) {
       epart[0] = h;
@@ -119,8 +121,6 @@ __device__ __forceinline__ void put_pair_energy(double sh, double sl, double* e_
     }
   }
 }
-
-constexpr int AT = 32;
 
 // Pair (k, j > k) of a slab group k0.. whose slab holds both rows k and j
 // and both columns k and j (columns j0 .. j0+ncols-1, j0 <= k), and whose
@@ -134,17 +134,19 @@ constexpr int AT = 32;
 // e_kj = sum_ab T_kj V_kj (compensated) written to e_kj and e_jk.  The
 // workgroup covers tile pairs [q0, q1) of the block.  VP and VQ are two
 // AT x (AT+1) LDS tiles of the caller.
+template <int AT, int NT>
 __device__ __forceinline__ void amplitude_mirror_block(double* S, double* Tslab, const double* eo, const double* ev,
-                                                       int nocc, int nvir, bool skip, double* e_pair, int k0, int j0,
-                                                       int ncols, int k, int j, int q0, int q1, double* epart,
-                                                       double (*VP)[AT + 1], double (*VQ)[AT + 1]) {
+                                                       int nocc, int nvir, bool skip, bool write_x, double* e_pair,
+                                                       int k0, int j0, int ncols, int k, int j, int q0, int q1,
+                                                       double* epart, double (*VP)[AT + 1], double (*VQ)[AT + 1]) {
+  constexpr int RS = NT / AT, NE = AT / RS;   // rows of a pass, passes over a tile
   const int64_t ld = (int64_t)ncols * nvir;
   double* bkj = S + ((int64_t)(k - k0) * nvir * ncols + (j - j0)) * nvir;  // element (a,b) of pair (k,j) at bkj[a*ld + b]
   double* bjk = S + ((int64_t)(j - k0) * nvir * ncols + (k - j0)) * nvir;
   double* tkj = Tslab + ((int64_t)(k - k0) * nvir * ncols + (j - j0)) * nvir;
   double* tjk = Tslab + ((int64_t)(j - k0) * nvir * ncols + (k - j0)) * nvir;
   const double ekj = eo[k] + eo[j];
-  const int t = threadIdx.x, tc = t & 31, tr0 = t >> 5;
+  const int t = threadIdx.x, tc = t % AT, tr0 = t / AT;
   const int nt = (nvir + AT - 1) / AT;
   double sh = 0.0, sl = 0.0;
   // one element position (a, b) given v = V_kj[a,b] and w = V_kj[b,a]
@@ -156,14 +158,15 @@ __device__ __forceinline__ void amplitude_mirror_block(double* S, double* Tslab,
     two_sum(sh, p, sh, e);
     sl += e;
     const int64_t o = (int64_t)a * ld + b;
-    bkj[o] = xkj; tkj[o] = t1;
-    bjk[o] = xjk; tjk[o] = t2;
+    tkj[o] = t1;
+    tjk[o] = t2;
+    if (write_x) { bkj[o] = xkj; bjk[o] = xjk; }
   };
-  double nP[4], nQ[4];
+  double nP[NE], nQ[NE];
   auto fetch = [&](int ta, int tb) {
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      const int r = tr0 + 8 * s;
+    for (int s = 0; s < NE; ++s) {
+      const int r = tr0 + RS * s;
       const int a = ta * AT + r, b = tb * AT + tc, a2 = tb * AT + r, b2 = ta * AT + tc;
       nP[s] = (!skip && a < nvir && b < nvir) ? bkj[(int64_t)a * ld + b] : 0.0;
       nQ[s] = (!skip && ta != tb && a2 < nvir && b2 < nvir) ? bkj[(int64_t)a2 * ld + b2] : 0.0;
@@ -173,23 +176,23 @@ __device__ __forceinline__ void amplitude_mirror_block(double* S, double* Tslab,
   tile_pair_at(q0, nt, ta, tb);
   if (q0 < q1) fetch(ta, tb);
   for (int q = q0; q < q1; ++q) {
-    double vP[4], vQ[4];
+    double vP[NE], vQ[NE];
 #pragma unroll
-    for (int s = 0; s < 4; ++s) { vP[s] = nP[s]; vQ[s] = nQ[s]; }
+    for (int s = 0; s < NE; ++s) { vP[s] = nP[s]; vQ[s] = nQ[s]; }
     const int cta = ta, ctb = tb;
     const bool diag = (cta == ctb);
     tile_pair_next(nt, ta, tb);
     if (q + 1 < q1) fetch(ta, tb);
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      const int r = tr0 + 8 * s;
+    for (int s = 0; s < NE; ++s) {
+      const int r = tr0 + RS * s;
       VP[r][tc] = vP[s];
       VQ[r][tc] = vQ[s];
     }
     lds_barrier();
 #pragma unroll 1
-    for (int s = 0; s < 4; ++s) {
-      const int r = tr0 + 8 * s;
+    for (int s = 0; s < NE; ++s) {
+      const int r = tr0 + RS * s;
       const int a = cta * AT + r, b = ctb * AT + tc;
       if (a < nvir && b < nvir) put(a, b, vP[s], diag ? VP[tc][r] : VQ[tc][r]);
       const int a2 = ctb * AT + r, b2 = cta * AT + tc;
@@ -197,20 +200,20 @@ __device__ __forceinline__ void amplitude_mirror_block(double* S, double* Tslab,
     }
     lds_barrier();
   }
-  put_pair_energy(sh, sl, e_pair, nocc, k, j, true, epart);
+  put_pair_energy<NT>(sh, sl, e_pair, nocc, k, j, true, epart);
 }
 
 // Amplitude pass over one slab group.
 // V/X slab: element (kk, a, jj, b) at S[((kk*nvir + a)*ncols + jj)*nvir + b],
 // kk < g, jj < ncols, occupied pair (k, j) = (k0 + kk, j0 + jj).
 // Each pair's nvir x nvir block is covered by W workgroups (w < W), each
-// taking a contiguous range of its 32 x 32 tile pairs (ta <= tb); with W > 1
+// taking a contiguous range of its AT x AT tile pairs (ta <= tb); with W > 1
 // the workgroups write (hi, lo) partial sums to epart[2 (p W + w)] for
 // pair_energy_reduce_kernel (p = kk * ncols + jj), else e_pair directly.
 // For each tile pair a workgroup reads V at (a,b) and (b,a), forms
 // X = V / D with D[a,b] = ((eps_k + eps_j) - eps_a) - eps_b in that order (so
 // X^T uses D[b,a] rounded its own way), then T = 2X - X^T, writes X over V
-// and T to the T slab (unless energy_only), and accumulates
+// (with write_x: P_ab and P_ij read X) and T to the T slab (unless energy_only), and accumulates
 // e_kj = sum_ab T[a,b] V[a,b] with compensated per-thread sums and a fixed
 // reduction order.  The next tile pair's V is fetched before the current one
 // is processed.
@@ -233,10 +236,12 @@ __device__ __forceinline__ bool pair_mirrored(int sym, int k0, int g, int j) {
   return sym == 1 || sym == 3 || (sym == 2 && j >= k0 && j < k0 + g);
 }
 
+template <int AT, int NT>
 __device__ __forceinline__ void amplitude_block(double* S, double* Tslab, const double* eo, const double* ev, int nocc,
                                                 int nvir, int k0, int j0, int ncols, int sym, int g, int energy_only,
-                                                const uint8_t* pair_skip, double* e_pair, int kk, int jj, int w,
+                                                int write_x, const uint8_t* pair_skip, double* e_pair, int kk, int jj, int w,
                                                 int W, double* epart_all) {
+  constexpr int RS = NT / AT, NE = AT / RS;
   __shared__ double XP[AT][AT + 1], XQ[AT][AT + 1];   // also the mirror path's V tiles
   const int k = k0 + kk, j = j0 + jj;
   const bool paired = pair_mirrored(sym, k0, g, j);
@@ -251,21 +256,21 @@ __device__ __forceinline__ void amplitude_block(double* S, double* Tslab, const 
   const int nt = (nvir + AT - 1) / AT, npt = nt * (nt + 1) / 2;
   const int q0 = (int)((int64_t)npt * w / W), q1 = (int)((int64_t)npt * (w + 1) / W);
   if ((sym == 2 || sym == 3) && j >= k0 && j < k0 + g && !energy_only && j > k) {
-    amplitude_mirror_block(S, Tslab, eo, ev, nocc, nvir, skip, e_pair, k0, j0, ncols, k, j, q0, q1, epart, XP, XQ);
+    amplitude_mirror_block<AT, NT>(S, Tslab, eo, ev, nocc, nvir, skip, write_x != 0, e_pair, k0, j0, ncols, k, j, q0, q1, epart, XP, XQ);
     return;
   }
   if (skip && energy_only) {
-    put_pair_energy(0.0, 0.0, e_pair, nocc, k, j, paired, epart);
+    put_pair_energy<NT>(0.0, 0.0, e_pair, nocc, k, j, paired, epart);
     return;
   }
   const double ekj = eo[k] + eo[j];
-  const int t = threadIdx.x, tc = t & 31, tr0 = t >> 5;  // 8 rows x 32 cols per pass
+  const int t = threadIdx.x, tc = t % AT, tr0 = t / AT;  // RS rows x AT columns a pass
   double sh = 0.0, sl = 0.0;
-  double nP[4], nQ[4];
+  double nP[NE], nQ[NE];
   auto fetch = [&](int ta, int tb) {
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      const int r = tr0 + 8 * s;
+    for (int s = 0; s < NE; ++s) {
+      const int r = tr0 + RS * s;
       const int a = ta * AT + r, b = tb * AT + tc;   // tile P element (a, b)
       const int a2 = tb * AT + r, b2 = ta * AT + tc; // tile Q element (a2, b2)
       nP[s] = (!skip && a < nvir && b < nvir) ? blk[(int64_t)a * ld + b] : 0.0;
@@ -278,14 +283,14 @@ __device__ __forceinline__ void amplitude_block(double* S, double* Tslab, const 
   for (int q = q0; q < q1; ++q) {
     const int cta = ta, ctb = tb;
     const bool diag = (cta == ctb);
-    double vP[4], vQ[4], xP[4], xQ[4];
+    double vP[NE], vQ[NE], xP[NE], xQ[NE];
 #pragma unroll
-    for (int s = 0; s < 4; ++s) { vP[s] = nP[s]; vQ[s] = nQ[s]; }
+    for (int s = 0; s < NE; ++s) { vP[s] = nP[s]; vQ[s] = nQ[s]; }
     tile_pair_next(nt, ta, tb);
     if (q + 1 < q1) fetch(ta, tb);
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      const int r = tr0 + 8 * s;
+    for (int s = 0; s < NE; ++s) {
+      const int r = tr0 + RS * s;
       const int a = cta * AT + r, b = ctb * AT + tc;
       const int a2 = ctb * AT + r, b2 = cta * AT + tc;
       double x = 0.0;
@@ -297,8 +302,8 @@ __device__ __forceinline__ void amplitude_block(double* S, double* Tslab, const 
     }
     lds_barrier();
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      const int r = tr0 + 8 * s;
+    for (int s = 0; s < NE; ++s) {
+      const int r = tr0 + RS * s;
       const int a = cta * AT + r, b = ctb * AT + tc;
       const double xt = diag ? XP[tc][r] : XQ[tc][r];   // X[b, a]
       const double tv = 2.0 * xP[s] - xt;
@@ -306,7 +311,8 @@ __device__ __forceinline__ void amplitude_block(double* S, double* Tslab, const 
         double p = tv * vP[s], e;
         two_sum(sh, p, sh, e);
         sl += e;
-        if (!energy_only) { blk[(int64_t)a * ld + b] = xP[s]; tblk[(int64_t)a * ld + b] = tv; }
+        if (!energy_only) tblk[(int64_t)a * ld + b] = tv;
+        if (write_x) blk[(int64_t)a * ld + b] = xP[s];
       }
       if (!diag) {
         const int a2 = ctb * AT + r, b2 = cta * AT + tc;
@@ -316,25 +322,27 @@ __device__ __forceinline__ void amplitude_block(double* S, double* Tslab, const 
           double p = tv2 * vQ[s], e;
           two_sum(sh, p, sh, e);
           sl += e;
-          if (!energy_only) { blk[(int64_t)a2 * ld + b2] = xQ[s]; tblk[(int64_t)a2 * ld + b2] = tv2; }
+          if (!energy_only) tblk[(int64_t)a2 * ld + b2] = tv2;
+          if (write_x) blk[(int64_t)a2 * ld + b2] = xQ[s];
         }
       }
     }
     lds_barrier();
   }
-  put_pair_energy(sh, sl, e_pair, nocc, k, j, paired, epart);
+  put_pair_energy<NT>(sh, sl, e_pair, nocc, k, j, paired, epart);
 }
 
 // One workgroup per (pair, w): blockIdx.x = (kk * ncols + jj) * W + w.
-__global__ __launch_bounds__(256) void amplitude_kernel(double* S, double* Tslab, const double* eo, const double* ev,
-                                                        int nocc, int nvir, int k0, int j0, int ncols, int sym, int g,
-                                                        int energy_only, const uint8_t* pair_skip, double* e_pair,
-                                                        int W, double* epart, const int32_t* status) {
+template <int AT, int NT>
+__global__ __launch_bounds__(NT) void amplitude_kernel(double* S, double* Tslab, const double* eo, const double* ev,
+                                                       int nocc, int nvir, int k0, int j0, int ncols, int sym, int g,
+                                                       int energy_only, int write_x, const uint8_t* pair_skip,
+                                                       double* e_pair, int W, double* epart, const int32_t* status) {
   if (*status != 0) return;
   const int p = blockIdx.x / W, w = blockIdx.x - p * W;
   const int kk = p / ncols, jj = p - kk * ncols;
-  amplitude_block(S, Tslab, eo, ev, nocc, nvir, k0, j0, ncols, sym, g, energy_only, pair_skip, e_pair, kk, jj, w, W,
-                  epart);
+  amplitude_block<AT, NT>(S, Tslab, eo, ev, nocc, nvir, k0, j0, ncols, sym, g, energy_only, write_x, pair_skip, e_pair,
+                          kk, jj, w, W, epart);
 }
 
 // e_kj from the W partial sums of each pair of a slab group (double-double,

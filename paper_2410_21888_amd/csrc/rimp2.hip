@@ -228,8 +228,16 @@ struct Plan {
 // of nvir x nvir: enough for about 8 waves of the resident workgroups, at
 // most kAmpSplitMax and at most one per tile pair.
 constexpr int64_t kAmpSplitMax = 64;
-int64_t amp_splits(int64_t pairs, int64_t nvir) {
-  const int64_t nt = (nvir + 31) / 32, npt = nt * (nt + 1) / 2;
+// Tile side of an amplitude launch (HBM-bound).  Rows of 64 doubles leave half
+// as many partly written cache lines as rows of 32: E+Gamma of 97/485/1746
+// 18.4 -> 8.8 ms (of that about 7 for X, which only P_ab and P_ij read and is
+// no longer written without them), with P of 61/305/1098 2.83 -> 2.24 ms, of
+// 37/211/733 384 -> 336 us.  A pass that writes nothing is faster with the
+// small tile's 8 workgroups a CU (100/600: 4.6 ms against 6.6), and so are few
+// virtual orbitals, which a tile of 64 would pad.
+int64_t amp_tile(int64_t nvir, bool energy_only) { return !energy_only && nvir >= 192 ? 64 : 32; }
+int64_t amp_splits(int64_t pairs, int64_t nvir, bool energy_only) {
+  const int64_t t = amp_tile(nvir, energy_only), nt = cdiv(nvir, t), npt = nt * (nt + 1) / 2;
   const int64_t w = (6144 + pairs - 1) / pairs;
   return std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(w, kAmpSplitMax), npt));
 }
@@ -329,7 +337,7 @@ int make_plan(int64_t nocc, int64_t nvir, int64_t naux, bool gamma, bool density
     for (int64_t k0 = 0; k0 < nocc;) {
       const int64_t gc = group_at(*p, k0);
       const int64_t pairs = gc * ((eonly || p->sym) ? nocc - k0 : nocc);
-      const int64_t W = amp_splits(pairs, nvir);
+      const int64_t W = amp_splits(pairs, nvir, eonly);
       if (W > 1) most = std::max(most, pairs * W);
       k0 += gc;
     }
@@ -864,14 +872,20 @@ int run_fragment(const Plan& P, const double* B, const double* eo, const double*
       }
     }
     {
-      const int64_t W = amp_splits(gc * ncols, nvir);
+      const int64_t W = amp_splits(gc * ncols, nvir, energy_only);
       double* epart = (double*)(ws + P.off_epart);
       const int sym = energy_only ? 1 : (P.sym ? 3 : 2);
       if ((rc = check_grid(gc * ncols * W, "amplitude"))) return rc;
-      if ((rc = traced(R_AMP, 0, 0, energy_only ? slab : 3.0 * slab, st, [&] {
-             hipLaunchKernelGGL(amplitude_kernel, dim3((unsigned)(gc * ncols * W)), dim3(256), 0, st, V, T, eo, ev,
-                                (int)nocc, (int)nvir, (int)k0, (int)j0, (int)ncols, sym, (int)gc,
-                                energy_only ? 1 : 0, skip, ep, (int)W, epart, status);
+      if ((rc = traced(R_AMP, 0, 0, energy_only ? slab : (P.density ? 3.0 : 2.0) * slab, st, [&] {
+             const int wx = P.density ? 1 : 0, eo_only = energy_only ? 1 : 0;
+             if (amp_tile(nvir, energy_only) == 64)
+               hipLaunchKernelGGL((amplitude_kernel<64, 512>), dim3((unsigned)(gc * ncols * W)), dim3(512), 0, st, V, T,
+                                  eo, ev, (int)nocc, (int)nvir, (int)k0, (int)j0, (int)ncols, sym, (int)gc, eo_only, wx,
+                                  skip, ep, (int)W, epart, status);
+             else
+               hipLaunchKernelGGL((amplitude_kernel<32, 256>), dim3((unsigned)(gc * ncols * W)), dim3(256), 0, st, V, T,
+                                  eo, ev, (int)nocc, (int)nvir, (int)k0, (int)j0, (int)ncols, sym, (int)gc, eo_only, wx,
+                                  skip, ep, (int)W, epart, status);
              if (W > 1)
                hipLaunchKernelGGL(pair_energy_reduce_kernel, dim3((unsigned)cdiv(gc * ncols, 256)), dim3(256), 0, st,
                                   (const double*)epart, (int)W, (int)nocc, (int)k0, (int)j0, (int)gc, (int)ncols, sym,
@@ -1150,7 +1164,7 @@ struct Wave {
   size_t host_off = 0;          // offset of this wave's tables in the pinned blob
   size_t bytes = 0;             // tables + fragment partitions
   // offsets within the tables
-  size_t o_fs, o_idx, o_amp, o_amp_pre, o_red, o_red_pre, o_cnt;
+  size_t o_fs, o_idx, o_amp, o_amp_pre[2], o_red, o_red_pre, o_cnt;   // o_amp_pre: tiles of 32, of 64 (amp_tile)
   // GEMM lists, index glist(role, candidate tile, loader): every GEMM is
   // listed once per candidate tile shape (kBatchTile)
   size_t o_g[kGLists], o_pre[kGLists];
@@ -1158,7 +1172,7 @@ struct Wave {
   int64_t items_g[kGLists];
   uint64_t sig = 0;             // hash of the wave's fragment sizes (autotuner key)
   int namp, nred_ab, nred_ij;
-  int64_t amp_blocks, red_blocks_ab, red_blocks_ij;
+  int64_t amp_blocks[2], red_blocks_ab, red_blocks_ij;
   // split products (precision RIMP2_SPLIT_INT8): grouped (ia|jb) and Gamma
   // product lists, run in reduction windows (win_* launches each), with one
   // work counter per launch
@@ -1290,7 +1304,7 @@ int batch_plan(int32_t nfrag, const rimp2_frag_desc* d, const rimp2_opts* opts, 
     W.o_fs = place(t, sizeof(FragSmall) * n);
     W.o_idx = place(t, sizeof(int32_t) * n);
     W.o_amp = place(t, sizeof(AmpDesc) * n);
-    W.o_amp_pre = place(t, sizeof(int64_t) * (n + 1));
+    for (size_t& o : W.o_amp_pre) o = place(t, sizeof(int64_t) * (n + 1));
     W.o_red = place(t, sizeof(ReduceDesc) * 2 * n);
     W.o_red_pre = place(t, sizeof(int64_t) * (2 * n + 1));
     for (int r = 0; r < kGLists; ++r) {
@@ -1326,7 +1340,7 @@ int batch_plan(int32_t nfrag, const rimp2_frag_desc* d, const rimp2_opts* opts, 
     std::vector<FragSmall> fs(n);
     std::vector<int32_t> idx(n);
     std::vector<AmpDesc> amp(n);
-    std::vector<int64_t> amp_pre(n + 1, 0);
+    std::vector<int64_t> amp_pre[2] = {std::vector<int64_t>(n + 1, 0), std::vector<int64_t>(n + 1, 0)};
     std::vector<ReduceDesc> red;
     std::vector<int64_t> red_pre(1, 0);
     GemmList gl[kGLists];
@@ -1369,8 +1383,10 @@ int batch_plan(int32_t nfrag, const rimp2_frag_desc* d, const rimp2_opts* opts, 
       double* ep = q.e_pair ? q.e_pair : relp<double>(base + P.off_e);
       fs[i] = FragSmall{q.eps_occ, q.eps_vir, ep, q.E, status, q.nocc, q.nvir};
       idx[i] = f;
-      amp[i] = AmpDesc{V, T, q.eps_occ, q.eps_vir, ep, status, q.nocc, q.nvir, (P.gamma || P.density) ? 0 : 1};
-      amp_pre[i + 1] = amp_pre[i] + nocc * nocc;
+      amp[i] = AmpDesc{V, T, q.eps_occ, q.eps_vir, ep, status, q.nocc, q.nvir, (P.gamma || P.density) ? 0 : 1,
+                       P.density ? 1 : 0};
+      const int big = amp_tile(nvir, !(P.gamma || P.density)) == 64 ? 1 : 0;
+      for (int b = 0; b < 2; ++b) amp_pre[b][i + 1] = amp_pre[b][i] + (b == big ? nocc * nocc : 0);
       if (split) {  // (ia|jb) and Gamma as INT8 digit products of the whole slab
         OzParams z{};
         z.M = L; z.N = L; z.kp = P.kpv; z.k0 = 0; z.kc = P.kpv;
@@ -1451,7 +1467,7 @@ int batch_plan(int32_t nfrag, const rimp2_frag_desc* d, const rimp2_opts* opts, 
     W.bytes = poff;
     ws = std::max(ws, poff);
     W.namp = n;
-    W.amp_blocks = amp_pre[n];
+    for (int b = 0; b < 2; ++b) W.amp_blocks[b] = amp_pre[b][n];
     W.nred_ab = (int)red.size();
     W.red_blocks_ab = red_pre.back();
     for (int r = 0; r < kGLists; ++r) { W.n_g[r] = (int)gl[r].p.size(); W.items_g[r] = gl[r].prefix.back(); }
@@ -1461,7 +1477,7 @@ int batch_plan(int32_t nfrag, const rimp2_frag_desc* d, const rimp2_opts* opts, 
     put(W.o_fs, fs.data(), sizeof(FragSmall) * n);
     put(W.o_idx, idx.data(), sizeof(int32_t) * n);
     put(W.o_amp, amp.data(), sizeof(AmpDesc) * n);
-    put(W.o_amp_pre, amp_pre.data(), sizeof(int64_t) * (n + 1));
+    for (int b = 0; b < 2; ++b) put(W.o_amp_pre[b], amp_pre[b].data(), sizeof(int64_t) * (n + 1));
     put(W.o_red, red.data(), sizeof(ReduceDesc) * red.size());
     put(W.o_red_pre, red_pre.data(), sizeof(int64_t) * red_pre.size());
     for (int r = 0; r < kGLists; ++r) {
@@ -1719,8 +1735,12 @@ int batch_run(rimp2_batch_s* B, int32_t* status_dev, void* workspace, size_t byt
     };
     if ((rc = B->split ? run_split(0) : run_role(0))) return rc;
     if ((rc = traced(R_AMP, 0, 0, 0, st, [&] {
-           hipLaunchKernelGGL(amplitude_grouped, dim3((unsigned)W.amp_blocks), dim3(256), 0, st,
-                              (const AmpDesc*)at(W.o_amp), (const int64_t*)at(W.o_amp_pre), n);
+           if (W.amp_blocks[0])
+             hipLaunchKernelGGL((amplitude_grouped<32, 256>), dim3((unsigned)W.amp_blocks[0]), dim3(256), 0, st,
+                                (const AmpDesc*)at(W.o_amp), (const int64_t*)at(W.o_amp_pre[0]), n);
+           if (W.amp_blocks[1])
+             hipLaunchKernelGGL((amplitude_grouped<64, 512>), dim3((unsigned)W.amp_blocks[1]), dim3(512), 0, st,
+                                (const AmpDesc*)at(W.o_amp), (const int64_t*)at(W.o_amp_pre[1]), n);
          })))
       return rc;
     if ((rc = B->split ? run_split(1) : run_role(1)) || (rc = run_role(2)) || (rc = run_role(3))) return rc;
