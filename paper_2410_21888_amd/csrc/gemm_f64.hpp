@@ -68,6 +68,10 @@ struct GemmParams {
   int64_t ldc;
   int64_t split_stride;
   int32_t accumulate;   // nonzero: C += A B instead of C = A B (no split-K)
+  // batch > 1: that many products of the same sizes in one launch (splits is
+  // 1); product z uses A + z batch_a, B + z batch_b and C + z split_stride
+  int32_t batch;
+  int64_t batch_a, batch_b;
   const int32_t* status;  // nonzero: do nothing
   // Optional pair screening of an (ia|jb) slab: row m belongs to occupied
   // orbital skip_k0 + m / skip_nvir, column n to skip_j0 + n / skip_nvir; a
@@ -113,7 +117,7 @@ __device__ __forceinline__ int xcd_remap(int w, int G) {
 // ROLE gives each contraction its own kernel symbol (profiler names);
 // ROLE_GAMMA_T and ROLE_AO also select the M-contiguous A loader.
 enum GemmRole { ROLE_INTS = 0, ROLE_GAMMA = 1, ROLE_PAB = 2, ROLE_PIJ = 3, ROLE_GAMMA_T = 4, ROLE_AO = 5,
-                ROLE_LTERM = 6 };
+                ROLE_LTERM = 6, ROLE_BATCH = 7 };
 // Roles whose A operand is M-contiguous.
 constexpr bool role_a_mcontig(int role) { return role == ROLE_GAMMA_T || role == ROLE_AO; }
 
@@ -604,15 +608,23 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, int tm, int tn, i
 
 
 // One workgroup per (split, tile); the hardware id is remapped XCD-aware.
+// Roles launched as batches of products.
+constexpr bool role_batched(int role) { return role == ROLE_AO || role == ROLE_BATCH; }
 template <int BM, int BN, int BK, bool B_NCONTIG, int ROLE, bool VEC, bool TRI, int FAST = 0>
 __global__ __launch_bounds__(256, 2) void gemm_f64_kernel(GemmParams p) {
   if (p.status != nullptr && *p.status != 0) return;
   __shared__ GemmLds<BM, BN, BK> lds;
   const int wl = xcd_remap(blockIdx.x, gridDim.x);
   const int ntiles = TRI ? p.tiles_m * (p.tiles_m + 1) / 2 : p.tiles_m * p.tiles_n;
-  const int z = wl / ntiles;   // 0 in a pair_upper launch: at most ntiles workgroups
+  int z = wl / ntiles;   // 0 in a pair_upper launch: at most ntiles workgroups
   int tm, tn;
   decode_tile<BM, BN, TRI>(p, wl - z * ntiles, tm, tn);
+  if (role_batched(ROLE) && p.batch > 1) {
+    if (role_a_mcontig(ROLE)) p.Am.base += z * p.batch_a; else p.A.base += z * p.batch_a;
+    if (B_NCONTIG) p.Bn.base += z * p.batch_b; else p.Bk.base += z * p.batch_b;
+    p.C += z * p.split_stride;
+    z = 0;
+  }
   if (tile_screened<BM, BN>(p, tm, tn)) return;
   gemm_tile<BM, BN, BK, B_NCONTIG, VEC, TRI, FAST, role_a_mcontig(ROLE)>(p, tm, tn, z, lds);
 }

@@ -54,12 +54,12 @@ namespace {
 
 // ---- kernel timing -------------------------------------------------------
 enum Role { R_GAP, R_INTS, R_AMP, R_GAMMA, R_PAB, R_PIJ, R_REDUCE, R_ESUM, R_STATUS, R_SPLIT, R_INTS8, R_GAMMA8,
-            R_GAMMA_T, R_GAMMA_AO, R_LTERM, R_RESPONSE, R_GAMMA_T8, R_NROLES };
+            R_GAMMA_T, R_GAMMA_AO, R_LTERM, R_RESPONSE, R_GAMMA_T8, R_GAMMA_METRIC, R_NROLES };
 const char* const kRoleName[R_NROLES] = {"gap_check",  "ints_gemm",     "amplitude",  "gamma_gemm",
                                          "pab_gemm",   "pij_gemm",      "splitk_reduce", "energy_sum",
                                          "status_copy", "digit_split", "ints_oz8",   "gamma_oz8",
                                          "gamma_t_gemm", "gamma_ao_gemm", "l_terms_gemm", "response",
-                                         "gamma_t_oz8"};
+                                         "gamma_t_oz8", "gamma_metric"};
 struct TraceRec {
   int role;
   hipEvent_t e0, e1;
@@ -168,14 +168,16 @@ struct GemmChoice {
 // tiles) and those that give every CU 1 to 8 workgroups.  With one tile shape and 64 splits of 2048 at most, P_ij of
 // nocc = 61 ran on 64 workgroups (8.0 ms, 1.6 ms now) and Gamma of 20/100/400 on
 // 64 (288 us, 90 us now).
-GemmChoice choose_gemm(int64_t M, int64_t N, int64_t K, bool tri, const int* bms, int64_t smax = kMaxSplits) {
+// batch: that many such products in one launch.
+GemmChoice choose_gemm(int64_t M, int64_t N, int64_t K, bool tri, const int* bms, int64_t smax = kMaxSplits,
+                       int64_t batch = 1) {
   GemmChoice best{0, 1};
   double best_us = 0.0;
   smax = std::max<int64_t>(1, std::min<int64_t>(smax, K / (4 * kBK)));
   for (; *bms; ++bms) {
     const TileCost* t = kTileCost;
     while (t->bm != *bms) ++t;
-    const int64_t tm = cdiv(M, t->bm), tn = cdiv(N, t->bm), tiles = tri ? tm * (tm + 1) / 2 : tm * tn;
+    const int64_t tm = cdiv(M, t->bm), tn = cdiv(N, t->bm), tiles = (tri ? tm * (tm + 1) / 2 : tm * tn) * batch;
     for (int64_t w = 1; w <= 12; ++w) {
       const int64_t s = std::min<int64_t>(smax, w <= 4 ? w : (w - 4) * (int64_t)kCUs / tiles);
       if (s < 1) continue;
@@ -201,7 +203,7 @@ GemmChoice grouped_choice(int bm, int64_t K, int64_t klen) {
 }
 // Tile shapes instantiated for each product.
 constexpr int kIntsTiles[] = {128, 64, 0}, kGammaTiles[] = {128, 64, 0}, kPabTiles[] = {128, 96, 64, 0},
-              kPijTiles[] = {128, 64, 32, 0}, kLtermTiles[] = {128, 64, 0};
+              kPijTiles[] = {128, 64, 32, 0}, kLtermTiles[] = {128, 64, 0}, kAoTiles[] = {128, 64, 0};
 
 struct Plan {
   int64_t nocc, nvir, naux;
@@ -407,6 +409,7 @@ bool kop_vec(const KOperand& o, int64_t K) {
 // even).  amc: A is M-contiguous (pairs of rows, like an N-contiguous B).
 bool gemm_vec(const GemmParams& gp, bool nc, bool amc = false) {
   const bool a = amc ? ((uintptr_t)gp.Am.base % 16 == 0 && gp.Am.ld % 2 == 0) : kop_vec(gp.A, gp.K);
+  if (gp.batch > 1 && (gp.batch_a % 2 || gp.batch_b % 2)) return false;
   return a && (nc ? ((uintptr_t)gp.Bn.base % 16 == 0 && gp.Bn.ld % 2 == 0) : kop_vec(gp.Bk, gp.K));
 }
 
@@ -450,7 +453,8 @@ int launch_gemm(GemmParams gp, hipStream_t st, int role, double af, double ab, b
   gp.splits = (int32_t)cdiv(gp.K, gp.kchunk);
   if (TRI && (gp.M != gp.N || BM != BN)) return fail(RIMP2_EINVAL, "triangular GEMM needs a square tile grid");
   if (gp.pair_upper && gp.splits != 1) return fail(RIMP2_EINVAL, "pair_upper GEMM without split-K only");
-  const int64_t nwg = gemm_tiles(gp, BM, BN, TRI) * gp.splits;
+  if (gp.batch > 1 && (gp.splits != 1 || !role_batched(ROLE))) return fail(RIMP2_EINVAL, "batched GEMM without split-K only");
+  const int64_t nwg = gemm_tiles(gp, BM, BN, TRI) * std::max(gp.splits, gp.batch);
   if (int rc = check_grid(nwg, "GEMM")) return rc;
   constexpr bool AMC = role_a_mcontig(ROLE);
   if (AMC && gp.splits != 1) return fail(RIMP2_EINVAL, "M-contiguous GEMM without split-K only");
@@ -1985,6 +1989,43 @@ int rimp2_autotune_reset(void) {
 
 // ---- adjacent gradient steps (include/rimp2_gradient.h) --------------------
 
+namespace {
+// GEMMs of the gradient steps, with the tile of the smallest estimate (no
+// split-K unless the caller planned it): A M-contiguous; A and B K-contiguous
+// (bm given); A K-contiguous and B N-contiguous.
+int launch_ao(const GemmParams& gp, hipStream_t st, int role, double af, double ab) {
+  const int bm = choose_gemm(gp.M, gp.N, gp.K, false, kAoTiles, 1, std::max(1, gp.batch)).bm;
+  return bm == 64 ? launch_gemm<64, 64, true, ROLE_AO, false>(gp, st, role, af, ab, false)
+                  : launch_gemm<128, 128, true, ROLE_AO, false>(gp, st, role, af, ab, false);
+}
+int launch_lterm(int bm, const GemmParams& gp, hipStream_t st, int role, double af, double ab) {
+  return bm == 64 ? launch_gemm<64, 64, false, ROLE_LTERM, false>(gp, st, role, af, ab, false)
+                  : launch_gemm<128, 128, false, ROLE_LTERM, false>(gp, st, role, af, ab, false);
+}
+int launch_batch(const GemmParams& gp, hipStream_t st, int role, double af, double ab) {
+  const int bm = choose_gemm(gp.M, gp.N, gp.K, false, kAoTiles, 1, std::max(1, gp.batch)).bm;
+  return bm == 64 ? launch_gemm<64, 64, true, ROLE_BATCH, false>(gp, st, role, af, ab, false)
+                  : launch_gemm<128, 128, true, ROLE_BATCH, false>(gp, st, role, af, ab, false);
+}
+}  // namespace
+
+int rimp2_gamma_metric(int32_t nocc, int32_t nvir, int32_t naux, const double* Gamma, const double* Jm, double* out,
+                       void* stream) {
+  if (nocc < 1 || nvir < 1 || naux < 1) return fail(RIMP2_EINVAL, "sizes must be >= 1");
+  if (!Gamma || !Jm || !out) return fail(RIMP2_EINVAL, "Gamma, Jm and out must not be NULL");
+  const int64_t M = (int64_t)nocc * nvir, n = naux;
+  const char *g0 = (const char*)Gamma, *g1 = (const char*)(Gamma + M * n), *o0 = (const char*)out,
+             *o1 = (const char*)(out + M * n);
+  if (o0 < g1 && g0 < o1) return fail(RIMP2_EINVAL, "out must not overlap Gamma");
+  GemmParams gp{};
+  gp.M = M; gp.N = n; gp.K = n; gp.kchunk = n;
+  gp.A = kop(Gamma, n, INT64_MAX, 0);   // row (i,a), reduction Q
+  gp.Bk = kop(Jm, n, INT64_MAX, 0);     // row P, reduction Q
+  gp.C = out; gp.ldc = n;
+  return launch_lterm(choose_gemm(M, n, n, false, kLtermTiles, 1).bm, gp, (hipStream_t)stream, R_GAMMA_METRIC,
+                      2.0 * M * n * n, 8.0 * (2.0 * M * n + n * n));
+}
+
 int rimp2_gamma_ao_workspace_size(int32_t nocc, int32_t nao, int32_t pcount, size_t* bytes) {
   if (!bytes) return fail(RIMP2_EINVAL, "bytes is NULL");
   if (nocc < 1 || nao < 1 || pcount < 1) return fail(RIMP2_EINVAL, "sizes must be >= 1");
@@ -2014,15 +2055,17 @@ int rimp2_gamma_ao(int32_t nocc, int32_t nvir, int32_t nao, int32_t naux, int32_
          hipLaunchKernelGGL(zero_u64_kernel, dim3(1), dim3(256), 0, st, status, 1);
        })))
     return rc;
-  // H[i][n][P] = sum_a C_vir[a][n] Gamma[i][a][p0 + P], one GEMM per occupied orbital
-  for (int64_t i = 0; i < nocc; ++i) {
+  // H[i][n][P] = sum_a C_vir[a][n] Gamma[i][a][p0 + P]: one launch over the
+  // occupied orbitals (one launch each held 4 workgroups at nao = pcount = 240:
+  // 40 x 35 us, 30 us now)
+  {
     GemmParams gp{};
     gp.M = na; gp.N = pc; gp.K = nvir; gp.kchunk = nvir;
     gp.Am = NOperand{C_vir, na};
-    gp.Bn = NOperand{Gamma + i * nvir * (int64_t)naux + p0, naux};
-    gp.C = H + i * na * pc; gp.ldc = pc; gp.status = (const int32_t*)status;
-    if ((rc = launch_gemm<128, 128, true, ROLE_AO, false>(gp, st, R_GAMMA_AO, 2.0 * na * pc * nvir,
-                                                           8.0 * (nvir * (na + pc) + na * pc), false)))
+    gp.Bn = NOperand{Gamma + p0, naux};
+    gp.batch = nocc; gp.batch_a = 0; gp.batch_b = (int64_t)nvir * naux; gp.split_stride = na * pc;
+    gp.C = H; gp.ldc = pc; gp.status = (const int32_t*)status;
+    if ((rc = launch_ao(gp, st, R_GAMMA_AO, 2.0 * nocc * na * pc * nvir, 8.0 * nocc * (nvir * (na + pc) + na * pc))))
       return rc;
   }
   // out[m][(n, P)] = sum_i C_occ[i][m] H[i][(n, P)]
@@ -2031,16 +2074,11 @@ int rimp2_gamma_ao(int32_t nocc, int32_t nvir, int32_t nao, int32_t naux, int32_
   gp.Am = NOperand{C_occ, na};
   gp.Bn = NOperand{H, na * pc};
   gp.C = out; gp.ldc = na * pc; gp.status = (const int32_t*)status;
-  return launch_gemm<128, 128, true, ROLE_AO, false>(gp, st, R_GAMMA_AO, 2.0 * na * na * pc * nocc,
-                                                     8.0 * (nocc * na + nocc * na * pc + na * na * pc), false);
+  return launch_ao(gp, st, R_GAMMA_AO, 2.0 * na * na * pc * nocc, 8.0 * (nocc * na + nocc * na * pc + na * na * pc));
 }
 
 namespace {
 // Split-K plan of the two L-term GEMMs: M x N outputs over reduction K.
-int launch_lterm(int bm, const GemmParams& gp, hipStream_t st, int role, double af, double ab) {
-  return bm == 64 ? launch_gemm<64, 64, false, ROLE_LTERM, false>(gp, st, role, af, ab, false)
-                  : launch_gemm<128, 128, false, ROLE_LTERM, false>(gp, st, role, af, ab, false);
-}
 struct LPlan {
   GemmChoice c1, c2;
   size_t part_bytes;
@@ -2111,61 +2149,113 @@ int rimp2_l_terms(int32_t nocc, int32_t nvir, int32_t nmo, int32_t naux, const d
   return RIMP2_OK;
 }
 
+}  // extern "C"
+
 // ---- orbital response: antisymmetrised-integral term, Z-vector, W ---------------
 namespace {
 
-// c_part[z][P] = sum over (r, s) pairs of chunk z of Bf[r][s][P] D[r][s]
-// (fixed chunking: deterministic after the ordered reduction).
-__global__ __launch_bounds__(256) void coulomb_vector_kernel(const double* Bf, const double* D, int64_t npairs,
-                                                             int64_t naux, int64_t chunk, double* part,
-                                                             const int32_t* status) {
+// The nonzero block of a density: D_rs = D[(r - r0) * ld + s - c0] for r0 <= r
+// < r0 + nr, c0 <= s < c0 + nc, and 0 outside it.
+struct DBlock {
+  const double* D;
+  int64_t ld, r0, nr, c0, nc;
+};
+
+// c_part[z][P] = sum over the pairs (r, s) of chunk z of the density's block
+// of Bf[r][s][P] D[r][s] (fixed chunking: deterministic after the ordered
+// reduction).
+__global__ __launch_bounds__(256) void coulomb_vector_kernel(const double* Bf, DBlock d, int64_t nmo, int64_t naux,
+                                                             int64_t chunk, double* part, const int32_t* status) {
   if (*status != 0) return;
   const int64_t P = (int64_t)blockIdx.x * 256 + threadIdx.x, z = blockIdx.y;
   if (P >= naux) return;
-  const int64_t rs0 = z * chunk, rs1 = min(npairs, rs0 + chunk);
+  const int64_t rs0 = z * chunk, rs1 = min(d.nr * d.nc, rs0 + chunk);
+  int64_t r = rs0 / d.nc, q = rs0 - r * d.nc;
   double s = 0.0;
-  for (int64_t rs = rs0; rs < rs1; ++rs) s += Bf[rs * naux + P] * D[rs];
+#pragma unroll 8
+  for (int64_t rs = rs0; rs < rs1; ++rs) {
+    s += Bf[((d.r0 + r) * nmo + d.c0 + q) * naux + P] * d.D[r * d.ld + q];
+    const bool next = ++q == d.nc;
+    q = next ? 0 : q;
+    r += next ? 1 : 0;
+  }
   part[z * naux + P] = s;
 }
 
-// out[p][q] = 2 sum_P Bf[p][q][P] c[P] - K[p][q] for p < nrows (rows r0..),
-// q < ncols (columns c0..); one wave per (p, q), lanes over P, fixed-order
-// wave reduction.
+// The antisymmetrised term G[p][q] = 2 sum_P Bf[r0 + p][c0 + q][P] c[P] - K[p][q]
+// for p < nrows, q < ncols; one wave per (p, q), lanes over P, fixed-order wave
+// reduction.  ROLE 0 writes it to F (row stride ldf).  For the Z-vector's rows
+// a and columns i (gap = (eps_a - eps_i)/2):
+//   ROLE 1  F = gap x[a][i] + G                                (operator)
+//   ROLE 2  F = L2[a][i] - L1[i][nocc + a] - G (right-hand side), diag = gap +
+//           sum_P Bf[a][i][P]^2 (the operator's diagonal), x = F / diag
+struct ZElem {
+  const double *eo, *ev, *L1, *L2;
+  double *x, *diag;
+};
+template <int ROLE>
 __global__ __launch_bounds__(256) void antisym_combine_kernel(const double* Bf, int64_t nmo, int64_t naux,
                                                               int64_t r0, int64_t nrows, int64_t c0, int64_t ncols,
                                                               const double* c, const double* K, double* F,
-                                                              int64_t ldf, const int32_t* status) {
+                                                              int64_t ldf, ZElem z, const int32_t* status) {
   if (*status != 0) return;
   const int64_t e = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   if (e >= nrows * ncols) return;
   const int64_t p = e / ncols, q = e - p * ncols;
   const double* row = Bf + ((r0 + p) * nmo + c0 + q) * naux;
-  double s = 0.0;
-  for (int64_t P = lane; P < naux; P += 64) s += row[P] * c[P];
-  for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
-  if (lane == 0) F[p * ldf + q] = 2.0 * s - K[p * ncols + q];
+  double s = 0.0, d = 0.0;
+#pragma unroll 4
+  for (int64_t P = lane; P < naux; P += 64) {
+    const double b = row[P];
+    s += b * c[P];
+    if (ROLE == 2) d += b * b;
+  }
+  for (int off = 32; off > 0; off >>= 1) {
+    s += __shfl_down(s, off, 64);
+    if (ROLE == 2) d += __shfl_down(d, off, 64);
+  }
+  if (lane != 0) return;
+  const double g = 2.0 * s - K[p * ncols + q];
+  if (ROLE == 0) {
+    F[p * ldf + q] = g;
+    return;
+  }
+  const double gap = (z.ev[p] - z.eo[q]) / 2.0;
+  if (ROLE == 1) {
+    F[e] = gap * z.x[e] + g;
+  } else {
+    const double rhs = (z.L2[p * nmo + q] - z.L1[q * nmo + ncols + p]) - g, dg = gap + d;
+    F[e] = rhs;
+    z.diag[e] = dg;
+    z.x[e] = rhs / dg;
+  }
 }
 
 struct AntisymPlan {
-  int64_t nmo, naux, nrows, ncols, chunks, chunk;
+  int64_t nmo, naux, nrows, ncols, nr, nc, chunks, chunk;
+  bool rows_first;
   GemmChoice c_k;
   size_t off_status, off_cpart, off_c, off_Y, off_Kp, off_K, total;
 };
 
-AntisymPlan antisym_plan(int64_t nmo, int64_t naux, int64_t nrows, int64_t ncols) {
+// nrows x ncols results from a density whose nonzero block is nr x nc.
+AntisymPlan antisym_plan(int64_t nmo, int64_t naux, int64_t nrows, int64_t ncols, int64_t nr, int64_t nc) {
   AntisymPlan A{};
-  A.nmo = nmo; A.naux = naux; A.nrows = nrows; A.ncols = ncols;
-  const int64_t npairs = nmo * nmo;
-  A.chunks = std::max<int64_t>(1, std::min<int64_t>(256, npairs / 64));
+  A.nmo = nmo; A.naux = naux; A.nrows = nrows; A.ncols = ncols; A.nr = nr; A.nc = nc;
+  const int64_t npairs = nr * nc;
+  A.chunks = std::max<int64_t>(1, std::min<int64_t>(256, npairs / 32));
   A.chunk = cdiv(npairs, A.chunks);
   A.chunks = cdiv(npairs, A.chunk);
-  A.c_k = choose_gemm(nrows, ncols, nmo * naux, false, kLtermTiles);
+  // the exchange part's order: D against Bf's columns (Y) or rows (Z) first,
+  // whichever takes fewer multiply-adds
+  A.rows_first = (double)nrows * nr * nc + (double)nrows * ncols * nr < (double)nc * ncols * nr + (double)nrows * ncols * nc;
+  A.c_k = choose_gemm(nrows, ncols, (A.rows_first ? nr : nc) * naux, false, kLtermTiles);
   size_t off = 0;
   A.off_status = off; off = align_up(off + 64);
   A.off_cpart = off; off = align_up(off + 8 * (size_t)A.chunks * naux);
   A.off_c = off; off = align_up(off + 8 * (size_t)naux);
-  A.off_Y = off; off = align_up(off + 8 * (size_t)nmo * ncols * naux);
+  A.off_Y = off; off = align_up(off + 8 * (size_t)(A.rows_first ? nrows * nr : nc * ncols) * naux);
   A.off_Kp = off; off = align_up(off + 8 * (size_t)A.c_k.splits * nrows * ncols);
   A.off_K = off; off = align_up(off + 8 * (size_t)nrows * ncols);
   A.total = off;
@@ -2174,12 +2264,17 @@ AntisymPlan antisym_plan(int64_t nmo, int64_t naux, int64_t nrows, int64_t ncols
 
 // F[p - r0][q - c0] (row stride ldf) = sum_rs G_pq^rs D_rs for the rows
 // [r0, r0 + nrows) and columns [c0, c0 + ncols), with G_pq^rs = 2 (pq|rs) -
-// (ps|rq) and (pq|rs) = sum_P Bf[p][q][P] Bf[r][s][P]:
+// (ps|rq) and (pq|rs) = sum_P Bf[p][q][P] Bf[r][s][P]; r and s run over D's
+// nonzero block only:
 //   Coulomb  2 sum_P Bf[p][q][P] c_P,   c_P = sum_rs Bf[r][s][P] D_rs
 //   exchange sum_(s,P) Bf[p][s][P] Y[s][q][P],   Y[s][q][P] = sum_r D_rs Bf[r][q][P]
-// The workspace's status word must be zero (the callers clear it).
-int antisym_run(const AntisymPlan& A, const double* Bf, const double* D, int64_t r0, int64_t c0, double* F,
-                int64_t ldf, char* ws, hipStream_t st) {
+//         or sum_(r,P) Z[p][r][P] Bf[r][q][P],   Z[p][r][P] = sum_s Bf[p][s][P] D_rs
+// A Z-vector operator application (only the virtual-occupied block of D holds
+// the vector) at 40/200/720 took 480 us over the whole of D and 80 us over
+// its block.  The workspace's status word must be zero (the callers clear it).
+template <int ROLE>
+int antisym_run(const AntisymPlan& A, const double* Bf, const DBlock& d, int64_t r0, int64_t c0, double* F, int64_t ldf,
+                const ZElem& z, char* ws, hipStream_t st) {
   const int64_t nmo = A.nmo, naux = A.naux, nrows = A.nrows, ncols = A.ncols;
   const int32_t* status = (const int32_t*)(ws + A.off_status);
   double* cpart = (double*)(ws + A.off_cpart);
@@ -2188,44 +2283,57 @@ int antisym_run(const AntisymPlan& A, const double* Bf, const double* D, int64_t
   double* Kp = (double*)(ws + A.off_Kp);
   double* K = (double*)(ws + A.off_K);
   int rc;
-  if ((rc = traced(R_RESPONSE, 0, 0, 8.0 * nmo * nmo * (naux + 1), st, [&] {
+  if ((rc = traced(R_RESPONSE, 0, 0, 8.0 * d.nr * d.nc * (naux + 1), st, [&] {
          hipLaunchKernelGGL(coulomb_vector_kernel, dim3((unsigned)cdiv(naux, 256), (unsigned)A.chunks), dim3(256), 0,
-                            st, Bf, D, nmo * nmo, naux, A.chunk, cpart, status);
+                            st, Bf, d, nmo, naux, A.chunk, cpart, status);
          hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)reduce_blocks(naux, A.chunks)), dim3(256), 0, st, c, naux,
                             (const double*)cpart, naux, naux, (int)A.chunks, (int64_t)1, naux, 1.0, 0, status);
        })))
     return rc;
-  {  // Y[s][(q, P)] = sum_r D[r][s] Bf[r][c0 + q][P]
+  GemmParams gk{};
+  gk.M = nrows; gk.N = ncols;
+  if (A.rows_first) {
+    // Z[p][r][P] = sum_s D[r][s] Bf[r0 + p][s][P], one product per row p
     GemmParams gp{};
-    gp.M = nmo; gp.N = ncols * naux; gp.K = nmo; gp.kchunk = nmo;
-    gp.Am = NOperand{D, nmo};
-    gp.Bn = NOperand{Bf + c0 * naux, nmo * naux};
+    gp.M = d.nr; gp.N = naux; gp.K = d.nc; gp.kchunk = d.nc;
+    gp.A = kop(d.D, d.ld, INT64_MAX, 0);
+    gp.Bn = NOperand{Bf + (r0 * nmo + d.c0) * naux, naux};
+    gp.batch = (int32_t)nrows; gp.batch_a = 0; gp.batch_b = nmo * naux; gp.split_stride = d.nr * naux;
+    gp.C = Y; gp.ldc = naux; gp.status = status;
+    if ((rc = launch_batch(gp, st, R_RESPONSE, 2.0 * nrows * d.nr * d.nc * naux,
+                           8.0 * (d.nr * d.nc + (double)nrows * (d.nr + d.nc) * naux))))
+      return rc;
+    // K[p][q] = sum over (r, P) of Z[p][r][P] Bf[r][c0 + q][P]
+    gk.K = d.nr * naux;
+    gk.A = kop(Y, d.nr * naux, INT64_MAX, 0);
+    gk.Bk = kop(Bf + (d.r0 * nmo + c0) * naux, naux, naux, nmo * naux);
+  } else {
+    // Y[s][(q, P)] = sum_r D[r][s] Bf[r][c0 + q][P]
+    GemmParams gp{};
+    gp.M = d.nc; gp.N = ncols * naux; gp.K = d.nr; gp.kchunk = d.nr;
+    gp.Am = NOperand{d.D, d.ld};
+    gp.Bn = NOperand{Bf + (d.r0 * nmo + c0) * naux, nmo * naux};
     gp.C = Y; gp.ldc = ncols * naux; gp.status = status;
-    if ((rc = launch_gemm<128, 128, true, ROLE_AO, false>(gp, st, R_RESPONSE, 2.0 * nmo * nmo * ncols * naux,
-                                                           8.0 * (nmo * nmo + 2.0 * nmo * ncols * naux), false)))
+    if ((rc = launch_ao(gp, st, R_RESPONSE, 2.0 * d.nr * d.nc * ncols * naux,
+                        8.0 * (d.nr * d.nc + (double)(d.nr + d.nc) * ncols * naux))))
       return rc;
+    // K[p][q] = sum over (s, P) of Bf[r0 + p][s][P] Y[s][q][P]
+    gk.K = d.nc * naux;
+    gk.A = kop(Bf + (r0 * nmo + d.c0) * naux, nmo * naux, INT64_MAX, 0);
+    gk.Bk = kop(Y, naux, naux, ncols * naux);
   }
-  {  // K[p][q] = sum over (s, P) of Bf[r0 + p][s][P] Y[s][q][P]
-    GemmParams gp{};
-    gp.M = nrows; gp.N = ncols; gp.K = nmo * naux;
-    gp.kchunk = cdiv(gp.K, A.c_k.splits);
-    gp.A = kop(Bf + r0 * nmo * naux, nmo * naux, INT64_MAX, 0);
-    gp.Bk = kop(Y, naux, naux, ncols * naux);
-    gp.C = Kp; gp.ldc = ncols; gp.split_stride = nrows * ncols; gp.status = status;
-    const int64_t splits = cdiv(gp.K, cdiv(gp.kchunk, kBK) * kBK);
-    if ((rc = launch_lterm(A.c_k.bm, gp, st, R_RESPONSE, 2.0 * nrows * ncols * nmo * naux,
-                           8.0 * (nrows + ncols) * nmo * naux)))
-      return rc;
-    const int64_t n = nrows * ncols;
-    if ((rc = traced(R_REDUCE, 0, 0, 8.0 * (splits + 1) * n, st, [&] {
-           hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)reduce_blocks(n, splits)), dim3(256), 0, st, K, ncols,
-                              (const double*)Kp, ncols, n, (int)splits, nrows, ncols, 1.0, 0, status);
-         })))
-      return rc;
-  }
-  return traced(R_RESPONSE, 0, 0, 8.0 * nrows * ncols * (naux + 2), st, [&] {
-    hipLaunchKernelGGL(antisym_combine_kernel, dim3((unsigned)cdiv(nrows * ncols, 4)), dim3(256), 0, st, Bf, nmo, naux,
-                       r0, nrows, c0, ncols, (const double*)c, (const double*)K, F, ldf, status);
+  gk.kchunk = cdiv(gk.K, A.c_k.splits);
+  gk.C = Kp; gk.ldc = ncols; gk.split_stride = nrows * ncols; gk.status = status;
+  const int64_t splits = cdiv(gk.K, cdiv(gk.kchunk, kBK) * kBK), n = nrows * ncols;
+  if ((rc = launch_lterm(A.c_k.bm, gk, st, R_RESPONSE, 2.0 * n * gk.K, 8.0 * (nrows + ncols) * gk.K))) return rc;
+  if ((rc = traced(R_REDUCE, 0, 0, 8.0 * (splits + 1) * n, st, [&] {
+         hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)reduce_blocks(n, splits)), dim3(256), 0, st, K, ncols,
+                            (const double*)Kp, ncols, n, (int)splits, nrows, ncols, 1.0, 0, status);
+       })))
+    return rc;
+  return traced(R_RESPONSE, 0, 0, 8.0 * n * (naux + 2), st, [&] {
+    hipLaunchKernelGGL(antisym_combine_kernel<ROLE>, dim3((unsigned)cdiv(n, 4)), dim3(256), 0, st, Bf, nmo, naux, r0,
+                       nrows, c0, ncols, (const double*)c, (const double*)K, F, ldf, z, status);
   });
 }
 
@@ -2247,59 +2355,62 @@ __global__ __launch_bounds__(256) void assemble_density_kernel(int64_t nocc, int
   D[e] = v;
 }
 
-// Z-vector pieces, element (a, i) of [nvir][nocc].
-//   mode 0: out = L2[a][i] - L1[i][nocc + a] - F[a][i]                (right-hand side)
-//   mode 1: out = (eps_a - eps_i)/2 x[a][i] + F[a][i]                 (operator)
-//   mode 2: out = (eps_a - eps_i)/2 + sum_P Bf[nocc+a][i][P]^2        (diagonal)
-__global__ __launch_bounds__(256) void zvector_elem_kernel(int mode, int64_t nocc, int64_t nvir, int64_t naux,
-                                                           const double* eo, const double* ev, const double* Bf,
-                                                           const double* L1, const double* L2, const double* x,
-                                                           const double* F, double* out) {
-  const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (e >= nocc * nvir) return;
-  const int64_t a = e / nocc, i = e - a * nocc, nmo = nocc + nvir;
-  const double gap = (ev[a] - eo[i]) / 2.0;
-  if (mode == 0) {
-    out[e] = (L2[a * nmo + i] - L1[i * nmo + nocc + a]) - F[e];
-  } else if (mode == 1) {
-    out[e] = gap * x[e] + F[e];
-  } else {
-    const double* row = Bf + ((nocc + a) * nmo + i) * naux;
-    double s = 0.0;
-    for (int64_t P = 0; P < naux; ++P) s += row[P] * row[P];
-    out[e] = gap + s;
-  }
-}
-
-// Sum over n of u[n] v[n] (w == null) or of u[n] v[n] / w[n], one workgroup,
-// fixed order; written to out[0].
-__global__ __launch_bounds__(256) void dot_kernel(const double* u, const double* v, const double* w, int64_t n,
-                                                  double* out) {
-  __shared__ double sh[256];
-  double s = 0.0;
-  for (int64_t k = threadIdx.x; k < n; k += 256) s += w ? u[k] * v[k] / w[k] : u[k] * v[k];
+// CG's vector algebra, one workgroup (its sums in a fixed order), on vectors of
+// nov elements; scal = (p.q, r.(r / diag), r.r, rhs.rhs).  Latency-bound: as one
+// launch per dot product and update, with a read-back for each dot product, an
+// iteration at nov = 8000 spent about 90 us on them; as one launch and one
+// read-back about 30.
+constexpr int kCgThreads = 1024;
+__device__ __forceinline__ double cg_sum(double s) {
+  __shared__ double sh[kCgThreads];
   sh[threadIdx.x] = s;
   __syncthreads();
-  for (int wdt = 128; wdt > 0; wdt >>= 1) {
-    if (threadIdx.x < wdt) sh[threadIdx.x] += sh[threadIdx.x + wdt];
+  for (int w = kCgThreads / 2; w > 0; w >>= 1) {
+    if ((int)threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
     __syncthreads();
   }
-  if (threadIdx.x == 0) out[0] = sh[0];
+  const double t = sh[0];
+  __syncthreads();
+  return t;
 }
-
-// CG vector updates.
-//   mode 0: y = u / w                       (preconditioned residual; initial guess)
-//   mode 1: x += alpha p; r -= alpha q      (u = p, v = q, y = x, z = r)
-//   mode 2: p = r / w + beta p              (u = r, y = p)
-//   mode 3: y = u - v                       (initial residual)
-__global__ __launch_bounds__(256) void cg_update_kernel(int mode, int64_t n, double alpha, const double* u,
-                                                        const double* v, const double* w, double* y, double* z) {
-  const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (k >= n) return;
-  if (mode == 0) y[k] = u[k] / w[k];
-  else if (mode == 1) { y[k] += alpha * u[k]; z[k] -= alpha * v[k]; }
-  else if (mode == 2) y[k] = u[k] / w[k] + alpha * y[k];
-  else y[k] = u[k] - v[k];
+// r = rhs - q, p = r / diag
+__global__ __launch_bounds__(kCgThreads) void cg_start_kernel(int64_t n, const double* rhs, const double* diag,
+                                                              const double* q, double* r, double* p, double* scal) {
+  double rz = 0.0, rr = 0.0, bb = 0.0;
+  for (int64_t k = threadIdx.x; k < n; k += kCgThreads) {
+    const double b = rhs[k], rk = b - q[k], d = diag[k];
+    r[k] = rk;
+    p[k] = rk / d;
+    rz += rk * rk / d;
+    rr += rk * rk;
+    bb += b * b;
+  }
+  rz = cg_sum(rz); rr = cg_sum(rr); bb = cg_sum(bb);
+  if (threadIdx.x == 0) { scal[1] = rz; scal[2] = rr; scal[3] = bb; }
+}
+// One iteration after q = A p: alpha = rz / p.q, x += alpha p, r -= alpha q,
+// p = r / diag + (rz_new / rz) p.  Only scal[0] is written when p.q is not > 0
+// (the operator is not positive definite along p).
+__global__ __launch_bounds__(kCgThreads) void cg_step_kernel(int64_t n, const double* diag, const double* q, double* x,
+                                                             double* r, double* p, double* scal) {
+  double s = 0.0;
+  for (int64_t k = threadIdx.x; k < n; k += kCgThreads) s += p[k] * q[k];
+  const double pq = cg_sum(s), rz = scal[1];
+  if (threadIdx.x == 0) scal[0] = pq;
+  if (!(pq > 0.0)) return;
+  const double alpha = rz / pq;
+  double rz_new = 0.0, rr = 0.0;
+  for (int64_t k = threadIdx.x; k < n; k += kCgThreads) {
+    const double rk = r[k] - alpha * q[k];
+    x[k] += alpha * p[k];
+    r[k] = rk;
+    rz_new += rk * rk / diag[k];
+    rr += rk * rk;
+  }
+  rz_new = cg_sum(rz_new); rr = cg_sum(rr);
+  const double beta = rz_new / rz;
+  for (int64_t k = threadIdx.x; k < n; k += kCgThreads) p[k] = r[k] / diag[k] + beta * p[k];
+  if (threadIdx.x == 0) { scal[1] = rz_new; scal[2] = rr; }
 }
 
 // W[p][q] = (eps_p + eps_q)/2 D[p][q] + (p < nocc ? F[p][q] + L1[p][q] : L2[p - nocc][q]),
@@ -2317,23 +2428,21 @@ __global__ __launch_bounds__(256) void w_assemble_kernel(int64_t nocc, int64_t n
 }
 
 struct ZPlan {
-  AntisymPlan A;
-  size_t off_D, off_F, off_rhs, off_diag, off_x, off_r, off_p, off_q, off_dot, total;
+  AntisymPlan full, vo;   // right-hand side (both diagonal blocks of D), operator (the virtual-occupied block)
+  size_t off_D, off_rhs, off_diag, off_r, off_p, off_q, off_dot, total;
 };
 
 ZPlan zvector_plan(int64_t nocc, int64_t nvir, int64_t naux) {
   ZPlan Z{};
   const int64_t nmo = nocc + nvir, nov = nocc * nvir;
-  Z.A = antisym_plan(nmo, naux, nvir, nocc);
-  size_t off = Z.A.total;
+  Z.full = antisym_plan(nmo, naux, nvir, nocc, nmo, nmo);
+  Z.vo = antisym_plan(nmo, naux, nvir, nocc, nvir, nocc);
+  size_t off = std::max(Z.full.total, Z.vo.total);
   Z.off_D = off; off = align_up(off + 8 * (size_t)nmo * nmo);
-  Z.off_F = off; off = align_up(off + 8 * (size_t)nov);
-  Z.off_rhs = off; off = align_up(off + 8 * (size_t)nov);
-  Z.off_diag = off; off = align_up(off + 8 * (size_t)nov);
-  Z.off_x = off; off = align_up(off + 8 * (size_t)nov);
-  Z.off_r = off; off = align_up(off + 8 * (size_t)nov);
-  Z.off_p = off; off = align_up(off + 8 * (size_t)nov);
-  Z.off_q = off; off = align_up(off + 8 * (size_t)nov);
+  for (size_t* o : {&Z.off_rhs, &Z.off_diag, &Z.off_r, &Z.off_p, &Z.off_q}) {
+    *o = off;
+    off = align_up(off + 8 * (size_t)nov);
+  }
   Z.off_dot = off; off = align_up(off + 64);
   Z.total = off;
   return Z;
@@ -2352,18 +2461,21 @@ int clear_status(char* ws, hipStream_t st) {
   });
 }
 
-int read_dot(const double* d, double* h, hipStream_t st) {
-  HIP_TRY(hipMemcpyAsync(h, d, sizeof(double), hipMemcpyDeviceToHost, st));
+// Reads the CG scalars back (the iteration's one synchronisation).
+int read_scal(const double* d, double* h, hipStream_t st) {
+  HIP_TRY(hipMemcpyAsync(h, d, 4 * sizeof(double), hipMemcpyDeviceToHost, st));
   HIP_TRY(hipStreamSynchronize(st));
   return RIMP2_OK;
 }
 
 }  // namespace
 
+extern "C" {
+
 int rimp2_antisym_workspace_size(int32_t nmo, int32_t naux, int32_t nrows, int32_t ncols, size_t* bytes) {
   if (!bytes) return fail(RIMP2_EINVAL, "bytes is NULL");
   if (nmo < 1 || naux < 1 || nrows < 1 || ncols < 1) return fail(RIMP2_EINVAL, "sizes must be >= 1");
-  *bytes = antisym_plan(nmo, naux, nrows, ncols).total;
+  *bytes = antisym_plan(nmo, naux, nrows, ncols, nmo, nmo).total;
   return RIMP2_OK;
 }
 
@@ -2375,12 +2487,12 @@ int rimp2_antisym_term(int32_t nmo, int32_t naux, int32_t r0, int32_t nrows, int
     return fail(RIMP2_EINVAL, "rows [r0, r0 + nrows) and columns [c0, c0 + ncols) must lie in [0, nmo), ldf >= ncols");
   if (!Bf || !D || !F || !workspace) return fail(RIMP2_EINVAL, "Bf, D, F and workspace must not be NULL");
   if ((uintptr_t)workspace % kAlign) return fail(RIMP2_EWORKSPACE, "workspace must be 256-byte aligned");
-  const AntisymPlan A = antisym_plan(nmo, naux, nrows, ncols);
+  const AntisymPlan A = antisym_plan(nmo, naux, nrows, ncols, nmo, nmo);
   if (workspace_bytes < A.total) return fail(RIMP2_ENOMEM, "workspace has %zu bytes, needs %zu", workspace_bytes, A.total);
   hipStream_t st = (hipStream_t)stream;
   int rc;
   if ((rc = clear_status((char*)workspace, st))) return rc;
-  return antisym_run(A, Bf, D, r0, c0, F, ldf, (char*)workspace, st);
+  return antisym_run<0>(A, Bf, DBlock{D, nmo, 0, nmo, 0, nmo}, r0, c0, F, ldf, ZElem{}, (char*)workspace, st);
 }
 
 int rimp2_zvector_workspace_size(int32_t nocc, int32_t nvir, int32_t naux, size_t* bytes) {
@@ -2405,78 +2517,53 @@ int rimp2_zvector(int32_t nocc, int32_t nvir, int32_t naux, const double* Bf, co
   if (workspace_bytes < Z.total) return fail(RIMP2_ENOMEM, "workspace has %zu bytes, needs %zu", workspace_bytes, Z.total);
   hipStream_t st = (hipStream_t)stream;
   char* ws = (char*)workspace;
-  const int64_t no = nocc, nv = nvir, na = naux, nmo = no + nv, nov = no * nv;
+  const int64_t no = nocc, nv = nvir, nmo = no + nv, nov = no * nv;
   double* D = (double*)(ws + Z.off_D);
-  double* F = (double*)(ws + Z.off_F);
   double* rhs = (double*)(ws + Z.off_rhs);
   double* diag = (double*)(ws + Z.off_diag);
   double* r = (double*)(ws + Z.off_r);
   double* pv = (double*)(ws + Z.off_p);
   double* q = (double*)(ws + Z.off_q);
-  double* dot = (double*)(ws + Z.off_dot);
+  double* scal = (double*)(ws + Z.off_dot);
   double* x = D_ai;
-  const unsigned gn = (unsigned)cdiv(nov, 256), gd = (unsigned)cdiv(nmo * nmo, 256);
-  auto elem = [&](int mode, const double* xin, double* out) {
-    return traced(R_RESPONSE, 0, 0, 8.0 * 3 * nov, st, [&] {
-      hipLaunchKernelGGL(zvector_elem_kernel, dim3(gn), dim3(256), 0, st, mode, no, nv, na, eps_occ, eps_vir, Bf, L1,
-                         L2, xin, (const double*)F, out);
-    });
-  };
-  auto density = [&](const double* Doo, const double* Dvv, const double* Dvo) {
-    return traced(R_RESPONSE, 0, 0, 8.0 * nmo * nmo, st, [&] {
-      hipLaunchKernelGGL(assemble_density_kernel, dim3(gd), dim3(256), 0, st, no, nv, Doo, Dvv, Dvo, 0, 0, D);
-    });
-  };
-  // out = (eps_a - eps_i)/2 v_ai + sum_bj G_ai^bj v_bj (only the (b, j) block of D holds v)
-  auto apply = [&](const double* v, double* out) -> int {
-    int r2;
-    if ((r2 = density(nullptr, nullptr, v))) return r2;
-    if ((r2 = antisym_run(Z.A, Bf, D, no, 0, F, no, ws, st))) return r2;
-    return elem(1, v, out);
-  };
-  auto dotp = [&](const double* u, const double* v, const double* w, double* h) -> int {
-    int r2;
-    if ((r2 = traced(R_RESPONSE, 0, 0, 16.0 * nov, st, [&] {
-           hipLaunchKernelGGL(dot_kernel, dim3(1), dim3(256), 0, st, u, v, w, nov, dot);
-         })))
-      return r2;
-    return read_dot(dot, h, st);
-  };
-  auto update = [&](int mode, double alpha, const double* u, const double* v, const double* w, double* y,
-                    double* z) {
-    return traced(R_RESPONSE, 0, 0, 8.0 * 4 * nov, st, [&] {
-      hipLaunchKernelGGL(cg_update_kernel, dim3(gn), dim3(256), 0, st, mode, nov, alpha, u, v, w, y, z);
-    });
+  // out = (eps_a - eps_i)/2 v_ai + sum_bj G_ai^bj v_bj
+  auto apply = [&](double* v, double* out) -> int {
+    return antisym_run<1>(Z.vo, Bf, DBlock{v, no, no, nv, 0, no}, no, 0, out, no,
+                          ZElem{eps_occ, eps_vir, nullptr, nullptr, v, nullptr}, ws, st);
   };
   if ((rc = clear_status(ws, st))) return rc;
-  // right-hand side: L''_ai - L'_ia - sum_pq G_ai^pq Dbar_pq, Dbar = D_ij (+) D_ab
-  if ((rc = density(P_ij, P_ab, nullptr))) return rc;
-  if ((rc = antisym_run(Z.A, Bf, D, no, 0, F, no, ws, st))) return rc;
-  if ((rc = elem(0, nullptr, rhs))) return rc;
-  if ((rc = elem(2, nullptr, diag))) return rc;   // Jacobi preconditioner: the operator's diagonal
-  // preconditioned conjugate gradients from x = rhs / diag
-  double bb = 0.0, rz = 0.0, rr = 0.0;
-  if ((rc = dotp(rhs, rhs, nullptr, &bb))) return rc;
-  if ((rc = update(0, 0.0, rhs, nullptr, diag, x, nullptr))) return rc;
+  // right-hand side L''_ai - L'_ia - sum_pq G_ai^pq Dbar_pq, Dbar = D_ij (+)
+  // D_ab; Jacobi preconditioner: the operator's diagonal; x = rhs / diagonal
+  if ((rc = traced(R_RESPONSE, 0, 0, 8.0 * nmo * nmo, st, [&] {
+         hipLaunchKernelGGL(assemble_density_kernel, dim3((unsigned)cdiv(nmo * nmo, 256)), dim3(256), 0, st, no, nv, P_ij,
+                            P_ab, (const double*)nullptr, 0, 0, D);
+       })))
+    return rc;
+  if ((rc = antisym_run<2>(Z.full, Bf, DBlock{D, nmo, 0, nmo, 0, nmo}, no, 0, rhs, no,
+                           ZElem{eps_occ, eps_vir, L1, L2, x, diag}, ws, st)))
+    return rc;
+  // preconditioned conjugate gradients
+  double h[4] = {0.0, 0.0, 0.0, 0.0};
   if ((rc = apply(x, q))) return rc;
-  if ((rc = update(3, 0.0, rhs, q, nullptr, r, nullptr))) return rc;
-  if ((rc = update(0, 0.0, r, nullptr, diag, pv, nullptr))) return rc;
-  if ((rc = dotp(r, r, diag, &rz))) return rc;
-  if ((rc = dotp(r, r, nullptr, &rr))) return rc;
-  const double target = tol * tol * bb;
+  if ((rc = traced(R_RESPONSE, 0, 0, 8.0 * 5 * nov, st, [&] {
+         hipLaunchKernelGGL(cg_start_kernel, dim3(1), dim3(kCgThreads), 0, st, nov, (const double*)rhs,
+                            (const double*)diag, (const double*)q, r, pv, scal);
+       })))
+    return rc;
+  if ((rc = read_scal(scal, h, st))) return rc;
+  const double bb = h[3], target = tol * tol * bb;
+  double rr = h[2];
   int it = 0;
   while (rr > target && it < max_iter) {
     if ((rc = apply(pv, q))) return rc;
-    double pq = 0.0;
-    if ((rc = dotp(pv, q, nullptr, &pq))) return rc;
-    if (!(pq > 0.0)) break;   // the operator is not positive definite along p
-    const double alpha = rz / pq;
-    if ((rc = update(1, alpha, pv, q, nullptr, x, r))) return rc;
-    double rz_new = 0.0;
-    if ((rc = dotp(r, r, diag, &rz_new))) return rc;
-    if ((rc = dotp(r, r, nullptr, &rr))) return rc;
-    if ((rc = update(2, rz_new / rz, r, nullptr, diag, pv, nullptr))) return rc;
-    rz = rz_new;
+    if ((rc = traced(R_RESPONSE, 0, 0, 8.0 * 8 * nov, st, [&] {
+           hipLaunchKernelGGL(cg_step_kernel, dim3(1), dim3(kCgThreads), 0, st, nov, (const double*)diag,
+                              (const double*)q, x, r, pv, scal);
+         })))
+      return rc;
+    if ((rc = read_scal(scal, h, st))) return rc;
+    if (!(h[0] > 0.0)) break;   // the operator is not positive definite along p
+    rr = h[2];
     ++it;
   }
   if (iterations) *iterations = it;
@@ -2493,7 +2580,7 @@ int rimp2_energy_weighted_density_workspace_size(int32_t nocc, int32_t nvir, int
   int rc;
   if ((rc = response_sizes(nocc, nvir, naux))) return rc;
   const int64_t nmo = (int64_t)nocc + nvir;
-  const AntisymPlan A = antisym_plan(nmo, naux, nocc, nmo);
+  const AntisymPlan A = antisym_plan(nmo, naux, nocc, nmo, nmo, nmo);
   *bytes = A.total + align_up(8 * (size_t)nmo * nmo) * 2;
   return RIMP2_OK;
 }
@@ -2513,7 +2600,7 @@ int rimp2_energy_weighted_density(int32_t nocc, int32_t nvir, int32_t naux, cons
   hipStream_t st = (hipStream_t)stream;
   char* ws = (char*)workspace;
   const int64_t no = nocc, nv = nvir, nmo = no + nv;
-  const AntisymPlan A = antisym_plan(nmo, naux, nocc, nmo);
+  const AntisymPlan A = antisym_plan(nmo, naux, nocc, nmo, nmo, nmo);
   double* Dm = (double*)(ws + A.total);
   double* F = (double*)(ws + A.total + align_up(8 * (size_t)nmo * nmo));
   const unsigned gd = (unsigned)cdiv(nmo * nmo, 256);
@@ -2523,7 +2610,7 @@ int rimp2_energy_weighted_density(int32_t nocc, int32_t nvir, int32_t naux, cons
          hipLaunchKernelGGL(assemble_density_kernel, dim3(gd), dim3(256), 0, st, no, nv, P_ij, P_ab, D_ai, 1, 0, Dm);
        })))
     return rc;
-  if ((rc = antisym_run(A, Bf, Dm, 0, 0, F, nmo, ws, st))) return rc;
+  if ((rc = antisym_run<0>(A, Bf, DBlock{Dm, nmo, 0, nmo, 0, nmo}, 0, 0, F, nmo, ZElem{}, ws, st))) return rc;
   // D = D^HF + D^MP2 for the energy-weighted piece
   if ((rc = traced(R_RESPONSE, 0, 0, 8.0 * nmo * nmo, st, [&] {
          hipLaunchKernelGGL(assemble_density_kernel, dim3(gd), dim3(256), 0, st, no, nv, P_ij, P_ab, D_ai, 1, 1, Dm);
