@@ -74,6 +74,14 @@ int rimp2_log_energy(int64_t n, const double* e, double* out, void* stream);
 int rimp2_screen_mask(int32_t nocc, const double* pred, double threshold_log10, uint8_t* skip,
                       double* skipped_energy, void* stream);
 
+/*
+ * The largest threshold_log10 in [-30, 0], by `iters` bisections, whose
+ * skipped_energy (as rimp2_screen_mask sums it) is at most budget_Eh; written
+ * to threshold_log10, device [1].  One workgroup.
+ */
+int rimp2_budget_threshold(int32_t nocc, const double* pred, double budget_Eh, int32_t iters,
+                           double* threshold_log10, void* stream);
+
 #ifdef __cplusplus
 }
 #endif

@@ -5,6 +5,8 @@
 #include <math.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "../../include/rimp2.h"
 #include "../../include/rimp2_screen.h"
 #include "common.hpp"
@@ -26,18 +28,23 @@ __device__ __forceinline__ double dsilu(double z) {
 }
 
 // ---- features ---------------------------------------------------------------
-// N[i][P] = ||B_i[:, P]||_2 (one workgroup per i, threads over P)
+// N[i][P] = ||B_i[:, P]||_2: a workgroup takes 64 columns P of one i, its four
+// waves every fourth row a.  HBM-bound; with one workgroup per i, 100 of them
+// read B (100/600/1800, 0.86 GB) in 1.9 ms, 0.15 ms now.
 __global__ __launch_bounds__(256) void colnorm_kernel(const double* B, int nvir, int naux, double* N) {
-  const int i = blockIdx.x;
-  const double* Bi = B + (int64_t)i * nvir * naux;
-  for (int P = threadIdx.x; P < naux; P += 256) {
-    double s = 0.0;
-    for (int a = 0; a < nvir; ++a) {
-      const double v = Bi[(int64_t)a * naux + P];
-      s += v * v;
-    }
-    N[(int64_t)i * naux + P] = sqrt(s);
+  __shared__ double sh[4][64];
+  const int np = (naux + 63) / 64, i = blockIdx.x / np, lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int P = (blockIdx.x - i * np) * 64 + lane;
+  const double* Bi = B + (int64_t)i * nvir * naux + min(P, naux - 1);
+  double s = 0.0;
+#pragma unroll 8
+  for (int a = w; a < nvir; a += 4) {
+    const double v = Bi[(int64_t)a * naux];
+    s += v * v;
   }
+  sh[w][lane] = s;
+  __syncthreads();
+  if (w == 0 && P < naux) N[(int64_t)i * naux + P] = sqrt(((sh[0][lane] + sh[1][lane]) + sh[2][lane]) + sh[3][lane]);
 }
 // nb[i] = ||B_i||_F from N, and evmin = min eps_vir (block 0 also)
 __global__ __launch_bounds__(256) void rownorm_kernel(const double* N, int naux, double* nb, const double* ev,
@@ -69,154 +76,230 @@ __global__ __launch_bounds__(256) void rownorm_kernel(const double* N, int naux,
     if (threadIdx.x == 0) *evmin = sh[0];
   }
 }
-// one thread per pair (i, j)
-__global__ __launch_bounds__(256) void pair_kernel(int nocc, int naux, const double* N, const double* nb,
-                                                   const double* eo, const double* r, const double* evmin,
-                                                   double* feat, double* bound) {
-  const int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (p >= (int64_t)nocc * nocc) return;
-  const int i = (int)(p / nocc), j = (int)(p - (int64_t)i * nocc);
+// One thread per pair (i, j), 16 x 16 pairs a workgroup; N's rows go through
+// LDS in blocks of PB columns, summed in increasing P.
+constexpr int PT = 16, PB = 32;
+__global__ __launch_bounds__(PT * PT) void pair_kernel(int nocc, int naux, const double* N, const double* nb,
+                                                       const double* eo, const double* r, const double* evmin,
+                                                       double* feat, double* bound) {
+  __shared__ double Ni[PT][PB + 1], Nj[PT][PB + 1];
+  const int tj = threadIdx.x % PT, ti = threadIdx.x / PT;
+  const int i0 = blockIdx.y * PT, j0 = blockIdx.x * PT, i = i0 + ti, j = j0 + tj;
+  double s = 0.0;
+  if (bound) {
+    for (int P0 = 0; P0 < naux; P0 += PB) {
+      for (int q = threadIdx.x; q < PT * PB; q += PT * PT) {
+        const int row = q / PB, c = q % PB, P = P0 + c;
+        Ni[row][c] = P < naux ? N[(int64_t)min(i0 + row, nocc - 1) * naux + P] : 0.0;
+        Nj[row][c] = P < naux ? N[(int64_t)min(j0 + row, nocc - 1) * naux + P] : 0.0;
+      }
+      __syncthreads();
+#pragma unroll
+      for (int c = 0; c < PB; ++c) s += Ni[ti][c] * Nj[tj][c];
+      __syncthreads();
+    }
+  }
+  if (i >= nocc || j >= nocc) return;
+  const int64_t p = (int64_t)i * nocc + j;
   const double dx = r[3 * i] - r[3 * j], dy = r[3 * i + 1] - r[3 * j + 1], dz = r[3 * i + 2] - r[3 * j + 2];
   double* f = feat + 4 * p;
   f[0] = sqrt(dx * dx + dy * dy + dz * dz) / 10.0;
   f[1] = log(nb[i]);
   f[2] = log(nb[j]);
   f[3] = (eo[i] + eo[j]) / 10.0;
-  if (bound) {
-    double s = 0.0;
-    for (int P = 0; P < naux; ++P) s += N[(int64_t)i * naux + P] * N[(int64_t)j * naux + P];
-    bound[p] = 3.0 * s * s / (2.0 * *evmin - eo[i] - eo[j]);
-  }
+  if (bound) bound[p] = 3.0 * s * s / (2.0 * *evmin - eo[i] - eo[j]);
 }
 
 // ---- network ------------------------------------------------------------------
-constexpr int FS = 64;   // samples per forward workgroup (64 threads = hidden units)
-__global__ __launch_bounds__(64) void mlp_forward_kernel(int64_t n, const double* x, const double* P, double* y) {
-  __shared__ double W2[H * H], X[FS][NIN], H1[FS][H + 1], H2[FS][H + 1];
-  const int t = threadIdx.x;
-  const int64_t s0 = (int64_t)blockIdx.x * FS;
-  for (int q = t; q < H * H; q += 64) W2[q] = P[OW2 + q];
-  for (int q = t; q < FS * NIN; q += 64) {
-    const int64_t s = s0 + q / NIN;
-    X[q / NIN][q % NIN] = s < n ? x[s * NIN + q % NIN] : 0.0;
-  }
-  __syncthreads();
-  double w1[NIN];
-  for (int k = 0; k < NIN; ++k) w1[k] = P[OW1 + t * NIN + k];
-  const double b1 = P[OB1 + t], b2 = P[OB2 + t];
-  for (int s = 0; s < FS; ++s) {
+// Four waves a workgroup, blocks of SB = 16 samples.  The 64 x 64 products run
+// on v_mfma_f64_16x16x4 (lane l: A[l%16][l/16], B[l/16][l%16]; register r of
+// lane l: D[4r + l/16][l%16]); wave w owns the hidden units [16 w, 16 w + 16).
+// Latency-bound: a block is a few microseconds of dependent steps, so the
+// blocks are spread over the CUs, one workgroup each.  (A first version, one
+// wave for 32 samples with a thread per hidden unit and 64-way bank conflicts
+// on W2's rows, took 122 us for 4096 samples' gradient, 15 us now, and its
+// reduction 35, 4 us now.)
+typedef double dbl4 __attribute__((ext_vector_type(4)));
+constexpr int SB = 16, MAXW = 256;   // samples per block, workgroups of a gradient launch
+constexpr int LD = H + 1;            // LDS row stride (no bank conflicts down a column)
+
+struct MlpLds {
+  double X[SB][NIN], W1[H][NIN], A1[SB][LD], T[SB][LD], y[SB];
+};
+
+// Hidden layers of one block for lane (g = l/16, c = l%16) of wave w: X is in
+// LDS; writes A1 = silu(Z1) to LDS.  Element r of z1 and z2 is sample 4r + g,
+// unit u = 16 w + c; w2[ks] = W2[u][4 ks + g].  Ends after a barrier that makes A1 visible.
+__device__ __forceinline__ void mlp_hidden(MlpLds& L, int u, int g, int c, double b1, double b2, const double (&w2)[16],
+                                           double (&z1)[4], dbl4& z2) {
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int s = 4 * r + g;
     double z = b1;
-    for (int k = 0; k < NIN; ++k) z += w1[k] * X[s][k];
-    H1[s][t] = silu(z);
+#pragma unroll
+    for (int k = 0; k < NIN; ++k) z += L.W1[u][k] * L.X[s][k];
+    z1[r] = z;
+    L.A1[s][u] = silu(z);
   }
   __syncthreads();
-  for (int s = 0; s < FS; ++s) {
-    double z = b2;
-    for (int u = 0; u < H; ++u) z += W2[t * H + u] * H1[s][u];
-    H2[s][t] = silu(z);
-  }
-  __syncthreads();
-  const int64_t s = s0 + t;
-  if (s < n) {
-    double o = P[OB3];
-    for (int u = 0; u < H; ++u) o += P[OW3 + u] * H2[t][u];
-    y[s] = o;
+  z2 = dbl4{b2, b2, b2, b2};
+#pragma unroll
+  for (int ks = 0; ks < 16; ++ks) z2 = __builtin_amdgcn_mfma_f64_16x16x4f64(L.A1[c][4 * ks + g], w2[ks], z2, 0, 0, 0);
+}
+// out[s] = b3 + sum_u W3[u] T[s][u] for the block's samples (T = silu(Z2)): 16
+// lanes a sample, fixed order; valid in the threads with threadIdx.x % 16 == 0.
+__device__ __forceinline__ double mlp_out(const MlpLds& L, const double* P) {
+  const int s = threadIdx.x >> 4, q = threadIdx.x & 15;
+  double o = 0.0;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) o += P[OW3 + q + 16 * k] * L.T[s][q + 16 * k];
+#pragma unroll
+  for (int d = 8; d > 0; d >>= 1) o += __shfl_down(o, d, 16);
+  return o + P[OB3];
+}
+__device__ __forceinline__ void mlp_load(MlpLds& L, int64_t n, int64_t s0, const double* x) {
+  for (int q = threadIdx.x; q < SB * NIN; q += 256) {
+    const int64_t s = s0 + q / NIN;
+    L.X[q / NIN][q % NIN] = s < n ? x[s * NIN + q % NIN] : 0.0;
   }
 }
 
-constexpr int BS = 32;   // samples per backward workgroup
-// per-workgroup gradient of sum_s (y - t)^2 / n (and the loss part) -> part[blockIdx][NP + 1]
-__global__ __launch_bounds__(64) void mlp_backward_kernel(int64_t n, const double* x, const double* tgt,
-                                                          const double* P, double* part) {
-  __shared__ double W2[H * H], X[BS][NIN], Z1[BS][H + 1], A1[BS][H + 1], Z2[BS][H + 1], A2[BS][H + 1];
-  __shared__ double dy[BS], red[64];
-  const int t = threadIdx.x;
-  const int64_t s0 = (int64_t)blockIdx.x * BS;
-  const int ns = (int)min<int64_t>(BS, n - s0);
-  for (int q = t; q < H * H; q += 64) W2[q] = P[OW2 + q];
-  for (int q = t; q < BS * NIN; q += 64) {
-    const int64_t s = s0 + q / NIN;
-    X[q / NIN][q % NIN] = (q / NIN) < ns ? x[s * NIN + q % NIN] : 0.0;
-  }
-  __syncthreads();
-  // forward, keeping pre-activations
-  for (int s = 0; s < BS; ++s) {
-    double z = P[OB1 + t];
-    for (int k = 0; k < NIN; ++k) z += P[OW1 + t * NIN + k] * X[s][k];
-    Z1[s][t] = z;
-    A1[s][t] = silu(z);
-  }
-  __syncthreads();
-  for (int s = 0; s < BS; ++s) {
-    double z = P[OB2 + t];
-    for (int u = 0; u < H; ++u) z += W2[t * H + u] * A1[s][u];
-    Z2[s][t] = z;
-    A2[s][t] = silu(z);
-  }
-  __syncthreads();
-  double lpart = 0.0;
-  if (t < BS) {
-    double o = P[OB3];
-    for (int u = 0; u < H; ++u) o += P[OW3 + u] * A2[t][u];
-    const double r = (t < ns) ? o - tgt[s0 + t] : 0.0;
-    dy[t] = 2.0 * r / (double)n;
-    lpart = r * r / (double)n;
-  }
-  red[t] = lpart;
-  __syncthreads();
-  double* g = part + (int64_t)blockIdx.x * (NP + 1);
-  // W3, b3
-  {
-    double gw = 0.0;
-    for (int s = 0; s < BS; ++s) gw += dy[s] * A2[s][t];
-    g[OW3 + t] = gw;
-    if (t == 0) {
-      double gb = 0.0, l = 0.0;
-      for (int s = 0; s < BS; ++s) gb += dy[s];
-      for (int q = 0; q < 64; ++q) l += red[q];
-      g[OB3] = gb;
-      g[NP] = l;
-    }
-  }
-  // dZ2[s][t] = dy[s] W3[t] silu'(Z2[s][t])  (into Z2)
-  const double w3 = P[OW3 + t];
-  for (int s = 0; s < BS; ++s) Z2[s][t] = dy[s] * w3 * dsilu(Z2[s][t]);
-  __syncthreads();
-  // W2[t][u] gradient, b2
-  {
-    double gb = 0.0;
-    for (int s = 0; s < BS; ++s) gb += Z2[s][t];
-    g[OB2 + t] = gb;
-    for (int u = 0; u < H; ++u) {
-      double gw = 0.0;
-      for (int s = 0; s < BS; ++s) gw += Z2[s][t] * A1[s][u];
-      g[OW2 + t * H + u] = gw;
-    }
-  }
-  // dA1[s][u] = sum_t dZ2[s][t] W2[t][u], thread = u; dZ1 into A2 (free now)
-  for (int s = 0; s < BS; ++s) {
-    double d = 0.0;
-    for (int q = 0; q < H; ++q) d += Z2[s][q] * W2[q * H + t];
-    A2[s][t] = d * dsilu(Z1[s][t]);
-  }
-  __syncthreads();
-  {
-    double gb = 0.0;
-    for (int s = 0; s < BS; ++s) gb += A2[s][t];
-    g[OB1 + t] = gb;
-    for (int k = 0; k < NIN; ++k) {
-      double gw = 0.0;
-      for (int s = 0; s < BS; ++s) gw += A2[s][t] * X[s][k];
-      g[OW1 + t * NIN + k] = gw;
-    }
+__global__ __launch_bounds__(256) void mlp_forward_kernel(int64_t n, const double* x, const double* P, double* y) {
+  __shared__ MlpLds L;
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6, g = lane >> 4, c = lane & 15, u = 16 * w + c;
+  double w2[16];
+#pragma unroll
+  for (int ks = 0; ks < 16; ++ks) w2[ks] = P[OW2 + u * H + 4 * ks + g];
+  L.W1[t / NIN][t % NIN] = P[OW1 + t];
+  const double b1 = P[OB1 + u], b2 = P[OB2 + u];
+  const int64_t nb = (n + SB - 1) / SB;
+  for (int64_t b = blockIdx.x; b < nb; b += gridDim.x) {
+    mlp_load(L, n, b * SB, x);
+    __syncthreads();
+    double z1[4];
+    dbl4 z2;
+    mlp_hidden(L, u, g, c, b1, b2, w2, z1, z2);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) L.T[4 * r + g][u] = silu(z2[r]);
+    __syncthreads();
+    const double o = mlp_out(L, P);
+    const int64_t s = b * SB + (t >> 4);
+    if ((t & 15) == 0 && s < n) y[s] = o;
   }
 }
-// grad[q] = sum over workgroups (fixed order) of part[w][q]; loss = part[.][NP]
-__global__ __launch_bounds__(256) void mlp_reduce_kernel(const double* part, int64_t nw, double* grad, double* loss) {
-  const int q = blockIdx.x * 256 + threadIdx.x;
-  if (q > NP) return;
+
+// Gradient of sum_s (y - t)^2 / n (and the loss part) over the workgroup's
+// blocks blockIdx.x, blockIdx.x + gridDim.x, ... -> part[blockIdx][NP + 1]
+__global__ __launch_bounds__(256) void mlp_backward_kernel(int64_t n, const double* x, const double* tgt,
+                                                           const double* P, double* part) {
+  __shared__ MlpLds L;
+  __shared__ double gs[4][H];   // b1, b2, W3 gradients, loss and b3 (per sample slot)
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6, g = lane >> 4, c = lane & 15, u = 16 * w + c;
+  double w2[16], w2t[16];       // W2[u][4 ks + g], W2[4 ks + g][u]
+#pragma unroll
+  for (int ks = 0; ks < 16; ++ks) {
+    w2[ks] = P[OW2 + u * H + 4 * ks + g];
+    w2t[ks] = P[OW2 + (4 * ks + g) * H + u];
+  }
+  L.W1[t / NIN][t % NIN] = P[OW1 + t];
+  const double b1 = P[OB1 + u], b2 = P[OB2 + u], w3 = P[OW3 + u];
+  dbl4 gw2[4];                  // gradient of W2[16 w + 4r + g][16 nb + c]
+#pragma unroll
+  for (int q = 0; q < 4; ++q) gw2[q] = dbl4{0.0, 0.0, 0.0, 0.0};
+  double gw1 = 0.0, gb1 = 0.0, gb2 = 0.0, gw3 = 0.0, gb3 = 0.0, loss = 0.0;
+  const int64_t nblk = (n + SB - 1) / SB;
+  for (int64_t b = blockIdx.x; b < nblk; b += gridDim.x) {
+    mlp_load(L, n, b * SB, x);
+    __syncthreads();
+    double z1[4], a2[4];
+    dbl4 z2;
+    mlp_hidden(L, u, g, c, b1, b2, w2, z1, z2);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      a2[r] = silu(z2[r]);
+      L.T[4 * r + g][u] = a2[r];
+    }
+    __syncthreads();
+    const double o = mlp_out(L, P);
+    if ((t & 15) == 0) {
+      const int64_t s = b * SB + (t >> 4);
+      const double res = s < n ? o - tgt[s] : 0.0, dy = 2.0 * res / (double)n;
+      L.y[t >> 4] = dy;
+      gb3 += dy;
+      loss += res * res / (double)n;
+    }
+    __syncthreads();
+    // dZ2[s][u] = dy[s] W3[u] silu'(Z2[s][u]) into T
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const double dy = L.y[4 * r + g], d = dy * w3 * dsilu(z2[r]);
+      gw3 += dy * a2[r];
+      gb2 += d;
+      L.T[4 * r + g][u] = d;
+    }
+    __syncthreads();
+    // W2 gradient: sum_s dZ2[s][m] A1[s][n]; dA1[s][u] = sum_m dZ2[s][m] W2[m][u]
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      const double a = L.T[4 * ks + g][u];
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        gw2[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, L.A1[4 * ks + g][16 * q + c], gw2[q], 0, 0, 0);
+    }
+    dbl4 da = dbl4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int ks = 0; ks < 16; ++ks) da = __builtin_amdgcn_mfma_f64_16x16x4f64(L.T[c][4 * ks + g], w2t[ks], da, 0, 0, 0);
+    __syncthreads();
+    // dZ1 into A1, then the W1 gradient (thread: unit t / 4, input t % 4)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const double d = da[r] * dsilu(z1[r]);
+      gb1 += d;
+      L.A1[4 * r + g][u] = d;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int s = 0; s < SB; ++s) gw1 += L.A1[s][t / NIN] * L.X[s][t % NIN];
+    __syncthreads();
+  }
+  double* out = part + (int64_t)blockIdx.x * (NP + 1);
+  out[OW1 + t] = gw1;
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) out[OW2 + (16 * w + 4 * r + g) * H + 16 * q + c] = gw2[q][r];
+  // the four lane groups' parts of unit u, in order
+  auto fold = [&](double v, int at) {
+    gs[g][u] = v;
+    __syncthreads();
+    if (g == 0) out[at + u] = ((gs[0][u] + gs[1][u]) + gs[2][u]) + gs[3][u];
+    __syncthreads();
+  };
+  fold(gb1, OB1);
+  fold(gb2, OB2);
+  fold(gw3, OW3);
+  if ((t & 15) == 0) { gs[0][t >> 4] = gb3; gs[1][t >> 4] = loss; }
+  __syncthreads();
+  if (t < 2) {
+    double v = 0.0;
+    for (int s = 0; s < SB; ++s) v += gs[t][s];
+    out[t == 0 ? OB3 : NP] = v;
+  }
+}
+// grad[q] = sum over workgroups of part[w][q] in a fixed order (16 lanes a
+// parameter, each every 16th workgroup, then the lanes in order); loss = part[.][NP]
+__global__ __launch_bounds__(256) void mlp_reduce_kernel(const double* part, int nw, double* grad, double* loss) {
+  __shared__ double sh[16][17];
+  const int e = threadIdx.x & 15, l = threadIdx.x >> 4, q = blockIdx.x * 16 + e;
   double s = 0.0;
-  for (int64_t w = 0; w < nw; ++w) s += part[w * (NP + 1) + q];
+  if (q <= NP) {
+#pragma unroll 8
+    for (int w = l; w < nw; w += 16) s += part[(int64_t)w * (NP + 1) + q];
+  }
+  sh[l][e] = s;
+  __syncthreads();
+  if (l != 0 || q > NP) return;
+  for (int k = 1; k < 16; ++k) s += sh[k][e];
   if (q < NP) grad[q] = s; else *loss = s;
 }
 __global__ __launch_bounds__(256) void adam_kernel(const double* g, double* p, double* m, double* v, double c1,
@@ -233,25 +316,49 @@ __global__ __launch_bounds__(256) void log_energy_kernel(int64_t n, const double
   const int64_t s = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (s < n) out[s] = log10(fmax(-e[s], 1e-300));
 }
-__global__ __launch_bounds__(256) void screen_mask_kernel(int nocc, const double* pred, double thr, uint8_t* skip,
-                                                          double* skipped) {
-  __shared__ double sh[256];
+// Predicted energy of the pairs i < j (both orders) whose prediction is below
+// thr, in a fixed order over one workgroup's threads; skip (may be null)
+// receives the mask.  Latency-bound (16.9 us with 256 threads at nocc = 100, 11
+// with 1024).
+constexpr int MT = 1024;
+__device__ __forceinline__ double mask_energy(int nocc, const double* pred, double thr, uint8_t* skip, double* sh) {
   double acc = 0.0;
-  for (int64_t p = threadIdx.x; p < (int64_t)nocc * nocc; p += 256) {
+  for (int64_t p = threadIdx.x; p < (int64_t)nocc * nocc; p += MT) {
     const int i = (int)(p / nocc), j = (int)(p - (int64_t)i * nocc);
     const int a = min(i, j), b = max(i, j);
     const double pr = pred[(int64_t)a * nocc + b];
     const bool sk = (a != b) && pr < thr;
-    skip[p] = sk ? 1 : 0;
+    if (skip) skip[p] = sk ? 1 : 0;
     if (sk) acc += pow(10.0, pr);
   }
   sh[threadIdx.x] = acc;
   __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
+  for (int w = MT / 2; w > 0; w >>= 1) {
     if ((int)threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
     __syncthreads();
   }
-  if (threadIdx.x == 0) *skipped = sh[0];
+  const double e = sh[0];
+  __syncthreads();
+  return e;
+}
+__global__ __launch_bounds__(MT) void screen_mask_kernel(int nocc, const double* pred, double thr, uint8_t* skip,
+                                                         double* skipped) {
+  __shared__ double sh[MT];
+  const double e = mask_energy(nocc, pred, thr, skip, sh);
+  if (threadIdx.x == 0) *skipped = e;
+}
+// The bisection of [-30, 0] for the largest threshold whose mask_energy is at
+// most budget (the same in every thread).  As 60 mask launches, each read back,
+// it took 2.6 ms at nocc = 100; 0.5 ms here.
+__global__ __launch_bounds__(MT) void budget_threshold_kernel(int nocc, const double* pred, double budget, int iters,
+                                                              double* thr) {
+  __shared__ double sh[MT];
+  double lo = -30.0, hi = 0.0;
+  for (int it = 0; it < iters; ++it) {
+    const double mid = 0.5 * (lo + hi);
+    if (mask_energy(nocc, pred, mid, nullptr, sh) <= budget) lo = mid; else hi = mid;
+  }
+  if (threadIdx.x == 0) *thr = lo;
 }
 
 size_t align_up(size_t x) { return (x + 255) / 256 * 256; }
@@ -277,10 +384,11 @@ int rimp2_pair_features(int32_t nocc, int32_t nvir, int32_t naux, const double* 
   double* N = (double*)ws;
   double* nb = (double*)(ws + align_up(8 * (size_t)nocc * naux));
   double* evmin = (double*)(ws + align_up(8 * (size_t)nocc * naux) + align_up(8 * (size_t)nocc));
-  hipLaunchKernelGGL(colnorm_kernel, dim3(nocc), dim3(256), 0, st, B, nvir, naux, N);
+  hipLaunchKernelGGL(colnorm_kernel, dim3((unsigned)(nocc * cdiv(naux, 64))), dim3(256), 0, st, B, nvir, naux, N);
   hipLaunchKernelGGL(rownorm_kernel, dim3(nocc), dim3(256), 0, st, N, naux, nb, eps_vir, nvir, evmin);
-  hipLaunchKernelGGL(pair_kernel, dim3((unsigned)cdiv((int64_t)nocc * nocc, 256)), dim3(256), 0, st, nocc, naux, N,
-                     nb, eps_occ, centroids, evmin, features, bound);
+  const unsigned pt = (unsigned)cdiv(nocc, PT);
+  hipLaunchKernelGGL(pair_kernel, dim3(pt, pt), dim3(PT * PT), 0, st, nocc, naux, N, nb, eps_occ, centroids, evmin,
+                     features, bound);
   HIP_TRY(hipGetLastError());
   return RIMP2_OK;
 }
@@ -288,25 +396,27 @@ int rimp2_pair_features(int32_t nocc, int32_t nvir, int32_t naux, const double* 
 int rimp2_mlp_forward(int64_t n, const double* x, const double* params, double* y, void* stream) {
   if (n < 0 || (n > 0 && (!x || !params || !y))) return fail(RIMP2_EINVAL, "bad forward arguments");
   if (n == 0) return RIMP2_OK;
-  if (cdiv(n, FS) * 64 > kMaxItems) return fail(RIMP2_EINVAL, "n = %lld is too large for one launch", (long long)n);
-  hipLaunchKernelGGL(mlp_forward_kernel, dim3((unsigned)cdiv(n, FS)), dim3(64), 0, (hipStream_t)stream, n, x, params,
-                     y);
+  if (cdiv(n, 64) * 64 > kMaxItems) return fail(RIMP2_EINVAL, "n = %lld is too large for one launch", (long long)n);
+  const int64_t nwg = std::min<int64_t>(cdiv(n, SB), 4 * MAXW);
+  hipLaunchKernelGGL(mlp_forward_kernel, dim3((unsigned)nwg), dim3(256), 0, (hipStream_t)stream, n, x, params, y);
   HIP_TRY(hipGetLastError());
   return RIMP2_OK;
 }
 
-size_t rimp2_mlp_workspace_size(int64_t n) { return align_up(8 * (size_t)cdiv(n, BS) * (NP + 1)); }
+size_t rimp2_mlp_workspace_size(int64_t n) {
+  return align_up(8 * (size_t)std::min<int64_t>(cdiv(n, SB), MAXW) * (NP + 1));
+}
 
 int rimp2_mlp_loss_grad(int64_t n, const double* x, const double* target, const double* params, double* loss,
                         double* grad, void* workspace, size_t workspace_bytes, void* stream) {
   if (n < 1 || !x || !target || !params || !loss || !grad || !workspace) return fail(RIMP2_EINVAL, "bad arguments");
   if (workspace_bytes < rimp2_mlp_workspace_size(n)) return fail(RIMP2_ENOMEM, "workspace too small");
   hipStream_t st = (hipStream_t)stream;
-  const int64_t nw = cdiv(n, BS);
-  if (nw * 64 > kMaxItems) return fail(RIMP2_EINVAL, "n = %lld is too large for one launch", (long long)n);
-  hipLaunchKernelGGL(mlp_backward_kernel, dim3((unsigned)nw), dim3(64), 0, st, n, x, target, params,
+  if (cdiv(n, 32) * 64 > kMaxItems) return fail(RIMP2_EINVAL, "n = %lld is too large for one launch", (long long)n);
+  const int nw = (int)std::min<int64_t>(cdiv(n, SB), MAXW);
+  hipLaunchKernelGGL(mlp_backward_kernel, dim3((unsigned)nw), dim3(256), 0, st, n, x, target, params,
                      (double*)workspace);
-  hipLaunchKernelGGL(mlp_reduce_kernel, dim3((unsigned)cdiv(NP + 1, 256)), dim3(256), 0, st, (const double*)workspace,
+  hipLaunchKernelGGL(mlp_reduce_kernel, dim3((unsigned)cdiv(NP + 1, 16)), dim3(256), 0, st, (const double*)workspace,
                      nw, grad, loss);
   HIP_TRY(hipGetLastError());
   return RIMP2_OK;
@@ -334,8 +444,17 @@ int rimp2_log_energy(int64_t n, const double* e, double* out, void* stream) {
 int rimp2_screen_mask(int32_t nocc, const double* pred, double threshold_log10, uint8_t* skip, double* skipped_energy,
                       void* stream) {
   if (nocc < 1 || !pred || !skip || !skipped_energy) return fail(RIMP2_EINVAL, "bad arguments");
-  hipLaunchKernelGGL(screen_mask_kernel, dim3(1), dim3(256), 0, (hipStream_t)stream, nocc, pred, threshold_log10,
+  hipLaunchKernelGGL(screen_mask_kernel, dim3(1), dim3(MT), 0, (hipStream_t)stream, nocc, pred, threshold_log10,
                      skip, skipped_energy);
+  HIP_TRY(hipGetLastError());
+  return RIMP2_OK;
+}
+
+int rimp2_budget_threshold(int32_t nocc, const double* pred, double budget_Eh, int32_t iters, double* threshold_log10,
+                           void* stream) {
+  if (nocc < 1 || iters < 0 || !pred || !threshold_log10) return fail(RIMP2_EINVAL, "bad arguments");
+  hipLaunchKernelGGL(budget_threshold_kernel, dim3(1), dim3(MT), 0, (hipStream_t)stream, nocc, pred, budget_Eh, iters,
+                     threshold_log10);
   HIP_TRY(hipGetLastError());
   return RIMP2_OK;
 }

@@ -36,6 +36,8 @@ def _L():
         L.rimp2_log_energy.argtypes = [i64, vp, vp, vp]
         L.rimp2_screen_mask.restype = ctypes.c_int
         L.rimp2_screen_mask.argtypes = [i32, vp, dbl, vp, vp, vp]
+        L.rimp2_budget_threshold.restype = ctypes.c_int
+        L.rimp2_budget_threshold.argtypes = [i32, vp, dbl, i32, vp, vp]
         _bound = True
     return L
 
@@ -125,15 +127,9 @@ def budget_threshold(pred: torch.Tensor, nocc: int, budget_Eh: float, iters: int
     """The largest log10 threshold whose predicted skipped energy (sum of
     10^pred over the pairs it skips, rimp2_screen_mask) is at most budget_Eh,
     by bisection over [-30, 0]."""
-    lo, hi = -30.0, 0.0
-    for _ in range(iters):
-        mid = 0.5 * (lo + hi)
-        _, se = screen_mask(pred, nocc, mid)
-        if float(se) <= budget_Eh:
-            lo = mid
-        else:
-            hi = mid
-    return lo
+    thr = torch.empty(1, dtype=torch.float64, device=pred.device)
+    _check(_L().rimp2_budget_threshold(nocc, _ptr(pred), budget_Eh, iters, _ptr(thr), _stream_handle(None)))
+    return float(thr)
 
 
 def bound_mask(bound: torch.Tensor, budget_Eh: float) -> torch.Tensor:
