@@ -707,23 +707,34 @@ void launch_split_cols(const double* X, int64_t K, int64_t N, int64_t ld, const 
   hipLaunchKernelGGL(split_cols_kernel<S>, dim3((unsigned)cdiv(kp, 32), (unsigned)cdiv(N, 32)), dim3(256), 0, st, X, K,
                      N, ld, cmax, D, kp, e, status);
 }
-// Tiles of a pair launch of 64 x 64 split products, as gemm_tiles counts them.
-int64_t oz8_tiles(const OzParams& op) {
+// Output tiles a split-product launch holds workgroups for (as gemm_tiles).
+int64_t oz8_tiles(const OzParams& op, int bm, int bn) {
   GemmParams gp{};
   gp.tiles_m = op.tiles_m; gp.tiles_n = op.tiles_n; gp.group_m = op.group_m;
   gp.pair_upper = op.pair_nvir > 0; gp.skip_nvir = op.pair_nvir; gp.skip_k0 = op.pair_k0; gp.skip_j0 = op.pair_j0;
   gp.pair_lo = op.pair_lo;
-  return gemm_tiles(gp, 64, 64, false);
+  return gemm_tiles(gp, bm, bn, false);
+}
+// Outputs' worth of 64 x 64 tiles at which the 128 x 128 tile of at most 5
+// digits (OzWide) computes one, measured 2.5 against 2.1 POP/s.
+constexpr double kOzWideRate = 1.2;
+// Tile side of a split product with S digits: 128 where its rate outweighs its
+// padding and it gives every CU a workgroup or more (8000 x 720, 378 tiles of
+// 128: 0.260 ms against 0.267).
+int oz8_side(int S, double tiles64, double tiles128) {
+  return S <= 5 && tiles128 >= 256 && 4.0 * tiles128 < kOzWideRate * tiles64 ? 128 : 64;
 }
 template <int S>
-void launch_oz8(OzParams op, bool windowed, hipStream_t st) {
-  const int64_t nwg = oz8_tiles(op);
+void launch_oz8(OzParams op, int side, bool windowed, hipStream_t st) {
+  const int64_t nwg = oz8_tiles(op, side, side);
+  if (S <= 5 && side == 128)
+    hipLaunchKernelGGL((gemm_oz8_kernel<S <= 5 ? S : 5, 2, OzWide>), dim3((unsigned)nwg), dim3(512), 0, st, op);
   // one LDS stage (two workgroups per CU) unless a windowed product with at
   // most 5 digits, where the double-buffered stage (still two per CU) was faster
-  if (windowed && S <= 5)
-    hipLaunchKernelGGL((gemm_oz8_kernel<S, 2>), dim3((unsigned)nwg), dim3(256), 0, st, op);
+  else if (windowed && S <= 5)
+    hipLaunchKernelGGL((gemm_oz8_kernel<S, 2, OzSmall>), dim3((unsigned)nwg), dim3(256), 0, st, op);
   else
-    hipLaunchKernelGGL((gemm_oz8_kernel<S, 1>), dim3((unsigned)nwg), dim3(256), 0, st, op);
+    hipLaunchKernelGGL((gemm_oz8_kernel<S, 1, OzSmall>), dim3((unsigned)nwg), dim3(256), 0, st, op);
 }
 #define RIMP2_SWITCH_S(S, CALL)                                   \
   switch (S) {                                                    \
@@ -747,6 +758,7 @@ __global__ void zero_u64_kernel(unsigned long long* p, int64_t n) {
 // staging bytes from beyond the L2, and the windows made the product about
 // 1.7x faster (windows of 5632: 1.6x).
 constexpr int64_t kOzWindow = 2816, kOzWindowMax = 8192;
+static_assert(kOzWindowMax <= kOzMaxK, "INT32 levels");
 
 // C[m, n] (m < M, n < N) from split digits; A rows start at a_row0.
 // acc0: the first window adds into C too (C already holds a partial sum).
@@ -764,14 +776,15 @@ int run_oz8(int S, const int8_t* A, int64_t a_slice, int64_t a_row0, const int32
   op.B = B; op.b_slice = b_slice; op.ea = ea; op.eb = eb;
   op.C = C; op.ldc = ldc;
   const bool windowed = kp > kOzWindowMax;
-  op.tiles_m = (int32_t)cdiv(M, 64); op.tiles_n = (int32_t)cdiv(N, 64); op.group_m = windowed ? 4 : 8;
+  const int side = oz8_side(S, (double)cdiv(M, 64) * cdiv(N, 64), (double)cdiv(M, 128) * cdiv(N, 128));
+  op.tiles_m = (int32_t)cdiv(M, side); op.tiles_n = (int32_t)cdiv(N, side); op.group_m = windowed && side == 64 ? 4 : 8;
   op.status = status;
   if (pairs) {
     op.pair_nvir = (int32_t)pairs->nvir; op.pair_k0 = (int32_t)pairs->k0; op.pair_j0 = (int32_t)pairs->j0;
     op.pair_lo = (int32_t)pairs->lo;
   }
-  const int64_t nwg = oz8_tiles(op);
-  if (int rc = check_grid(nwg, "split GEMM")) return rc;
+  const int64_t nwg = oz8_tiles(op, side, side);
+  if (int rc = check_grid(nwg * (side / 64), "split GEMM")) return rc;
   const double ef = 2.0 * (double)M * N * kp * ((double)nwg / ((double)op.tiles_m * op.tiles_n));
   const int64_t kc = windowed ? kOzWindow : kp;
   for (int64_t k0 = 0;; k0 += kc) {
@@ -780,7 +793,7 @@ int run_oz8(int S, const int8_t* A, int64_t a_slice, int64_t a_row0, const int32
     op.accumulate = (k0 > 0 || acc0) ? 1 : 0;
     const double fr = kp > 0 ? (double)op.kc / (double)kp : 1.0;
     if (int rc = traced(role, af * fr, ef * fr, ab * fr, st,
-                        [&] { RIMP2_SWITCH_S(S, launch_oz8<SS>(op, windowed, st)); }))
+                        [&] { RIMP2_SWITCH_S(S, launch_oz8<SS>(op, side, windowed, st)); }))
       return rc;
     if (k0 + kc >= kp) return RIMP2_OK;
   }
@@ -1184,6 +1197,7 @@ struct Wave {
   int n_oz[2] = {0, 0};
   int64_t items_oz[2] = {0, 0};
   int win_oz[2] = {0, 0};
+  int side_oz[2] = {64, 64};      // tile side of each product
   // grouped digit splits: lists 0 (B rows), 1 (B columns: zero, maxima), 2 (B
   // column digits), 3 (T rows); each with its op table and four prefix arrays
   // (one per mode; only the one its launch uses is read)
@@ -1327,6 +1341,15 @@ int batch_plan(int32_t nfrag, const rimp2_frag_desc* d, const rimp2_opts* opts, 
         W.win_oz[0] = std::max<int>(W.win_oz[0], (int)cdiv(P.kpv, kOzWindow));
         if (P.gamma) W.win_oz[1] = std::max<int>(W.win_oz[1], (int)cdiv(P.kpg, kOzWindow));
       }
+      // one tile shape for the wave's Gamma products, by their tiles together
+      // ((ia|jb) runs at 64: its defaults are 7 digits)
+      double t64 = 0.0, t128 = 0.0;
+      for (int32_t f : W.frags)
+        if (const Plan& P = B->plan[f]; P.gamma) {
+          t64 += (double)cdiv(P.nocc * P.nvir, 64) * cdiv(P.naux, 64);
+          t128 += (double)cdiv(P.nocc * P.nvir, 128) * cdiv(P.naux, 128);
+        }
+      W.side_oz[1] = oz8_side(B->plan[W.frags[0]].sg, t64, t128);
       W.o_cnt_oz = place(t, sizeof(unsigned long long) * kQueues * (W.win_oz[0] + W.win_oz[1]));
       for (int r = 0; r < Wave::kDigitLists; ++r) {
         W.o_dop[r] = place(t, sizeof(DigitOp) * n);
@@ -1398,11 +1421,12 @@ int batch_plan(int32_t nfrag, const rimp2_frag_desc* d, const rimp2_opts* opts, 
         z.B = z.A; z.b_slice = z.a_slice;
         z.ea = relp<int32_t>(base + P.off_ev); z.eb = z.ea;
         z.C = V; z.ldc = L;
-        z.tiles_m = (int32_t)cdiv(L, 64); z.tiles_n = z.tiles_m; z.group_m = 8;
+        const int64_t sz = W.side_oz[0];
+        z.tiles_m = (int32_t)cdiv(L, sz); z.tiles_n = z.tiles_m; z.group_m = 8;
         z.pair_nvir = (int32_t)nvir;   // blocks j < k: the amplitude pass mirrors them (pair_k0 = pair_j0 = pair_lo = 0)
         z.status = status;
         oz[0].push_back(z);
-        oz_pre[0].push_back(oz_pre[0].back() + oz8_tiles(z));
+        oz_pre[0].push_back(oz_pre[0].back() + oz8_tiles(z, sz, sz));
         // digits of every B row (both operands of the (ia|jb) products)
         add_dop(0, DigitOp{q.B, naux, L, naux, P.kpv, 0, relp<int8_t>(base + P.off_dbv),
                            relp<int32_t>(base + P.off_ev), nullptr, status}, L, 0, 0, 0);
@@ -1413,10 +1437,11 @@ int batch_plan(int32_t nfrag, const rimp2_frag_desc* d, const rimp2_opts* opts, 
           y.B = relp<int8_t>(base + P.off_dbg); y.b_slice = naux * P.kpg;
           y.ea = relp<int32_t>(base + P.off_et); y.eb = relp<int32_t>(base + P.off_eg);
           y.C = q.Gamma; y.ldc = naux;
-          y.tiles_m = (int32_t)cdiv(L, 64); y.tiles_n = (int32_t)cdiv(naux, 64); y.group_m = 8;
+          const int64_t sy = W.side_oz[1];
+          y.tiles_m = (int32_t)cdiv(L, sy); y.tiles_n = (int32_t)cdiv(naux, sy); y.group_m = 8;
           y.status = status;
           oz[1].push_back(y);
-          oz_pre[1].push_back(oz_pre[1].back() + oz8_tiles(y));
+          oz_pre[1].push_back(oz_pre[1].back() + oz8_tiles(y, sy, sy));
           // column digits of B (maxima first) and row digits of the T slab
           unsigned long long* cm = relp<unsigned long long>(base + P.off_cmax);
           const int64_t gxm = cdiv(naux, 256), gxd = cdiv(P.kpg, 32);
@@ -1594,16 +1619,18 @@ __global__ void relocate_oz_kernel(char* base, OzParams* z, int n) {
 }
 
 // One grouped split-product launch over reduction window `window` of every
-// problem in G (same NBUF choice as launch_oz8 for a windowed product).
+// problem in G (the shapes and buffering of launch_oz8 for a windowed product).
 template <int S>
-int launch_oz8_grouped(const OzGroup& G, int64_t items, int64_t window, int role, hipStream_t st) {
+int launch_oz8_grouped(const OzGroup& G, int64_t items, int side, int64_t window, int role, hipStream_t st) {
   if (G.nprob == 0 || items == 0) return RIMP2_OK;
-  const int64_t grid = std::min<int64_t>(items, kSlots);
+  const int64_t grid = std::min<int64_t>(items, side == 128 ? kSlots / 2 : kSlots);
   return traced(role, 0, 0, 0, st, [&] {
-    if (S <= 5)
-      hipLaunchKernelGGL((gemm_oz8_grouped<S, 2>), dim3((unsigned)grid), dim3(256), 0, st, G, window, kOzWindow);
+    if (S <= 5 && side == 128)
+      hipLaunchKernelGGL((gemm_oz8_grouped<S <= 5 ? S : 5, 2, OzWide>), dim3((unsigned)grid), dim3(512), 0, st, G, window,
+                         kOzWindow);
     else
-      hipLaunchKernelGGL((gemm_oz8_grouped<S, 1>), dim3((unsigned)grid), dim3(256), 0, st, G, window, kOzWindow);
+      hipLaunchKernelGGL((gemm_oz8_grouped<S, S <= 5 ? 2 : 1, OzSmall>), dim3((unsigned)grid), dim3(256), 0, st, G,
+                         window, kOzWindow);
   });
 }
 
@@ -1732,7 +1759,7 @@ int batch_run(rimp2_batch_s* B, int32_t* status_dev, void* workspace, size_t byt
       for (int w = 0; w < W.win_oz[r]; ++w) {
         const OzGroup G{(const OzParams*)at(W.o_oz[r]), (const int64_t*)at(W.o_oz_pre[r]), W.n_oz[r], cnt + w * kQueues};
         const int role = r == 0 ? R_INTS8 : R_GAMMA8;
-        RIMP2_SWITCH_S(S, rc2 = launch_oz8_grouped<SS>(G, W.items_oz[r], w, role, st));
+        RIMP2_SWITCH_S(S, rc2 = launch_oz8_grouped<SS>(G, W.items_oz[r], W.side_oz[r], w, role, st));
         if (rc2) return rc2;
       }
       return RIMP2_OK;

@@ -11,8 +11,9 @@
 //   C[m,n] = 2^(ea[m] + eb[n] - 12) * sum_{L=2..S+1} 128^(2-L) * sum_{s+t=L} D_s(A) D_t(B)^T
 // (the products with s + t > S + 1 are below the digit truncation and are
 // dropped: S(S+1)/2 integer products).  Each level is summed exactly in INT32
-// by v_mfma_i32_16x16x64_i8; to rule out overflow the levels are moved into
-// FP64 accumulators every kFlushK reduction steps (S * kFlushK * 64 * 64 < 2^31).
+// by v_mfma_i32_16x16x64_i8; a launch reduces over at most kOzMaxK indices, so
+// no level can overflow (7 * kOzMaxK * 64 * 64 < 2^31), and then combines the
+// levels in FP64.
 //
 // MFMA lane layout (measured on gfx950): lane l supplies A[l%16][16(l/16)+b]
 // and B[16(l/16)+b][l%16] for byte b; accumulator register r of lane l holds
@@ -25,7 +26,7 @@
 namespace rimp2 {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
-constexpr int64_t kFlushK = 65536;
+constexpr int64_t kOzMaxK = 65536;
 
 // Row-scaled digits of a K-contiguous FP64 matrix X[rows][K] (row stride ld):
 // D[s][row][kp] (kp = K rounded up to 64, zero padded) and exps[row].
@@ -143,34 +144,55 @@ struct OzParams {
   const int32_t* status;
 };
 
-// 256 threads = 4 waves in 2 x 2; workgroup tile 64 x 64, wave tile 32 x 32
-// (2 x 2 MFMA blocks).  All S digit slices of a 64-wide reduction step are
-// staged in LDS (S * 8 KB): wave w moves row block w (16 rows x 64 bytes,
-// 1 KB) of every (slice, operand).  Within a 1 KB block lane l writes bytes
-// [16 l, 16 l + 16), and it loads row r = l / 4, 16-byte chunk
-// (l % 4) ^ ((r / 4) % 4): an XOR swizzle that makes the MFMA fragment reads
-// (16 lanes reading 16 rows of one chunk) free of bank conflicts.
-// NBUF = 2 double-buffers the stage (the next step's copy runs under this
-// step's MFMAs); NBUF = 1 keeps one stage, copied after the step's MFMAs, so
-// that two workgroups share a CU at any S (measured the faster of the two).
-template <int S>
+// Tile shapes.  The waves form a WM x WN grid, each with MI x NI blocks of 16 x
+// 16 outputs; the S digit slices of a 64-wide reduction step of both operands
+// are staged in LDS (1 KB per slice and 16 rows), NBUF stages deep.  Within a
+// 1 KB block lane l writes bytes [16 l, 16 l + 16), and it loads row r = l / 4,
+// 16-byte chunk (l % 4) ^ oz8_swizzle(r): the 16-lane groups in which the LDS
+// serves the fragment reads (lanes 0-3, 12-15, 20-27; 4-11, 16-19, 28-31; the
+// same from 32 on) then meet no bank twice.  (With (r / 4) % 4 half of the
+// LDS's active cycles were conflicts.)
+// Bound by operand delivery under a power limit: random digits in registers
+// alone reach 3.95 POP/s, a tile that stages from a warm L2 2.8, and the 7-digit
+// (ia|jb) product of 40/900/3000 runs at 2.2.
+//   OzSmall: 4 waves of 32 x 32, 64 x 64 outputs, two workgroups a CU.  NBUF = 2
+//     double-buffers the stage; NBUF = 1 keeps one, copied after the step's
+//     MFMAs, so that two workgroups share a CU at any S.
+//   OzWide (S <= 5): 8 waves of 64 x 32, 128 x 128 outputs, one workgroup a CU
+//     with two stages (S = 5: all 160 KB).  It stages half the bytes per
+//     product: Gamma windows of 36000 x 3000 x 2816 at 5 digits 4.4 -> 3.7 ms
+//     (2.1 -> 2.5 POP/s).  Reading the next stage's first fragments before the
+//     barrier spilled registers and took 4.7.
+struct OzSmall {
+  static constexpr int WM = 2, WN = 2, MI = 2, NI = 2;
+};
+struct OzWide {
+  static constexpr int WM = 2, WN = 4, MI = 4, NI = 2;
+};
+// 0, 2, 3, 1 for rows 0-3, 4-7, 8-11, 12-15 of a block.
+__device__ __forceinline__ int oz8_swizzle(int r) { return (0x78 >> (2 * (r >> 2))) & 3; }
+template <class T>
+struct OzShape {
+  static constexpr int BM = T::WM * T::MI * 16, BN = T::WN * T::NI * 16, THREADS = T::WM * T::WN * 64;
+};
+template <int S, class T = OzSmall>
 struct OzLds {
-  static constexpr int STAGE = S * 2 * 4 * 1024;   // S slices x (A, B) x 4 row blocks x 1 KB
+  static constexpr int STAGE = S * (OzShape<T>::BM + OzShape<T>::BN) * 64;
 };
 
 // A tile whose pairs all have pair_lo <= j < k is skipped when p.pair_nvir >
 // 0: the amplitude pass forms those blocks from their mirror.
-__device__ __forceinline__ bool oz8_tile_skipped(const OzParams& p, int64_t m0, int64_t n0) {
+__device__ __forceinline__ bool oz8_tile_skipped(const OzParams& p, int64_t m0, int64_t n0, int bn) {
   if (p.pair_nvir <= 0) return false;
-  return p.pair_j0 + min(n0 + 63, p.N - 1) / p.pair_nvir < p.pair_k0 + m0 / p.pair_nvir &&
+  return p.pair_j0 + min(n0 + bn - 1, p.N - 1) / p.pair_nvir < p.pair_k0 + m0 / p.pair_nvir &&
          p.pair_j0 + n0 / p.pair_nvir >= p.pair_lo;
 }
 
 // Logical tile t of a launch: raster groups of group_m row tiles, of a pair
 // launch the tiles they keep.
-__device__ __forceinline__ void oz8_decode(const OzParams& p, int t, int& tm, int& tn) {
+__device__ __forceinline__ void oz8_decode(const OzParams& p, int bm, int bn, int t, int& tm, int& tn) {
   if (p.pair_nvir > 0) {
-    decode_pair_tile(t, p.pair_k0, p.pair_j0, p.pair_lo, p.pair_nvir, 64, 64, p.tiles_m, p.tiles_n, p.group_m, tm, tn);
+    decode_pair_tile(t, p.pair_k0, p.pair_j0, p.pair_lo, p.pair_nvir, bm, bn, p.tiles_m, p.tiles_n, p.group_m, tm, tn);
   } else {
     const int gsz = p.group_m * p.tiles_n, grp = t / gsz, first_m = grp * p.group_m;
     const int gm = min(p.group_m, p.tiles_m - first_m), tin = t - grp * gsz;
@@ -179,146 +201,154 @@ __device__ __forceinline__ void oz8_decode(const OzParams& p, int t, int& tm, in
   }
 }
 
-// One 64 x 64 output tile at (m0, n0) over the reduction window [k0, k0 + kc).
-template <int S, int NBUF>
-__device__ __forceinline__ void oz8_tile(const OzParams& p, int64_t m0, int64_t n0,
-                                         int8_t (*lds)[OzLds<S>::STAGE]) {
+// One output tile at (m0, n0) over the reduction window [k0, k0 + kc).
+template <int S, int NBUF, class T>
+__device__ __forceinline__ void oz8_tile(const OzParams& p, int64_t m0, int64_t n0, int8_t (*lds)[OzLds<S, T>::STAGE]) {
+  constexpr int MI = T::MI, NI = T::NI, RA = OzShape<T>::BM / 16, RB = OzShape<T>::BN / 16;   // row blocks of A, B
+  constexpr int NW = T::WM * T::WN, CA = RA / NW, CB = RB / NW;   // row blocks each wave copies
+  static_assert(RA % NW == 0 && RB % NW == 0, "row blocks per wave");
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, g = lane >> 4, l16 = lane & 15;
-  const int wm = wv >> 1, wn = wv & 1;
+  const int wm = wv / T::WN, wn = wv % T::WN;
 
-  // copy: rows past the end read the last row (their outputs are not stored)
-  const int dr = lane >> 2, dc = (lane & 3) ^ ((dr >> 2) & 3);
-  const int64_t rowA = p.a_row0 + min(m0 + 16 * wv + dr, p.M - 1), rowB = min(n0 + 16 * wv + dr, p.N - 1);
-  const int8_t* srcA = p.A + rowA * p.kp + 16 * dc;
-  const int8_t* srcB = p.B + rowB * p.kp + 16 * dc;
+  // copy: rows past the end read the last row (their outputs are not stored);
+  // a scalar base and a 32-bit lane offset per row block
+  const int dr = lane >> 2, dc = (lane & 3) ^ oz8_swizzle(dr);
+  const int8_t *tileA = p.A + (p.a_row0 + m0) * p.kp, *tileB = p.B + n0 * p.kp;
+  uint32_t offA[CA], offB[CB];
+#pragma unroll
+  for (int c = 0; c < CA; ++c)
+    offA[c] = (uint32_t)(min((int64_t)(16 * (wv + NW * c) + dr), p.M - 1 - m0) * p.kp + 16 * dc);
+#pragma unroll
+  for (int c = 0; c < CB; ++c)
+    offB[c] = (uint32_t)(min((int64_t)(16 * (wv + NW * c) + dr), p.N - 1 - n0) * p.kp + 16 * dc);
   auto copy = [&](int buf, int64_t k) {
 #pragma unroll
     for (int s = 0; s < S; ++s) {
-      __builtin_amdgcn_global_load_lds((const void*)(srcA + s * p.a_slice + k),
-                                       (void*)(lds[buf] + ((s * 2 + 0) * 4 + wv) * 1024), 16, 0, 0);
-      __builtin_amdgcn_global_load_lds((const void*)(srcB + s * p.b_slice + k),
-                                       (void*)(lds[buf] + ((s * 2 + 1) * 4 + wv) * 1024), 16, 0, 0);
+      const int8_t *a = tileA + (s * p.a_slice + k), *b = tileB + (s * p.b_slice + k);
+#pragma unroll
+      for (int c = 0; c < CA; ++c)
+        __builtin_amdgcn_global_load_lds((const void*)(a + offA[c]),
+                                         (void*)(lds[buf] + (s * (RA + RB) + wv + NW * c) * 1024), 16, 0, 0);
+#pragma unroll
+      for (int c = 0; c < CB; ++c)
+        __builtin_amdgcn_global_load_lds((const void*)(b + offB[c]),
+                                         (void*)(lds[buf] + (s * (RA + RB) + RA + wv + NW * c) * 1024), 16, 0, 0);
     }
   };
   // fragment of lane (g, l16): row l16 of a row block, data chunk g
-  const int fpos = (l16 * 4 + (g ^ ((l16 >> 2) & 3))) * 16;
+  const int fpos = (l16 * 4 + (g ^ oz8_swizzle(l16))) * 16;
 
-  v4i acc[S][2][2];
-  auto zero_acc = [&]() {
+  v4i acc[S][MI][NI];
 #pragma unroll
-    for (int L = 0; L < S; ++L)
+  for (int L = 0; L < S; ++L)
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < MI; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) acc[L][i][j] = v4i{0, 0, 0, 0};
-  };
-  // flush: the levels of each output are combined in FP64, scaled by the
-  // output's exponents (a power of two: exact) and added to C; the first flush
-  // of a launch that does not accumulate stores.  C holds the running sum
-  // between flushes, so no FP64 accumulators stay live in the loop.
-  bool first_flush = p.accumulate == 0;
-  auto flush = [&]() {
-    int xa[2][4], xb[2];   // exponents of this lane's output rows and columns
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int64_t m = m0 + wm * 32 + 16 * i + 4 * g + r;
-        xa[i][r] = m < p.M ? p.ea[p.a_row0 + m] : 0;
-      }
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int64_t n = n0 + wn * 32 + 16 * j + l16;
-      xb[j] = n < p.N ? p.eb[n] : 0;
-    }
-    double w[2][2][4];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          double v = 0.0;
-#pragma unroll
-          for (int L = S - 1; L >= 0; --L) v = v * (1.0 / 128.0) + (double)acc[L][i][j][r];
-          w[i][j][r] = ldexp(v, xa[i][r] + xb[j] - 12);
-        }
-    zero_acc();
-    // per row block i: the C reads (clamped: always in bounds and without a
-    // branch, so the 8 loads go out together; what an out-of-range output
-    // reads is never stored), then the stores
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      if (!first_flush) {
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const int64_t m = min(m0 + wm * 32 + 16 * i + 4 * g + r, p.M - 1);
-            const int64_t n = min(n0 + wn * 32 + 16 * j + l16, p.N - 1);
-            w[i][j][r] += p.C[m * p.ldc + n];
-          }
-      }
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int64_t m = m0 + wm * 32 + 16 * i + 4 * g + r, n = n0 + wn * 32 + 16 * j + l16;
-          if (m < p.M && n < p.N) p.C[m * p.ldc + n] = w[i][j][r];
-        }
-    }
-    first_flush = false;
-  };
-  zero_acc();
+      for (int j = 0; j < NI; ++j) acc[L][i][j] = v4i{0, 0, 0, 0};
 
   const int nsteps = (int)(p.kc / 64);
-  const int flush_every = (int)(kFlushK / 64);
-  if (nsteps > 0) copy(0, p.k0);
-  for (int st = 0; st < nsteps; ++st) {
-    const int b = (NBUF == 2) ? (st & 1) : 0;
-    // LDS copies count in vmcnt: wait for this wave's, then the barrier makes
-    // every wave's visible (and frees the other buffer)
+  auto frag_a = [&](const int8_t* L0, int s, v4i (&f)[MI]) {
+#pragma unroll
+    for (int i = 0; i < MI; ++i) f[i] = *(const v4i*)(L0 + (s * (RA + RB) + wm * MI + i) * 1024);
+  };
+  auto frag_b = [&](const int8_t* L0, int t, v4i (&f)[NI]) {
+#pragma unroll
+    for (int j = 0; j < NI; ++j) f[j] = *(const v4i*)(L0 + (t * (RA + RB) + RA + wn * NI + j) * 1024);
+  };
+  // LDS copies count in vmcnt: wait for this wave's (a barrier alone does not),
+  // then the barrier makes every wave's visible and frees the stage they all read
+  auto stage_barrier = [] {
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
+  };
+  if (nsteps > 0) copy(0, p.k0);
+  stage_barrier();
+  for (int st = 0; st < nsteps; ++st) {
+    const int b = NBUF == 2 ? st & 1 : 0;
     if (NBUF == 2 && st + 1 < nsteps) copy(b ^ 1, p.k0 + (int64_t)(st + 1) * 64);
-    const int8_t* L0 = lds[b];
-    v4i fb[S][2];
+    const int8_t* L0 = lds[b] + fpos;
+    v4i fb[S][NI];
 #pragma unroll
-    for (int t = 0; t < S; ++t)
-#pragma unroll
-      for (int j = 0; j < 2; ++j) fb[t][j] = *(const v4i*)(L0 + ((t * 2 + 1) * 4 + 2 * wn + j) * 1024 + fpos);
+    for (int t = 0; t < S; ++t) frag_b(L0, t, fb[t]);
 #pragma unroll
     for (int s = 0; s < S; ++s) {
-      v4i fa[2];
-#pragma unroll
-      for (int i = 0; i < 2; ++i) fa[i] = *(const v4i*)(L0 + ((s * 2 + 0) * 4 + 2 * wm + i) * 1024 + fpos);
+      v4i fa[MI];
+      frag_a(L0, s, fa);
 #pragma unroll
       for (int t = 0; t < S - s; ++t)
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+        for (int i = 0; i < MI; ++i)
 #pragma unroll
-          for (int j = 0; j < 2; ++j)
+          for (int j = 0; j < NI; ++j)
             acc[s + t][i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa[i], fb[t][j], acc[s + t][i][j], 0, 0, 0);
     }
-    if (NBUF == 1 && st + 1 < nsteps) {
-      __syncthreads();   // every wave is done reading the stage
-      copy(0, p.k0 + (int64_t)(st + 1) * 64);
+    if (st + 1 < nsteps) {
+      stage_barrier();   // every wave is done reading the stage (and, of two, the next one is there)
+      if (NBUF == 1) {
+        copy(0, p.k0 + (int64_t)(st + 1) * 64);
+        stage_barrier();
+      }
     }
-    if ((st + 1) % flush_every == 0) flush();
   }
-  flush();
+
+  // the levels of each output are combined in FP64, scaled by the output's
+  // exponents (a power of two: exact) and stored, or added to C
+  int xb[NI];   // exponents of this lane's output columns
+#pragma unroll
+  for (int j = 0; j < NI; ++j) {
+    const int64_t n = n0 + (wn * NI + j) * 16 + l16;
+    xb[j] = n < p.N ? p.eb[n] : 0;
+  }
+  // per row block i: the C reads (clamped: always in bounds and without a
+  // branch, so the loads go out together; what an out-of-range output reads is
+  // never stored), then the stores
+#pragma unroll
+  for (int i = 0; i < MI; ++i) {
+    double w[NI][4];
+    if (p.accumulate) {
+#pragma unroll
+      for (int j = 0; j < NI; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int64_t m = min(m0 + (wm * MI + i) * 16 + 4 * g + r, p.M - 1);
+          const int64_t n = min(n0 + (wn * NI + j) * 16 + l16, p.N - 1);
+          w[j][r] = p.C[m * p.ldc + n];
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int64_t m = m0 + (wm * MI + i) * 16 + 4 * g + r;
+      const int xa = m < p.M ? p.ea[p.a_row0 + m] : 0;
+#pragma unroll
+      for (int j = 0; j < NI; ++j) {
+        double v = 0.0;
+#pragma unroll
+        for (int L = S - 1; L >= 0; --L) v = v * (1.0 / 128.0) + (double)acc[L][i][j][r];
+        v = ldexp(v, xa + xb[j] - 12);
+        w[j][r] = p.accumulate ? v + w[j][r] : v;
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < NI; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int64_t m = m0 + (wm * MI + i) * 16 + 4 * g + r, n = n0 + (wn * NI + j) * 16 + l16;
+        if (m < p.M && n < p.N) p.C[m * p.ldc + n] = w[j][r];
+      }
+  }
 }
 
-template <int S, int NBUF>
-__global__ __launch_bounds__(256, 2) void gemm_oz8_kernel(OzParams p) {
+template <int S, int NBUF, class T>
+__global__ __launch_bounds__(OzShape<T>::THREADS, 2) void gemm_oz8_kernel(OzParams p) {
   if (p.status != nullptr && *p.status != 0) return;
-  __shared__ __attribute__((aligned(1024))) int8_t lds[NBUF][OzLds<S>::STAGE];
+  __shared__ __attribute__((aligned(1024))) int8_t lds[NBUF][OzLds<S, T>::STAGE];
+  constexpr int BM = OzShape<T>::BM, BN = OzShape<T>::BN;
   const int wl = xcd_remap(blockIdx.x, gridDim.x);
   int tm, tn;
-  oz8_decode(p, wl, tm, tn);
-  const int64_t m0 = (int64_t)tm * 64, n0 = (int64_t)tn * 64;
-  if (oz8_tile_skipped(p, m0, n0)) return;
-  oz8_tile<S, NBUF>(p, m0, n0, lds);
+  oz8_decode(p, BM, BN, wl, tm, tn);
+  const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
+  if (oz8_tile_skipped(p, m0, n0, BN)) return;
+  oz8_tile<S, NBUF, T>(p, m0, n0, lds);
 }
 
 // Work queues of a persistent grouped launch: kQueues counters (all zero at
@@ -352,10 +382,10 @@ __device__ __forceinline__ long long queue_resolve(unsigned long long* counter, 
 // Persistent grouped launch over the split products of many fragments:
 // problem f owns work items [prefix[f], prefix[f+1]) = its tiles, problems
 // ordered largest first.  Each workgroup takes items from the queues
-// (queue_resolve) until all are taken.  window >= 0 runs
+// (queue_resolve) until all are taken.  The launch runs
 // reduction window `window` of every problem (k0 = window * wlen, the first
 // window stores and later ones add into C; problems with fewer windows skip
-// their items); window < 0 runs each problem's whole reduction.
+// their items).
 struct OzGroup {
   const OzParams* probs;
   const int64_t* prefix;   // [nprob + 1]
@@ -363,9 +393,10 @@ struct OzGroup {
   unsigned long long* counter;   // [kQueues]
 };
 
-template <int S, int NBUF>
-__global__ __launch_bounds__(256, 2) void gemm_oz8_grouped(OzGroup G, int64_t window, int64_t wlen) {
-  __shared__ __attribute__((aligned(1024))) int8_t lds[NBUF][OzLds<S>::STAGE];
+template <int S, int NBUF, class T>
+__global__ __launch_bounds__(OzShape<T>::THREADS, 2) void gemm_oz8_grouped(OzGroup G, int64_t window, int64_t wlen) {
+  __shared__ __attribute__((aligned(1024))) int8_t lds[NBUF][OzLds<S, T>::STAGE];
+  constexpr int BM = OzShape<T>::BM, BN = OzShape<T>::BN;
   // the item is passed on in the stage's own LDS: with two stages of 5 digits
   // (80 KB) a word more would leave one workgroup on a CU instead of two
   // (Gamma windows of two fragments of 72/360/1296: 6.2 -> 2.9 ms each)
@@ -377,7 +408,7 @@ __global__ __launch_bounds__(256, 2) void gemm_oz8_grouped(OzGroup G, int64_t wi
     if (threadIdx.x == 0)
       *item = queue_resolve(G.counter, total, left > 0 ? atomicAdd(G.counter + queue, 1ull) : 0, queue, left);
     __syncthreads();
-    const long long t = *item;
+    const long long t = __builtin_amdgcn_readfirstlane((int)*item);   // the problem stays in scalar registers
     __syncthreads();
     if (t < 0) break;
     int lo = 0, hi = G.nprob - 1;   // last f with prefix[f] <= t
@@ -387,18 +418,16 @@ __global__ __launch_bounds__(256, 2) void gemm_oz8_grouped(OzGroup G, int64_t wi
     }
     OzParams p = G.probs[lo];
     if (p.status != nullptr && *p.status != 0) continue;
-    if (window >= 0) {
-      p.k0 = window * wlen;
-      if (p.k0 >= p.kp && window > 0) continue;
-      p.kc = min(wlen, p.kp - p.k0);
-      p.accumulate = window > 0;
-    }
+    p.k0 = window * wlen;
+    if (p.k0 >= p.kp && window > 0) continue;
+    p.kc = min(wlen, p.kp - p.k0);
+    p.accumulate = window > 0;
     const int64_t u = t - G.prefix[lo];
     int tm, tn;
-    oz8_decode(p, (int)u, tm, tn);
-    const int64_t m0 = (int64_t)tm * 64, n0 = (int64_t)tn * 64;
-    if (oz8_tile_skipped(p, m0, n0)) continue;
-    oz8_tile<S, NBUF>(p, m0, n0, lds);
+    oz8_decode(p, BM, BN, (int)u, tm, tn);
+    const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
+    if (oz8_tile_skipped(p, m0, n0, BN)) continue;
+    oz8_tile<S, NBUF, T>(p, m0, n0, lds);
   }
 }
 
