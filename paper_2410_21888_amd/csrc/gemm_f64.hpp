@@ -629,45 +629,48 @@ __global__ __launch_bounds__(256, 2) void gemm_f64_kernel(GemmParams p) {
   gemm_tile<BM, BN, BK, B_NCONTIG, VEC, TRI, FAST, role_a_mcontig(ROLE)>(p, tm, tn, z, lds);
 }
 
-// Persistent grouped launch over many independent GEMMs (one per fragment):
-// problem f owns work items [prefix[f], prefix[f+1]) = its tiles x splits,
-// problems ordered largest first.  Each workgroup takes items from *counter
-// (which must be zero at launch) until all are taken; no workgroup waits on
-// another, so every one exits.
-struct GemmGroup {
-  const GemmParams* probs;
+// Grouped launch over many independent GEMMs (one per fragment): problem f owns
+// work items [prefix[f], prefix[f+1]) = its tiles x splits, problems ordered
+// largest first, one workgroup per item.  Workgroups are dispatched round-robin
+// over the 8 XCDs; blocks of `block` consecutive items go to one XCD in turn, so
+// that its workgroups share operand panels in its L2.  (Persistent workgroups
+// that took items from counters fetched an item across the fabric before each
+// tile, and their loop left the 128 x 128 tiles short of registers.)
+template <class P>
+struct Grouped {
+  const P* probs;
   const int64_t* prefix;   // [nprob + 1]
-  int32_t nprob;
-  unsigned long long* counter;
+  int32_t nprob, block;
 };
+// The workgroup's problem and item within it; false: past the last item.
+template <class P>
+__device__ __forceinline__ bool grouped_item(const Grouped<P>& G, int& f, int& u) {
+  const int n = blockIdx.x >> 3, q = n / G.block;
+  const int64_t t = ((int64_t)q * 8 + (blockIdx.x & 7)) * G.block + (n - q * G.block);
+  if (t >= G.prefix[G.nprob]) return false;
+  int lo = 0, hi = G.nprob - 1;   // last f with prefix[f] <= t
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (G.prefix[mid] <= t) lo = mid; else hi = mid - 1;
+  }
+  f = lo;
+  u = (int)(t - G.prefix[lo]);
+  return true;
+}
 
 template <int BM, int BN, int BK, bool B_NCONTIG, int ROLE, bool VEC, bool TRI, int FAST = 0>
-__global__ __launch_bounds__(256, 2) void gemm_f64_grouped(GemmGroup G) {
+__global__ __launch_bounds__(256, 2) void gemm_f64_grouped(Grouped<GemmParams> G) {
   __shared__ GemmLds<BM, BN, BK> lds;
-  __shared__ long long item;
-  const long long total = G.prefix[G.nprob];
-  for (;;) {
-    if (threadIdx.x == 0) item = (long long)atomicAdd(G.counter, 1ull);
-    __syncthreads();
-    // the same in every lane: readfirstlane keeps the problem in scalar registers
-    const long long t = __builtin_amdgcn_readfirstlane((int)item);
-    __syncthreads();
-    if (t >= total) break;
-    int lo = 0, hi = G.nprob - 1;   // last f with prefix[f] <= t
-    while (lo < hi) {
-      const int mid = (lo + hi + 1) >> 1;
-      if (G.prefix[mid] <= t) lo = mid; else hi = mid - 1;
-    }
-    const GemmParams p = G.probs[lo];
-    if (p.status != nullptr && *p.status != 0) continue;
-    const int u = (int)(t - G.prefix[lo]);
-    const int ntiles = TRI ? p.tiles_m * (p.tiles_m + 1) / 2 : p.tiles_m * p.tiles_n;
-    const int z = u / ntiles;
-    int tm, tn;
-    decode_tile<BM, BN, TRI>(p, u - z * ntiles, tm, tn);
-    if (tile_screened<BM, BN>(p, tm, tn)) continue;
-    gemm_tile<BM, BN, BK, B_NCONTIG, VEC, TRI, FAST>(p, tm, tn, z, lds);
-  }
+  int f, u;
+  if (!grouped_item(G, f, u)) return;
+  const GemmParams p = G.probs[f];
+  if (p.status != nullptr && *p.status != 0) return;
+  const int ntiles = TRI ? p.tiles_m * (p.tiles_m + 1) / 2 : p.tiles_m * p.tiles_n;
+  const int z = u / ntiles;
+  int tm, tn;
+  decode_tile<BM, BN, TRI>(p, u - z * ntiles, tm, tn);
+  if (tile_screened<BM, BN>(p, tm, tn)) return;
+  gemm_tile<BM, BN, BK, B_NCONTIG, VEC, TRI, FAST>(p, tm, tn, z, lds);
 }
 
 }  // namespace rimp2

@@ -111,7 +111,6 @@ int traced(int role, double af, double ef, double ab, hipStream_t st, F&& launch
 
 constexpr size_t kAlign = 256;
 constexpr int kBK = 16;
-constexpr int64_t kSlots = 512;       // resident workgroups of a persistent launch: 2 per CU on 256 CUs
 
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
@@ -190,20 +189,24 @@ GemmChoice choose_gemm(int64_t M, int64_t N, int64_t K, bool tri, const int* bms
   }
   return best;
 }
-// Grouped (batch) roles (ia|jb), Gamma, P_ab, P_ij: candidate square tiles, the
-// default first.
-constexpr int kBatchTile[4][2] = {{128, 64}, {128, 64}, {128, 64}, {64, 32}};
+// Tile shapes instantiated for each product.
+constexpr int kIntsTiles[] = {128, 64, 0}, kGammaTiles[] = {128, 64, 0}, kPabTiles[] = {128, 96, 64, 0},
+              kPijTiles[] = {128, 96, 64, 32, 0}, kLtermTiles[] = {128, 64, 0}, kAoTiles[] = {128, 64, 0};
+
 // Split-K factor of a grouped P_ab or P_ij product of K reduction indices: a
 // wave's fragments fill the chip together, so the splits only keep its items
 // short (klen).  With 64 splits whatever the length, the P_ij items of nocc =
 // 60, nvir = 300 were 84000 long, and the launch waited for them.
 constexpr int64_t kGroupedPab = 4096, kGroupedPij = 2048;
-GemmChoice grouped_choice(int bm, int64_t K, int64_t klen) {
-  return GemmChoice{bm, std::max<int64_t>(1, std::min<int64_t>(kMaxSplits, cdiv(K, klen)))};
+int64_t grouped_splits(int64_t K, int64_t klen) { return std::max<int64_t>(1, std::min<int64_t>(kMaxSplits, cdiv(K, klen))); }
+// Estimate of a grouped product's `tiles` of side bm, on a chip that the wave's
+// other products keep full: P_ij of nocc = 30 costs a third with tiles of 32
+// what it costs with 64, P_ab of nvir = 300 two thirds with 64 of 128.
+double grouped_cost(int bm, int64_t tiles) {
+  const TileCost* c = kTileCost;
+  while (c->bm != bm) ++c;
+  return tiles * (c->a + c->b * c->resident) / c->resident;
 }
-// Tile shapes instantiated for each product.
-constexpr int kIntsTiles[] = {128, 64, 0}, kGammaTiles[] = {128, 64, 0}, kPabTiles[] = {128, 96, 64, 0},
-              kPijTiles[] = {128, 64, 32, 0}, kLtermTiles[] = {128, 64, 0}, kAoTiles[] = {128, 64, 0};
 
 struct Plan {
   int64_t nocc, nvir, naux;
@@ -303,8 +306,8 @@ int make_plan(int64_t nocc, int64_t nvir, int64_t naux, bool gamma, bool density
   p->max_splits = max_splits;
   p->c_ab = p->c_ij = p->c_gam = GemmChoice{0, 0};
   if (density && grouped) {
-    p->c_ab = grouped_choice(kBatchTile[2][0], nocc * nocc * nvir, kGroupedPab);
-    p->c_ij = grouped_choice(kBatchTile[3][0], nocc * nvir * nvir, kGroupedPij);
+    p->c_ab.splits = grouped_splits(nocc * nocc * nvir, kGroupedPab);   // (the wave's lists choose the tiles)
+    p->c_ij.splits = grouped_splits(nocc * nvir * nvir, kGroupedPij);
   } else if (density) {
     p->c_ab = choose_gemm(nvir, nvir, g * nocc * nvir, true, kPabTiles, max_splits);
     p->c_ij = choose_gemm(nocc, nocc, g * nvir * nvir, true, kPijTiles, max_splits);
@@ -548,6 +551,7 @@ int launch_role(int role, int bm, const GemmParams& gp, hipStream_t st, double a
                         : launch_gemm<128, 128, false, ROLE_PAB, true>(gp, st, role, af, ab, general);
     case R_PIJ:
       return bm == 32    ? launch_gemm<32, 32, false, ROLE_PIJ, true>(gp, st, role, af, ab, general)
+             : bm == 96  ? launch_gemm<96, 96, false, ROLE_PIJ, true>(gp, st, role, af, ab, general)
              : bm == 128 ? launch_gemm<128, 128, false, ROLE_PIJ, true>(gp, st, role, af, ab, general)
                          : launch_gemm<64, 64, false, ROLE_PIJ, true>(gp, st, role, af, ab, general);
     default:
@@ -1167,13 +1171,20 @@ struct DigitOp {
 };
 
 // ---- batches -----------------------------------------------------------------
-// Grouped GEMM lists of a wave: 4 roles x 2 candidate tiles x 5 loaders
-// (0, 1, 2: the fast loader's levels 1, 2, 3; 3: the general loader with
-// 16-byte loads, 4: the general loader, 8-byte loads).
-constexpr int kGLoaders = 5, kGLists = 8 * kGLoaders;
-struct GemmList {            // grouped GEMM problems of one role in one wave
-  std::vector<GemmParams> p;
-  std::vector<int64_t> prefix;  // work items (tiles x splits)
+// Grouped GEMMs of a wave: every role has two candidate tile choices, each a
+// table of all its problems, sorted into lists of one tile side and loader (0, 1,
+// 2: the fast loader's levels 1, 2, 3; 3: the general loader with 16-byte loads,
+// 4: the general loader, 8-byte loads), largest problem first.
+constexpr int kGLoaders = 5, kGKeys = 4 * kGLoaders;
+struct GemmList {
+  int bm, loader, first, n;   // entries [first, first + n) of the table
+  int64_t items;              // work items (tiles x splits)
+  size_t pre;                 // offset of its prefix array within the table's prefixes
+};
+struct GemmEntry {
+  int bm, loader;
+  GemmParams p;
+  int64_t items;
 };
 struct Wave {
   std::vector<int32_t> frags;   // original fragment indices, largest first
@@ -1181,19 +1192,17 @@ struct Wave {
   size_t host_off = 0;          // offset of this wave's tables in the pinned blob
   size_t bytes = 0;             // tables + fragment partitions
   // offsets within the tables
-  size_t o_fs, o_idx, o_amp, o_amp_pre[2], o_red, o_red_pre, o_cnt;   // o_amp_pre: tiles of 32, of 64 (amp_tile)
-  // GEMM lists, index glist(role, candidate tile, loader): every GEMM is
-  // listed once per candidate tile shape (kBatchTile)
-  size_t o_g[kGLists], o_pre[kGLists];
-  int n_g[kGLists];
-  int64_t items_g[kGLists];
+  size_t o_fs, o_idx, o_amp, o_amp_pre[2], o_red, o_red_pre;   // o_amp_pre: tiles of 32, of 64 (amp_tile)
+  size_t o_g[4][2], o_pre[4][2];   // tables and prefixes by role and candidate
+  std::vector<GemmList> lists[4][2];
+  int n_g[4] = {0, 0, 0, 0};       // problems of each role
+  int tile_g[4][2] = {};           // tile side of the largest problem (autotuner report)
   uint64_t sig = 0;             // hash of the wave's fragment sizes (autotuner key)
   int namp, nred_ab, nred_ij;
   int64_t amp_blocks[2], red_blocks_ab, red_blocks_ij;
   // split products (precision RIMP2_SPLIT_INT8): grouped (ia|jb) and Gamma
-  // product lists, run in reduction windows (win_* launches each), with one
-  // work counter per launch
-  size_t o_oz[2] = {0, 0}, o_oz_pre[2] = {0, 0}, o_cnt_oz = 0;
+  // product lists, run in reduction windows (win_* launches each)
+  size_t o_oz[2] = {0, 0}, o_oz_pre[2] = {0, 0};
   int n_oz[2] = {0, 0};
   int64_t items_oz[2] = {0, 0};
   int win_oz[2] = {0, 0};
@@ -1231,10 +1240,11 @@ bool kop_vec_rel(const KOperand& o, int64_t K) {
   return aligned16(o.base) && o.rs % 2 == 0 && (plain || (o.kdiv % 2 == 0 && o.ks1 % 2 == 0));
 }
 
-// Grouped GEMM roles of a wave (candidate tiles: kBatchTile) and list index.
+// Grouped GEMM roles of a wave and their tiles (those launch_group_list has).
 const int kBatchRole[4] = {R_INTS, R_GAMMA, R_PAB, R_PIJ};
-int glist(int rho, int cand, int loader) { return (rho * 2 + cand) * kGLoaders + loader; }
-// loader of a grouped GEMM (see kGLists); vec: 16-byte loads are aligned;
+constexpr int kBatchPijTiles[] = {96, 64, 32, 0};
+const int* const kBatchTiles[4] = {kIntsTiles, kGammaTiles, kPabTiles, kBatchPijTiles};
+// loader of a grouped GEMM (see GemmList); vec: 16-byte loads are aligned;
 // general: the general loader only
 int loader_of(const GemmParams& g, int bm, bool nc, bool vec, bool general) {
   const int f = general ? 0 : fast_level(g, bm, nc);
@@ -1325,11 +1335,11 @@ int batch_plan(int32_t nfrag, const rimp2_frag_desc* d, const rimp2_opts* opts, 
     for (size_t& o : W.o_amp_pre) o = place(t, sizeof(int64_t) * (n + 1));
     W.o_red = place(t, sizeof(ReduceDesc) * 2 * n);
     W.o_red_pre = place(t, sizeof(int64_t) * (2 * n + 1));
-    for (int r = 0; r < kGLists; ++r) {
-      W.o_g[r] = place(t, sizeof(GemmParams) * n);
-      W.o_pre[r] = place(t, sizeof(int64_t) * (n + 1));
-    }
-    W.o_cnt = place(t, kGLists * sizeof(unsigned long long));
+    for (int r = 0; r < 4; ++r)
+      for (int c = 0; c < 2; ++c) {
+        W.o_g[r][c] = place(t, sizeof(GemmParams) * n);
+        W.o_pre[r][c] = place(t, sizeof(int64_t) * (n + kGKeys));
+      }
     if (split) {
       for (int r = 0; r < 2; ++r) {
         W.o_oz[r] = place(t, sizeof(OzParams) * n);
@@ -1350,7 +1360,6 @@ int batch_plan(int32_t nfrag, const rimp2_frag_desc* d, const rimp2_opts* opts, 
           t128 += (double)cdiv(P.nocc * P.nvir, 128) * cdiv(P.naux, 128);
         }
       W.side_oz[1] = oz8_side(B->plan[W.frags[0]].sg, t64, t128);
-      W.o_cnt_oz = place(t, sizeof(unsigned long long) * kQueues * (W.win_oz[0] + W.win_oz[1]));
       for (int r = 0; r < Wave::kDigitLists; ++r) {
         W.o_dop[r] = place(t, sizeof(DigitOp) * n);
         for (int m = 0; m < 4; ++m) W.o_dpre[r][m] = place(t, sizeof(int64_t) * (n + 1));
@@ -1370,8 +1379,7 @@ int batch_plan(int32_t nfrag, const rimp2_frag_desc* d, const rimp2_opts* opts, 
     std::vector<int64_t> amp_pre[2] = {std::vector<int64_t>(n + 1, 0), std::vector<int64_t>(n + 1, 0)};
     std::vector<ReduceDesc> red;
     std::vector<int64_t> red_pre(1, 0);
-    GemmList gl[kGLists];
-    for (auto& l : gl) l.prefix.assign(1, 0);
+    std::vector<GemmEntry> ge[4][2];
     std::vector<OzParams> oz[2];
     std::vector<int64_t> oz_pre[2] = {{0}, {0}};
     std::vector<DigitOp> dop[Wave::kDigitLists];
@@ -1384,14 +1392,27 @@ int batch_plan(int32_t nfrag, const rimp2_frag_desc* d, const rimp2_opts* opts, 
       const int64_t w[4] = {rows_wgs, zero_wgs, max_wgs, dig_wgs};
       for (int m = 0; m < 4; ++m) dpre[r][m].push_back(dpre[r][m].back() + w[m]);
     };
-    // every GEMM goes to the lists of both candidate tiles of its role
+    // a GEMM goes to both candidates' tables of its role: with the tile of the
+    // smallest grouped_cost, and with the next best
     auto add = [&](int rho, const GemmParams& g0, bool vec) {
-      for (int c = 0; c < 2; ++c) {
+      int best[2] = {0, 0};
+      double cost[2] = {0.0, 0.0};
+      for (const int* t = kBatchTiles[rho]; *t; ++t) {
         GemmParams g = g0;
-        const int64_t items = finalize_gemm(g, kBatchTile[rho][c], kBatchTile[rho][c], rho >= 2);
-        GemmList& l = gl[glist(rho, c, loader_of(g, kBatchTile[rho][c], rho == 1, vec, general))];
-        l.p.push_back(g);
-        l.prefix.push_back(l.prefix.back() + items);
+        const double c = grouped_cost(*t, finalize_gemm(g, *t, *t, rho >= 2) / g.splits);
+        if (best[0] == 0 || c < kSmallerTile * cost[0]) {
+          best[1] = best[0]; cost[1] = cost[0];
+          best[0] = *t; cost[0] = c;
+        } else if (best[1] == 0 || c < cost[1]) {
+          best[1] = *t; cost[1] = c;
+        }
+      }
+      for (int c = 0; c < 2; ++c) {
+        GemmEntry e{best[c], 0, g0, 0};
+        e.items = finalize_gemm(e.p, e.bm, e.bm, rho >= 2);
+        e.loader = loader_of(e.p, e.bm, rho == 1, vec, general);
+        if (ge[rho][c].empty()) W.tile_g[rho][c] = e.bm;
+        ge[rho][c].push_back(e);
       }
     };
     uint64_t sig = 1469598103934665603ull;  // FNV-1a over the fragment sizes and outputs
@@ -1479,14 +1500,14 @@ int batch_plan(int32_t nfrag, const rimp2_frag_desc* d, const rimp2_opts* opts, 
         ga.Bk = KOperand{V, L, L, nvir * L};
         ga.C = Wab; ga.ldc = nvir; ga.split_stride = nvir * nvir; ga.status = status;
         add(2, ga, kop_vec_rel(ga.A, ga.K) && kop_vec_rel(ga.Bk, ga.K));
-        (void)finalize_gemm(ga, kBatchTile[2][0], kBatchTile[2][0], true);   // splits for the reduction
+        (void)finalize_gemm(ga, 64, 64, true);   // splits for the reduction
         GemmParams gi{};
         gi.M = nocc; gi.N = nocc; gi.K = nocc * nvir * nvir; gi.kchunk = cdiv(gi.K, P.c_ij.splits);
         gi.A = KOperand{T, nvir, nvir, L};
         gi.Bk = KOperand{V, nvir, nvir, L};
         gi.C = Wij; gi.ldc = nocc; gi.split_stride = nocc * nocc; gi.status = status;
         add(3, gi, kop_vec_rel(gi.A, gi.K) && kop_vec_rel(gi.Bk, gi.K));
-        (void)finalize_gemm(gi, kBatchTile[3][0], kBatchTile[3][0], true);
+        (void)finalize_gemm(gi, 64, 64, true);
         ReduceDesc ra{q.P_ab, Wab, status, nvir, nvir, nvir * nvir, nvir, nvir, 1.0, ga.splits, 0};
         ReduceDesc ri{q.P_ij, Wij, status, nocc, nocc, nocc * nocc, nocc, nocc, -1.0, gi.splits, 0};
         red.push_back(ra); red_pre.push_back(red_pre.back() + reduce_blocks(nvir * nvir, ga.splits));
@@ -1499,7 +1520,6 @@ int batch_plan(int32_t nfrag, const rimp2_frag_desc* d, const rimp2_opts* opts, 
     for (int b = 0; b < 2; ++b) W.amp_blocks[b] = amp_pre[b][n];
     W.nred_ab = (int)red.size();
     W.red_blocks_ab = red_pre.back();
-    for (int r = 0; r < kGLists; ++r) { W.n_g[r] = (int)gl[r].p.size(); W.items_g[r] = gl[r].prefix.back(); }
     W.sig = sig;
     char* blob = B->blob.data() + W.host_off;
     auto put = [&](size_t off, const void* src, size_t bytes) { if (bytes) memcpy(blob + off, src, bytes); };
@@ -1509,10 +1529,26 @@ int batch_plan(int32_t nfrag, const rimp2_frag_desc* d, const rimp2_opts* opts, 
     for (int b = 0; b < 2; ++b) put(W.o_amp_pre[b], amp_pre[b].data(), sizeof(int64_t) * (n + 1));
     put(W.o_red, red.data(), sizeof(ReduceDesc) * red.size());
     put(W.o_red_pre, red_pre.data(), sizeof(int64_t) * red_pre.size());
-    for (int r = 0; r < kGLists; ++r) {
-      put(W.o_g[r], gl[r].p.data(), sizeof(GemmParams) * gl[r].p.size());
-      put(W.o_pre[r], gl[r].prefix.data(), sizeof(int64_t) * gl[r].prefix.size());
-    }
+    for (int r = 0; r < 4; ++r)
+      for (int c = 0; c < 2; ++c) {
+        std::vector<GemmEntry>& e = ge[r][c];
+        std::stable_sort(e.begin(), e.end(), [](const GemmEntry& x, const GemmEntry& y) {
+          return x.bm != y.bm ? x.bm > y.bm : x.loader < y.loader;
+        });
+        W.n_g[r] = (int)e.size();
+        size_t pre = W.o_pre[r][c];
+        for (size_t i = 0; i < e.size();) {
+          GemmList l{e[i].bm, e[i].loader, (int)i, 0, 0, pre};
+          std::vector<int64_t> prefix(1, 0);
+          for (; i < e.size() && e[i].bm == l.bm && e[i].loader == l.loader; ++i, ++l.n) {
+            put(W.o_g[r][c] + sizeof(GemmParams) * i, &e[i].p, sizeof(GemmParams));
+            prefix.push_back(l.items += e[i].items);
+          }
+          put(pre, prefix.data(), sizeof(int64_t) * prefix.size());
+          pre += sizeof(int64_t) * prefix.size();
+          W.lists[r][c].push_back(l);
+        }
+      }
     if (split) {
       for (int r = 0; r < 2; ++r) {
         W.n_oz[r] = (int)oz[r].size();
@@ -1535,19 +1571,31 @@ int batch_plan(int32_t nfrag, const rimp2_frag_desc* d, const rimp2_opts* opts, 
   return RIMP2_OK;
 }
 
+// Items of a grouped launch that go to one XCD in turn, at most `most`: 64 (an 8
+// x 8 block of tiles) for the products that wait for their operands (split, P_ab
+// and P_ij); 8 for FP64 (ia|jb) and Gamma, which are MFMA-bound and whose tiles
+// are long (up to milliseconds), so that the XCDs finish together (24 monomers'
+// Gamma: 35.4 ms with 64, 34.2 with 8).
+constexpr int kLongBlock = 8, kOperandBlock = 64;
+int grouped_block(int64_t items, int most) { return (int)std::max<int64_t>(1, std::min<int64_t>(most, items / 64)); }
+int64_t grouped_grid(int64_t items, int most) {
+  const int64_t per = 8 * grouped_block(items, most);
+  return cdiv(items, per) * per;
+}
+
 template <int BM, int BN, bool NC, int ROLE, bool VEC, bool TRI, int FAST>
-int launch_grouped(const GemmGroup& G, int64_t items, int role, hipStream_t st) {
-  if (G.nprob == 0 || items == 0) return RIMP2_OK;
-  const int64_t grid = std::min<int64_t>(items, kSlots);
+int launch_grouped(const Grouped<GemmParams>& G, int64_t items, int role, hipStream_t st) {
+  const int64_t grid = grouped_grid(items, role == R_INTS || role == R_GAMMA ? kLongBlock : kOperandBlock);
+  if (int rc = check_grid(grid, "grouped GEMM")) return rc;
   return traced(role, 0, 0, 0, st, [&] {
     hipLaunchKernelGGL((gemm_f64_grouped<BM, BN, kBK, NC, ROLE, VEC, TRI, FAST>), dim3((unsigned)grid), dim3(256), 0,
                        st, G);
   });
 }
 
-// One grouped launch of batch role rho with candidate tile c (kBatchTile) over
-// its list of one loader (see kGLists).
-int launch_group_list(int rho, int c, int loader, const GemmGroup& G, int64_t items, hipStream_t st) {
+// One grouped launch of batch role rho over a list of one tile side and loader
+// (see GemmList).
+int launch_group_list(int rho, int bm, int loader, const Grouped<GemmParams>& G, int64_t items, hipStream_t st) {
   const int role = kBatchRole[rho];
 #define RIMP2_G(BM, NC, ROLE, TRI, F2, F3)                                                            \
   switch (loader) {                                                                                   \
@@ -1557,16 +1605,19 @@ int launch_group_list(int rho, int c, int loader, const GemmGroup& G, int64_t it
     case 3: return launch_grouped<BM, BM, NC, ROLE, true, TRI, 0>(G, items, role, st);                \
     default: return launch_grouped<BM, BM, NC, ROLE, false, TRI, 0>(G, items, role, st);              \
   }
-  switch (rho * 2 + c) {
-    // (ia|jb) and Gamma have no runs: their lists hold loader 0 or a general one
-    case 0: RIMP2_G(128, false, ROLE_INTS, false, 1, 1);
-    case 1: RIMP2_G(64, false, ROLE_INTS, false, 1, 1);
-    case 2: RIMP2_G(128, true, ROLE_GAMMA, false, 1, 1);
-    case 3: RIMP2_G(64, true, ROLE_GAMMA, false, 1, 1);
-    case 4: RIMP2_G(128, false, ROLE_PAB, true, 2, 3);
-    case 5: RIMP2_G(64, false, ROLE_PAB, true, 2, 3);
-    case 6: RIMP2_G(64, false, ROLE_PIJ, true, 2, 3);
-    default: RIMP2_G(32, false, ROLE_PIJ, true, 2, 3);
+  // (ia|jb) and Gamma have no runs: their lists hold loader 0 or a general one
+  switch (rho * 1000 + bm) {
+    case 128: RIMP2_G(128, false, ROLE_INTS, false, 1, 1);
+    case 64: RIMP2_G(64, false, ROLE_INTS, false, 1, 1);
+    case 1128: RIMP2_G(128, true, ROLE_GAMMA, false, 1, 1);
+    case 1064: RIMP2_G(64, true, ROLE_GAMMA, false, 1, 1);
+    case 2128: RIMP2_G(128, false, ROLE_PAB, true, 2, 3);
+    case 2096: RIMP2_G(96, false, ROLE_PAB, true, 2, 3);
+    case 2064: RIMP2_G(64, false, ROLE_PAB, true, 2, 3);
+    case 3096: RIMP2_G(96, false, ROLE_PIJ, true, 2, 3);
+    case 3064: RIMP2_G(64, false, ROLE_PIJ, true, 2, 3);
+    case 3032: RIMP2_G(32, false, ROLE_PIJ, true, 2, 3);
+    default: return fail(RIMP2_EINVAL, "no grouped GEMM for role %d with tiles of %d", role, bm);
   }
 #undef RIMP2_G
 }
@@ -1621,9 +1672,10 @@ __global__ void relocate_oz_kernel(char* base, OzParams* z, int n) {
 // One grouped split-product launch over reduction window `window` of every
 // problem in G (the shapes and buffering of launch_oz8 for a windowed product).
 template <int S>
-int launch_oz8_grouped(const OzGroup& G, int64_t items, int side, int64_t window, int role, hipStream_t st) {
+int launch_oz8_grouped(const Grouped<OzParams>& G, int64_t items, int side, int64_t window, int role, hipStream_t st) {
   if (G.nprob == 0 || items == 0) return RIMP2_OK;
-  const int64_t grid = std::min<int64_t>(items, side == 128 ? kSlots / 2 : kSlots);
+  const int64_t grid = grouped_grid(items, kOperandBlock);
+  if (int rc = check_grid(grid * (side / 64), "grouped split product")) return rc;
   return traced(role, 0, 0, 0, st, [&] {
     if (S <= 5 && side == 128)
       hipLaunchKernelGGL((gemm_oz8_grouped<S <= 5 ? S : 5, 2, OzWide>), dim3((unsigned)grid), dim3(512), 0, st, G, window,
@@ -1660,21 +1712,19 @@ int batch_run(rimp2_batch_s* B, int32_t* status_dev, void* workspace, size_t byt
   }
   for (const Wave& W : B->waves) {
     const int n = (int)W.frags.size();
-    GemmParams* gp0 = (GemmParams*)(ws + W.host_off + W.o_g[0]);
     auto at = [&](size_t o) { return ws + W.host_off + o; };
     if ((rc = traced(R_STATUS, 0, 0, 0, st, [&] {
-           // relocate every table (GEMM lists are contiguous per role; relocate each list)
-           for (int r = 0; r < kGLists; ++r)
-             if (W.n_g[r])
-               hipLaunchKernelGGL(relocate_tables_kernel, dim3((unsigned)cdiv(W.n_g[r], 256)), dim3(256), 0, st, ws,
-                                  (GemmParams*)at(W.o_g[r]), W.n_g[r], (AmpDesc*)nullptr, 0, (ReduceDesc*)nullptr, 0,
-                                  (FragSmall*)nullptr, 0);
+           // relocate every table
+           for (int r = 0; r < 4; ++r)
+             for (int c = 0; c < (B->autotune ? 2 : 1); ++c)
+               if (W.n_g[r])
+                 hipLaunchKernelGGL(relocate_tables_kernel, dim3((unsigned)cdiv(W.n_g[r], 256)), dim3(256), 0, st, ws,
+                                    (GemmParams*)at(W.o_g[r][c]), W.n_g[r], (AmpDesc*)nullptr, 0, (ReduceDesc*)nullptr,
+                                    0, (FragSmall*)nullptr, 0);
            const int m = std::max(n, W.nred_ab);
-           hipLaunchKernelGGL(relocate_tables_kernel, dim3((unsigned)cdiv(m, 256)), dim3(256), 0, st, ws, gp0, 0,
-                              (AmpDesc*)at(W.o_amp), n, (ReduceDesc*)at(W.o_red), W.nred_ab, (FragSmall*)at(W.o_fs),
-                              n);
-           hipLaunchKernelGGL(zero_u64_kernel, dim3(1), dim3(256), 0, st, (unsigned long long*)at(W.o_cnt),
-                              (int64_t)kGLists);
+           hipLaunchKernelGGL(relocate_tables_kernel, dim3((unsigned)cdiv(m, 256)), dim3(256), 0, st, ws,
+                              (GemmParams*)nullptr, 0, (AmpDesc*)at(W.o_amp), n, (ReduceDesc*)at(W.o_red), W.nred_ab,
+                              (FragSmall*)at(W.o_fs), n);
            hipLaunchKernelGGL(gap_check_grouped, dim3((unsigned)n), dim3(256), 0, st, (const FragSmall*)at(W.o_fs));
            if (B->split) {
              for (int r = 0; r < 2; ++r)
@@ -1685,41 +1735,29 @@ int batch_run(rimp2_batch_s* B, int32_t* status_dev, void* workspace, size_t byt
                if (W.n_dop[r])
                  hipLaunchKernelGGL(relocate_digit_kernel, dim3((unsigned)cdiv(W.n_dop[r], 256)), dim3(256), 0, st,
                                     ws, (DigitOp*)at(W.o_dop[r]), W.n_dop[r]);
-             const int nc = kQueues * (W.win_oz[0] + W.win_oz[1]);
-             if (nc)
-               hipLaunchKernelGGL(zero_u64_kernel, dim3((unsigned)cdiv(nc, 256)), dim3(256), 0, st,
-                                  (unsigned long long*)at(W.o_cnt_oz), (int64_t)nc);
            }
          })))
       return rc;
-    auto grp = [&](int r) {
-      return GemmGroup{(const GemmParams*)at(W.o_g[r]), (const int64_t*)at(W.o_pre[r]), W.n_g[r],
-                       (unsigned long long*)at(W.o_cnt) + r};
-    };
-    // each GEMM role: the lists of one candidate tile (with autotuning the
-    // tuned one for this wave's fragment sizes)
+    // each GEMM role: the lists of one candidate (with autotuning the tuned one
+    // for this wave's fragment sizes)
     auto run_role = [&](int rho) -> int {
-      auto items_of = [&](int c) {
-        int64_t n = 0;
-        for (int k = 0; k < kGLoaders; ++k) n += W.items_g[glist(rho, c, k)];
-        return n;
-      };
-      const int64_t i0 = items_of(0);
-      if (i0 == 0) return RIMP2_OK;
+      if (W.n_g[rho] == 0) return RIMP2_OK;
       auto launch = [&](int c) -> int {
-        for (int k = 0; k < kGLoaders; ++k) {
-          const int li = glist(rho, c, k);
-          const int r = launch_group_list(rho, c, k, grp(li), W.items_g[li], st);
-          if (r) return r;
+        for (const GemmList& l : W.lists[rho][c]) {
+          const Grouped<GemmParams> G{(const GemmParams*)at(W.o_g[rho][c]) + l.first, (const int64_t*)at(l.pre), l.n,
+                                      grouped_block(l.items, rho < 2 ? kLongBlock : kOperandBlock)};
+          if (int r = launch_group_list(rho, l.bm, l.loader, G, l.items, st)) return r;
         }
         return RIMP2_OK;
       };
       if (!B->autotune) return launch(0);
       int dev = 0;
       HIP_TRY(hipGetDevice(&dev));
-      const int64_t i1 = items_of(1);
-      const TuneKey key{dev, kBatchRole[rho], 2, n, i0, i1, (int64_t)(W.sig >> 1)};
-      const TileShape cand[2] = {{kBatchTile[rho][0], kBatchTile[rho][0]}, {kBatchTile[rho][1], kBatchTile[rho][1]}};
+      int64_t items[2] = {0, 0};
+      for (int c = 0; c < 2; ++c)
+        for (const GemmList& l : W.lists[rho][c]) items[c] += l.items;
+      const TuneKey key{dev, kBatchRole[rho], 2, n, items[0], items[1], (int64_t)(W.sig >> 1)};
+      const TileShape cand[2] = {{W.tile_g[rho][0], W.tile_g[rho][0]}, {W.tile_g[rho][1], W.tile_g[rho][1]}};
       return tuned(key, 2, cand, st, launch);
     };
     // split products: the per-fragment digit splits, then one grouped launch
@@ -1755,9 +1793,9 @@ int batch_run(rimp2_batch_s* B, int32_t* status_dev, void* workspace, size_t byt
       }
       if (W.n_oz[r] == 0) return RIMP2_OK;
       const int S = r == 0 ? B->plan[W.frags[0]].sv : B->plan[W.frags[0]].sg;
-      unsigned long long* cnt = (unsigned long long*)at(W.o_cnt_oz) + (r == 0 ? 0 : W.win_oz[0] * kQueues);
       for (int w = 0; w < W.win_oz[r]; ++w) {
-        const OzGroup G{(const OzParams*)at(W.o_oz[r]), (const int64_t*)at(W.o_oz_pre[r]), W.n_oz[r], cnt + w * kQueues};
+        const Grouped<OzParams> G{(const OzParams*)at(W.o_oz[r]), (const int64_t*)at(W.o_oz_pre[r]), W.n_oz[r],
+                                  grouped_block(W.items_oz[r], kOperandBlock)};
         const int role = r == 0 ? R_INTS8 : R_GAMMA8;
         RIMP2_SWITCH_S(S, rc2 = launch_oz8_grouped<SS>(G, W.items_oz[r], W.side_oz[r], w, role, st));
         if (rc2) return rc2;

@@ -351,84 +351,28 @@ __global__ __launch_bounds__(OzShape<T>::THREADS, 2) void gemm_oz8_kernel(OzPara
   oz8_tile<S, NBUF, T>(p, m0, n0, lds);
 }
 
-// Work queues of a persistent grouped launch: kQueues counters (all zero at
-// launch), one per XCD (workgroups are dispatched round-robin over them).
-// Queue q owns the blocks q, q + 8, q + 16, ... of kQueueBlock consecutive
-// items, so the 64 workgroups an XCD holds work on neighbouring tiles and share
-// their operand panels in its L2, as the one-tile launches do (xcd_remap); a
-// workgroup whose queue is used up goes on to the next one, and ends after the
-// last.  A queue's items grow with its counter, so once one is past the end
-// all later ones are.  No workgroup waits on another.  From one counter each
-// XCD saw every eighth tile: the grouped split Gamma products of eight
-// fragments (nocc 5 to 72) took 72 ms, and 60 ms with queues and rasters.
-// (The FP64 grouped products are MFMA-bound and keep one counter: queues left
-// the large ones as they were, and the P_ij splits, few items, lost 30%.)
-constexpr int kQueues = 8, kQueueBlock = 64;
-__device__ __forceinline__ long long queue_item(unsigned long long n, int q) {
-  return (long long)((n / kQueueBlock * kQueues + q) * kQueueBlock + n % kQueueBlock);
-}
-// Item of count n taken from queue q, or of the following queues (-1: none is
-// left); `left` counts the queues not yet seen to be used up.
-__device__ __forceinline__ long long queue_resolve(unsigned long long* counter, long long total, unsigned long long n,
-                                                   int& q, int& left) {
-  long long t = queue_item(n, q);
-  while (t >= total && --left > 0) {
-    q = (q + 1) % kQueues;
-    t = queue_item(atomicAdd(counter + q, 1ull), q);
-  }
-  return t < total ? t : -1;
-}
-
-// Persistent grouped launch over the split products of many fragments:
-// problem f owns work items [prefix[f], prefix[f+1]) = its tiles, problems
-// ordered largest first.  Each workgroup takes items from the queues
-// (queue_resolve) until all are taken.  The launch runs
-// reduction window `window` of every problem (k0 = window * wlen, the first
-// window stores and later ones add into C; problems with fewer windows skip
-// their items).
-struct OzGroup {
-  const OzParams* probs;
-  const int64_t* prefix;   // [nprob + 1]
-  int32_t nprob;
-  unsigned long long* counter;   // [kQueues]
-};
-
+// Grouped launch over the split products of many fragments (see Grouped): it
+// runs reduction window `window` of every problem (k0 = window * wlen, the first
+// window stores and later ones add into C; the items of problems with fewer
+// windows end at once).
 template <int S, int NBUF, class T>
-__global__ __launch_bounds__(OzShape<T>::THREADS, 2) void gemm_oz8_grouped(OzGroup G, int64_t window, int64_t wlen) {
+__global__ __launch_bounds__(OzShape<T>::THREADS, 2) void gemm_oz8_grouped(Grouped<OzParams> G, int64_t window,
+                                                                         int64_t wlen) {
   __shared__ __attribute__((aligned(1024))) int8_t lds[NBUF][OzLds<S, T>::STAGE];
   constexpr int BM = OzShape<T>::BM, BN = OzShape<T>::BN;
-  // the item is passed on in the stage's own LDS: with two stages of 5 digits
-  // (80 KB) a word more would leave one workgroup on a CU instead of two
-  // (Gamma windows of two fragments of 72/360/1296: 6.2 -> 2.9 ms each)
-  long long* item = (long long*)&lds[0][0];
-  const long long total = G.prefix[G.nprob];
-  int queue = blockIdx.x % kQueues, left = kQueues;
-  for (;;) {
-    __syncthreads();   // every wave is done with the last tile's stage
-    if (threadIdx.x == 0)
-      *item = queue_resolve(G.counter, total, left > 0 ? atomicAdd(G.counter + queue, 1ull) : 0, queue, left);
-    __syncthreads();
-    const long long t = __builtin_amdgcn_readfirstlane((int)*item);   // the problem stays in scalar registers
-    __syncthreads();
-    if (t < 0) break;
-    int lo = 0, hi = G.nprob - 1;   // last f with prefix[f] <= t
-    while (lo < hi) {
-      const int mid = (lo + hi + 1) >> 1;
-      if (G.prefix[mid] <= t) lo = mid; else hi = mid - 1;
-    }
-    OzParams p = G.probs[lo];
-    if (p.status != nullptr && *p.status != 0) continue;
-    p.k0 = window * wlen;
-    if (p.k0 >= p.kp && window > 0) continue;
-    p.kc = min(wlen, p.kp - p.k0);
-    p.accumulate = window > 0;
-    const int64_t u = t - G.prefix[lo];
-    int tm, tn;
-    oz8_decode(p, BM, BN, (int)u, tm, tn);
-    const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
-    if (oz8_tile_skipped(p, m0, n0, BN)) continue;
-    oz8_tile<S, NBUF, T>(p, m0, n0, lds);
-  }
+  int f, u;
+  if (!grouped_item(G, f, u)) return;
+  OzParams p = G.probs[f];
+  if (p.status != nullptr && *p.status != 0) return;
+  p.k0 = window * wlen;
+  if (p.k0 >= p.kp && window > 0) return;
+  p.kc = min(wlen, p.kp - p.k0);
+  p.accumulate = window > 0;
+  int tm, tn;
+  oz8_decode(p, BM, BN, u, tm, tn);
+  const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
+  if (oz8_tile_skipped(p, m0, n0, BN)) return;
+  oz8_tile<S, NBUF, T>(p, m0, n0, lds);
 }
 
 }  // namespace rimp2
