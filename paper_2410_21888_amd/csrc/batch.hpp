@@ -35,14 +35,6 @@ struct AmpDesc {
   const int32_t* status;
   int32_t nocc, nvir, energy_only, write_x;
 };
-struct ReduceDesc {
-  double* out;
-  const double* W;
-  const int32_t* status;
-  int64_t ldo, ldw, zs, M, N;
-  double alpha;
-  int32_t splits, accumulate;
-};
 struct FragSmall {       // gap check, energy sum and status copy
   const double* eo;
   const double* ev;

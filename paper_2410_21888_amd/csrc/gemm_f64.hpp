@@ -38,6 +38,8 @@
 
 #include <type_traits>
 
+#include "kernels.hpp"
+
 namespace rimp2 {
 
 typedef double dbl4 __attribute__((ext_vector_type(4)));
@@ -85,6 +87,12 @@ struct GemmParams {
   // blocks the same launch computes); workgroups are launched for the tiles
   // that pair_cols_skipped keeps.  Never with split-K.
   int32_t pair_upper, pair_lo;
+  // The first (ia|jb) launch of a fragment (its status is null: V is scratch)
+  // also checks the orbital energies, in one more workgroup that writes
+  // gap_status for the kernels after it; null otherwise.
+  int32_t* gap_status;
+  const double *gap_eo, *gap_ev;
+  int32_t gap_nocc, gap_nvir;
 };
 
 // True when the tile need not be computed (uniform): every occupied pair it
@@ -614,7 +622,15 @@ template <int BM, int BN, int BK, bool B_NCONTIG, int ROLE, bool VEC, bool TRI, 
 __global__ __launch_bounds__(256, 2) void gemm_f64_kernel(GemmParams p) {
   if (p.status != nullptr && *p.status != 0) return;
   __shared__ GemmLds<BM, BN, BK> lds;
-  const int wl = xcd_remap(blockIdx.x, gridDim.x);
+  int nwg = gridDim.x;
+  if (ROLE == ROLE_INTS && p.gap_status != nullptr) {
+    --nwg;
+    if ((int)blockIdx.x == nwg) {
+      gap_check_block(p.gap_eo, p.gap_nocc, p.gap_ev, p.gap_nvir, p.gap_status);
+      return;
+    }
+  }
+  const int wl = xcd_remap(blockIdx.x, nwg);
   const int ntiles = TRI ? p.tiles_m * (p.tiles_m + 1) / 2 : p.tiles_m * p.tiles_n;
   int z = wl / ntiles;   // 0 in a pair_upper launch: at most ntiles workgroups
   int tm, tn;
@@ -627,6 +643,40 @@ __global__ __launch_bounds__(256, 2) void gemm_f64_kernel(GemmParams p) {
   }
   if (tile_screened<BM, BN>(p, tm, tn)) return;
   gemm_tile<BM, BN, BK, B_NCONTIG, VEC, TRI, FAST, role_a_mcontig(ROLE)>(p, tm, tn, z, lds);
+}
+
+// Gamma, P_ab and P_ij of a fragment whose products are each too small to fill
+// the chip, in one launch: workgroups [0, n_gam) take Gamma's tiles (64), the
+// longest, then P_ab's (64) and P_ij's (32).  FW: the fast loader's level of P_ab
+// and P_ij (2 or 3).  Every element is summed as in the separate launches.
+// Latency-bound; one after another they took 25 us at nocc = 5, nvir = 25, naux =
+// 90 and 126 us at 20/100/400, together 11 and 108.
+struct TailParams {
+  GemmParams gam, ab, ij;
+  int32_t n_gam, n_ab;
+};
+template <int FW>
+__global__ __launch_bounds__(256, 4) void gemm_f64_tail(TailParams t) {
+  if (*t.gam.status != 0) return;
+  __shared__ __attribute__((aligned(16))) char lds[sizeof(GemmLds<64, 64, 16>)];
+  int w = blockIdx.x, tm, tn;
+  if (w < t.n_gam) {
+    const int n = t.gam.tiles_m * t.gam.tiles_n, z = w / n;
+    decode_tile<64, 64, false>(t.gam, w - z * n, tm, tn);
+    gemm_tile<64, 64, 16, true, true, false, 1>(t.gam, tm, tn, z, *(GemmLds<64, 64, 16>*)lds);
+    return;
+  }
+  w -= t.n_gam;
+  if (w < t.n_ab) {
+    const int n = t.ab.tiles_m * (t.ab.tiles_m + 1) / 2, z = w / n;
+    decode_tile<64, 64, true>(t.ab, w - z * n, tm, tn);
+    gemm_tile<64, 64, 16, false, true, true, FW>(t.ab, tm, tn, z, *(GemmLds<64, 64, 16>*)lds);
+    return;
+  }
+  w -= t.n_ab;
+  const int n = t.ij.tiles_m * (t.ij.tiles_m + 1) / 2, z = w / n;
+  decode_tile<32, 32, true>(t.ij, w - z * n, tm, tn);
+  gemm_tile<32, 32, 16, false, true, true, FW>(t.ij, tm, tn, z, *(GemmLds<32, 32, 16>*)lds);
 }
 
 // Grouped launch over many independent GEMMs (one per fragment): problem f owns

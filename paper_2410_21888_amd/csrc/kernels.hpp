@@ -432,10 +432,38 @@ __device__ __forceinline__ void energy_sum_block(const double* e, int64_t count,
   }
 }
 
-__global__ __launch_bounds__(256) void energy_sum_kernel(const double* e, int64_t count, double* E,
-                                                         const int32_t* status) {
-  if (*status != 0) return;
-  energy_sum_block(e, count, E);
+// One split-K reduction.
+struct ReduceDesc {
+  double* out;
+  const double* W;
+  const int32_t* status;
+  int64_t ldo, ldw, zs, M, N;
+  double alpha;
+  int32_t splits, accumulate;
+};
+// The reductions of one fragment's products and (E not null) its energy sum, in
+// one launch: reduction i takes workgroups [first[i], first[i + 1]), the last
+// workgroup the sum.
+constexpr int kFinishMax = 3;
+struct FinishParams {
+  ReduceDesc r[kFinishMax];
+  int32_t first[kFinishMax + 1], n;
+  const double* e;
+  int64_t count;
+  double* E;
+  const int32_t* status;
+};
+__global__ __launch_bounds__(256) void finish_kernel(FinishParams f) {
+  if (*f.status != 0) return;
+  const int b = blockIdx.x;
+#pragma unroll
+  for (int i = 0; i < kFinishMax; ++i)
+    if (i < f.n && b >= f.first[i] && b < f.first[i + 1]) {
+      const ReduceDesc& r = f.r[i];
+      splitk_reduce_block(r.out, r.ldo, r.W, r.ldw, r.zs, r.splits, r.M, r.N, r.alpha, r.accumulate, b - f.first[i]);
+      return;
+    }
+  if (f.E != nullptr) energy_sum_block(f.e, f.count, f.E);
 }
 
 // status_out[idx] = *status (per-fragment status of a batch).

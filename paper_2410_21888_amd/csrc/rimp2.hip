@@ -54,12 +54,12 @@ namespace {
 
 // ---- kernel timing -------------------------------------------------------
 enum Role { R_GAP, R_INTS, R_AMP, R_GAMMA, R_PAB, R_PIJ, R_REDUCE, R_ESUM, R_STATUS, R_SPLIT, R_INTS8, R_GAMMA8,
-            R_GAMMA_T, R_GAMMA_AO, R_LTERM, R_RESPONSE, R_GAMMA_T8, R_GAMMA_METRIC, R_NROLES };
+            R_GAMMA_T, R_GAMMA_AO, R_LTERM, R_RESPONSE, R_GAMMA_T8, R_GAMMA_METRIC, R_TAIL, R_NROLES };
 const char* const kRoleName[R_NROLES] = {"gap_check",  "ints_gemm",     "amplitude",  "gamma_gemm",
                                          "pab_gemm",   "pij_gemm",      "splitk_reduce", "energy_sum",
                                          "status_copy", "digit_split", "ints_oz8",   "gamma_oz8",
                                          "gamma_t_gemm", "gamma_ao_gemm", "l_terms_gemm", "response",
-                                         "gamma_t_oz8", "gamma_metric"};
+                                         "gamma_t_oz8", "gamma_metric", "small_gemms"};
 struct TraceRec {
   int role;
   hipEvent_t e0, e1;
@@ -475,23 +475,24 @@ int launch_gemm(GemmParams gp, hipStream_t st, int role, double af, double ab, b
     ef *= (double)kept / ((double)gp.tiles_m * gp.tiles_n);
   }
   const int fast = general ? 0 : fast_level(gp, BM, NC, AMC);
+  const int64_t grid = nwg + (ROLE == ROLE_INTS && gp.gap_status ? 1 : 0);
   // the roles whose K operands have runs
   constexpr bool RUNS = ROLE == ROLE_PAB || ROLE == ROLE_PIJ || ROLE == ROLE_LTERM;
   if (!RUNS && fast > 1) return fail(RIMP2_EINVAL, "GEMM role %d with a two-level reduction", ROLE);
   return traced(role, af, ef, ab, st, [&] {
     if (fast == 1)
-      hipLaunchKernelGGL((gemm_f64_kernel<BM, BN, kBK, NC, ROLE, true, TRI, 1>), dim3((unsigned)nwg), dim3(256), 0,
+      hipLaunchKernelGGL((gemm_f64_kernel<BM, BN, kBK, NC, ROLE, true, TRI, 1>), dim3((unsigned)grid), dim3(256), 0,
                          st, gp);
     else if (RUNS && fast == 2)
-      hipLaunchKernelGGL((gemm_f64_kernel<BM, BN, kBK, NC, ROLE, true, TRI, RUNS ? 2 : 0>), dim3((unsigned)nwg),
+      hipLaunchKernelGGL((gemm_f64_kernel<BM, BN, kBK, NC, ROLE, true, TRI, RUNS ? 2 : 0>), dim3((unsigned)grid),
                          dim3(256), 0, st, gp);
     else if (RUNS && fast == 3)
-      hipLaunchKernelGGL((gemm_f64_kernel<BM, BN, kBK, NC, ROLE, true, TRI, RUNS ? 3 : 0>), dim3((unsigned)nwg),
+      hipLaunchKernelGGL((gemm_f64_kernel<BM, BN, kBK, NC, ROLE, true, TRI, RUNS ? 3 : 0>), dim3((unsigned)grid),
                          dim3(256), 0, st, gp);
     else if (vec)
-      hipLaunchKernelGGL((gemm_f64_kernel<BM, BN, kBK, NC, ROLE, true, TRI>), dim3((unsigned)nwg), dim3(256), 0, st, gp);
+      hipLaunchKernelGGL((gemm_f64_kernel<BM, BN, kBK, NC, ROLE, true, TRI>), dim3((unsigned)grid), dim3(256), 0, st, gp);
     else
-      hipLaunchKernelGGL((gemm_f64_kernel<BM, BN, kBK, NC, ROLE, false, TRI>), dim3((unsigned)nwg), dim3(256), 0, st, gp);
+      hipLaunchKernelGGL((gemm_f64_kernel<BM, BN, kBK, NC, ROLE, false, TRI>), dim3((unsigned)grid), dim3(256), 0, st, gp);
   });
 }
 
@@ -805,6 +806,63 @@ int run_oz8(int S, const int8_t* A, int64_t a_slice, int64_t a_row0, const int32
 
 KOperand kop(const double* base, int64_t rs, int64_t kdiv, int64_t ks1) { return KOperand{base, rs, kdiv, ks1}; }
 
+// tiles, splits and group size of a GEMM, as launch_gemm sets them
+int64_t finalize_gemm(GemmParams& gp, int BM, int BN, bool tri) {
+  gp.tiles_m = (int32_t)cdiv(gp.M, BM);
+  gp.tiles_n = (int32_t)cdiv(gp.N, BN);
+  gp.group_m = 8;
+  if (gp.kchunk <= 0) gp.kchunk = gp.K;
+  gp.kchunk = cdiv(gp.kchunk, kBK) * kBK;
+  gp.splits = (int32_t)cdiv(gp.K, gp.kchunk);
+  return gemm_tiles(gp, BM, BN, tri) * gp.splits;
+}
+
+int launch_finish(const FinishParams& f, hipStream_t st) {
+  if (f.n > 1 && f.first[f.n] >= kMaxWorkgroups) {   // more than one launch covers: the first reduction by itself
+    FinishParams a = f, b = f;
+    a.n = 1;
+    a.E = nullptr;
+    b.n = f.n - 1;
+    for (int i = 0; i < b.n; ++i) {
+      b.r[i] = f.r[i + 1];
+      b.first[i + 1] = f.first[i + 2] - f.first[1];
+    }
+    if (int rc = launch_finish(a, st)) return rc;
+    return launch_finish(b, st);
+  }
+  const int64_t grid = f.first[f.n] + (f.E ? 1 : 0);
+  double bytes = f.E ? 8.0 * f.count : 0.0;
+  for (int i = 0; i < f.n; ++i) bytes += 8.0 * (f.r[i].splits + 1 + f.r[i].accumulate) * f.r[i].M * f.r[i].N;
+  return traced(f.n ? R_REDUCE : R_ESUM, 0, 0, bytes, st,
+                [&] { hipLaunchKernelGGL(finish_kernel, dim3((unsigned)grid), dim3(256), 0, st, f); });
+}
+
+// Loader level (2 or 3) of gemm_f64_tail for a fragment's Gamma, P_ab and P_ij
+// products, 0: separate launches.  One launch where the plan gives all of them
+// small tiles (no product fills the chip by itself with large ones); the
+// general loader and the autotuner's trials run apart.
+int tail_level(const Plan& P, GemmParams gg, GemmParams ga, GemmParams gi) {
+  if (P.autotune || P.general || P.c_gam.bm != 64 || P.c_ab.bm != 64 || P.c_ij.bm != 32) return 0;
+  for (GemmParams* p : {&gg, &ga, &gi}) p->kchunk = cdiv(p->kchunk, kBK) * kBK;
+  const int fg = fast_level(gg, 64, true), fa = fast_level(ga, 64, false), fi = fast_level(gi, 32, false);
+  return fg && fa && fi ? std::max({2, fa, fi}) : 0;
+}
+
+int launch_tail(int level, const GemmParams& gg, const GemmParams& ga, const GemmParams& gi, double af, double ab,
+                hipStream_t st) {
+  TailParams t{gg, ga, gi, 0, 0};
+  t.n_gam = (int32_t)finalize_gemm(t.gam, 64, 64, false);
+  t.n_ab = (int32_t)finalize_gemm(t.ab, 64, 64, true);
+  const int64_t grid = t.n_gam + t.n_ab + finalize_gemm(t.ij, 32, 32, true);
+  if (int rc = check_grid(grid, "small GEMMs")) return rc;
+  return traced(R_TAIL, af, af, ab, st, [&] {
+    if (level == 3)
+      hipLaunchKernelGGL(gemm_f64_tail<3>, dim3((unsigned)grid), dim3(256), 0, st, t);
+    else
+      hipLaunchKernelGGL(gemm_f64_tail<2>, dim3((unsigned)grid), dim3(256), 0, st, t);
+  });
+}
+
 // Enqueue the whole path for one fragment.  Pointers already validated.
 int run_fragment(const Plan& P, const double* B, const double* eo, const double* ev, double* E, double* Gam,
                  double* Pij, double* Pab, double* e_user, char* ws, const uint8_t* skip, hipStream_t st) {
@@ -815,7 +873,8 @@ int run_fragment(const Plan& P, const double* B, const double* eo, const double*
   double* T = (double*)(ws + P.off_T);
   double* ep = e_user ? e_user : (double*)(ws + P.off_e);
   int rc;
-  if ((rc = traced(R_GAP, 0, 0, 8.0 * (o + v), st, [&] {
+  // (the FP64 path checks the gap inside its first (ia|jb) launch)
+  if (P.split && (rc = traced(R_GAP, 0, 0, 8.0 * (o + v), st, [&] {
          hipLaunchKernelGGL(gap_check_kernel, dim3(1), dim3(256), 0, st, eo, (int)nocc, ev, (int)nvir, status);
        })))
     return rc;
@@ -851,6 +910,14 @@ int run_fragment(const Plan& P, const double* B, const double* eo, const double*
         return rc;
     }
   }
+  FinishParams fin{};
+  fin.e = ep; fin.count = nocc * nocc; fin.E = E; fin.status = status;
+  // queues a split-K reduction of the group for its finish launch
+  auto reduce = [&](double* out, const double* W, int64_t M, int64_t N, int64_t splits, double alpha, int acc) {
+    fin.r[fin.n] = ReduceDesc{out, W, status, N, N, M * N, M, N, alpha, (int32_t)splits, acc};
+    fin.first[fin.n + 1] = fin.first[fin.n] + (int32_t)reduce_blocks(M * N, splits);
+    ++fin.n;
+  };
   for (int64_t k0 = 0, gc = 0; k0 < nocc; k0 += gc) {
     gc = group_at(P, k0);
     // (ia|jb) slab: rows (kk, a) of B starting at k0, columns (j, b) over all of B;
@@ -870,6 +937,11 @@ int run_fragment(const Plan& P, const double* B, const double* eo, const double*
       // computed and the amplitude pass forms them from their transposes
       gp.pair_upper = 1;
       gp.pair_lo = (int32_t)k0;
+      if (k0 == 0 && !P.split) {
+        gp.status = nullptr;
+        gp.gap_status = status; gp.gap_eo = eo; gp.gap_ev = ev;
+        gp.gap_nocc = (int32_t)nocc; gp.gap_nvir = (int32_t)nvir;
+      }
       // algorithmic FLOPs: unordered pairs whose first orbital is in the group
       // (energy only: exactly the pairs (k, j >= k) computed; otherwise the
       // unordered-pair share of the ordered pairs computed)
@@ -1012,84 +1084,73 @@ int run_fragment(const Plan& P, const double* B, const double* eo, const double*
           return rc;
         }
       }
-    } else if (P.gamma) {
-      GemmParams gp{};
-      gp.M = gc * nvir; gp.N = naux; gp.K = L;
-      gp.kchunk = cdiv(L, P.c_gam.splits);
-      gp.A = kop(T, L, INT64_MAX, 0);
-      gp.Bn = NOperand{B, naux};
+    }
+    GemmParams gg{};   // ordered path: Gamma[k, a, P] = sum over (j, b) of T[k, a, j, b] B[j, b, P]
+    const bool gam64 = P.gamma && !P.sym && !P.split;
+    double afg = 0.0, abg = 0.0;
+    if (P.gamma && !P.sym) {
       double* out = Gam + k0 * nvir * naux;
-      const double af = 2.0 * g * v * x * o * v, ab = slab + 8.0 * o * v * x + 8.0 * g * v * x;
+      afg = 2.0 * g * v * x * o * v;
+      abg = slab + 8.0 * o * v * x + 8.0 * g * v * x;
       if (P.split) {
         if ((rc = traced(R_SPLIT, 0, 0, slab + (double)P.sg * g * v * P.kpg, st, [&] {
                RIMP2_SWITCH_S(P.sg, launch_split_rows<SS>(T, gc * nvir, L, L, dt, P.kpg, ext, status, st));
              })))
           return rc;
         if ((rc = run_oz8(P.sg, dt, gc * nvir * P.kpg, 0, ext, dbg, naux * P.kpg, exg, gc * nvir, naux, P.kpg, out,
-                          naux, status, R_GAMMA8, af, (double)P.sg * (g * v + x) * P.kpg + 8.0 * g * v * x, st)))
-          return rc;
-      } else if (P.c_gam.splits > 1) {
-        double* W = (double*)(ws + P.off_gam);
-        gp.C = W; gp.ldc = naux; gp.split_stride = gc * nvir * naux; gp.status = status;
-        if ((rc = launch_tuned(R_GAMMA, P.c_gam.bm, gp, P.autotune, P.general, st, af, ab))) return rc;
-        const int64_t splits = cdiv(L, cdiv(cdiv(L, P.c_gam.splits), kBK) * kBK);
-        const int64_t n = gc * nvir * naux;
-        if ((rc = traced(R_REDUCE, 0, 0, 8.0 * (splits + 1) * n, st, [&] {
-               hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)reduce_blocks(n, splits)), dim3(256), 0, st, out, naux, W,
-                                  naux, gc * nvir * naux, (int)splits, gc * nvir, naux, 1.0, 0, status);
-             })))
+                          naux, status, R_GAMMA8, afg, (double)P.sg * (g * v + x) * P.kpg + 8.0 * g * v * x, st)))
           return rc;
       } else {
-        gp.C = out; gp.ldc = naux; gp.split_stride = 0; gp.status = status;
-        if ((rc = launch_tuned(R_GAMMA, P.c_gam.bm, gp, P.autotune, P.general, st, af, ab))) return rc;
+        gg.M = gc * nvir; gg.N = naux; gg.K = L; gg.kchunk = cdiv(L, P.c_gam.splits);
+        gg.A = kop(T, L, INT64_MAX, 0);
+        gg.Bn = NOperand{B, naux};
+        gg.C = out; gg.ldc = naux; gg.status = status;
+        if (P.c_gam.splits > 1) {
+          gg.C = (double*)(ws + P.off_gam);
+          gg.split_stride = gg.M * naux;
+          reduce(out, gg.C, gg.M, naux, cdiv(L, cdiv(gg.kchunk, kBK) * kBK), 1.0, 0);
+        }
       }
     }
+    GemmParams ga{}, gi{};
     if (P.density) {
       const int accumulate = k0 > 0 ? 1 : 0;
-      {  // P_ab[a,b] += sum over (kk, j, c) of T[kk,a,j,c] X[kk,b,j,c]
-        GemmParams gp{};
-        const int64_t K = gc * L;
-        gp.M = nvir; gp.N = nvir; gp.K = K;
-        gp.kchunk = cdiv(K, P.c_ab.splits);
-        gp.A = kop(T, L, L, nvir * L);
-        gp.Bk = kop(V, L, L, nvir * L);
-        double* W = (double*)(ws + P.off_pab);
-        gp.C = W; gp.ldc = nvir; gp.split_stride = nvir * nvir; gp.status = status;
-        const int64_t splits = cdiv(K, cdiv(cdiv(K, P.c_ab.splits), kBK) * kBK);
-        if ((rc = launch_tuned(R_PAB, P.c_ab.bm, gp, P.autotune, P.general, st, 2.0 * v * v * g * o * v,
-                               2.0 * slab + 8.0 * splits * v * v)))
-          return rc;
-        if ((rc = traced(R_REDUCE, 0, 0, 8.0 * (splits + 2) * v * v, st, [&] {
-               hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)reduce_blocks(nvir * nvir, splits)), dim3(256), 0, st, Pab,
-                                  nvir, W, nvir, nvir * nvir, (int)splits, nvir, nvir, 1.0, accumulate, status);
-             })))
-          return rc;
-      }
-      {  // P_ij[i,j] -= sum over (kk, a, b) of T[kk,a,i,b] X[kk,a,j,b]
-        GemmParams gp{};
-        const int64_t K = gc * nvir * nvir;
-        gp.M = nocc; gp.N = nocc; gp.K = K;
-        gp.kchunk = cdiv(K, P.c_ij.splits);
-        gp.A = kop(T, nvir, nvir, L);
-        gp.Bk = kop(V, nvir, nvir, L);
-        double* W = (double*)(ws + P.off_pij);
-        gp.C = W; gp.ldc = nocc; gp.split_stride = nocc * nocc; gp.status = status;
-        const int64_t splits = cdiv(K, cdiv(cdiv(K, P.c_ij.splits), kBK) * kBK);
-        // each slab's contribution to P_ij is symmetric: upper-triangular tiles, mirrored
-        if ((rc = launch_tuned(R_PIJ, P.c_ij.bm, gp, P.autotune, P.general, st, 2.0 * o * o * g * v * v,
-                               2.0 * slab + 8.0 * splits * o * o)))
-          return rc;
-        if ((rc = traced(R_REDUCE, 0, 0, 8.0 * (splits + 2) * o * o, st, [&] {
-               hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)reduce_blocks(nocc * nocc, splits)), dim3(256), 0, st, Pij,
-                                  nocc, W, nocc, nocc * nocc, (int)splits, nocc, nocc, -1.0, accumulate, status);
-             })))
-          return rc;
-      }
+      // P_ab[a,b] += sum over (kk, j, c) of T[kk,a,j,c] X[kk,b,j,c]
+      ga.M = nvir; ga.N = nvir; ga.K = gc * L; ga.kchunk = cdiv(ga.K, P.c_ab.splits);
+      ga.A = kop(T, L, L, nvir * L);
+      ga.Bk = kop(V, L, L, nvir * L);
+      ga.C = (double*)(ws + P.off_pab); ga.ldc = nvir; ga.split_stride = nvir * nvir; ga.status = status;
+      reduce(Pab, ga.C, nvir, nvir, cdiv(ga.K, cdiv(ga.kchunk, kBK) * kBK), 1.0, accumulate);
+      // P_ij[i,j] -= sum over (kk, a, b) of T[kk,a,i,b] X[kk,a,j,b]; each slab's
+      // contribution is symmetric: upper-triangular tiles, mirrored
+      gi.M = nocc; gi.N = nocc; gi.K = gc * nvir * nvir; gi.kchunk = cdiv(gi.K, P.c_ij.splits);
+      gi.A = kop(T, nvir, nvir, L);
+      gi.Bk = kop(V, nvir, nvir, L);
+      gi.C = (double*)(ws + P.off_pij); gi.ldc = nocc; gi.split_stride = nocc * nocc; gi.status = status;
+      reduce(Pij, gi.C, nocc, nocc, cdiv(gi.K, cdiv(gi.kchunk, kBK) * kBK), -1.0, accumulate);
+    }
+    const double afa = 2.0 * v * v * g * o * v, aba = 2.0 * slab + 8.0 * v * v, afi = 2.0 * o * o * g * v * v,
+                 abi = 2.0 * slab + 8.0 * o * o;
+    int tail = 0;
+    if (gam64 && P.density) tail = tail_level(P, gg, ga, gi);
+    if (tail) {
+      if ((rc = launch_tail(tail, gg, ga, gi, afg + afa + afi, abg + aba + abi, st))) return rc;
+    } else {
+      if (gam64 && (rc = launch_tuned(R_GAMMA, P.c_gam.bm, gg, P.autotune, P.general, st, afg, abg))) return rc;
+      if (P.density && ((rc = launch_tuned(R_PAB, P.c_ab.bm, ga, P.autotune, P.general, st, afa, aba)) ||
+                        (rc = launch_tuned(R_PIJ, P.c_ij.bm, gi, P.autotune, P.general, st, afi, abi))))
+        return rc;
+    }
+    // the group's reductions, and with the last group's the energy
+    const bool last = k0 + gc >= nocc;
+    if (fin.n > 0 && !last) {
+      FinishParams f = fin;
+      f.E = nullptr;
+      if ((rc = launch_finish(f, st))) return rc;
+      fin.n = 0;
     }
   }
-  return traced(R_ESUM, 0, 0, 8.0 * o * o, st, [&] {
-    hipLaunchKernelGGL(energy_sum_kernel, dim3(1), dim3(256), 0, st, ep, nocc * nocc, E, status);
-  });
+  return launch_finish(fin, st);
 }
 
 int want_of(const double* Gam, const double* Pij, const double* Pab, int* want) {
@@ -1249,17 +1310,6 @@ const int* const kBatchTiles[4] = {kIntsTiles, kGammaTiles, kPabTiles, kBatchPij
 int loader_of(const GemmParams& g, int bm, bool nc, bool vec, bool general) {
   const int f = general ? 0 : fast_level(g, bm, nc);
   return f ? f - 1 : vec ? 3 : 4;
-}
-
-// tiles, splits and group size of a GEMM, as launch_gemm sets them
-int64_t finalize_gemm(GemmParams& gp, int BM, int BN, bool tri) {
-  gp.tiles_m = (int32_t)cdiv(gp.M, BM);
-  gp.tiles_n = (int32_t)cdiv(gp.N, BN);
-  gp.group_m = 8;
-  if (gp.kchunk <= 0) gp.kchunk = gp.K;
-  gp.kchunk = cdiv(gp.kchunk, kBK) * kBK;
-  gp.splits = (int32_t)cdiv(gp.K, gp.kchunk);
-  return gemm_tiles(gp, BM, BN, tri) * gp.splits;
 }
 
 size_t place(size_t& off, size_t bytes) {

@@ -36,7 +36,7 @@ COPY_KERNEL = "__amd_rocclr_copyBuffer"
 CALIB_BYTES = 1 << 30        # bench.py --calib-copy moves 1 GiB each way
 
 _GEMM_ROLES = {"0": "ints_gemm", "1": "gamma_gemm", "2": "pab_gemm", "3": "pij_gemm", "4": "gamma_t_gemm",
-               "5": "gamma_ao_gemm", "6": "l_terms_gemm"}
+               "5": "gamma_ao_gemm", "6": "l_terms_gemm", "7": "response"}
 
 
 # the sources the fragment path's kernels are built from (screening and the
@@ -95,7 +95,8 @@ def role_of(name: str) -> str:
         return _GEMM_ROLES[m.group(2)]
     for key, role in (("gemm_oz8_", None), ("amplitude", "amplitude"),
                       ("pair_energy_reduce", "amplitude (pair energy reduce)"),
-                      ("splitk_reduce", "splitk_reduce"), ("reduce_grouped", "splitk_reduce"),
+                      ("splitk_reduce", "splitk_reduce"), ("finish_kernel", "splitk_reduce"),
+                      ("gemm_f64_tail", "small_gemms"), ("reduce_grouped", "splitk_reduce"),
                       ("energy_sum", "energy_sum"), ("gap_check", "gap_check"), ("split_rows", "digit_split"),
                       ("split_cols", "digit_split"), ("colmax", "digit_split"), ("zero_u64", "digit_split"),
                       ("digit_split_grouped", "digit_split"), ("relocate_digit", "status_copy"),
