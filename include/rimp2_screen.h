@@ -61,6 +61,17 @@ int rimp2_mlp_loss_grad(int64_t n, const double* x, const double* target, const 
 int rimp2_mlp_adam(const double* grad, double* params, double* m, double* v, int64_t step, double lr, double beta1,
                    double beta2, double eps, void* stream);
 
+/*
+ * `steps` training steps in a row, step k on the minibatch of the rows
+ * idx[k * n .. k * n + n - 1] of x and target (device [steps][n], each a valid
+ * row): what rimp2_mlp_loss_grad and rimp2_mlp_adam (step first_step + k) do for
+ * each, without the minibatches and gradients written out.  loss device [1]:
+ * the last step's.  workspace: rimp2_mlp_workspace_size(n) bytes.
+ */
+int rimp2_mlp_fit(int64_t n, int32_t steps, const double* x, const double* target, const int64_t* idx,
+                  double* params, double* m, double* v, int64_t first_step, double lr, double beta1,
+                  double beta2, double eps, double* loss, void* workspace, size_t workspace_bytes, void* stream);
+
 /* out[s] = log10(max(-e[s], 1e-300)) for s < n (training targets from pair energies). */
 int rimp2_log_energy(int64_t n, const double* e, double* out, void* stream);
 

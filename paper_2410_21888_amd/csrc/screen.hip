@@ -157,10 +157,11 @@ __device__ __forceinline__ double mlp_out(const MlpLds& L, const double* P) {
   for (int d = 8; d > 0; d >>= 1) o += __shfl_down(o, d, 16);
   return o + P[OB3];
 }
-__device__ __forceinline__ void mlp_load(MlpLds& L, int64_t n, int64_t s0, const double* x) {
+// Samples s0.. of x, or of its rows idx[s] (idx not null).
+__device__ __forceinline__ void mlp_load(MlpLds& L, int64_t n, int64_t s0, const double* x, const int64_t* idx) {
   for (int q = threadIdx.x; q < SB * NIN; q += 256) {
     const int64_t s = s0 + q / NIN;
-    L.X[q / NIN][q % NIN] = s < n ? x[s * NIN + q % NIN] : 0.0;
+    L.X[q / NIN][q % NIN] = s < n ? x[(idx ? idx[s] : s) * NIN + q % NIN] : 0.0;
   }
 }
 
@@ -174,7 +175,7 @@ __global__ __launch_bounds__(256) void mlp_forward_kernel(int64_t n, const doubl
   const double b1 = P[OB1 + u], b2 = P[OB2 + u];
   const int64_t nb = (n + SB - 1) / SB;
   for (int64_t b = blockIdx.x; b < nb; b += gridDim.x) {
-    mlp_load(L, n, b * SB, x);
+    mlp_load(L, n, b * SB, x, nullptr);
     __syncthreads();
     double z1[4];
     dbl4 z2;
@@ -191,7 +192,7 @@ __global__ __launch_bounds__(256) void mlp_forward_kernel(int64_t n, const doubl
 // Gradient of sum_s (y - t)^2 / n (and the loss part) over the workgroup's
 // blocks blockIdx.x, blockIdx.x + gridDim.x, ... -> part[blockIdx][NP + 1]
 __global__ __launch_bounds__(256) void mlp_backward_kernel(int64_t n, const double* x, const double* tgt,
-                                                           const double* P, double* part) {
+                                                           const int64_t* idx, const double* P, double* part) {
   __shared__ MlpLds L;
   __shared__ double gs[4][H];   // b1, b2, W3 gradients, loss and b3 (per sample slot)
   const int t = threadIdx.x, lane = t & 63, w = t >> 6, g = lane >> 4, c = lane & 15, u = 16 * w + c;
@@ -209,7 +210,7 @@ __global__ __launch_bounds__(256) void mlp_backward_kernel(int64_t n, const doub
   double gw1 = 0.0, gb1 = 0.0, gb2 = 0.0, gw3 = 0.0, gb3 = 0.0, loss = 0.0;
   const int64_t nblk = (n + SB - 1) / SB;
   for (int64_t b = blockIdx.x; b < nblk; b += gridDim.x) {
-    mlp_load(L, n, b * SB, x);
+    mlp_load(L, n, b * SB, x, idx);
     __syncthreads();
     double z1[4], a2[4];
     dbl4 z2;
@@ -223,7 +224,7 @@ __global__ __launch_bounds__(256) void mlp_backward_kernel(int64_t n, const doub
     const double o = mlp_out(L, P);
     if ((t & 15) == 0) {
       const int64_t s = b * SB + (t >> 4);
-      const double res = s < n ? o - tgt[s] : 0.0, dy = 2.0 * res / (double)n;
+      const double res = s < n ? o - tgt[idx ? idx[s] : s] : 0.0, dy = 2.0 * res / (double)n;
       L.y[t >> 4] = dy;
       gb3 += dy;
       loss += res * res / (double)n;
@@ -286,9 +287,23 @@ __global__ __launch_bounds__(256) void mlp_backward_kernel(int64_t n, const doub
     out[t == 0 ? OB3 : NP] = v;
   }
 }
-// grad[q] = sum over workgroups of part[w][q] in a fixed order (16 lanes a
-// parameter, each every 16th workgroup, then the lanes in order); loss = part[.][NP]
-__global__ __launch_bounds__(256) void mlp_reduce_kernel(const double* part, int nw, double* grad, double* loss) {
+// One Adam step of parameter q with gradient gq.
+struct AdamArgs {
+  double *p, *m, *v;
+  double c1, c2, lr, b1, b2, eps;
+};
+__device__ __forceinline__ void adam_step(const AdamArgs& a, int q, double gq) {
+  const double mq = a.b1 * a.m[q] + (1.0 - a.b1) * gq, vq = a.b2 * a.v[q] + (1.0 - a.b2) * gq * gq;
+  a.m[q] = mq;
+  a.v[q] = vq;
+  a.p[q] -= a.lr * (mq / a.c1) / (sqrt(vq / a.c2) + a.eps);
+}
+// The gradient of parameter q, the sum over workgroups of part[w][q] in a fixed
+// order (16 lanes a parameter, each every 16th workgroup, then the lanes in
+// order), goes to grad[q], or (ADAM) into an Adam step; loss = part[.][NP].
+template <bool ADAM>
+__global__ __launch_bounds__(256) void mlp_reduce_kernel(const double* part, int nw, double* grad, double* loss,
+                                                         AdamArgs a) {
   __shared__ double sh[16][17];
   const int e = threadIdx.x & 15, l = threadIdx.x >> 4, q = blockIdx.x * 16 + e;
   double s = 0.0;
@@ -300,17 +315,13 @@ __global__ __launch_bounds__(256) void mlp_reduce_kernel(const double* part, int
   __syncthreads();
   if (l != 0 || q > NP) return;
   for (int k = 1; k < 16; ++k) s += sh[k][e];
-  if (q < NP) grad[q] = s; else *loss = s;
+  if (q == NP) *loss = s;
+  else if (ADAM) adam_step(a, q, s);
+  else grad[q] = s;
 }
-__global__ __launch_bounds__(256) void adam_kernel(const double* g, double* p, double* m, double* v, double c1,
-                                                   double c2, double lr, double b1, double b2, double eps) {
+__global__ __launch_bounds__(256) void adam_kernel(const double* g, AdamArgs a) {
   const int q = blockIdx.x * 256 + threadIdx.x;
-  if (q >= NP) return;
-  const double gq = g[q];
-  const double mq = b1 * m[q] + (1.0 - b1) * gq, vq = b2 * v[q] + (1.0 - b2) * gq * gq;
-  m[q] = mq;
-  v[q] = vq;
-  p[q] -= lr * (mq / c1) / (sqrt(vq / c2) + eps);
+  if (q < NP) adam_step(a, q, g[q]);
 }
 __global__ __launch_bounds__(256) void log_energy_kernel(int64_t n, const double* e, double* out) {
   const int64_t s = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -414,10 +425,10 @@ int rimp2_mlp_loss_grad(int64_t n, const double* x, const double* target, const 
   hipStream_t st = (hipStream_t)stream;
   if (cdiv(n, 32) * 64 > kMaxItems) return fail(RIMP2_EINVAL, "n = %lld is too large for one launch", (long long)n);
   const int nw = (int)std::min<int64_t>(cdiv(n, SB), MAXW);
-  hipLaunchKernelGGL(mlp_backward_kernel, dim3((unsigned)nw), dim3(256), 0, st, n, x, target, params,
-                     (double*)workspace);
-  hipLaunchKernelGGL(mlp_reduce_kernel, dim3((unsigned)cdiv(NP + 1, 16)), dim3(256), 0, st, (const double*)workspace,
-                     nw, grad, loss);
+  hipLaunchKernelGGL(mlp_backward_kernel, dim3((unsigned)nw), dim3(256), 0, st, n, x, target, (const int64_t*)nullptr,
+                     params, (double*)workspace);
+  hipLaunchKernelGGL(mlp_reduce_kernel<false>, dim3((unsigned)cdiv(NP + 1, 16)), dim3(256), 0, st,
+                     (const double*)workspace, nw, grad, loss, AdamArgs{});
   HIP_TRY(hipGetLastError());
   return RIMP2_OK;
 }
@@ -425,10 +436,30 @@ int rimp2_mlp_loss_grad(int64_t n, const double* x, const double* target, const 
 int rimp2_mlp_adam(const double* grad, double* params, double* m, double* v, int64_t step, double lr, double beta1,
                    double beta2, double eps, void* stream) {
   if (!grad || !params || !m || !v || step < 1) return fail(RIMP2_EINVAL, "bad Adam arguments");
-  const double c1 = 1.0 - pow(beta1, (double)step), c2 = 1.0 - pow(beta2, (double)step);
-  hipLaunchKernelGGL(adam_kernel, dim3((unsigned)cdiv(NP, 256)), dim3(256), 0, (hipStream_t)stream, grad, params, m,
-                     v, c1, c2, lr, beta1, beta2, eps);
+  const AdamArgs a{params, m, v, 1.0 - pow(beta1, (double)step), 1.0 - pow(beta2, (double)step), lr, beta1, beta2, eps};
+  hipLaunchKernelGGL(adam_kernel, dim3((unsigned)cdiv(NP, 256)), dim3(256), 0, (hipStream_t)stream, grad, a);
   HIP_TRY(hipGetLastError());
+  return RIMP2_OK;
+}
+
+int rimp2_mlp_fit(int64_t n, int32_t steps, const double* x, const double* target, const int64_t* idx, double* params,
+                  double* m, double* v, int64_t first_step, double lr, double beta1, double beta2, double eps,
+                  double* loss, void* workspace, size_t workspace_bytes, void* stream) {
+  if (n < 1 || steps < 0 || !x || !target || !idx || !params || !m || !v || first_step < 1 || !loss || !workspace)
+    return fail(RIMP2_EINVAL, "bad fit arguments");
+  if (workspace_bytes < rimp2_mlp_workspace_size(n)) return fail(RIMP2_ENOMEM, "workspace too small");
+  if (cdiv(n, 32) * 64 > kMaxItems) return fail(RIMP2_EINVAL, "n = %lld is too large for one launch", (long long)n);
+  hipStream_t st = (hipStream_t)stream;
+  const int nw = (int)std::min<int64_t>(cdiv(n, SB), MAXW);
+  for (int32_t k = 0; k < steps; ++k) {
+    const double t = (double)(first_step + k);
+    const AdamArgs a{params, m, v, 1.0 - pow(beta1, t), 1.0 - pow(beta2, t), lr, beta1, beta2, eps};
+    hipLaunchKernelGGL(mlp_backward_kernel, dim3((unsigned)nw), dim3(256), 0, st, n, x, target, idx + k * n,
+                       (const double*)params, (double*)workspace);
+    hipLaunchKernelGGL(mlp_reduce_kernel<true>, dim3((unsigned)cdiv(NP + 1, 16)), dim3(256), 0, st,
+                       (const double*)workspace, nw, (double*)nullptr, loss, a);
+    HIP_TRY(hipGetLastError());
+  }
   return RIMP2_OK;
 }
 

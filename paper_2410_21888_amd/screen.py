@@ -32,6 +32,8 @@ def _L():
         L.rimp2_mlp_loss_grad.argtypes = [i64, vp, vp, vp, vp, vp, vp, sz, vp]
         L.rimp2_mlp_adam.restype = ctypes.c_int
         L.rimp2_mlp_adam.argtypes = [vp, vp, vp, vp, i64, dbl, dbl, dbl, dbl, vp]
+        L.rimp2_mlp_fit.restype = ctypes.c_int
+        L.rimp2_mlp_fit.argtypes = [i64, i32] + [vp] * 6 + [i64] + [dbl] * 4 + [vp, vp, sz, vp]
         L.rimp2_log_energy.restype = ctypes.c_int
         L.rimp2_log_energy.argtypes = [i64, vp, vp, vp]
         L.rimp2_screen_mask.restype = ctypes.c_int
@@ -153,6 +155,8 @@ def bound_mask(bound: torch.Tensor, budget_Eh: float) -> torch.Tensor:
 class Trainer:
     """Adam on the mean squared error, minibatches drawn by a seeded host RNG."""
 
+    DRAWS = 8   # steps per upload of drawn minibatches
+
     def __init__(self, params: torch.Tensor, lr: float = 1e-3):
         self.params = params
         self.m = torch.zeros_like(params)
@@ -165,14 +169,19 @@ class Trainer:
         rng = np.random.default_rng(seed)
         n = x.shape[0]
         b = min(batch, n)
+        L = _L()
         if b not in self._ws:
-            self._ws[b] = torch.empty(_L().rimp2_mlp_workspace_size(b), dtype=torch.uint8, device=x.device)
-        loss = None
-        for _ in range(steps):
-            idx = torch.from_numpy(rng.choice(n, size=b, replace=False)).to(x.device)
-            xb = x.index_select(0, idx).contiguous()
-            tb = t.index_select(0, idx).contiguous()
-            loss, grad = mlp_loss_grad(xb, tb, self.params, workspace=self._ws[b])
-            self.step += 1
-            adam(grad, self.params, self.m, self.v, self.step, self.lr)
-        return float(loss) if loss is not None else float("nan")
+            self._ws[b] = torch.empty(L.rimp2_mlp_workspace_size(b), dtype=torch.uint8, device=x.device)
+        ws = self._ws[b]
+        x, t = x.contiguous(), t.contiguous()
+        loss = torch.empty(1, dtype=torch.float64, device=x.device)
+        # a few steps' draws at a time: the host draws the next ones while the
+        # GPU trains on these
+        for k0 in range(0, steps, self.DRAWS):
+            k = min(self.DRAWS, steps - k0)
+            idx = torch.from_numpy(np.stack([rng.choice(n, size=b, replace=False) for _ in range(k)])).to(x.device)
+            _check(L.rimp2_mlp_fit(b, k, _ptr(x), _ptr(t), _ptr(idx), _ptr(self.params), _ptr(self.m), _ptr(self.v),
+                                   self.step + 1, self.lr, 0.9, 0.999, 1e-8, _ptr(loss), _ptr(ws), ws.numel(),
+                                   _stream_handle(None)))
+            self.step += k
+        return float(loss) if steps > 0 else float("nan")

@@ -51,3 +51,23 @@ def test_budget_threshold_is_the_bisection(nocc, budget):
         else:
             hi = mid
     assert SC.budget_threshold(pred, nocc, budget) == lo
+
+
+@pytest.mark.parametrize("n,batch,steps", [(50, 17, 1), (300, 64, 8), (300, 300, 9), (700, 5000, 17)])
+def test_fit_is_its_single_steps(n, batch, steps):
+    """Trainer.fit (steps in a row, rows gathered in the kernel) against the
+    same steps through mlp_loss_grad and adam on written-out minibatches: the
+    same sums in the same order, bit for bit; step counts around an upload."""
+    rng = np.random.default_rng(n + steps)
+    dx, dt, p = to_dev(rng.standard_normal((n, 4)), rng.standard_normal(n), rng.standard_normal(S.NP) * 0.3)
+    say("fit n=%d batch=%d steps=%d" % (n, batch, steps))
+    q, m, v = p.clone(), torch.zeros_like(p), torch.zeros_like(p)
+    tr = SC.Trainer(p.clone(), lr=1e-2)
+    last = tr.fit(dx, dt, steps=steps, batch=batch, seed=3)
+    draw, loss = np.random.default_rng(3), None
+    for k in range(steps):
+        idx = torch.from_numpy(draw.choice(n, size=min(batch, n), replace=False)).to("cuda:0")
+        loss, grad = SC.mlp_loss_grad(dx.index_select(0, idx), dt.index_select(0, idx), q)
+        SC.adam(grad, q, m, v, k + 1, 1e-2)
+    assert tr.step == steps and float(loss) == last
+    assert torch.equal(tr.params, q) and torch.equal(tr.m, m) and torch.equal(tr.v, v)
