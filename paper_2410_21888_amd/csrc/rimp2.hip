@@ -2297,10 +2297,16 @@ __global__ __launch_bounds__(256) void coulomb_vector_kernel(const double* Bf, D
   part[z * naux + P] = s;
 }
 
-// The antisymmetrised term G[p][q] = 2 sum_P Bf[r0 + p][c0 + q][P] c[P] - K[p][q]
-// for p < nrows, q < ncols; one wave per (p, q), lanes over P, fixed-order wave
-// reduction.  ROLE 0 writes it to F (row stride ldf).  For the Z-vector's rows
-// a and columns i (gap = (eps_a - eps_i)/2):
+// The antisymmetrised term G[p][q] = 2 sum_P Bf[r0 + p][c0 + q][P] c[P] - sum_s
+// Kp[s][p][q] (the splits of the exchange product) for p < nrows, q < ncols.
+// A workgroup takes kCombine neighbouring (p, q): its waves two each for the sum
+// over P (lanes over P), all of them together for the sums over the splits
+// (lanes over the pairs first, so that a split's row is read in whole sectors);
+// every sum in a fixed order.  Bound by the read of Bf.  A launch
+// of its own for the splits before one wave per (p, q) took 7 + 11 us at 200 x
+// 40 pairs of 720; the splits read by that wave, one double a sector, 18; this 13.
+// ROLE 0 writes G to F (row stride ldf).  For the Z-vector's rows a and columns
+// i (gap = (eps_a - eps_i)/2):
 //   ROLE 1  F = gap x[a][i] + G                                (operator)
 //   ROLE 2  F = L2[a][i] - L1[i][nocc + a] - G (right-hand side), diag = gap +
 //           sum_P Bf[a][i][P]^2 (the operator's diagonal), x = F / diag
@@ -2308,30 +2314,48 @@ struct ZElem {
   const double *eo, *ev, *L1, *L2;
   double *x, *diag;
 };
+constexpr int kCombine = 8;
 template <int ROLE>
 __global__ __launch_bounds__(256) void antisym_combine_kernel(const double* Bf, int64_t nmo, int64_t naux,
                                                               int64_t r0, int64_t nrows, int64_t c0, int64_t ncols,
-                                                              const double* c, const double* K, double* F,
-                                                              int64_t ldf, ZElem z, const int32_t* status) {
+                                                              const double* c, const double* Kp, int splits,
+                                                              double* F, int64_t ldf, ZElem z,
+                                                              const int32_t* status) {
   if (*status != 0) return;
-  const int64_t e = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
-  if (e >= nrows * ncols) return;
-  const int64_t p = e / ncols, q = e - p * ncols;
-  const double* row = Bf + ((r0 + p) * nmo + c0 + q) * naux;
-  double s = 0.0, d = 0.0;
+  __shared__ double sk[4][kCombine], ss[kCombine], sd[kCombine];
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const int64_t n = nrows * ncols, e0 = (int64_t)blockIdx.x * kCombine;
+  // the last workgroup's missing pairs repeat the last pair
+  const int64_t e1 = min(n - 1, e0 + 2 * wave), e2 = min(n - 1, e0 + 2 * wave + 1);
+  const double* row1 = Bf + ((r0 + e1 / ncols) * nmo + c0 + e1 % ncols) * naux;
+  const double* row2 = Bf + ((r0 + e2 / ncols) * nmo + c0 + e2 % ncols) * naux;
+  const int64_t ek = min(n - 1, e0 + (t & (kCombine - 1)));
+  double k = 0.0, s1 = 0.0, s2 = 0.0, d1 = 0.0, d2 = 0.0;
+#pragma unroll 2
+  for (int sp = t / kCombine; sp < splits; sp += 256 / kCombine) k += Kp[sp * n + ek];
 #pragma unroll 4
   for (int64_t P = lane; P < naux; P += 64) {
-    const double b = row[P];
-    s += b * c[P];
-    if (ROLE == 2) d += b * b;
+    const double b1 = row1[P], b2 = row2[P], cp = c[P];
+    s1 += b1 * cp;
+    s2 += b2 * cp;
+    if (ROLE == 2) { d1 += b1 * b1; d2 += b2 * b2; }
   }
   for (int off = 32; off > 0; off >>= 1) {
-    s += __shfl_down(s, off, 64);
-    if (ROLE == 2) d += __shfl_down(d, off, 64);
+    if (off >= kCombine) k += __shfl_down(k, off, 64);
+    s1 += __shfl_down(s1, off, 64);
+    s2 += __shfl_down(s2, off, 64);
+    if (ROLE == 2) { d1 += __shfl_down(d1, off, 64); d2 += __shfl_down(d2, off, 64); }
   }
-  if (lane != 0) return;
-  const double g = 2.0 * s - K[p * ncols + q];
+  if (lane < kCombine) sk[wave][lane] = k;
+  if (lane == 0) {
+    ss[2 * wave] = s1; ss[2 * wave + 1] = s2;
+    if (ROLE == 2) { sd[2 * wave] = d1; sd[2 * wave + 1] = d2; }
+  }
+  __syncthreads();
+  const int64_t e = e0 + t;
+  if (t >= kCombine || e >= n) return;
+  const int64_t p = e / ncols, q = e - p * ncols;
+  const double g = 2.0 * ss[t] - (((sk[0][t] + sk[1][t]) + sk[2][t]) + sk[3][t]);
   if (ROLE == 0) {
     F[p * ldf + q] = g;
     return;
@@ -2340,7 +2364,7 @@ __global__ __launch_bounds__(256) void antisym_combine_kernel(const double* Bf, 
   if (ROLE == 1) {
     F[e] = gap * z.x[e] + g;
   } else {
-    const double rhs = (z.L2[p * nmo + q] - z.L1[q * nmo + ncols + p]) - g, dg = gap + d;
+    const double rhs = (z.L2[p * nmo + q] - z.L1[q * nmo + ncols + p]) - g, dg = gap + sd[t];
     F[e] = rhs;
     z.diag[e] = dg;
     z.x[e] = rhs / dg;
@@ -2351,7 +2375,7 @@ struct AntisymPlan {
   int64_t nmo, naux, nrows, ncols, nr, nc, chunks, chunk;
   bool rows_first;
   GemmChoice c_k;
-  size_t off_status, off_cpart, off_c, off_Y, off_Kp, off_K, total;
+  size_t off_status, off_cpart, off_c, off_Y, off_Kp, total;
 };
 
 // nrows x ncols results from a density whose nonzero block is nr x nc.
@@ -2372,7 +2396,6 @@ AntisymPlan antisym_plan(int64_t nmo, int64_t naux, int64_t nrows, int64_t ncols
   A.off_c = off; off = align_up(off + 8 * (size_t)naux);
   A.off_Y = off; off = align_up(off + 8 * (size_t)(A.rows_first ? nrows * nr : nc * ncols) * naux);
   A.off_Kp = off; off = align_up(off + 8 * (size_t)A.c_k.splits * nrows * ncols);
-  A.off_K = off; off = align_up(off + 8 * (size_t)nrows * ncols);
   A.total = off;
   return A;
 }
@@ -2396,7 +2419,6 @@ int antisym_run(const AntisymPlan& A, const double* Bf, const DBlock& d, int64_t
   double* c = (double*)(ws + A.off_c);
   double* Y = (double*)(ws + A.off_Y);
   double* Kp = (double*)(ws + A.off_Kp);
-  double* K = (double*)(ws + A.off_K);
   int rc;
   if ((rc = traced(R_RESPONSE, 0, 0, 8.0 * d.nr * d.nc * (naux + 1), st, [&] {
          hipLaunchKernelGGL(coulomb_vector_kernel, dim3((unsigned)cdiv(naux, 256), (unsigned)A.chunks), dim3(256), 0,
@@ -2441,14 +2463,9 @@ int antisym_run(const AntisymPlan& A, const double* Bf, const DBlock& d, int64_t
   gk.C = Kp; gk.ldc = ncols; gk.split_stride = nrows * ncols; gk.status = status;
   const int64_t splits = cdiv(gk.K, cdiv(gk.kchunk, kBK) * kBK), n = nrows * ncols;
   if ((rc = launch_lterm(A.c_k.bm, gk, st, R_RESPONSE, 2.0 * n * gk.K, 8.0 * (nrows + ncols) * gk.K))) return rc;
-  if ((rc = traced(R_REDUCE, 0, 0, 8.0 * (splits + 1) * n, st, [&] {
-         hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)reduce_blocks(n, splits)), dim3(256), 0, st, K, ncols,
-                            (const double*)Kp, ncols, n, (int)splits, nrows, ncols, 1.0, 0, status);
-       })))
-    return rc;
-  return traced(R_RESPONSE, 0, 0, 8.0 * n * (naux + 2), st, [&] {
-    hipLaunchKernelGGL(antisym_combine_kernel<ROLE>, dim3((unsigned)cdiv(n, 4)), dim3(256), 0, st, Bf, nmo, naux, r0,
-                       nrows, c0, ncols, (const double*)c, (const double*)K, F, ldf, z, status);
+  return traced(R_RESPONSE, 0, 0, 8.0 * n * (naux + splits + 1), st, [&] {
+    hipLaunchKernelGGL(antisym_combine_kernel<ROLE>, dim3((unsigned)cdiv(n, kCombine)), dim3(256), 0, st, Bf, nmo, naux, r0,
+                       nrows, c0, ncols, (const double*)c, (const double*)Kp, (int)splits, F, ldf, z, status);
   });
 }
 
@@ -2474,58 +2491,101 @@ __global__ __launch_bounds__(256) void assemble_density_kernel(int64_t nocc, int
 // nov elements; scal = (p.q, r.(r / diag), r.r, rhs.rhs).  Latency-bound: as one
 // launch per dot product and update, with a read-back for each dot product, an
 // iteration at nov = 8000 spent about 90 us on them; as one launch and one
-// read-back about 30.
+// read-back about 30, 18 of them in the kernel with its sums over LDS in ten
+// barriers each and every vector read once a pass, 11 like this.
 constexpr int kCgThreads = 1024;
-__device__ __forceinline__ double cg_sum(double s) {
-  __shared__ double sh[kCgThreads];
-  sh[threadIdx.x] = s;
-  __syncthreads();
-  for (int w = kCgThreads / 2; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
-    __syncthreads();
+constexpr int kCgWaves = kCgThreads / 64;
+// The sums of N values over the workgroup: a shuffle tree in each wave, then
+// one over the waves' totals, which every wave does for itself.
+template <int N>
+__device__ __forceinline__ void cg_sum(double (&v)[N]) {
+  __shared__ double sh[N][kCgWaves];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    for (int off = 32; off > 0; off >>= 1) v[i] += __shfl_down(v[i], off, 64);
+    if (lane == 0) sh[i][wave] = v[i];
   }
-  const double t = sh[0];
   __syncthreads();
-  return t;
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    v[i] = sh[i][lane & (kCgWaves - 1)];
+    for (int off = kCgWaves / 2; off > 0; off >>= 1) v[i] += __shfl_xor(v[i], off, 64);
+  }
 }
 // r = rhs - q, p = r / diag
 __global__ __launch_bounds__(kCgThreads) void cg_start_kernel(int64_t n, const double* rhs, const double* diag,
                                                               const double* q, double* r, double* p, double* scal) {
-  double rz = 0.0, rr = 0.0, bb = 0.0;
+  double sum[3] = {0.0, 0.0, 0.0};   // r.(r / diag), r.r, rhs.rhs
   for (int64_t k = threadIdx.x; k < n; k += kCgThreads) {
     const double b = rhs[k], rk = b - q[k], d = diag[k];
     r[k] = rk;
     p[k] = rk / d;
-    rz += rk * rk / d;
-    rr += rk * rk;
-    bb += b * b;
+    sum[0] += rk * rk / d;
+    sum[1] += rk * rk;
+    sum[2] += b * b;
   }
-  rz = cg_sum(rz); rr = cg_sum(rr); bb = cg_sum(bb);
-  if (threadIdx.x == 0) { scal[1] = rz; scal[2] = rr; scal[3] = bb; }
+  cg_sum(sum);
+  if (threadIdx.x == 0) { scal[1] = sum[0]; scal[2] = sum[1]; scal[3] = sum[2]; }
 }
 // One iteration after q = A p: alpha = rz / p.q, x += alpha p, r -= alpha q,
 // p = r / diag + (rz_new / rz) p.  Only scal[0] is written when p.q is not > 0
-// (the operator is not positive definite along p).
+// (the operator is not positive definite along p).  The first kCgHeld elements
+// of each thread stay in registers from the loads to the stores, all loads
+// being issued at once; the rest of a longer vector is read again in each of
+// the three passes.
+constexpr int kCgHeld = 8;
 __global__ __launch_bounds__(kCgThreads) void cg_step_kernel(int64_t n, const double* diag, const double* q, double* x,
                                                              double* r, double* p, double* scal) {
-  double s = 0.0;
-  for (int64_t k = threadIdx.x; k < n; k += kCgThreads) s += p[k] * q[k];
-  const double pq = cg_sum(s), rz = scal[1];
-  if (threadIdx.x == 0) scal[0] = pq;
-  if (!(pq > 0.0)) return;
-  const double alpha = rz / pq;
-  double rz_new = 0.0, rr = 0.0;
-  for (int64_t k = threadIdx.x; k < n; k += kCgThreads) {
+  const int64_t t = threadIdx.x, rest = t + (int64_t)kCgHeld * kCgThreads;
+  const double rz = scal[1];
+  double hp[kCgHeld], hq[kCgHeld], hr[kCgHeld], hd[kCgHeld], hx[kCgHeld];
+#pragma unroll
+  for (int j = 0; j < kCgHeld; ++j) {
+    const int64_t k = t + (int64_t)j * kCgThreads;
+    const bool in = k < n;
+    hp[j] = in ? p[k] : 0.0;
+    hq[j] = in ? q[k] : 0.0;
+    hr[j] = in ? r[k] : 0.0;
+    hd[j] = in ? diag[k] : 1.0;
+    hx[j] = in ? x[k] : 0.0;
+  }
+  double pq[1] = {0.0};
+#pragma unroll
+  for (int j = 0; j < kCgHeld; ++j) pq[0] += hp[j] * hq[j];
+  for (int64_t k = rest; k < n; k += kCgThreads) pq[0] += p[k] * q[k];
+  cg_sum(pq);
+  if (t == 0) scal[0] = pq[0];
+  if (!(pq[0] > 0.0)) return;
+  const double alpha = rz / pq[0];
+  double sum[2] = {0.0, 0.0};   // r.(r / diag), r.r
+#pragma unroll
+  for (int j = 0; j < kCgHeld; ++j) {
+    hr[j] -= alpha * hq[j];
+    hd[j] = hr[j] / hd[j];
+    sum[0] += hr[j] * hd[j];
+    sum[1] += hr[j] * hr[j];
+  }
+  for (int64_t k = rest; k < n; k += kCgThreads) {
     const double rk = r[k] - alpha * q[k];
     x[k] += alpha * p[k];
     r[k] = rk;
-    rz_new += rk * rk / diag[k];
-    rr += rk * rk;
+    sum[0] += rk * (rk / diag[k]);
+    sum[1] += rk * rk;
   }
-  rz_new = cg_sum(rz_new); rr = cg_sum(rr);
-  const double beta = rz_new / rz;
-  for (int64_t k = threadIdx.x; k < n; k += kCgThreads) p[k] = r[k] / diag[k] + beta * p[k];
-  if (threadIdx.x == 0) { scal[1] = rz_new; scal[2] = rr; }
+  cg_sum(sum);
+  const double beta = sum[0] / rz;
+#pragma unroll
+  for (int j = 0; j < kCgHeld; ++j) {
+    const int64_t k = t + (int64_t)j * kCgThreads;
+    if (k < n) {
+      x[k] = hx[j] + alpha * hp[j];
+      r[k] = hr[j];
+      p[k] = hd[j] + beta * hp[j];
+    }
+  }
+  for (int64_t k = rest; k < n; k += kCgThreads) p[k] = r[k] / diag[k] + beta * p[k];
+  if (t == 0) { scal[1] = sum[0]; scal[2] = sum[1]; }
 }
 
 // W[p][q] = (eps_p + eps_q)/2 D[p][q] + (p < nocc ? F[p][q] + L1[p][q] : L2[p - nocc][q]),
