@@ -2420,11 +2420,19 @@ int antisym_run(const AntisymPlan& A, const double* Bf, const DBlock& d, int64_t
   double* Y = (double*)(ws + A.off_Y);
   double* Kp = (double*)(ws + A.off_Kp);
   int rc;
-  if ((rc = traced(R_RESPONSE, 0, 0, 8.0 * d.nr * d.nc * (naux + 1), st, [&] {
+  // c is the trace of Z over r = p, or of Y over s = q, where those run over the
+  // same orbitals (the Z-vector's operator, every full density); else a pass
+  // over Bf of its own.  At 40/200/720 the pass and its reduction took 24 us, the
+  // trace 5.
+  const bool trace = A.rows_first ? (r0 == d.r0 && nrows == d.nr) : (c0 == d.c0 && ncols == d.nc);
+  auto sum_c = [&](const double* part, int64_t terms, int64_t stride) {
+    hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)reduce_blocks(naux, terms)), dim3(256), 0, st, c, naux, part,
+                       naux, stride, (int)terms, (int64_t)1, naux, 1.0, 0, status);
+  };
+  if (!trace && (rc = traced(R_RESPONSE, 0, 0, 8.0 * d.nr * d.nc * (naux + 1), st, [&] {
          hipLaunchKernelGGL(coulomb_vector_kernel, dim3((unsigned)cdiv(naux, 256), (unsigned)A.chunks), dim3(256), 0,
                             st, Bf, d, nmo, naux, A.chunk, cpart, status);
-         hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)reduce_blocks(naux, A.chunks)), dim3(256), 0, st, c, naux,
-                            (const double*)cpart, naux, naux, (int)A.chunks, (int64_t)1, naux, 1.0, 0, status);
+         sum_c(cpart, A.chunks, naux);
        })))
     return rc;
   GemmParams gk{};
@@ -2458,6 +2466,10 @@ int antisym_run(const AntisymPlan& A, const double* Bf, const DBlock& d, int64_t
     gk.K = d.nc * naux;
     gk.A = kop(Bf + (r0 * nmo + d.c0) * naux, nmo * naux, INT64_MAX, 0);
     gk.Bk = kop(Y, naux, naux, ncols * naux);
+  }
+  if (trace) {
+    const int64_t terms = A.rows_first ? d.nr : d.nc, width = A.rows_first ? d.nr : ncols;
+    if ((rc = traced(R_RESPONSE, 0, 0, 8.0 * (terms + 1) * naux, st, [&] { sum_c(Y, terms, (width + 1) * naux); }))) return rc;
   }
   gk.kchunk = cdiv(gk.K, A.c_k.splits);
   gk.C = Kp; gk.ldc = ncols; gk.split_stride = nrows * ncols; gk.status = status;
