@@ -113,8 +113,8 @@ int rimp2_antisym_term(int32_t nmo, int32_t naux, int32_t r0, int32_t nrows, int
  *   D_ai          device, write [nvir][nocc]
  *   iterations    host, write (may be NULL): iterations run
  *   rel_residual  host, write (may be NULL): ||rhs - A D_ai|| / ||rhs||
- * The call synchronises `stream` once per iteration (the host reads the CG
- * scalars).  Returns RIMP2_ENOCONV, with D_ai holding the last iterate, when
+ * The call synchronises `stream` once for every four iterations (the host reads
+ * the CG scalars; what is queued past the last iteration does nothing).  Returns RIMP2_ENOCONV, with D_ai holding the last iterate, when
  * the tolerance is not reached or the operator is not positive definite
  * along a search direction.
  */

@@ -2500,7 +2500,9 @@ __global__ __launch_bounds__(256) void assemble_density_kernel(int64_t nocc, int
 }
 
 // CG's vector algebra, one workgroup (its sums in a fixed order), on vectors of
-// nov elements; scal = (p.q, r.(r / diag), r.r, rhs.rhs).  Latency-bound: as one
+// nov elements; scal = (p.q, r.(r / diag), r.r, rhs.rhs, iterations).  Both set
+// the status word once there is nothing left to iterate (r.r <= tol^2 rhs.rhs, or
+// the break below), which empties every launch that follows.  Latency-bound: as one
 // launch per dot product and update, with a read-back for each dot product, an
 // iteration at nov = 8000 spent about 90 us on them; as one launch and one
 // read-back about 30, 18 of them in the kernel with its sums over LDS in ten
@@ -2527,7 +2529,8 @@ __device__ __forceinline__ void cg_sum(double (&v)[N]) {
 }
 // r = rhs - q, p = r / diag
 __global__ __launch_bounds__(kCgThreads) void cg_start_kernel(int64_t n, const double* rhs, const double* diag,
-                                                              const double* q, double* r, double* p, double* scal) {
+                                                              const double* q, double* r, double* p, double* scal,
+                                                              double tol, int32_t* status) {
   double sum[3] = {0.0, 0.0, 0.0};   // r.(r / diag), r.r, rhs.rhs
   for (int64_t k = threadIdx.x; k < n; k += kCgThreads) {
     const double b = rhs[k], rk = b - q[k], d = diag[k];
@@ -2538,7 +2541,10 @@ __global__ __launch_bounds__(kCgThreads) void cg_start_kernel(int64_t n, const d
     sum[2] += b * b;
   }
   cg_sum(sum);
-  if (threadIdx.x == 0) { scal[1] = sum[0]; scal[2] = sum[1]; scal[3] = sum[2]; }
+  if (threadIdx.x == 0) {
+    scal[1] = sum[0]; scal[2] = sum[1]; scal[3] = sum[2]; scal[4] = 0.0;
+    if (!(sum[1] > tol * tol * sum[2])) *status = 1;
+  }
 }
 // One iteration after q = A p: alpha = rz / p.q, x += alpha p, r -= alpha q,
 // p = r / diag + (rz_new / rz) p.  Only scal[0] is written when p.q is not > 0
@@ -2548,7 +2554,9 @@ __global__ __launch_bounds__(kCgThreads) void cg_start_kernel(int64_t n, const d
 // the three passes.
 constexpr int kCgHeld = 8;
 __global__ __launch_bounds__(kCgThreads) void cg_step_kernel(int64_t n, const double* diag, const double* q, double* x,
-                                                             double* r, double* p, double* scal) {
+                                                             double* r, double* p, double* scal, double tol,
+                                                             int32_t* status) {
+  if (*status != 0) return;
   const int64_t t = threadIdx.x, rest = t + (int64_t)kCgHeld * kCgThreads;
   const double rz = scal[1];
   double hp[kCgHeld], hq[kCgHeld], hr[kCgHeld], hd[kCgHeld], hx[kCgHeld];
@@ -2568,7 +2576,10 @@ __global__ __launch_bounds__(kCgThreads) void cg_step_kernel(int64_t n, const do
   for (int64_t k = rest; k < n; k += kCgThreads) pq[0] += p[k] * q[k];
   cg_sum(pq);
   if (t == 0) scal[0] = pq[0];
-  if (!(pq[0] > 0.0)) return;
+  if (!(pq[0] > 0.0)) {
+    if (t == 0) *status = 1;
+    return;
+  }
   const double alpha = rz / pq[0];
   double sum[2] = {0.0, 0.0};   // r.(r / diag), r.r
 #pragma unroll
@@ -2597,7 +2608,10 @@ __global__ __launch_bounds__(kCgThreads) void cg_step_kernel(int64_t n, const do
     }
   }
   for (int64_t k = rest; k < n; k += kCgThreads) p[k] = r[k] / diag[k] + beta * p[k];
-  if (t == 0) { scal[1] = sum[0]; scal[2] = sum[1]; }
+  if (t == 0) {
+    scal[1] = sum[0]; scal[2] = sum[1]; scal[4] += 1.0;
+    if (!(sum[1] > tol * tol * scal[3])) *status = 1;
+  }
 }
 
 // W[p][q] = (eps_p + eps_q)/2 D[p][q] + (p < nocc ? F[p][q] + L1[p][q] : L2[p - nocc][q]),
@@ -2648,9 +2662,12 @@ int clear_status(char* ws, hipStream_t st) {
   });
 }
 
-// Reads the CG scalars back (the iteration's one synchronisation).
+// Reads the CG scalars back (one synchronisation for kCgBatch iterations: a
+// read-back and the empty queue after it cost 25 us at 40/200/720, the launches
+// of an iteration after the last, which the status word empties, 15).
+constexpr int kCgBatch = 4;
 int read_scal(const double* d, double* h, hipStream_t st) {
-  HIP_TRY(hipMemcpyAsync(h, d, 4 * sizeof(double), hipMemcpyDeviceToHost, st));
+  HIP_TRY(hipMemcpyAsync(h, d, 5 * sizeof(double), hipMemcpyDeviceToHost, st));
   HIP_TRY(hipStreamSynchronize(st));
   return RIMP2_OK;
 }
@@ -2730,29 +2747,29 @@ int rimp2_zvector(int32_t nocc, int32_t nvir, int32_t naux, const double* Bf, co
                            ZElem{eps_occ, eps_vir, L1, L2, x, diag}, ws, st)))
     return rc;
   // preconditioned conjugate gradients
-  double h[4] = {0.0, 0.0, 0.0, 0.0};
+  int32_t* done = (int32_t*)(ws + Z.vo.off_status);
+  double h[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
   if ((rc = apply(x, q))) return rc;
   if ((rc = traced(R_RESPONSE, 0, 0, 8.0 * 5 * nov, st, [&] {
          hipLaunchKernelGGL(cg_start_kernel, dim3(1), dim3(kCgThreads), 0, st, nov, (const double*)rhs,
-                            (const double*)diag, (const double*)q, r, pv, scal);
+                            (const double*)diag, (const double*)q, r, pv, scal, tol, done);
        })))
     return rc;
-  if ((rc = read_scal(scal, h, st))) return rc;
-  const double bb = h[3], target = tol * tol * bb;
-  double rr = h[2];
+  double bb, rr, target;
   int it = 0;
-  while (rr > target && it < max_iter) {
-    if ((rc = apply(pv, q))) return rc;
-    if ((rc = traced(R_RESPONSE, 0, 0, 8.0 * 8 * nov, st, [&] {
-           hipLaunchKernelGGL(cg_step_kernel, dim3(1), dim3(kCgThreads), 0, st, nov, (const double*)diag,
-                              (const double*)q, x, r, pv, scal);
-         })))
-      return rc;
+  do {
+    for (int b = std::min(kCgBatch, max_iter - it); b > 0; --b) {
+      if ((rc = apply(pv, q))) return rc;
+      if ((rc = traced(R_RESPONSE, 0, 0, 8.0 * 8 * nov, st, [&] {
+             hipLaunchKernelGGL(cg_step_kernel, dim3(1), dim3(kCgThreads), 0, st, nov, (const double*)diag,
+                                (const double*)q, x, r, pv, scal, tol, done);
+           })))
+        return rc;
+    }
     if ((rc = read_scal(scal, h, st))) return rc;
-    if (!(h[0] > 0.0)) break;   // the operator is not positive definite along p
-    rr = h[2];
-    ++it;
-  }
+    rr = h[2]; bb = h[3]; target = tol * tol * bb; it = (int)h[4];
+    // h[0] = p.q: the operator is not positive definite along p
+  } while (rr > target && it < max_iter && h[0] > 0.0);
   if (iterations) *iterations = it;
   const double rel_res = bb > 0.0 ? sqrt(rr / bb) : sqrt(rr);
   if (rel_residual) *rel_residual = rel_res;

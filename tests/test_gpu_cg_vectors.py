@@ -10,8 +10,10 @@ about 60): 3e-12 at most, 1e-11 asked.
 """
 import numpy as np
 import pytest
+import torch
 
 from oracle import rimp2_oracle as O
+import paper_2410_21888_amd as rm
 from paper_2410_21888_amd import gradient as G
 from gpu_util import to_dev, say
 from test_gpu_response import full_factor
@@ -45,3 +47,24 @@ def test_zvector_residual(shape):
     rel = np.linalg.norm(r) / np.linalg.norm(rhs)
     say("  %d iterations, residual of the solution %.2e" % (it, rel))
     assert rel <= 1e-11
+
+
+@pytest.mark.parametrize("tol", [1e-2, 1e-4, 1e-6, 1e-8, 1e-10])
+def test_zvector_stops_where_it_converges(tol):
+    """Iterations are queued four at a time: whatever remainder the last one falls on,
+    a limit of just as many gives the same bits, and one fewer is too few."""
+    nocc, nvir, naux = 6, 30, 64
+    nmo = nocc + nvir
+    Bf, eo, ev = full_factor(nocc, nvir, naux, 7)
+    rng = np.random.default_rng(8)
+    args = to_dev(Bf, eo, ev, np.eye(nocc), np.eye(nvir), rng.standard_normal((nocc, nmo)),
+                  rng.standard_normal((nvir, nmo)))
+    D, it, res = G.zvector(*args, tol=tol)
+    say("zvector tol %g: %d iterations" % (tol, it))
+    assert it >= 1 and res <= tol
+    D2, it2, res2 = G.zvector(*args, tol=tol, max_iter=it)
+    assert it2 == it and res2 == res and torch.equal(D, D2)
+    if it > 1:
+        with pytest.raises(rm.Rimp2Error) as ei:
+            G.zvector(*args, tol=tol, max_iter=it - 1)
+        assert ei.value.code == rm.RIMP2_ENOCONV
