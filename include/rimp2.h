@@ -91,7 +91,7 @@ typedef struct {
                                formed, e_ij = e_ji = 0, and X_ij = T_ij = 0 in
                                Gamma and P (screening) */
   int32_t autotune;         /* nonzero: choose each FP64 GEMM's tile shape in situ
-                               (rimp2_autotune_report); 0 = fixed shapes */
+                               (rimp2_autotune_report); 0 = the plan's own */
   int32_t gemm_loader;      /* 0: each FP64 GEMM takes the fastest operand
                                loader its shape allows; 1: the general loader
                                only.  Both sum every element in the same order,
@@ -205,11 +205,11 @@ typedef struct {
  * A fragment whose whole slab (all its occupied pairs) fits the wave budget
  * (opts->slab_budget_bytes, default 64 GiB) is packed into a wave; each step
  * of a wave -- gap check, (ia|jb), amplitudes, Gamma, P_ab, P_ij, reductions,
- * E -- is ONE grouped launch over all of its fragments (the GEMMs are
- * persistent launches whose workgroups take (fragment, tile) items from a
- * counter, largest fragment first).  Larger fragments run alone, as
+ * E -- is ONE grouped launch over all of its fragments (the GEMMs with one
+ * workgroup per (fragment, tile) item, each fragment's product with its own
+ * tile shape).  Larger fragments run alone, as
  * rimp2_fragment does.  With opts->precision = RIMP2_SPLIT_INT8 the (ia|jb)
- * and Gamma products of a wave are grouped split products (one persistent
+ * and Gamma products of a wave are grouped split products (one
  * launch per reduction window of 2816 over all fragments of the wave), after
  * grouped digit splits (one launch per split step over the wave); P_ab and
  * P_ij stay FP64.  pair_skip must be NULL.  With opts->autotune the grouped FP64 GEMM
@@ -283,7 +283,7 @@ int rimp2_timing_collect(rimp2_kernel_stat* stats, int32_t capacity, int32_t* co
  * stream; the host never waits for them, and once every candidate's events
  * have completed (checked without blocking at the next launch of the shape),
  * the candidate with the smallest time is used from then on.  Until then
- * launches use the fixed default.  Nothing is trialled while the stream is
+ * launches use the tile that the plan chose.  Nothing is trialled while the stream is
  * being captured into a graph.  The tile shape does not change the order in
  * which any output element is summed, so results are bitwise identical
  * whichever candidate runs.  The table is process-wide and thread-safe.

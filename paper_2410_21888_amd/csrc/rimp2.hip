@@ -737,7 +737,7 @@ void launch_oz8(OzParams op, int side, bool windowed, hipStream_t st) {
   // one LDS stage (two workgroups per CU) unless a windowed product with at
   // most 5 digits, where the double-buffered stage (still two per CU) was faster
   else if (windowed && S <= 5)
-    hipLaunchKernelGGL((gemm_oz8_kernel<S, 2, OzSmall>), dim3((unsigned)nwg), dim3(256), 0, st, op);
+    hipLaunchKernelGGL((gemm_oz8_kernel<S <= 5 ? S : 5, 2, OzSmall>), dim3((unsigned)nwg), dim3(256), 0, st, op);
   else
     hipLaunchKernelGGL((gemm_oz8_kernel<S, 1, OzSmall>), dim3((unsigned)nwg), dim3(256), 0, st, op);
 }
