@@ -156,6 +156,17 @@ double gemm_us(const TileCost& t, int64_t tiles, int64_t K, int64_t splits) {
 // with 64, estimated alike).
 constexpr double kSmallerTile = 0.97;
 
+// What the table does not hold of long reductions.  Tiles that live long drift
+// apart, the operand panels they share fall out of the caches, and one sum of
+// many terms rounds more than the sum of several: splits of at most kSplitLen,
+// as far as kLongSplits go (P_ab of 6 orbitals' slabs of 200/1800, 2.2M long:
+// 124 ms in 4 splits, 122 in 64; Gamma of 200/1800/6000, 360000 long, takes 665
+// to 670 ms in 3, 11 or 61).  And operands that no cache holds reach the tiles
+// at 8 TB/s of staged bytes at most (P_ij of the same slabs: 36 ms with tiles
+// of 32, which the table prefers, 31 with 64).
+constexpr int64_t kSplitLen = 32768, kLongSplits = 64;
+constexpr double kCacheBytes = 256e6, kStageBytesPerUs = 8e6;
+
 struct GemmChoice {
   int bm;           // square tile
   int64_t splits;   // split-K factor
@@ -173,14 +184,16 @@ GemmChoice choose_gemm(int64_t M, int64_t N, int64_t K, bool tri, const int* bms
   GemmChoice best{0, 1};
   double best_us = 0.0;
   smax = std::max<int64_t>(1, std::min<int64_t>(smax, K / (4 * kBK)));
+  const int64_t smin = std::min<int64_t>({smax, kLongSplits, cdiv(K, kSplitLen)});
+  const bool streamed = 8.0 * (M + N) * K > kCacheBytes;
   for (; *bms; ++bms) {
     const TileCost* t = kTileCost;
     while (t->bm != *bms) ++t;
     const int64_t tm = cdiv(M, t->bm), tn = cdiv(N, t->bm), tiles = (tri ? tm * (tm + 1) / 2 : tm * tn) * batch;
     for (int64_t w = 1; w <= 12; ++w) {
-      const int64_t s = std::min<int64_t>(smax, w <= 4 ? w : (w - 4) * (int64_t)kCUs / tiles);
-      if (s < 1) continue;
-      const double us = gemm_us(*t, tiles, K, s) + (s > 1 ? kReduceUs + 8.0 * (s + 1) * M * N / kReduceBytesPerUs : 0.0);
+      const int64_t s = std::max<int64_t>(smin, std::min<int64_t>(smax, w <= 4 ? w : (w - 4) * (int64_t)kCUs / tiles));
+      const double staged = streamed ? 16.0 * tiles * t->bm * K / kStageBytesPerUs : 0.0;
+      const double us = std::max(gemm_us(*t, tiles, K, s), staged) + (s > 1 ? kReduceUs + 8.0 * (s + 1) * M * N / kReduceBytesPerUs : 0.0);
       if (best.bm == 0 || us < best_us * (t->bm < best.bm ? kSmallerTile : 1.0)) {
         best_us = us;
         best = GemmChoice{t->bm, s};
