@@ -160,10 +160,11 @@ constexpr double kSmallerTile = 0.97;
 // apart, the operand panels they share fall out of the caches, and one sum of
 // many terms rounds more than the sum of several: splits of at most kSplitLen,
 // as far as kLongSplits go (P_ab of 6 orbitals' slabs of 200/1800, 2.2M long:
-// 124 ms in 4 splits, 122 in 64; Gamma of 200/1800/6000, 360000 long, takes 665
-// to 670 ms in 3, 11 or 61).  And operands that no cache holds reach the tiles
-// at 8 TB/s of staged bytes at most (P_ij of the same slabs: 36 ms with tiles
-// of 32, which the table prefers, 31 with 64).
+// 129 ms and 5.0e11 bytes of HBM in 4 splits, 116 ms and 3.8e11 in 64; Gamma of
+// 200/1800/6000, 360000 long: 679 ms and 1.35e12 in 3, 667 and 9.7e11 in 11).
+// And operands that no cache holds reach the tiles at 8 TB/s of staged bytes at
+// most (P_ij of the same slabs: 35 ms with tiles of 32, which the table prefers,
+// 30 with 64).
 constexpr int64_t kSplitLen = 32768, kLongSplits = 64;
 constexpr double kCacheBytes = 256e6, kStageBytesPerUs = 8e6;
 
