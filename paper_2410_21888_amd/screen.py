@@ -152,6 +152,25 @@ def bound_mask(bound: torch.Tensor, budget_Eh: float) -> torch.Tensor:
     return torch.from_numpy(m).to(bound.device)
 
 
+def _check_fit(x: torch.Tensor, t: torch.Tensor, params: torch.Tensor) -> None:
+    """Refuses what rimp2_mlp_fit could not gather in bounds: its kernels read
+    rows of four features and one target a row straight from x and t."""
+    if x.dim() < 1 or x.numel() != 4 * x.shape[0]:
+        raise ValueError("x must hold four features a row, got shape %s" % (tuple(x.shape),))
+    if t.dim() < 1 or t.numel() != t.shape[0] or t.shape[0] < x.shape[0]:
+        raise ValueError("t must hold one target for each of the %d rows of x, got shape %s"
+                         % (x.shape[0], tuple(t.shape)))
+    if params.numel() < N_PARAMS or not params.is_contiguous():
+        raise ValueError("params must hold %d contiguous parameters, got shape %s" % (N_PARAMS, tuple(params.shape)))
+    for name, a in (("x", x), ("t", t), ("params", params)):
+        if a.dtype != torch.float64:
+            raise ValueError("%s must be float64, got %s" % (name, a.dtype))
+        if a.device != x.device:
+            raise ValueError("%s is on %s, x on %s" % (name, a.device, x.device))
+    if not x.is_cuda:
+        raise ValueError("x, t and params must be on the GPU, got %s" % x.device)
+
+
 class Trainer:
     """Adam on the mean squared error, minibatches drawn by a seeded host RNG."""
 
@@ -166,6 +185,8 @@ class Trainer:
         self._ws = {}
 
     def fit(self, x: torch.Tensor, t: torch.Tensor, steps: int, batch: int, seed: int = 0) -> float:
+        if steps > 0:
+            _check_fit(x, t, self.params)
         rng = np.random.default_rng(seed)
         n = x.shape[0]
         b = min(batch, n)
