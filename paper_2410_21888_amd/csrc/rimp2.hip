@@ -2541,13 +2541,16 @@ __device__ __forceinline__ void cg_sum(double (&v)[N]) {
     for (int off = kCgWaves / 2; off > 0; off >>= 1) v[i] += __shfl_xor(v[i], off, 64);
   }
 }
-// r = rhs - q, p = r / diag
+// x = p (the first iterate), r = rhs - q, p = r / diag.  x is the caller's
+// array, first written here, after every read of the caller's inputs: it may lie
+// over them.
 __global__ __launch_bounds__(kCgThreads) void cg_start_kernel(int64_t n, const double* rhs, const double* diag,
-                                                              const double* q, double* r, double* p, double* scal,
-                                                              double tol, int32_t* status) {
+                                                              const double* q, double* x, double* r, double* p,
+                                                              double* scal, double tol, int32_t* status) {
   double sum[3] = {0.0, 0.0, 0.0};   // r.(r / diag), r.r, rhs.rhs
   for (int64_t k = threadIdx.x; k < n; k += kCgThreads) {
     const double b = rhs[k], rk = b - q[k], d = diag[k];
+    x[k] = p[k];
     r[k] = rk;
     p[k] = rk / d;
     sum[0] += rk * rk / d;
@@ -2751,22 +2754,23 @@ int rimp2_zvector(int32_t nocc, int32_t nvir, int32_t naux, const double* Bf, co
   };
   if ((rc = clear_status(ws, st))) return rc;
   // right-hand side L''_ai - L'_ia - sum_pq G_ai^pq Dbar_pq, Dbar = D_ij (+)
-  // D_ab; Jacobi preconditioner: the operator's diagonal; x = rhs / diagonal
+  // D_ab; Jacobi preconditioner: the operator's diagonal; first iterate rhs /
+  // diagonal, in pv
   if ((rc = traced(R_RESPONSE, 0, 0, 8.0 * nmo * nmo, st, [&] {
          hipLaunchKernelGGL(assemble_density_kernel, dim3((unsigned)cdiv(nmo * nmo, 256)), dim3(256), 0, st, no, nv, P_ij,
                             P_ab, (const double*)nullptr, 0, 0, D);
        })))
     return rc;
   if ((rc = antisym_run<2>(Z.full, Bf, DBlock{D, nmo, 0, nmo, 0, nmo}, no, 0, rhs, no,
-                           ZElem{eps_occ, eps_vir, L1, L2, x, diag}, ws, st)))
+                           ZElem{eps_occ, eps_vir, L1, L2, pv, diag}, ws, st)))
     return rc;
   // preconditioned conjugate gradients
   int32_t* done = (int32_t*)(ws + Z.vo.off_status);
   double h[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-  if ((rc = apply(x, q))) return rc;
+  if ((rc = apply(pv, q))) return rc;
   if ((rc = traced(R_RESPONSE, 0, 0, 8.0 * 5 * nov, st, [&] {
          hipLaunchKernelGGL(cg_start_kernel, dim3(1), dim3(kCgThreads), 0, st, nov, (const double*)rhs,
-                            (const double*)diag, (const double*)q, r, pv, scal, tol, done);
+                            (const double*)diag, (const double*)q, x, r, pv, scal, tol, done);
        })))
     return rc;
   double bb, rr, target;
