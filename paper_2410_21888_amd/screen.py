@@ -128,9 +128,9 @@ def load_params(path: str, device) -> tuple[torch.Tensor, dict]:
 def budget_threshold(pred: torch.Tensor, nocc: int, budget_Eh: float, iters: int = 60) -> float:
     """The largest log10 threshold whose predicted skipped energy (sum of
     10^pred over the pairs it skips, rimp2_screen_mask) is at most budget_Eh,
-    by bisection over [-30, 0]."""
+    by bisection over [-30, 0] (without iterations, or fewer than none: -30)."""
     thr = torch.empty(1, dtype=torch.float64, device=pred.device)
-    _check(_L().rimp2_budget_threshold(nocc, _ptr(pred), budget_Eh, iters, _ptr(thr), _stream_handle(None)))
+    _check(_L().rimp2_budget_threshold(nocc, _ptr(pred), budget_Eh, max(iters, 0), _ptr(thr), _stream_handle(None)))
     return float(thr)
 
 
