@@ -154,9 +154,10 @@ int rimp2_fragment(int32_t nocc, int32_t nvir, int32_t naux,
  * inside the library's device code: each GPU that runs the library holds its
  * own copy from the first call on that device until the process ends.  The
  * call allocates nothing (no hipMalloc, hipFree, events or host tables): its
- * plan takes the largest slab group whose workspace fits the array (or
- * opts->slab_group when given), and a fragment whose workspace does not fit
- * even with one occupied orbital per group returns RIMP2_ENOMEM.
+ * plan divides the array between the slab group and the split-K partial sums
+ * as its time estimate has it (the slab group is opts->slab_group when given),
+ * and a fragment whose workspace does not fit even with one occupied orbital
+ * per group and without splits returns RIMP2_ENOMEM.
  * opts->autotune is not available here (RIMP2_ENOTSUP), and the timing of
  * rimp2_timing_enable records nothing for this call.
  *

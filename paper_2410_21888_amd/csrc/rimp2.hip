@@ -173,12 +173,31 @@ struct GemmChoice {
   int64_t splits;   // split-K factor
 };
 
+const TileCost& tile_cost(int bm) {
+  const TileCost* t = kTileCost;
+  while (t->bm != bm) ++t;
+  return *t;
+}
+int64_t square_tiles(int64_t M, int64_t N, int bm, bool tri) {
+  const int64_t tm = cdiv(M, bm), tn = cdiv(N, bm);
+  return tri ? tm * (tm + 1) / 2 : tm * tn;
+}
+// Estimate of an M x N x K product (`batch` of them in one launch) with choice
+// c, its reduction included.
+double product_us(int64_t M, int64_t N, int64_t K, bool tri, const GemmChoice& c, int64_t batch = 1) {
+  const int64_t tiles = square_tiles(M, N, c.bm, tri) * batch;
+  const bool streamed = 8.0 * (M + N) * K > kCacheBytes;
+  const double staged = streamed ? 16.0 * tiles * c.bm * K / kStageBytesPerUs : 0.0;
+  const double reduce = c.splits > 1 ? kReduceUs + 8.0 * (c.splits + 1) * M * N / kReduceBytesPerUs : 0.0;
+  return std::max(gemm_us(tile_cost(c.bm), tiles, K, c.splits), staged) + reduce;
+}
+
 // The tile (one of `bms`, 0 ends the list) and split-K factor (at most smax)
 // with the smallest estimate for an M x N x K product (tri: upper-triangular
 // tiles).  Split factors tried: 1 to 4 (they fill a ragged last round of many
-// tiles) and those that give every CU 1 to 8 workgroups.  With one tile shape and 64 splits of 2048 at most, P_ij of
-// nocc = 61 ran on 64 workgroups (8.0 ms, 1.6 ms now) and Gamma of 20/100/400 on
-// 64 (288 us, 90 us now).
+// tiles) and those that give every CU 1 to 8 workgroups.  With one tile shape
+// and 64 splits of 2048 at most, P_ij of nocc = 61 ran on 64 workgroups (8.0 ms,
+// 1.6 ms now) and Gamma of 20/100/400 on 64 (288 us, 90 us now).
 // batch: that many such products in one launch.
 GemmChoice choose_gemm(int64_t M, int64_t N, int64_t K, bool tri, const int* bms, int64_t smax = kMaxSplits,
                        int64_t batch = 1) {
@@ -186,18 +205,14 @@ GemmChoice choose_gemm(int64_t M, int64_t N, int64_t K, bool tri, const int* bms
   double best_us = 0.0;
   smax = std::max<int64_t>(1, std::min<int64_t>(smax, K / (4 * kBK)));
   const int64_t smin = std::min<int64_t>({smax, kLongSplits, cdiv(K, kSplitLen)});
-  const bool streamed = 8.0 * (M + N) * K > kCacheBytes;
   for (; *bms; ++bms) {
-    const TileCost* t = kTileCost;
-    while (t->bm != *bms) ++t;
-    const int64_t tm = cdiv(M, t->bm), tn = cdiv(N, t->bm), tiles = (tri ? tm * (tm + 1) / 2 : tm * tn) * batch;
+    const int64_t tiles = square_tiles(M, N, *bms, tri) * batch;
     for (int64_t w = 1; w <= 12; ++w) {
       const int64_t s = std::max<int64_t>(smin, std::min<int64_t>(smax, w <= 4 ? w : (w - 4) * (int64_t)kCUs / tiles));
-      const double staged = streamed ? 16.0 * tiles * t->bm * K / kStageBytesPerUs : 0.0;
-      const double us = std::max(gemm_us(*t, tiles, K, s), staged) + (s > 1 ? kReduceUs + 8.0 * (s + 1) * M * N / kReduceBytesPerUs : 0.0);
-      if (best.bm == 0 || us < best_us * (t->bm < best.bm ? kSmallerTile : 1.0)) {
+      const double us = product_us(M, N, K, tri, GemmChoice{*bms, s}, batch);
+      if (best.bm == 0 || us < best_us * (*bms < best.bm ? kSmallerTile : 1.0)) {
         best_us = us;
-        best = GemmChoice{t->bm, s};
+        best = GemmChoice{*bms, s};
       }
     }
   }
@@ -217,9 +232,8 @@ int64_t grouped_splits(int64_t K, int64_t klen) { return std::max<int64_t>(1, st
 // other products keep full: P_ij of nocc = 30 costs a third with tiles of 32
 // what it costs with 64, P_ab of nvir = 300 two thirds with 64 of 128.
 double grouped_cost(int bm, int64_t tiles) {
-  const TileCost* c = kTileCost;
-  while (c->bm != bm) ++c;
-  return tiles * (c->a + c->b * c->resident) / c->resident;
+  const TileCost& c = tile_cost(bm);
+  return tiles * (c.a + c.b * c.resident) / c.resident;
 }
 
 struct Plan {
@@ -231,7 +245,7 @@ struct Plan {
   bool split;                // RIMP2_SPLIT_INT8
   bool autotune;             // in-situ tile choice of the FP64 GEMMs
   bool general;              // FP64 GEMMs take the general loader only
-  int64_t max_splits;        // cap of every split-K factor
+  double part_bytes;         // cap of the split-K partial sums of each product
   int sv, sg;                // digits per operand of (ia|jb) and of Gamma
   int64_t kpv, kpg;          // padded reduction lengths of the split products
   size_t off_dbv, off_ev, off_dbg, off_eg, off_cmax, off_dt, off_et;
@@ -274,17 +288,24 @@ int64_t group_at(const Plan& P, int64_t k0) {
   return std::max<int64_t>(1, std::min<int64_t>({(int64_t)(P.budget / per_k), P.nocc - k0, red}));
 }
 
+// Split-K factor whose partial sums of an M x N product stay within the plan's cap.
+int64_t split_cap(const Plan& P, int64_t M, int64_t N) {
+  return std::max<int64_t>(1, (int64_t)std::min((double)kMaxSplits, P.part_bytes / (8.0 * M * N)));
+}
+
 // Tile and split-K factor of the symmetric path's Gamma GEMM over the row
 // blocks of a group of gc orbitals starting at k0 (reduction over the pairs
 // j >= k0).
 GemmChoice sym_gamma_choice(const Plan& P, int64_t k0, int64_t gc) {
-  return choose_gemm(gc * P.nvir, P.naux, (P.nocc - k0) * P.nvir, false, kGammaTiles, P.max_splits);
+  const int64_t M = gc * P.nvir;
+  return choose_gemm(M, P.naux, (P.nocc - k0) * P.nvir, false, kGammaTiles, split_cap(P, M, P.naux));
 }
 
 // grouped: the fragment runs in a batch wave (whole slab, no split amplitude
-// partials).  max_splits bounds the split-K partials in the workspace.
+// partials).  part_bytes bounds each product's split-K partials in the workspace.
+constexpr double kAnyPartBytes = 1e30;
 int make_plan(int64_t nocc, int64_t nvir, int64_t naux, bool gamma, bool density, const rimp2_opts* o, Plan* p,
-              bool grouped = false, int64_t max_splits = kMaxSplits) {
+              bool grouped = false, double part_bytes = kAnyPartBytes) {
   if (nocc < 1 || nvir < 1 || naux < 1 || nocc > (1 << 20) || nvir > (1 << 24) || naux > (1 << 24))
     return fail(RIMP2_EINVAL, "sizes must be >= 1 (nocc=%lld nvir=%lld naux=%lld)", (long long)nocc,
                 (long long)nvir, (long long)naux);
@@ -317,16 +338,17 @@ int make_plan(int64_t nocc, int64_t nvir, int64_t naux, bool gamma, bool density
     g = std::max<int64_t>(1, std::min<int64_t>(g, nocc));
   }
   p->g = g;
-  p->max_splits = max_splits;
+  p->part_bytes = part_bytes;
   p->c_ab = p->c_ij = p->c_gam = GemmChoice{0, 0};
   if (density && grouped) {
     p->c_ab.splits = grouped_splits(nocc * nocc * nvir, kGroupedPab);   // (the wave's lists choose the tiles)
     p->c_ij.splits = grouped_splits(nocc * nvir * nvir, kGroupedPij);
   } else if (density) {
-    p->c_ab = choose_gemm(nvir, nvir, g * nocc * nvir, true, kPabTiles, max_splits);
-    p->c_ij = choose_gemm(nocc, nocc, g * nvir * nvir, true, kPijTiles, max_splits);
+    p->c_ab = choose_gemm(nvir, nvir, g * nocc * nvir, true, kPabTiles, split_cap(*p, nvir, nvir));
+    p->c_ij = choose_gemm(nocc, nocc, g * nvir * nvir, true, kPijTiles, split_cap(*p, nocc, nocc));
   }
-  if (gamma) p->c_gam = choose_gemm(g * nvir, naux, nocc * nvir, false, kGammaTiles, grouped ? 1 : max_splits);
+  if (gamma)
+    p->c_gam = choose_gemm(g * nvir, naux, nocc * nvir, false, kGammaTiles, grouped ? 1 : split_cap(*p, g * nvir, naux));
   // slab elements (g x ncols pair blocks) and Gamma split partials of the
   // largest group
   double slab_elems = (double)g * nocc * nvir * nvir, gam_part = (double)p->c_gam.splits * g * nvir * naux;
@@ -511,23 +533,62 @@ int launch_gemm(GemmParams gp, hipStream_t st, int role, double af, double ab, b
 }
 
 
-// Tile of an (ia|jb) launch, over the tiles it keeps (no split-K: the
-// amplitude pass needs whole sums).
-int ints_tile(GemmParams gp) {
+// Sizes and pair fields of the (ia|jb) product of the slab group of gc orbitals
+// at k0: rows (kk, a) from k0, columns (j, b) over all orbitals, or (energy only
+// and the symmetric Gamma path, where pairs j < k come from their mirror) over
+// j >= k0.  Pairs with both orbitals in the group: blocks (k, j < k) are not
+// computed and the amplitude pass forms them from their transposes.
+GemmParams ints_product(const Plan& P, int64_t k0, int64_t gc) {
+  GemmParams gp{};
+  const int64_t j0 = (P.sym || !(P.gamma || P.density)) ? k0 : 0;
+  gp.M = gc * P.nvir; gp.N = (P.nocc - j0) * P.nvir; gp.K = P.naux; gp.kchunk = P.naux;
+  gp.skip_nvir = (int32_t)P.nvir; gp.skip_k0 = (int32_t)k0; gp.skip_j0 = (int32_t)j0; gp.skip_nocc = (int32_t)P.nocc;
+  gp.pair_upper = 1;
+  gp.pair_lo = (int32_t)k0;
+  return gp;
+}
+// Estimate of an (ia|jb) product over the tiles it keeps (no split-K: the
+// amplitude pass needs whole sums), and the tile with the smallest.
+double ints_us(GemmParams gp, int bm) {
+  // (raster groups of one row: exactly the tiles that are not skipped)
+  gp.tiles_m = (int32_t)cdiv(gp.M, bm); gp.tiles_n = (int32_t)cdiv(gp.N, bm); gp.group_m = 1;
+  return gemm_us(tile_cost(bm), gemm_tiles(gp, bm, bm, false), gp.K, 1);
+}
+int ints_tile(const GemmParams& gp) {
   int best = 0;
   double best_us = 0.0;
   for (const int* t = kIntsTiles; *t; ++t) {
-    const TileCost* c = kTileCost;
-    while (c->bm != *t) ++c;
-    // (raster groups of one row: exactly the tiles that are not skipped)
-    gp.tiles_m = (int32_t)cdiv(gp.M, *t); gp.tiles_n = (int32_t)cdiv(gp.N, *t); gp.group_m = 1;
-    const double us = gemm_us(*c, gemm_tiles(gp, *t, *t, false), gp.K, 1);
+    const double us = ints_us(gp, *t);
     if (best == 0 || us < best_us * kSmallerTile) {
       best = *t;
       best_us = us;
     }
   }
   return best;
+}
+
+// Estimate of a plan's products and of the launches of its slab groups, which
+// compares plans of one fragment (the amplitude passes, alike in all of them,
+// are left out; split products count as FP64 ones).
+constexpr double kGroupUs = 20.0;   // five or six launches a group
+double plan_us(const Plan& P) {
+  double us = 0.0;
+  for (int64_t k0 = 0, gc = 0; k0 < P.nocc; k0 += gc) {
+    gc = group_at(P, k0);
+    const GemmParams gp = ints_product(P, k0, gc);
+    us += kGroupUs + ints_us(gp, ints_tile(gp));
+    if (P.gamma) {
+      GemmChoice c = P.sym ? sym_gamma_choice(P, k0, gc) : P.c_gam;
+      if (P.split) c.splits = 1;
+      us += product_us(gp.M, P.naux, gp.N, false, c);
+    }
+    if (const int64_t later = (P.nocc - k0 - gc) * P.nvir; P.sym && later > 0)   // the transposed blocks' product
+      us += product_us(later, P.naux, gp.M, false, choose_gemm(later, P.naux, gp.M, false, kGammaTiles, 1));
+    if (P.density)
+      us += product_us(P.nvir, P.nvir, gc * P.nocc * P.nvir, true, P.c_ab) +
+            product_us(P.nocc, P.nocc, gc * P.nvir * P.nvir, true, P.c_ij);
+  }
+  return us;
 }
 
 // ---- in-situ tile autotuner (Sec. "GEMM runtime auto-tuning") -------------
@@ -934,23 +995,14 @@ int run_fragment(const Plan& P, const double* B, const double* eo, const double*
   };
   for (int64_t k0 = 0, gc = 0; k0 < nocc; k0 += gc) {
     gc = group_at(P, k0);
-    // (ia|jb) slab: rows (kk, a) of B starting at k0, columns (j, b) over all of B;
-    // energy only and the symmetric Gamma path: columns j >= k0 only (pairs
-    // j < k come from their mirror)
-    const int64_t j0 = (energy_only || P.sym) ? k0 : 0, ncols = nocc - j0, Lc = ncols * nvir;
+    GemmParams gp = ints_product(P, k0, gc);
+    const int64_t j0 = gp.skip_j0, ncols = nocc - j0, Lc = ncols * nvir;
     const double g = (double)gc, slab = 8.0 * g * (double)ncols * v * v;
     {
-      GemmParams gp{};
-      gp.M = gc * nvir; gp.N = Lc; gp.K = naux; gp.kchunk = naux;
       gp.A = kop(B + k0 * nvir * naux, naux, INT64_MAX, 0);
       gp.Bk = kop(B + j0 * nvir * naux, naux, INT64_MAX, 0);
       gp.C = V; gp.ldc = Lc; gp.split_stride = 0; gp.status = status;
-      gp.skip = skip; gp.skip_nvir = (int32_t)nvir; gp.skip_k0 = (int32_t)k0; gp.skip_j0 = (int32_t)j0;
-      gp.skip_nocc = (int32_t)nocc;
-      // pairs with both orbitals in the slab group: blocks (k, j < k) are not
-      // computed and the amplitude pass forms them from their transposes
-      gp.pair_upper = 1;
-      gp.pair_lo = (int32_t)k0;
+      gp.skip = skip;
       if (k0 == 0 && !P.split) {
         gp.status = nullptr;
         gp.gap_status = status; gp.gap_eo = eo; gp.gap_ev = ev;
@@ -1198,35 +1250,59 @@ int scratch_address(char** out) {
   return RIMP2_OK;
 }
 
-constexpr int64_t kNoallocSplits = 1;
+// Bytes of the largest array of split-K partial sums that fewer splits would shrink.
+double largest_part(const Plan& P) {
+  auto part = [](const GemmChoice& c, double elems) { return c.splits > 1 ? 8.0 * c.splits * elems : 0.0; };
+  double most = std::max(part(P.c_ab, (double)P.nvir * P.nvir), part(P.c_ij, (double)P.nocc * P.nocc));
+  if (P.gamma && !P.split && !P.sym) most = std::max(most, part(P.c_gam, (double)P.g * P.nvir * P.naux));
+  if (P.gamma && !P.split && P.sym)
+    for (int64_t k0 = 0, gc = 0; k0 < P.nocc; k0 += gc) {
+      gc = group_at(P, k0);
+      most = std::max(most, part(sym_gamma_choice(P, k0, gc), (double)gc * P.nvir * P.naux));
+    }
+  return most;
+}
+
 // The plan of rimp2_fragment_noalloc: the caller's options with, unless the
 // caller fixed the slab group, the largest slab budget whose workspace fits
-// the scratch array.
+// the scratch array.  Slabs and split-K partial sums share the array, so plans
+// with ever smaller partial sums are tried until one holds the whole fragment in
+// a slab or has no splits left, and the smallest estimate is taken.  (The plan's
+// own factors or else one split of each product, nothing between: P_ij of
+// 51/427/1404 summed 182000 terms a workgroup.)
 int noalloc_plan(int64_t nocc, int64_t nvir, int64_t naux, int want, const rimp2_opts* opts, Plan* P) {
   rimp2_opts o{};
   if (opts) o = *opts;
   if (o.autotune) return fail(RIMP2_ENOTSUP, "autotuning records events: not available without allocation");
   const bool gamma = want & RIMP2_WANT_GAMMA, density = want & RIMP2_WANT_DENSITY;
   int rc;
-  // with the plan's own split-K factors, and where their partials leave no
-  // room with few splits
-  for (int64_t max_splits : {kMaxSplits, kNoallocSplits}) {
-    if (o.slab_group == 0) {
-      o.slab_budget_bytes = kScratchBytes;
-      for (int it = 0; it < 64; ++it) {
-        if ((rc = make_plan(nocc, nvir, naux, gamma, density, &o, P, false, max_splits))) return rc;
-        if (P->total <= kScratchBytes) return RIMP2_OK;
-        const size_t over = P->total - kScratchBytes;
-        if (o.slab_budget_bytes <= over + 1) break;
-        o.slab_budget_bytes -= over + 1;   // the slabs shrink by at least the overshoot (or g reaches 1)
-      }
+  double best_us = -1.0;
+  Plan Q;
+  for (double part_bytes = kAnyPartBytes;; part_bytes = largest_part(Q) / 2.0) {
+    if (o.slab_group == 0) o.slab_budget_bytes = kScratchBytes;
+    if ((rc = make_plan(nocc, nvir, naux, gamma, density, &o, &Q, false, part_bytes))) return rc;
+    for (int it = 0; o.slab_group == 0 && it < 64 && Q.total > kScratchBytes; ++it) {
+      const size_t over = Q.total - kScratchBytes;
+      if (o.slab_budget_bytes <= over + 1) break;
+      o.slab_budget_bytes -= over + 1;   // the slabs shrink by at least the overshoot (or g reaches 1)
+      if ((rc = make_plan(nocc, nvir, naux, gamma, density, &o, &Q, false, part_bytes))) return rc;
     }
-    if ((rc = make_plan(nocc, nvir, naux, gamma, density, &o, P, false, max_splits))) return rc;
-    if (P->total <= kScratchBytes) return RIMP2_OK;
+    if (Q.total <= kScratchBytes) {
+      const bool whole = group_at(Q, 0) == nocc;
+      const double us = whole && best_us < 0.0 ? 0.0 : plan_us(Q);
+      if (best_us < 0.0 || us < best_us) {
+        best_us = us;
+        *P = Q;
+      }
+      if (whole) break;
+    }
+    if (largest_part(Q) == 0.0) break;
   }
-  return fail(RIMP2_ENOMEM, "fragment nocc=%lld nvir=%lld naux=%lld needs %zu bytes of scratch, more than the "
-                "%zu of rimp2_fragment_noalloc", (long long)nocc, (long long)nvir, (long long)naux, P->total,
+  if (best_us < 0.0)
+    return fail(RIMP2_ENOMEM, "fragment nocc=%lld nvir=%lld naux=%lld needs %zu bytes of scratch, more than the "
+                "%zu of rimp2_fragment_noalloc", (long long)nocc, (long long)nvir, (long long)naux, Q.total,
                 kScratchBytes);
+  return RIMP2_OK;
 }
 
 
