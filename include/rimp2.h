@@ -84,7 +84,9 @@ typedef struct {
   int32_t split_slices_gamma; /* RIMP2_SPLIT_INT8: digits per operand of Gamma,
                                3..7 (0 = 5) */
   size_t  slab_budget_bytes;/* cap on the slab part of the workspace when
-                               slab_group == 0; 0 = 64 GiB */
+                               slab_group == 0; 0 = 64 GiB.  The split-K partial
+                               sums of Gamma, P_ab and P_ij come on top: each at
+                               most an eighth of this, or 2 GiB if that is more */
   const uint8_t* pair_skip; /* device [nocc][nocc] or NULL: a nonzero (i,j) or
                                (j,i) marks the unordered occupied pair {i,j}
                                as screened out: its (ia|jb) blocks are not

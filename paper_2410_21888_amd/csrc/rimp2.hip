@@ -288,8 +288,10 @@ int64_t group_at(const Plan& P, int64_t k0) {
   return std::max<int64_t>(1, std::min<int64_t>({(int64_t)(P.budget / per_k), P.nocc - k0, red}));
 }
 
-// Split-K factor whose partial sums of an M x N product stay within the plan's cap.
+// Largest split-K factor of an M x N product: its partial sums stay within the
+// plan's cap, and one launch covers its reduction.
 int64_t split_cap(const Plan& P, int64_t M, int64_t N) {
+  if (cdiv(M * N, 256) > kMaxWorkgroups) return 1;
   return std::max<int64_t>(1, (int64_t)std::min((double)kMaxSplits, P.part_bytes / (8.0 * M * N)));
 }
 
@@ -301,8 +303,14 @@ GemmChoice sym_gamma_choice(const Plan& P, int64_t k0, int64_t gc) {
   return choose_gemm(M, P.naux, (P.nocc - k0) * P.nvir, false, kGammaTiles, split_cap(P, M, P.naux));
 }
 
+// Each product's split-K partial sums take at most this share of the slab budget,
+// or kPartFloor where that is more (kSplitLen's splits of a whole Gamma would take
+// 14 GB beside the slabs of 279/5366/7205, and P_ab's as much; the splits that
+// fill the chip stay below the floor).
+constexpr double kPartShare = 1.0 / 8.0, kPartFloor = 2.0 * (1ull << 30);
+
 // grouped: the fragment runs in a batch wave (whole slab, no split amplitude
-// partials).  part_bytes bounds each product's split-K partials in the workspace.
+// partials).  part_bytes: a tighter cap of each product's partial sums.
 constexpr double kAnyPartBytes = 1e30;
 int make_plan(int64_t nocc, int64_t nvir, int64_t naux, bool gamma, bool density, const rimp2_opts* o, Plan* p,
               bool grouped = false, double part_bytes = kAnyPartBytes) {
@@ -338,7 +346,7 @@ int make_plan(int64_t nocc, int64_t nvir, int64_t naux, bool gamma, bool density
     g = std::max<int64_t>(1, std::min<int64_t>(g, nocc));
   }
   p->g = g;
-  p->part_bytes = part_bytes;
+  p->part_bytes = std::min(part_bytes, std::max(kPartFloor, kPartShare * p->budget));
   p->c_ab = p->c_ij = p->c_gam = GemmChoice{0, 0};
   if (density && grouped) {
     p->c_ab.splits = grouped_splits(nocc * nocc * nvir, kGroupedPab);   // (the wave's lists choose the tiles)
