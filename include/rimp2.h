@@ -281,7 +281,7 @@ int rimp2_timing_collect(rimp2_kernel_stat* stats, int32_t capacity, int32_t* co
  * shapes of the FP64 MFMA GEMMs of rimp2_fragment (and of the fragments a
  * batch runs alone), not transposed operand layouts: the slab layout already
  * fixes the operands.  A shape is (role, M, N, K, split length, 16-byte-load
- * eligibility) on one device.  With opts->autotune set, the first launches of
+ * eligibility, the plan's own tile) on one device.  With opts->autotune set, the first launches of
  * a shape run each candidate twice, bracketed by events on the launch's
  * stream; the host never waits for them, and once every candidate's events
  * have completed (checked without blocking at the next launch of the shape),

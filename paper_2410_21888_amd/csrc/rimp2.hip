@@ -643,11 +643,16 @@ int launch_role(int role, int bm, const GemmParams& gp, hipStream_t st, double a
   }
 }
 
+// bm0: the plan's own tile, candidate 0.  Two plans of one fragment (other slab
+// groups) can give a shape different tiles, and an entry's trials and decision
+// name candidates by their place.  vec: 16-byte loads (+ 2: the general loader
+// only); 2 with `general` telling the loaders apart for a grouped launch.
 struct TuneKey {
-  int dev, role, vec;
+  int dev, role, vec, general, bm0;
   int64_t M, N, K, kchunk;
   bool operator<(const TuneKey& o) const {
-    return std::tie(dev, role, vec, M, N, K, kchunk) < std::tie(o.dev, o.role, o.vec, o.M, o.N, o.K, o.kchunk);
+    return std::tie(dev, role, vec, general, bm0, M, N, K, kchunk) <
+           std::tie(o.dev, o.role, o.vec, o.general, o.bm0, o.M, o.N, o.K, o.kchunk);
   }
 };
 struct TunePending {
@@ -779,7 +784,7 @@ int launch_tuned(int role, int bm0, const GemmParams& gp, bool autotune, bool ge
   HIP_TRY(hipGetDevice(&dev));
   // the key's loader field: 16-byte loads, and whether the fast loaders are allowed
   const int loader = (gemm_vec(gp, role == R_GAMMA || role == R_GAMMA_T, role == R_GAMMA_T) ? 1 : 0) + (general ? 2 : 0);
-  const TuneKey key{dev, role, loader, gp.M, gp.N, gp.K, gp.kchunk};
+  const TuneKey key{dev, role, loader, 0, bm0, gp.M, gp.N, gp.K, gp.kchunk};
   return tuned(key, nvar, c, st, [&](int v) { return launch_role(role, c[v].bm, gp, st, af, ab, general); });
 }
 
@@ -1378,6 +1383,7 @@ struct Wave {
 
 struct rimp2_batch_s {
   bool autotune = false;
+  bool general = false;            // FP64 GEMMs take the general loader only
   bool split = false;              // grouped split-precision products
   std::vector<rimp2_frag_desc> d;
   std::vector<int32_t> solo;       // fragments run alone
@@ -1428,6 +1434,7 @@ int batch_plan(int32_t nfrag, const rimp2_frag_desc* d, const rimp2_opts* opts, 
   if (opts && (opts->gemm_loader < 0 || opts->gemm_loader > 1))
     return fail(RIMP2_EINVAL, "gemm_loader must be 0 or 1 (got %d)", opts->gemm_loader);
   const bool general = opts && opts->gemm_loader == 1;
+  B->general = general;
   B->plan.resize(nfrag);
   const size_t budget = (opts && opts->slab_budget_bytes) ? opts->slab_budget_bytes : (size_t)64 << 30;
   std::vector<int32_t> order(nfrag), grouped;
@@ -1904,7 +1911,8 @@ int batch_run(rimp2_batch_s* B, int32_t* status_dev, void* workspace, size_t byt
       int64_t items[2] = {0, 0};
       for (int c = 0; c < 2; ++c)
         for (const GemmList& l : W.lists[rho][c]) items[c] += l.items;
-      const TuneKey key{dev, kBatchRole[rho], 2, n, items[0], items[1], (int64_t)(W.sig >> 1)};
+      const TuneKey key{dev, kBatchRole[rho], 2,        B->general ? 1 : 0,    W.tile_g[rho][0],
+                        n,   items[0],        items[1], (int64_t)(W.sig >> 1)};
       const TileShape cand[2] = {{W.tile_g[rho][0], W.tile_g[rho][0]}, {W.tile_g[rho][1], W.tile_g[rho][1]}};
       return tuned(key, 2, cand, st, launch);
     };
