@@ -34,8 +34,9 @@
  *  - Conditions only the device can see (an orbital-energy gap that would make
  *    a denominator >= 0, or a NaN orbital energy) are written as RIMP2_EGAP to
  *    the device status word in the workspace; every kernel of the call then
- *    does nothing and the outputs are left unwritten.  Read it with
- *    rimp2_read_status() after the stream has run the call.
+ *    does nothing and the outputs are left unwritten (a small fragment's first
+ *    (ia|jb) product, up to about 100 us into the workspace, runs beside the
+ *    check).  Read it with rimp2_read_status() after the stream has run the call.
  *  - Layouts are row-major with the last index fastest:
  *      B, Gamma  [nocc][nvir][naux]     eps_occ [nocc]    eps_vir [nvir]
  *      P_ij, e_pair [nocc][nocc]        P_ab [nvir][nvir] E [2] = (hi, lo)

@@ -87,8 +87,8 @@ struct GemmParams {
   // blocks the same launch computes); workgroups are launched for the tiles
   // that pair_cols_skipped keeps.  Never with split-K.
   int32_t pair_upper, pair_lo;
-  // The first (ia|jb) launch of a fragment (its status is null: V is scratch)
-  // also checks the orbital energies, in one more workgroup that writes
+  // The first (ia|jb) launch of a small fragment (its status is null: V is
+  // scratch) also checks the orbital energies, in one more workgroup that writes
   // gap_status for the kernels after it; null otherwise.
   int32_t* gap_status;
   const double *gap_eo, *gap_ev;

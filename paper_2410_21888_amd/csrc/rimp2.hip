@@ -951,6 +951,12 @@ int launch_tail(int level, const GemmParams& gg, const GemmParams& ga, const Gem
   });
 }
 
+// Estimate of a first (ia|jb) product up to which the gap check is one more of
+// its workgroups instead of a launch before it.  The launch costs 4 to 5 us (of
+// 31 at 5/25/90, of 184 at 20/100/400, with products of 9 and 68); a fragment
+// that the check rejects pays for the product, so a long one waits for the check.
+constexpr double kFoldGapUs = 100.0;
+
 // Enqueue the whole path for one fragment.  Pointers already validated.
 int run_fragment(const Plan& P, const double* B, const double* eo, const double* ev, double* E, double* Gam,
                  double* Pij, double* Pab, double* e_user, char* ws, const uint8_t* skip, hipStream_t st) {
@@ -961,8 +967,12 @@ int run_fragment(const Plan& P, const double* B, const double* eo, const double*
   double* T = (double*)(ws + P.off_T);
   double* ep = e_user ? e_user : (double*)(ws + P.off_e);
   int rc;
-  // (the FP64 path checks the gap inside its first (ia|jb) launch)
-  if (P.split && (rc = traced(R_GAP, 0, 0, 8.0 * (o + v), st, [&] {
+  bool fold_gap = false;   // the gap check runs inside the first (ia|jb) launch
+  if (!P.split) {
+    const GemmParams first = ints_product(P, 0, group_at(P, 0));
+    fold_gap = ints_us(first, ints_tile(first)) <= kFoldGapUs;
+  }
+  if (!fold_gap && (rc = traced(R_GAP, 0, 0, 8.0 * (o + v), st, [&] {
          hipLaunchKernelGGL(gap_check_kernel, dim3(1), dim3(256), 0, st, eo, (int)nocc, ev, (int)nvir, status);
        })))
     return rc;
@@ -1016,7 +1026,7 @@ int run_fragment(const Plan& P, const double* B, const double* eo, const double*
       gp.Bk = kop(B + j0 * nvir * naux, naux, INT64_MAX, 0);
       gp.C = V; gp.ldc = Lc; gp.split_stride = 0; gp.status = status;
       gp.skip = skip;
-      if (k0 == 0 && !P.split) {
+      if (k0 == 0 && fold_gap) {
         gp.status = nullptr;
         gp.gap_status = status; gp.gap_eo = eo; gp.gap_ev = ev;
         gp.gap_nocc = (int32_t)nocc; gp.gap_nvir = (int32_t)nvir;
