@@ -239,8 +239,8 @@ __device__ __forceinline__ bool pair_mirrored(int sym, int k0, int g, int j) {
 template <int AT, int NT>
 __device__ __forceinline__ void amplitude_block(double* S, double* Tslab, const double* eo, const double* ev, int nocc,
                                                 int nvir, int k0, int j0, int ncols, int sym, int g, int energy_only,
-                                                int write_x, const uint8_t* pair_skip, double* e_pair, int kk, int jj, int w,
-                                                int W, double* epart_all) {
+                                                int write_x, const uint8_t* pair_skip, double* e_pair, int kk, int jj,
+                                                int w, int W, double* epart_all) {
   constexpr int RS = NT / AT, NE = AT / RS;
   __shared__ double XP[AT][AT + 1], XQ[AT][AT + 1];   // also the mirror path's V tiles
   const int k = k0 + kk, j = j0 + jj;
@@ -256,7 +256,8 @@ __device__ __forceinline__ void amplitude_block(double* S, double* Tslab, const 
   const int nt = (nvir + AT - 1) / AT, npt = nt * (nt + 1) / 2;
   const int q0 = (int)((int64_t)npt * w / W), q1 = (int)((int64_t)npt * (w + 1) / W);
   if ((sym == 2 || sym == 3) && j >= k0 && j < k0 + g && !energy_only && j > k) {
-    amplitude_mirror_block<AT, NT>(S, Tslab, eo, ev, nocc, nvir, skip, write_x != 0, e_pair, k0, j0, ncols, k, j, q0, q1, epart, XP, XQ);
+    amplitude_mirror_block<AT, NT>(S, Tslab, eo, ev, nocc, nvir, skip, write_x != 0, e_pair, k0, j0, ncols, k, j, q0,
+                                   q1, epart, XP, XQ);
     return;
   }
   if (skip && energy_only) {
@@ -311,8 +312,10 @@ __device__ __forceinline__ void amplitude_block(double* S, double* Tslab, const 
         double p = tv * vP[s], e;
         two_sum(sh, p, sh, e);
         sl += e;
-        if (!energy_only) tblk[(int64_t)a * ld + b] = tv;
-        if (write_x) blk[(int64_t)a * ld + b] = xP[s];
+        if (!energy_only) {
+          tblk[(int64_t)a * ld + b] = tv;
+          if (write_x) blk[(int64_t)a * ld + b] = xP[s];
+        }
       }
       if (!diag) {
         const int a2 = ctb * AT + r, b2 = cta * AT + tc;
@@ -322,8 +325,10 @@ __device__ __forceinline__ void amplitude_block(double* S, double* Tslab, const 
           double p = tv2 * vQ[s], e;
           two_sum(sh, p, sh, e);
           sl += e;
-          if (!energy_only) tblk[(int64_t)a2 * ld + b2] = tv2;
-          if (write_x) blk[(int64_t)a2 * ld + b2] = xQ[s];
+          if (!energy_only) {
+            tblk[(int64_t)a2 * ld + b2] = tv2;
+            if (write_x) blk[(int64_t)a2 * ld + b2] = xQ[s];
+          }
         }
       }
     }
