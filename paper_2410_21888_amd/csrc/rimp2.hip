@@ -207,8 +207,10 @@ GemmChoice choose_gemm(int64_t M, int64_t N, int64_t K, bool tri, const int* bms
   const int64_t smin = std::min<int64_t>({smax, kLongSplits, cdiv(K, kSplitLen)});
   for (; *bms; ++bms) {
     const int64_t tiles = square_tiles(M, N, *bms, tri) * batch;
-    for (int64_t w = 1; w <= 12; ++w) {
+    for (int64_t w = 1, last = 0; w <= 12; ++w) {
       const int64_t s = std::max<int64_t>(smin, std::min<int64_t>(smax, w <= 4 ? w : (w - 4) * (int64_t)kCUs / tiles));
+      if (s == last) continue;
+      last = s;
       const double us = product_us(M, N, K, tri, GemmChoice{*bms, s}, batch);
       if (best.bm == 0 || us < best_us * (*bms < best.bm ? kSmallerTile : 1.0)) {
         best_us = us;
