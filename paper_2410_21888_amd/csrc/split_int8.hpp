@@ -293,18 +293,18 @@ __device__ __forceinline__ void oz8_tile(const OzParams& p, int64_t m0, int64_t 
 
   // the levels of each output are combined in FP64, scaled by the output's
   // exponents (a power of two: exact) and stored, or added to C
+  // per row block i: the reads of exponents and C (clamped: always in bounds and
+  // without a branch, so the loads go out together; what an out-of-range output
+  // reads is never stored), then the stores
   int xb[NI];   // exponents of this lane's output columns
 #pragma unroll
-  for (int j = 0; j < NI; ++j) {
-    const int64_t n = n0 + (wn * NI + j) * 16 + l16;
-    xb[j] = n < p.N ? p.eb[n] : 0;
-  }
-  // per row block i: the C reads (clamped: always in bounds and without a
-  // branch, so the loads go out together; what an out-of-range output reads is
-  // never stored), then the stores
+  for (int j = 0; j < NI; ++j) xb[j] = p.eb[min(n0 + (wn * NI + j) * 16 + l16, p.N - 1)];
 #pragma unroll
   for (int i = 0; i < MI; ++i) {
     double w[NI][4];
+    int xa[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) xa[r] = p.ea[p.a_row0 + min(m0 + (wm * MI + i) * 16 + 4 * g + r, p.M - 1)];
     if (p.accumulate) {
 #pragma unroll
       for (int j = 0; j < NI; ++j)
@@ -317,14 +317,12 @@ __device__ __forceinline__ void oz8_tile(const OzParams& p, int64_t m0, int64_t 
     }
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int64_t m = m0 + (wm * MI + i) * 16 + 4 * g + r;
-      const int xa = m < p.M ? p.ea[p.a_row0 + m] : 0;
 #pragma unroll
       for (int j = 0; j < NI; ++j) {
         double v = 0.0;
 #pragma unroll
         for (int L = S - 1; L >= 0; --L) v = v * (1.0 / 128.0) + (double)acc[L][i][j][r];
-        v = ldexp(v, xa + xb[j] - 12);
+        v = ldexp(v, xa[r] + xb[j] - 12);
         w[j][r] = p.accumulate ? v + w[j][r] : v;
       }
     }
