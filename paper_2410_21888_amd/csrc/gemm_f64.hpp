@@ -85,8 +85,9 @@ struct GemmParams {
   // pair_upper (same row/column to pair mapping): a tile all of whose pairs
   // have pair_lo <= j < k is not computed (their blocks are the transposes of
   // blocks the same launch computes); workgroups are launched for the tiles
-  // that pair_cols_skipped keeps.  Never with split-K.
-  int32_t pair_upper, pair_lo;
+  // that pair_cols_skipped keeps (pair_map: those are not all of them).  Never
+  // with split-K.
+  int32_t pair_upper, pair_lo, pair_map;
   // The first (ia|jb) launch of a small fragment (its status is null: V is
   // scratch) also checks the orbital energies, in one more workgroup that writes
   // gap_status for the kernels after it; null otherwise.
@@ -151,7 +152,8 @@ __host__ __device__ inline int64_t pair_cols_skipped(int64_t k_lo, int64_t j0, i
 // nearly all of the work and the last ones nearly none, and the product ran
 // at half its rate.  MFMA-bound; energy of nocc = 100, nvir = 600, naux =
 // 1800: 178 -> 99 ms (36.7 -> 66 TFLOP/s); nocc = 97, nvir = 485, naux =
-// 1746: 107 -> 59 ms.
+// 1746: 107 -> 59 ms.  (A launch that keeps all of its tiles takes the plain raster:
+// the map costs 1 us a workgroup, of 10 where the product is that small.)
 __device__ __forceinline__ void decode_pair_tile(int64_t t, int64_t k0, int64_t j0, int64_t pair_lo,
                                                  int64_t nvir, int bm, int bn, int tiles_m, int tiles_n, int group_m,
                                                  int& tm, int& tn) {
@@ -189,7 +191,7 @@ __device__ __forceinline__ void decode_pair_tile(int64_t t, int64_t k0, int64_t 
 }
 
 // Decodes logical tile index t (< tiles of one split) into (tm, tn):
-// triangular order (TRI), the kept tiles of a pair_upper launch, or groups of
+// triangular order (TRI), the kept tiles of a pair_upper launch (pair_map), or groups of
 // group_m m-tiles.
 template <int BM, int BN, bool TRI>
 __device__ __forceinline__ void decode_tile(const GemmParams& p, int t, int& tm, int& tn) {
@@ -197,7 +199,7 @@ __device__ __forceinline__ void decode_tile(const GemmParams& p, int t, int& tm,
     tm = 0;
     while (t >= p.tiles_m - tm) { t -= p.tiles_m - tm; ++tm; }
     tn = tm + t;
-  } else if (p.pair_upper) {
+  } else if (p.pair_map) {
     decode_pair_tile(t, p.skip_k0, p.skip_j0, p.pair_lo, p.skip_nvir, BM, BN, p.tiles_m, p.tiles_n, p.group_m, tm,
                      tn);
   } else {

@@ -503,7 +503,8 @@ int launch_gemm(GemmParams gp, hipStream_t st, int role, double af, double ab, b
   if (TRI && (gp.M != gp.N || BM != BN)) return fail(RIMP2_EINVAL, "triangular GEMM needs a square tile grid");
   if (gp.pair_upper && gp.splits != 1) return fail(RIMP2_EINVAL, "pair_upper GEMM without split-K only");
   if (gp.batch > 1 && (gp.splits != 1 || !role_batched(ROLE))) return fail(RIMP2_EINVAL, "batched GEMM without split-K only");
-  const int64_t nwg = gemm_tiles(gp, BM, BN, TRI) * std::max(gp.splits, gp.batch);
+  const int64_t tiles = gemm_tiles(gp, BM, BN, TRI), nwg = tiles * std::max(gp.splits, gp.batch);
+  gp.pair_map = gp.pair_upper && tiles < (int64_t)gp.tiles_m * gp.tiles_n;
   if (int rc = check_grid(nwg, "GEMM")) return rc;
   constexpr bool AMC = role_a_mcontig(ROLE);
   if (AMC && gp.splits != 1) return fail(RIMP2_EINVAL, "M-contiguous GEMM without split-K only");
@@ -879,6 +880,7 @@ int run_oz8(int S, const int8_t* A, int64_t a_slice, int64_t a_row0, const int32
     op.pair_lo = (int32_t)pairs->lo;
   }
   const int64_t nwg = oz8_tiles(op, side, side);
+  op.pair_map = nwg < (int64_t)op.tiles_m * op.tiles_n;
   if (int rc = check_grid(nwg * (side / 64), "split GEMM")) return rc;
   const double ef = 2.0 * (double)M * N * kp * ((double)nwg / ((double)op.tiles_m * op.tiles_n));
   const int64_t kc = windowed ? kOzWindow : kp;
@@ -904,7 +906,9 @@ int64_t finalize_gemm(GemmParams& gp, int BM, int BN, bool tri) {
   if (gp.kchunk <= 0) gp.kchunk = gp.K;
   gp.kchunk = cdiv(gp.kchunk, kBK) * kBK;
   gp.splits = (int32_t)cdiv(gp.K, gp.kchunk);
-  return gemm_tiles(gp, BM, BN, tri) * gp.splits;
+  const int64_t tiles = gemm_tiles(gp, BM, BN, tri);
+  gp.pair_map = gp.pair_upper && tiles < (int64_t)gp.tiles_m * gp.tiles_n;
+  return tiles * gp.splits;
 }
 
 int launch_finish(const FinishParams& f, hipStream_t st) {
@@ -1613,8 +1617,10 @@ int batch_plan(int32_t nfrag, const rimp2_frag_desc* d, const rimp2_opts* opts, 
         z.tiles_m = (int32_t)cdiv(L, sz); z.tiles_n = z.tiles_m; z.group_m = 8;
         z.pair_nvir = (int32_t)nvir;   // blocks j < k: the amplitude pass mirrors them (pair_k0 = pair_j0 = pair_lo = 0)
         z.status = status;
+        const int64_t tiles = oz8_tiles(z, sz, sz);
+        z.pair_map = tiles < (int64_t)z.tiles_m * z.tiles_n;
         oz[0].push_back(z);
-        oz_pre[0].push_back(oz_pre[0].back() + oz8_tiles(z, sz, sz));
+        oz_pre[0].push_back(oz_pre[0].back() + tiles);
         // digits of every B row (both operands of the (ia|jb) products)
         add_dop(0, DigitOp{q.B, naux, L, naux, P.kpv, 0, relp<int8_t>(base + P.off_dbv),
                            relp<int32_t>(base + P.off_ev), nullptr, status}, L, 0, 0, 0);

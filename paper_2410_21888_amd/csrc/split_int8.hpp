@@ -139,8 +139,9 @@ struct OzParams {
   int32_t tiles_m, tiles_n, group_m;
   // pair_nvir > 0: rows are (k, a) from orbital pair_k0 (a_row0 = pair_k0
   // pair_nvir), columns (j, b) from orbital pair_j0, and tiles that hold only
-  // pairs pair_lo <= j < k are left out (oz8_tile_skipped, decode_pair_tile)
-  int32_t pair_nvir, pair_k0, pair_j0, pair_lo;
+  // pairs pair_lo <= j < k are left out (oz8_tile_skipped, decode_pair_tile;
+  // pair_map: the launch holds workgroups for fewer than all tiles)
+  int32_t pair_nvir, pair_k0, pair_j0, pair_lo, pair_map;
   const int32_t* status;
 };
 
@@ -191,7 +192,7 @@ __device__ __forceinline__ bool oz8_tile_skipped(const OzParams& p, int64_t m0, 
 // Logical tile t of a launch: raster groups of group_m row tiles, of a pair
 // launch the tiles they keep.
 __device__ __forceinline__ void oz8_decode(const OzParams& p, int bm, int bn, int t, int& tm, int& tn) {
-  if (p.pair_nvir > 0) {
+  if (p.pair_map) {
     decode_pair_tile(t, p.pair_k0, p.pair_j0, p.pair_lo, p.pair_nvir, bm, bn, p.tiles_m, p.tiles_n, p.group_m, tm, tn);
   } else {
     const int gsz = p.group_m * p.tiles_n, grp = t / gsz, first_m = grp * p.group_m;
