@@ -898,11 +898,15 @@ int run_oz8(int S, const int8_t* A, int64_t a_slice, int64_t a_row0, const int32
 
 KOperand kop(const double* base, int64_t rs, int64_t kdiv, int64_t ks1) { return KOperand{base, rs, kdiv, ks1}; }
 
-// tiles, splits and group size of a GEMM, as launch_gemm sets them
+// tiles, splits and group size of a GEMM, as launch_gemm sets them, but raster
+// groups of one row for (ia|jb): a group of 8 also keeps tiles that only some of
+// its rows need, and their workgroups, which end at once, fall unevenly on the
+// CUs of a grouped launch (24 of 40/200/720: 19.6 ms with groups of 8, 18.3 with
+// one; persistent workgroups that passed such tiles over: 18.5)
 int64_t finalize_gemm(GemmParams& gp, int BM, int BN, bool tri) {
   gp.tiles_m = (int32_t)cdiv(gp.M, BM);
   gp.tiles_n = (int32_t)cdiv(gp.N, BN);
-  gp.group_m = 8;
+  gp.group_m = gp.pair_upper ? 1 : 8;
   if (gp.kchunk <= 0) gp.kchunk = gp.K;
   gp.kchunk = cdiv(gp.kchunk, kBK) * kBK;
   gp.splits = (int32_t)cdiv(gp.K, gp.kchunk);
