@@ -86,10 +86,12 @@ int rimp2_l_terms(int32_t nocc, int32_t nvir, int32_t nmo, int32_t naux, const d
  *   (pq|rs) = sum_P Bf[p][q][P] Bf[r][s][P]
  *
  *   D  device, read [nmo][nmo];  F device, write, row stride ldf >= ncols
- * The Coulomb part is two fixed-order reductions over the auxiliary index;
- * the exchange part two FP64 MFMA GEMMs (Y[s][q][P] = sum_r D[r][s]
- * Bf[r][q][P], then a contraction over (s, P) with split-K partials and an
- * ordered reduction), so results are deterministic.
+ * The exchange part is two FP64 MFMA GEMMs (Y[s][q][P] = sum_r D[r][s]
+ * Bf[r][q][P], then a contraction over (s, P); or, where fewer rows than
+ * columns make it cheaper, Z[p][r][P] = sum_s D[r][s] Bf[p][s][P] and then
+ * (r, P)) with split-K partials added in order; the Coulomb part's vector is Y's
+ * (Z's) trace where it has one, else a pass over Bf of its own, again in a fixed
+ * order, so results are deterministic.
  */
 int rimp2_antisym_workspace_size(int32_t nmo, int32_t naux, int32_t nrows, int32_t ncols, size_t* bytes);
 int rimp2_antisym_term(int32_t nmo, int32_t naux, int32_t r0, int32_t nrows, int32_t c0, int32_t ncols,
@@ -105,8 +107,8 @@ int rimp2_antisym_term(int32_t nmo, int32_t naux, int32_t r0, int32_t nrows, int
  * with Dbar = D_ij (+) D_ab (P_ij and P_ab of rimp2_fragment), L1 = L'
  * [nocc][nmo] and L2 = L'' [nvir][nmo] (rimp2_l_terms).  Solved by conjugate
  * gradients with the operator's diagonal as preconditioner, starting from
- * rhs / diagonal; every operator application is one rimp2_antisym_term
- * evaluation.  The operator is the orbital Hessian, positive definite for a
+ * rhs / diagonal; every operator application is the antisymmetrised term over
+ * the virtual-occupied block of the density alone.  The operator is the orbital Hessian, positive definite for a
  * stable closed-shell reference; CG stops when ||rhs - A D_ai|| <= tol ||rhs||
  * or after max_iter iterations.
  *
@@ -114,9 +116,10 @@ int rimp2_antisym_term(int32_t nmo, int32_t naux, int32_t r0, int32_t nrows, int
  *   iterations    host, write (may be NULL): iterations run
  *   rel_residual  host, write (may be NULL): ||rhs - A D_ai|| / ||rhs||
  * The call synchronises `stream` once for every four iterations (the host reads
- * the CG scalars; what is queued past the last iteration does nothing).  Returns RIMP2_ENOCONV, with D_ai holding the last iterate, when
- * the tolerance is not reached or the operator is not positive definite
- * along a search direction.
+ * the CG scalars; what is queued past the last iteration does nothing).  D_ai is
+ * first written after the last read of the inputs L1 and L2.  Returns
+ * RIMP2_ENOCONV, with D_ai holding the last iterate, when the tolerance is not
+ * reached or the operator is not positive definite along a search direction.
  */
 int rimp2_zvector_workspace_size(int32_t nocc, int32_t nvir, int32_t naux, size_t* bytes);
 int rimp2_zvector(int32_t nocc, int32_t nvir, int32_t naux, const double* Bf, const double* eps_occ,

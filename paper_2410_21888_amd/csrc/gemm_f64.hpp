@@ -135,8 +135,8 @@ constexpr bool role_a_mcontig(int role) { return role == ROLE_GAMMA_T || role ==
 // [from, from + return) hold only pairs pair_lo <= j < k_lo.  Columns are j0 +
 // n / nvir.  The rows of a group start at the same or a later orbital, so a
 // tile left out here is one tile_screened would drop.
-__host__ __device__ inline int64_t pair_cols_skipped(int64_t k_lo, int64_t j0, int64_t pair_lo, int64_t nvir, int64_t bn,
-                                                     int64_t tiles_n, int64_t* from) {
+__host__ __device__ inline int64_t pair_cols_skipped(int64_t k_lo, int64_t j0, int64_t pair_lo, int64_t nvir,
+                                                     int64_t bn, int64_t tiles_n, int64_t* from) {
   const int64_t below = (k_lo - j0) * nvir / bn;   // tiles whose last column has j < k_lo
   const int64_t lo = pair_lo > j0 ? ((pair_lo - j0) * nvir + bn - 1) / bn : 0;
   *from = lo;
@@ -616,10 +616,9 @@ __device__ __forceinline__ void gemm_tile(const GemmParams& p, int tm, int tn, i
       }
 }
 
-
-// One workgroup per (split, tile); the hardware id is remapped XCD-aware.
 // Roles launched as batches of products.
 constexpr bool role_batched(int role) { return role == ROLE_AO || role == ROLE_BATCH; }
+// One workgroup per (split, tile); the hardware id is remapped XCD-aware.
 template <int BM, int BN, int BK, bool B_NCONTIG, int ROLE, bool VEC, bool TRI, int FAST = 0>
 __global__ __launch_bounds__(256, 2) void gemm_f64_kernel(GemmParams p) {
   if (p.status != nullptr && *p.status != 0) return;

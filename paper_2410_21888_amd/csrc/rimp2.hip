@@ -147,7 +147,8 @@ constexpr int64_t kMaxSplits = 1024;
 double gemm_us(const TileCost& t, int64_t tiles, int64_t K, int64_t splits) {
   const double chunks = (double)cdiv(cdiv(K, splits), kBK);
   const int64_t w = cdiv(tiles * splits, (int64_t)kCUs), rounds = w / t.resident, rest = w % t.resident;
-  return rounds * (kTileFill + chunks * (t.a + t.b * t.resident)) + (rest ? kTileFill + chunks * (t.a + t.b * rest) : 0.0);
+  return rounds * (kTileFill + chunks * (t.a + t.b * t.resident)) +
+         (rest ? kTileFill + chunks * (t.a + t.b * rest) : 0.0);
 }
 
 // A smaller tile has to be estimated 3% faster than the larger one: it stages
@@ -229,7 +230,9 @@ constexpr int kIntsTiles[] = {128, 64, 0}, kGammaTiles[] = {128, 64, 0}, kPabTil
 // short (klen).  With 64 splits whatever the length, the P_ij items of nocc =
 // 60, nvir = 300 were 84000 long, and the launch waited for them.
 constexpr int64_t kGroupedPab = 4096, kGroupedPij = 2048;
-int64_t grouped_splits(int64_t K, int64_t klen) { return std::max<int64_t>(1, std::min<int64_t>(kMaxSplits, cdiv(K, klen))); }
+int64_t grouped_splits(int64_t K, int64_t klen) {
+  return std::max<int64_t>(1, std::min<int64_t>(kMaxSplits, cdiv(K, klen)));
+}
 // Estimate of a grouped product's `tiles` of side bm, on a chip that the wave's
 // other products keep full: P_ij of nocc = 30 costs a third with tiles of 32
 // what it costs with 64, P_ab of nvir = 300 two thirds with 64 of 128.
@@ -358,7 +361,8 @@ int make_plan(int64_t nocc, int64_t nvir, int64_t naux, bool gamma, bool density
     p->c_ij = choose_gemm(nocc, nocc, g * nvir * nvir, true, kPijTiles, split_cap(*p, nocc, nocc));
   }
   if (gamma)
-    p->c_gam = choose_gemm(g * nvir, naux, nocc * nvir, false, kGammaTiles, grouped ? 1 : split_cap(*p, g * nvir, naux));
+    p->c_gam = choose_gemm(g * nvir, naux, nocc * nvir, false, kGammaTiles,
+                           grouped ? 1 : split_cap(*p, g * nvir, naux));
   // slab elements (g x ncols pair blocks) and Gamma split partials of the
   // largest group
   double slab_elems = (double)g * nocc * nvir * nvir, gam_part = (double)p->c_gam.splits * g * nvir * naux;
@@ -465,9 +469,9 @@ bool gemm_vec(const GemmParams& gp, bool nc, bool amc = false) {
 // The kernels' FAST level of a GEMM (0: the general loader).  It needs runs of
 // the K operands at least one chunk long (a chunk crosses at most one run
 // boundary), and of an M-contiguous A (N-contiguous B) an even number of rows
-// (columns) or a whole tile of side bm to read pairs from.  2 when a K operand's runs are even and can end inside a
-// chunk, 3 when they are odd; alignment, odd strides and odd lengths do not
-// matter.  (Odd sizes took the general loader with 8-byte loads: Gamma of
+// (columns) or a whole tile of side bm to read pairs from.  2 when a K operand's
+// runs are even and can end inside a chunk, 3 when they are odd; alignment, odd
+// strides and odd lengths do not matter.  (Odd sizes took the general loader with 8-byte loads: Gamma of
 // nocc = 97, nvir = 485, naux = 1746 ran at 57 TFLOP/s, and at 64 here.)
 int fast_level(const GemmParams& gp, int bm, bool nc, bool amc = false) {
   auto runs = [&](const KOperand& o) { return o.kdiv >= gp.K || o.kdiv >= kBK; };
@@ -502,7 +506,8 @@ int launch_gemm(GemmParams gp, hipStream_t st, int role, double af, double ab, b
   gp.splits = (int32_t)cdiv(gp.K, gp.kchunk);
   if (TRI && (gp.M != gp.N || BM != BN)) return fail(RIMP2_EINVAL, "triangular GEMM needs a square tile grid");
   if (gp.pair_upper && gp.splits != 1) return fail(RIMP2_EINVAL, "pair_upper GEMM without split-K only");
-  if (gp.batch > 1 && (gp.splits != 1 || !role_batched(ROLE))) return fail(RIMP2_EINVAL, "batched GEMM without split-K only");
+  if (gp.batch > 1 && (gp.splits != 1 || !role_batched(ROLE)))
+    return fail(RIMP2_EINVAL, "batched GEMM without split-K only");
   const int64_t tiles = gemm_tiles(gp, BM, BN, TRI), nwg = tiles * std::max(gp.splits, gp.batch);
   gp.pair_map = gp.pair_upper && tiles < (int64_t)gp.tiles_m * gp.tiles_n;
   if (int rc = check_grid(nwg, "GEMM")) return rc;
@@ -1123,8 +1128,8 @@ int run_fragment(const Plan& P, const double* B, const double* eo, const double*
         if ((rc = launch_tuned(R_GAMMA, cg.bm, gp, P.autotune, P.general, st, af, ab))) return rc;
         const int64_t n = gc * nvir * naux;
         if ((rc = traced(R_REDUCE, 0, 0, 8.0 * (splits + 1 + acc) * n, st, [&] {
-               hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)reduce_blocks(n, splits)), dim3(256), 0, st, out, naux, W,
-                                  naux, gc * nvir * naux, (int)splits, gc * nvir, naux, 1.0, acc, status);
+               hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)reduce_blocks(n, splits)), dim3(256), 0, st, out,
+                                  naux, W, naux, gc * nvir * naux, (int)splits, gc * nvir, naux, 1.0, acc, status);
              })))
           return rc;
       } else {
@@ -1179,7 +1184,8 @@ int run_fragment(const Plan& P, const double* B, const double* eo, const double*
                             Gam + (k0 + gc) * nvir * naux, naux, status, R_GAMMA_T8, aft,
                             (double)P.sg * (r * v + x) * kg + 8.0 * (1 + acc) * r * v * x, st, acc)))
             return rc;
-        } else if ((rc = launch_tuned(R_GAMMA_T, choose_gemm(gt.M, gt.N, gt.K, false, kGammaTiles, 1).bm, gt, P.autotune, P.general, st, aft, abt))) {
+        } else if ((rc = launch_tuned(R_GAMMA_T, choose_gemm(gt.M, gt.N, gt.K, false, kGammaTiles, 1).bm, gt,
+                                      P.autotune, P.general, st, aft, abt))) {
           return rc;
         }
       }
@@ -1382,8 +1388,8 @@ struct Wave {
   int n_g[4] = {0, 0, 0, 0};       // problems of each role
   int tile_g[4][2] = {};           // tile side of the largest problem (autotuner report)
   uint64_t sig = 0;             // hash of the wave's fragment sizes (autotuner key)
-  int namp, nred_ab, nred_ij;
-  int64_t amp_blocks[2], red_blocks_ab, red_blocks_ij;
+  int nred = 0;                 // split-K reductions
+  int64_t amp_blocks[2], red_blocks = 0;
   // split products (precision RIMP2_SPLIT_INT8): grouped (ia|jb) and Gamma
   // product lists, run in reduction windows (win_* launches each)
   size_t o_oz[2] = {0, 0}, o_oz_pre[2] = {0, 0};
@@ -1619,7 +1625,8 @@ int batch_plan(int32_t nfrag, const rimp2_frag_desc* d, const rimp2_opts* opts, 
         z.C = V; z.ldc = L;
         const int64_t sz = W.side_oz[0];
         z.tiles_m = (int32_t)cdiv(L, sz); z.tiles_n = z.tiles_m; z.group_m = 8;
-        z.pair_nvir = (int32_t)nvir;   // blocks j < k: the amplitude pass mirrors them (pair_k0 = pair_j0 = pair_lo = 0)
+        // blocks j < k: the amplitude pass mirrors them (pair_k0 = pair_j0 = pair_lo = 0)
+        z.pair_nvir = (int32_t)nvir;
         z.status = status;
         const int64_t tiles = oz8_tiles(z, sz, sz);
         z.pair_map = tiles < (int64_t)z.tiles_m * z.tiles_n;
@@ -1693,10 +1700,9 @@ int batch_plan(int32_t nfrag, const rimp2_frag_desc* d, const rimp2_opts* opts, 
     }
     W.bytes = poff;
     ws = std::max(ws, poff);
-    W.namp = n;
     for (int b = 0; b < 2; ++b) W.amp_blocks[b] = amp_pre[b][n];
-    W.nred_ab = (int)red.size();
-    W.red_blocks_ab = red_pre.back();
+    W.nred = (int)red.size();
+    W.red_blocks = red_pre.back();
     W.sig = sig;
     char* blob = B->blob.data() + W.host_off;
     auto put = [&](size_t off, const void* src, size_t bytes) { if (bytes) memcpy(blob + off, src, bytes); };
@@ -1855,8 +1861,8 @@ int launch_oz8_grouped(const Grouped<OzParams>& G, int64_t items, int side, int6
   if (int rc = check_grid(grid * (side / 64), "grouped split product")) return rc;
   return traced(role, 0, 0, 0, st, [&] {
     if (S <= 5 && side == 128)
-      hipLaunchKernelGGL((gemm_oz8_grouped<S <= 5 ? S : 5, 2, OzWide>), dim3((unsigned)grid), dim3(512), 0, st, G, window,
-                         kOzWindow);
+      hipLaunchKernelGGL((gemm_oz8_grouped<S <= 5 ? S : 5, 2, OzWide>), dim3((unsigned)grid), dim3(512), 0, st, G,
+                         window, kOzWindow);
     else
       hipLaunchKernelGGL((gemm_oz8_grouped<S, S <= 5 ? 2 : 1, OzSmall>), dim3((unsigned)grid), dim3(256), 0, st, G,
                          window, kOzWindow);
@@ -1898,9 +1904,9 @@ int batch_run(rimp2_batch_s* B, int32_t* status_dev, void* workspace, size_t byt
                  hipLaunchKernelGGL(relocate_tables_kernel, dim3((unsigned)cdiv(W.n_g[r], 256)), dim3(256), 0, st, ws,
                                     (GemmParams*)at(W.o_g[r][c]), W.n_g[r], (AmpDesc*)nullptr, 0, (ReduceDesc*)nullptr,
                                     0, (FragSmall*)nullptr, 0);
-           const int m = std::max(n, W.nred_ab);
+           const int m = std::max(n, W.nred);
            hipLaunchKernelGGL(relocate_tables_kernel, dim3((unsigned)cdiv(m, 256)), dim3(256), 0, st, ws,
-                              (GemmParams*)nullptr, 0, (AmpDesc*)at(W.o_amp), n, (ReduceDesc*)at(W.o_red), W.nred_ab,
+                              (GemmParams*)nullptr, 0, (AmpDesc*)at(W.o_amp), n, (ReduceDesc*)at(W.o_red), W.nred,
                               (FragSmall*)at(W.o_fs), n);
            hipLaunchKernelGGL(gap_check_grouped, dim3((unsigned)n), dim3(256), 0, st, (const FragSmall*)at(W.o_fs));
            if (B->split) {
@@ -1991,9 +1997,9 @@ int batch_run(rimp2_batch_s* B, int32_t* status_dev, void* workspace, size_t byt
          })))
       return rc;
     if ((rc = B->split ? run_split(1) : run_role(1)) || (rc = run_role(2)) || (rc = run_role(3))) return rc;
-    if (W.nred_ab && (rc = traced(R_REDUCE, 0, 0, 0, st, [&] {
-                        hipLaunchKernelGGL(reduce_grouped, dim3((unsigned)W.red_blocks_ab), dim3(256), 0, st,
-                                           (const ReduceDesc*)at(W.o_red), (const int64_t*)at(W.o_red_pre), W.nred_ab);
+    if (W.nred && (rc = traced(R_REDUCE, 0, 0, 0, st, [&] {
+                        hipLaunchKernelGGL(reduce_grouped, dim3((unsigned)W.red_blocks), dim3(256), 0, st,
+                                           (const ReduceDesc*)at(W.o_red), (const int64_t*)at(W.o_red_pre), W.nred);
                       })))
       return rc;
     if ((rc = traced(R_ESUM, 0, 0, 0, st, [&] {
@@ -2516,7 +2522,8 @@ AntisymPlan antisym_plan(int64_t nmo, int64_t naux, int64_t nrows, int64_t ncols
   A.chunks = cdiv(npairs, A.chunk);
   // the exchange part's order: D against Bf's columns (Y) or rows (Z) first,
   // whichever takes fewer multiply-adds
-  A.rows_first = (double)nrows * nr * nc + (double)nrows * ncols * nr < (double)nc * ncols * nr + (double)nrows * ncols * nc;
+  A.rows_first =
+      (double)nrows * nr * nc + (double)nrows * ncols * nr < (double)nc * ncols * nr + (double)nrows * ncols * nc;
   A.c_k = choose_gemm(nrows, ncols, (A.rows_first ? nr : nc) * naux, false, kLtermTiles);
   size_t off = 0;
   A.off_status = off; off = align_up(off + 64);
@@ -2554,8 +2561,8 @@ int antisym_run(const AntisymPlan& A, const double* Bf, const DBlock& d, int64_t
   // trace 5.
   const bool trace = A.rows_first ? (r0 == d.r0 && nrows == d.nr) : (c0 == d.c0 && ncols == d.nc);
   auto sum_c = [&](const double* part, int64_t terms, int64_t stride) {
-    hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)reduce_blocks(naux, terms)), dim3(256), 0, st, c, naux, part,
-                       naux, stride, (int)terms, (int64_t)1, naux, 1.0, 0, status);
+    hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)reduce_blocks(naux, terms)), dim3(256), 0, st, c, naux,
+                       part, naux, stride, (int)terms, (int64_t)1, naux, 1.0, 0, status);
   };
   if (!trace && (rc = traced(R_RESPONSE, 0, 0, 8.0 * d.nr * d.nc * (naux + 1), st, [&] {
          hipLaunchKernelGGL(coulomb_vector_kernel, dim3((unsigned)cdiv(naux, 256), (unsigned)A.chunks), dim3(256), 0,
@@ -2597,15 +2604,16 @@ int antisym_run(const AntisymPlan& A, const double* Bf, const DBlock& d, int64_t
   }
   if (trace) {
     const int64_t terms = A.rows_first ? d.nr : d.nc, width = A.rows_first ? d.nr : ncols;
-    if ((rc = traced(R_RESPONSE, 0, 0, 8.0 * (terms + 1) * naux, st, [&] { sum_c(Y, terms, (width + 1) * naux); }))) return rc;
+    if ((rc = traced(R_RESPONSE, 0, 0, 8.0 * (terms + 1) * naux, st, [&] { sum_c(Y, terms, (width + 1) * naux); })))
+      return rc;
   }
   gk.kchunk = cdiv(gk.K, A.c_k.splits);
   gk.C = Kp; gk.ldc = ncols; gk.split_stride = nrows * ncols; gk.status = status;
   const int64_t splits = cdiv(gk.K, cdiv(gk.kchunk, kBK) * kBK), n = nrows * ncols;
   if ((rc = launch_lterm(A.c_k.bm, gk, st, R_RESPONSE, 2.0 * n * gk.K, 8.0 * (nrows + ncols) * gk.K))) return rc;
   return traced(R_RESPONSE, 0, 0, 8.0 * n * (naux + splits + 1), st, [&] {
-    hipLaunchKernelGGL(antisym_combine_kernel<ROLE>, dim3((unsigned)cdiv(n, kCombine)), dim3(256), 0, st, Bf, nmo, naux, r0,
-                       nrows, c0, ncols, (const double*)c, (const double*)Kp, (int)splits, F, ldf, z, status);
+    hipLaunchKernelGGL(antisym_combine_kernel<ROLE>, dim3((unsigned)cdiv(n, kCombine)), dim3(256), 0, st, Bf, nmo, naux,
+                       r0, nrows, c0, ncols, (const double*)c, (const double*)Kp, (int)splits, F, ldf, z, status);
   });
 }
 
@@ -2871,8 +2879,8 @@ int rimp2_zvector(int32_t nocc, int32_t nvir, int32_t naux, const double* Bf, co
   // D_ab; Jacobi preconditioner: the operator's diagonal; first iterate rhs /
   // diagonal, in pv
   if ((rc = traced(R_RESPONSE, 0, 0, 8.0 * nmo * nmo, st, [&] {
-         hipLaunchKernelGGL(assemble_density_kernel, dim3((unsigned)cdiv(nmo * nmo, 256)), dim3(256), 0, st, no, nv, P_ij,
-                            P_ab, (const double*)nullptr, 0, 0, D);
+         hipLaunchKernelGGL(assemble_density_kernel, dim3((unsigned)cdiv(nmo * nmo, 256)), dim3(256), 0, st, no, nv,
+                            P_ij, P_ab, (const double*)nullptr, 0, 0, D);
        })))
     return rc;
   if ((rc = antisym_run<2>(Z.full, Bf, DBlock{D, nmo, 0, nmo, 0, nmo}, no, 0, rhs, no,

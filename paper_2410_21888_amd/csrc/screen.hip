@@ -15,7 +15,9 @@ using namespace rimp2;
 
 namespace {
 
-// a dispatch's grid size is a 32-bit count of work-items
+// a dispatch's grid size is a 32-bit count of work-items (the network's entry
+// points refuse sample counts by it, as they always have, though their launches
+// have at most 1024 workgroups)
 constexpr int64_t kMaxItems = 0xffffffffLL;
 constexpr int H = RIMP2_MLP_HIDDEN, NIN = RIMP2_MLP_IN, NP = RIMP2_MLP_PARAMS;
 constexpr int OW1 = 0, OB1 = OW1 + H * NIN, OW2 = OB1 + H, OB2 = OW2 + H * H, OW3 = OB2 + H, OB3 = OW3 + H;

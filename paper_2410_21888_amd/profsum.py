@@ -102,7 +102,6 @@ def role_of(name: str) -> str:
                       ("digit_split_grouped", "digit_split"), ("relocate_digit", "status_copy"),
                       ("copy_status", "status_copy"), ("status_copy", "status_copy"),
                       ("relocate_tables", "status_copy"), ("relocate_oz", "status_copy"),
-                      ("zero_counters", "status_copy"),
                       (COPY_KERNEL, "(runtime copy)"), ("at::native", "(torch)"), ("three_index", "(input generator)")):
         if key in name:
             if role is None:   # the split-precision products, by digit count
