@@ -162,10 +162,10 @@ constexpr double kSmallerTile = 0.97;
 // many terms rounds more than the sum of several: splits of at most kSplitLen,
 // as far as kLongSplits go (P_ab of 6 orbitals' slabs of 200/1800, 2.2M long:
 // 122 ms in 4 splits, 116 in 64; Gamma rows of 200/1800/6000, up to 360000 long,
-// in 2 to 4 or 2 to 11: 673 ms in both, 1.35e12 or 8.8e11 bytes of HBM, a sampled
-// row 5.4e-15 or 1.6e-15 off).  And operands that no cache holds reach the
-// tiles at 8 TB/s of staged bytes at most (P_ij of the same slabs: 36 ms with
-// tiles of 32, which the table prefers, 30 with 64).
+// in 2 to 4 or 2 to 11: 673 ms in both, a sampled row 5.4e-15 or 1.6e-15 off).
+// And operands that no cache holds reach the tiles at 8 TB/s of staged bytes at
+// most (P_ij of the same slabs: 36 ms with tiles of 32, which the table prefers,
+// 30 with 64).
 constexpr int64_t kSplitLen = 32768, kLongSplits = 64;
 constexpr double kCacheBytes = 256e6, kStageBytesPerUs = 8e6;
 
